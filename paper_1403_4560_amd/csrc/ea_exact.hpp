@@ -14,8 +14,9 @@
 // A value adds its 53-bit significand, cut into three 32-bit digits, to three
 // consecutive limbs, so each limb grows by less than 2^32 per value: fewer
 // than 2^30 values can never overflow a limb, and the additions commute (plain
-// integer adds, or integer atomics in LDS).  Normalizing carries every limb
-// into [0, 2^32) and leaves the sign as a final carry of 0 or -1.  Non-finite
+// integer adds, or integer atomics in LDS).  Carrying the limbs that a set of
+// values touches (a few of the XL, as values of one kind span a few binades)
+// leaves a two's complement number of 32-bit digits.  Non-finite
 // values are counted apart (NaN, +inf, -inf) and decide the result as IEEE
 // addition would: any NaN, or +inf together with -inf, gives NaN; otherwise an
 // infinity wins.
@@ -24,11 +25,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-namespace ea {
+#include "ea_types.hpp"
 
-// Limbs: bit offsets 0 .. 2097 hold one value (significand at offset up to
-// 2045, 53 bits); the rest is headroom for the carries of up to 2^30 values.
-constexpr int XL = 68;
+namespace ea {
 
 struct ExactDigits {
     int i;               // lowest limb touched
@@ -59,90 +58,112 @@ __device__ __forceinline__ ExactDigits exact_digits(double x, bool neg)
     return r;
 }
 
-// lim += x (or -= x), x finite.
-__device__ __forceinline__ void exact_add(int64_t *lim, double x, bool neg = false)
+// The lowest limb a finite x touches, or -1 for a zero (which touches none).
+__device__ __forceinline__ int exact_limb(double x)
 {
-    const ExactDigits g = exact_digits(x, neg);
-    lim[g.i] += g.d0;
-    lim[g.i + 1] += g.d1;
-    lim[g.i + 2] += g.d2;
+    const uint64_t b = (uint64_t)__double_as_longlong(x);
+    const int be = (int)((b >> 52) & 0x7ff);
+    if ((b << 1) == 0) return -1;
+    return (be ? be - 1 : 0) >> 5;
 }
 
-// The same on limbs shared by a workgroup (LDS), by integer atomics.
-__device__ __forceinline__ void exact_add_atomic(unsigned long long *lim, double x)
+// lim[k stride] += digit k of x, on limbs shared by a workgroup (LDS), by
+// integer atomics.
+__device__ __forceinline__ void exact_add_atomic(unsigned long long *lim, double x, int stride)
 {
     const ExactDigits g = exact_digits(x, false);
-    atomicAdd(lim + g.i, (unsigned long long)g.d0);
-    atomicAdd(lim + g.i + 1, (unsigned long long)g.d1);
-    atomicAdd(lim + g.i + 2, (unsigned long long)g.d2);
+    lim += g.i * stride;
+    atomicAdd(lim, (unsigned long long)g.d0);
+    atomicAdd(lim + stride, (unsigned long long)g.d1);
+    atomicAdd(lim + 2 * stride, (unsigned long long)g.d2);
 }
 
-// Carry every limb into [0, 2^32); returns the final carry (0, or -1 for a
-// negative sum in two's complement).
-__device__ __forceinline__ int64_t exact_normalize(int64_t *lim)
+// A sum's window: values whose lowest limbs lie in [imin, imax] have a sum
+// that is a two's complement number of the digits imin .. imax + 3 (fewer than
+// 2^30 values of magnitude below 2^(32 (imax + 3)); digit imax + 3 is the
+// signed top).
+constexpr int XWIN = 3;
+
+// Carry limbs lo .. hi (already summed over their copies) into digits, the top
+// one in two's complement.
+__device__ __forceinline__ void exact_carry(const long long *lim, uint32_t *dig, int lo, int hi)
 {
     int64_t carry = 0;
-    for (int k = 0; k < XL; ++k) {
+    for (int k = lo; k <= hi; ++k) {
         const int64_t v = lim[k] + carry;
-        lim[k] = v & 0xffffffffll;
+        dig[k] = (uint32_t)v;
         carry = v >> 32;  // arithmetic shift: floor division by 2^32
     }
-    return carry;
 }
 
-// The sum held by normalized limbs and their final carry, rounded once to
-// binary64 (nearest, ties to even; an exact zero is +0).  Destroys lim.
-__device__ __forceinline__ double exact_round_normalized(int64_t *lim, int64_t carry)
-{
-    const bool neg = carry < 0;
-    if (neg) {  // magnitude = 2^(32 XL) - digits
-        int64_t c = 1;
-        for (int k = 0; k < XL; ++k) {
-            const int64_t v = (~lim[k] & 0xffffffffll) + c;
-            lim[k] = v & 0xffffffffll;
-            c = v >> 32;
-        }
+// The leading digits of a magnitude whose digits arrive from the lowest up:
+// the highest nonzero digit, the two below it, and whether any lower bit is set.
+struct LeadingDigits {
+    uint32_t w0 = 0, w1 = 0, w2 = 0, p1 = 0, p2 = 0;
+    bool sticky = false, low = false;
+    int top = -1;
+
+    __device__ __forceinline__ void push(uint32_t v, int k)
+    {
+        const bool nz = v != 0;
+        w0 = nz ? v : w0;
+        w1 = nz ? p1 : w1;
+        w2 = nz ? p2 : w2;
+        sticky = nz ? low : sticky;
+        top = nz ? k : top;
+        low |= p2 != 0;
+        p2 = p1;
+        p1 = v;
     }
-    int top = XL - 1;
-    while (top >= 0 && lim[top] == 0) --top;
-    if (top < 0) return 0.0;
-    const int b = 32 * top + (32 - __builtin_clz((uint32_t)lim[top]));  // bit length of the magnitude
-    double r;
-    if (b <= 53) {  // exact: subnormal, or normal with at most 53 bits
-        const uint64_t v = (uint64_t)lim[0] | (top >= 1 ? (uint64_t)lim[1] << 32 : 0ull);
-        r = ldexp((double)v, -1074);
-    } else {
-        // T: the 64 bits below the leading one (inclusive); sticky: any lower bit
-        const int s = b - 64;
-        uint64_t T;
-        bool sticky = false;
-        if (s <= 0) {
-            T = ((uint64_t)lim[0] | ((uint64_t)lim[1] << 32)) << (-s);
-        } else {
-            const int w = s >> 5, q = s & 31;
-            const uint64_t x = (uint64_t)lim[w] | ((uint64_t)lim[w + 1] << 32);
-            const uint64_t y = w + 2 < XL ? (uint64_t)lim[w + 2] : 0ull;
-            T = q ? (x >> q) | (y << (64 - q)) : x;
-            sticky = q && ((uint64_t)lim[w] & ((1ull << q) - 1)) != 0;
-            for (int k = 0; k < w; ++k) sticky |= lim[k] != 0;
-        }
+
+    // The magnitude rounded once to binary64 (nearest, ties to even).
+    __device__ __forceinline__ double round() const
+    {
+        if (top < 0) return 0.0;
+        const uint64_t hi = (uint64_t)w0 << 32 | w1;
+        const int lz = __builtin_clz(w0);
+        const int b = 32 * top + 32 - lz;  // bit length
+        if (b <= 53)  // exact: subnormal, or normal with at most 53 bits
+            return ldexp((double)(top >= 1 ? hi : (uint64_t)w0), -1074);
+        // T: the 64 bits from the leading one down; the rest decides ties
+        const uint64_t T = lz ? hi << lz | w2 >> (32 - lz) : hi;
+        const bool more = sticky || (uint32_t)(w2 << lz) != 0;
         uint64_t mant = T >> 11;
         const uint64_t rest = T & 0x7ff;
-        if ((rest & 0x400) && ((rest & 0x3ff) || sticky || (mant & 1))) ++mant;
+        if ((rest & 0x400) && ((rest & 0x3ff) || more || (mant & 1))) ++mant;
         int e = b - 53;
         if (mant == (1ull << 53)) {
             mant >>= 1;
             ++e;
         }
-        r = ldexp((double)mant, e - 1074);  // exact, or overflow to infinity
+        return ldexp((double)mant, e - 1074);  // exact, or overflow to infinity
     }
-    return neg ? -r : r;
-}
+};
 
-__device__ __forceinline__ double exact_round(int64_t *lim)
+// The sum held by digits lo .. hi less x (finite; 0 takes nothing away),
+// rounded once to binary64 (an exact zero is +0).  The digits are read twice,
+// for the sign of the difference and then for its magnitude, so that no digit
+// array is kept in registers.
+__device__ __forceinline__ double exact_round_less(const uint32_t *dig, int lo, int hi, double x)
 {
-    const int64_t c = exact_normalize(lim);
-    return exact_round_normalized(lim, c);
+    const ExactDigits g = exact_digits(x, true);
+    const auto digit = [&](int k) {
+        const int64_t t = k == hi ? (int64_t)(int32_t)dig[k] : (int64_t)dig[k];
+        const int j = k - g.i;
+        return t + (j == 0 ? g.d0 : j == 1 ? g.d1 : j == 2 ? g.d2 : 0);
+    };
+    int64_t c = 0;
+    for (int k = lo; k <= hi; ++k) c = (digit(k) + c) >> (k == hi ? 63 : 32);
+    const bool neg = c < 0;
+    LeadingDigits m;
+    c = 0;
+    for (int k = lo; k <= hi; ++k) {
+        const int64_t d = digit(k), v = (neg ? -d : d) + c;
+        m.push((uint32_t)v, k);
+        c = v >> 32;
+    }
+    const double r = m.round();
+    return neg ? -r : r;
 }
 
 // Result of a sum with non-finite terms (counts n_nan, n_pinf, n_ninf), or

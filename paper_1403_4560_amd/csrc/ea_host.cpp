@@ -40,8 +40,10 @@ __global__ void energy_kernel(const SampleDev *, const int32_t *, const int8_t *
                               int32_t *);
 __global__ void snapshot_kernel(const SampleDev *, const int32_t *, const int8_t *, const int32_t *,
                                 const int64_t *, const int32_t *, int, uint32_t *, double *);
-__global__ void finalize_kernel(const SampleDev *, const int32_t *, int, int, double, const double *, int, double *,
-                                double *, double *);
+__global__ void finalize_sums_kernel(const int32_t *, int, int, const double *, FinColumn *);
+__global__ void finalize_values_kernel(const int32_t *, int, int, int, int, double, const double *, const FinColumn *,
+                                       double *, double *);
+__global__ void finalize_errors_kernel(int, const double *, double *);
 }  // namespace ea
 
 using namespace ea;
@@ -133,7 +135,7 @@ struct ea_ensemble {
     // device buffers
     DevBuf samples, items, spins, J, beta, beta32, lut, was, EJ, M, flips, swaps, acc, frames, frameE,
         state, slot_sample, costab, sintab, scratchE, scratchM, finout, walkers, dEJ, dM, sow, Ju, mslots, Jbits,
-        sel;
+        sel, fincols;
     int64_t frames_cap = 0;  // frames allocated
     std::vector<double> beta_host;  // [total_slots], to check that a finalize selection is one system
     std::vector<int32_t> sel_idx;   // [S] a finalize call's selection (no allocation per call)
@@ -306,7 +308,7 @@ void destroy_all(ea_ensemble *e)
                       &e->was, &e->EJ, &e->M, &e->flips, &e->swaps, &e->acc, &e->frames,
                       &e->frameE, &e->state, &e->slot_sample, &e->costab, &e->sintab,
                       &e->scratchE, &e->scratchM, &e->finout, &e->walkers, &e->dEJ, &e->dM,
-                      &e->sow, &e->Ju, &e->mslots, &e->Jbits, &e->sel, &e->jkrep, &e->batchbuf};
+                      &e->sow, &e->Ju, &e->mslots, &e->Jbits, &e->sel, &e->jkrep, &e->batchbuf, &e->fincols};
     for (DevBuf *b : bufs) dfree(*b);
     if (e->own_stream && e->stream) (void)hipStreamDestroy(e->stream);
     delete e;
@@ -892,9 +894,12 @@ ea_status run_sweeps(ea_ensemble *e, int64_t n, bool unbatched)
 
 // The selection of a finalize call: n indices into the ensemble (every
 // sample when sel is NULL), distinct, all of one system -- the same lattice
-// size, temperature ladder (every beta, bit for bit) and field.  Copies it to
-// the device.  Uses only the ensemble's own host buffers (no allocation).
-ea_status finalize_selection(ea_ensemble *e, const int32_t *sel, int32_t n, int min_count, int *count)
+// size, temperature ladder (every beta, bit for bit) and field.  *s0 receives the
+// first sample; the first slots of a given selection go to the device (every
+// sample of one system needs none: sample i starts at slot i n_T).  Uses only
+// the ensemble's own host buffers (no allocation).
+ea_status finalize_selection(ea_ensemble *e, const int32_t *sel, int32_t n, int min_count, int *count,
+                             int *s0)
 {
     int32_t *idx = e->sel_idx.data();
     int cnt = e->S;
@@ -923,9 +928,12 @@ ea_status finalize_selection(ea_ensemble *e, const int32_t *sel, int32_t n, int 
         if (std::memcmp(&e->beta_host[b.slot_off], &e->beta_host[a.slot_off], sizeof(double) * a.nT) != 0)
             return fail(EA_EINVAL, "samples %d and %d have different temperature ladders", idx[0], idx[i]);
     }
+    *s0 = idx[0];
+    *count = cnt;
+    if (!sel) return EA_OK;
+    for (int i = 0; i < cnt; ++i) idx[i] = e->smp[idx[i]].slot_off;
     HIP_TRY(e, hipMemcpyAsync(e->sel.p, idx, sizeof(int32_t) * cnt, hipMemcpyHostToDevice, e->stream));
     HIP_TRY(e, hipStreamSynchronize(e->stream));
-    *count = cnt;
     return EA_OK;
 }
 
@@ -939,10 +947,9 @@ ea_status run_finalize(ea_ensemble *e, const int32_t *sel, int32_t n, double *ou
                        double *rep)
 {
     const bool jk = out_err != nullptr;
-    int count = 0;
-    ea_status st = finalize_selection(e, sel, n, jk ? 2 : 1, &count);
+    int count = 0, s0 = 0;
+    ea_status st = finalize_selection(e, sel, n, jk ? 2 : 1, &count, &s0);
     if (st) return st;
-    const int s0 = e->sel_idx[0];
     const int L = e->smp[s0].L, nT = e->smp[s0].nT;
     if (jk && !rep) {
         const size_t need = jk_rep_doubles(nT, count) * sizeof(double);
@@ -957,10 +964,21 @@ ea_status run_finalize(ea_ensemble *e, const int32_t *sel, int32_t n, double *ou
     }
     const double two_sin = 2.0 * std::sin(M_PI / (double)L);
     double *dm = (double *)e->finout.p, *de = dm + (size_t)MAX_T * EA_NOBS;
-    hipLaunchKernelGGL(finalize_kernel, dim3(nT), dim3(256), 0, e->stream, (const SampleDev *)e->samples.p,
-                       (const int32_t *)e->sel.p, count, L, two_sin, (const double *)e->acc.p, jk ? 1 : 0, rep, dm,
-                       de);
+    const int32_t *off = sel ? (const int32_t *)e->sel.p : nullptr;
+    const double *acc = (const double *)e->acc.p;
+    FinColumn *cols = (FinColumn *)e->fincols.p;
+    hipLaunchKernelGGL(finalize_sums_kernel, dim3(NACC / FIN_SUM_COLS, nT), dim3(256), 0, e->stream, off, count, nT,
+                       acc, cols);
     HIP_TRY(e, hipGetLastError());
+    const int tiles = jk ? (count + FIN_VAL_TILE - 1) / FIN_VAL_TILE : 1;
+    hipLaunchKernelGGL(finalize_values_kernel, dim3(tiles, nT), dim3(256), 0, e->stream, off, jk ? count : 0, count, nT,
+                       L, two_sin, acc, (const FinColumn *)cols, rep, dm);
+    HIP_TRY(e, hipGetLastError());
+    if (jk) {
+        hipLaunchKernelGGL(finalize_errors_kernel, dim3(EA_NOBS - 1, nT), dim3(256), 0, e->stream, count,
+                           (const double *)rep, de);
+        HIP_TRY(e, hipGetLastError());
+    }
     HIP_TRY(e, hipMemcpyAsync(out_mean, dm, sizeof(double) * nT * EA_NOBS, hipMemcpyDeviceToHost, e->stream));
     if (jk) HIP_TRY(e, hipMemcpyAsync(out_err, de, sizeof(double) * nT * EA_NOBS, hipMemcpyDeviceToHost, e->stream));
     HIP_TRY(e, hipStreamSynchronize(e->stream));
@@ -1366,6 +1384,9 @@ ea_status ea_create_ensemble(const ea_desc *d, void *hip_stream, ea_ensemble **o
             ALLOC_BUF(*bufs[k], sz[k]);
         }
     }
+    int nT_max = 1;
+    for (const SampleHost &s : e->smp) nT_max = std::max(nT_max, s.nT);
+    ALLOC_BUF(e->fincols, sizeof(FinColumn) * NACC * (size_t)nT_max);
 #undef ALLOC_BUF
     {
         ea_status fs = ensure_frames(e, e->plan.chunk);

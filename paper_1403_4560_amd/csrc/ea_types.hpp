@@ -133,6 +133,26 @@ struct BatchArgs {
     int32_t *counter;  // reserved
 };
 
+// Limbs of an exact sum (ea_exact.hpp): bit offsets 0 .. 2097 hold one value
+// (significand at offset up to 2045, 53 bits); the rest is headroom for the
+// carries of up to 2^30 values.
+constexpr int XL = 68;
+
+// The exact sum over samples of one accumulator column of a slot: digits lo ..
+// hi in two's complement, the counts of non-finite values (NaN, +inf, -inf)
+// and the rounded sum divided by the number of samples.
+struct FinColumn {
+    double D;
+    int32_t lo, hi;
+    int32_t spec[3];
+    int32_t pad;
+    uint32_t dig[XL];
+};
+
+// Columns of a slot that one workgroup of the sums sums, and samples of a slot
+// that one workgroup of the jackknife replicates takes (ea_finalize.hip).
+constexpr int FIN_SUM_COLS = 4, FIN_VAL_TILE = 16;
+
 // Number of measurement sweeps among completed-sweep counts 1..x.
 __host__ __device__ inline int64_t measurements_upto(int64_t x, int32_t m, int64_t start)
 {

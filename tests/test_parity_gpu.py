@@ -414,6 +414,34 @@ def test_finalize_exact_sums_on_adversarial_accumulators(torch_cuda, S, seed):
         same_obs({k: v[1] for k, v in got.items()}, {k: v[1] for k, v in rjk.items()})
 
 
+@pytest.mark.parametrize("S", [2, 6, 32, 33, 65, 257])
+def test_finalize_at_tile_edges(torch_cuda, S):
+    """Selections around the kernels' tiles (32 samples of a replicate tile, 64
+    of a sum's step, 256 of an error's), whole and as a reversed selection less
+    its last sample: bit-identical to the oracle."""
+    from paper_1403_4560_amd import binding
+    nT, L = 3, 4
+    work = W.make_workload([L] * S, nT, (0.5, 2.0), 0.2, name="tile edges")
+    if S > 5:
+        acc = adversarial_accumulators(S, nT, S)
+    else:
+        rng = np.random.default_rng(S)
+        acc = rng.normal(size=(S, nT, O.NACC)) * 2.0 ** rng.integers(-40, 40, size=(S, nT, O.NACC))
+        acc[..., 0] = 7.0
+    print("case: finalize tile edges S=%d" % S, flush=True)
+    with binding.Ensemble(work) as ens:
+        ens.load_accumulators(acc=[acc[s] for s in range(S)])
+        sels = [None] + ([list(range(S - 1))[::-1]] if S > 2 else [])
+        got = [(s, ens.finalize(s), ens.finalize_jackknife(s), ens.finalize_jackknife(s, noalloc=True)) for s in sels]
+    for sel, fin, jk, jk2 in got:
+        a = acc if sel is None else acc[sel]
+        same_obs(fin, O.observables(a, L))
+        rjk = O.jackknife(a, L)
+        for j in (jk, jk2):
+            same_obs({k: v[0] for k, v in j.items()}, {k: v[0] for k, v in rjk.items()})
+            same_obs({k: v[1] for k, v in j.items()}, {k: v[1] for k, v in rjk.items()})
+
+
 def test_failed_frame_allocation_leaves_the_ensemble_usable(torch_cuda):
     """A chunk whose snapshot frames cannot be allocated fails with
     EA_ENOMEM and leaves the ensemble as it was (old frames and capacity):
