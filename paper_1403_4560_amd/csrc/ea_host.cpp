@@ -38,6 +38,11 @@ __global__ void exchange_bracket_kernel(uint32_t, uint32_t, unsigned long long *
 template <int JK>
 __global__ void energy_kernel(const SampleDev *, const int32_t *, const int8_t *, const void *, int64_t *,
                               int32_t *);
+template <bool TO_NATURAL>
+__global__ void split_spins_kernel(const SampleDev *, const int32_t *, const int32_t *, int64_t, int64_t, int8_t *,
+                                   int8_t *);
+template <class T>
+__global__ void split_couplings_kernel(const SampleDev *, int, int64_t, const T *, T *, int32_t *);
 __global__ void snapshot_kernel(const SampleDev *, const int32_t *, const int8_t *, const int32_t *,
                                 const int64_t *, const int32_t *, int, uint32_t *, double *);
 __global__ void finalize_sums_kernel(const int32_t *, int, int, const double *, FinColumn *);
@@ -126,6 +131,7 @@ struct ea_ensemble {
     int64_t mstart = 0;
     std::vector<SampleHost> smp;
     int64_t total_slots = 0, spin_bytes = 0, J_elems = 0, frame_words = 0;
+    int nT_max = 1, N_max = 1;  // over the samples
     hipStream_t stream = nullptr;
     bool own_stream = false;
     bool dead = false;
@@ -135,7 +141,7 @@ struct ea_ensemble {
     // device buffers
     DevBuf samples, items, spins, J, beta, beta32, lut, was, EJ, M, flips, swaps, acc, frames, frameE,
         state, slot_sample, costab, sintab, scratchE, scratchM, finout, walkers, dEJ, dM, sow, Ju, mslots, Jbits,
-        sel, fincols;
+        sel, fincols, stage;
     int64_t frames_cap = 0;  // frames allocated
     std::vector<double> beta_host;  // [total_slots], to check that a finalize selection is one system
     std::vector<int32_t> sel_idx;   // [S] a finalize call's selection (no allocation per call)
@@ -218,7 +224,22 @@ void dfree(DevBuf &b)
     b.owned = true;
 }
 
-int parity(int L, int i) { return (i % L + (i / L) % L + i / (L * L)) & 1; }
+// The index of the first of n spins that is not +-1, or -1.  Whole blocks are
+// checked without a branch (v + 1 is 0 or 2), so that a valid array costs one
+// pass over the memory.
+int64_t bad_spin(const int8_t *v, int64_t n)
+{
+    constexpr int64_t BLOCK = 4096;
+    for (int64_t i = 0; i < n; i += BLOCK) {
+        const int64_t m = std::min(BLOCK, n - i);
+        uint8_t bad = 0;
+        for (int64_t j = 0; j < m; ++j) bad |= (uint8_t)((uint8_t)(v[i + j] + 1) & 0xFDu);
+        if (!bad) continue;
+        for (int64_t j = 0; j < m; ++j)
+            if (v[i + j] != 1 && v[i + j] != -1) return i + j;
+    }
+    return -1;
+}
 
 bool usable(const ea_ensemble *e)
 {
@@ -271,10 +292,8 @@ ea_status validate(const ea_desc *d)
                 if (v != 1 && v != -1) return fail(EA_EINVAL, "sample %d: coupling %lld not +-1", s, (long long)i);
             }
         }
-        for (int64_t i = 0; i < 2 * nT * N; ++i) {
-            const int8_t v = d->spins0[soff + i];
-            if (v != 1 && v != -1) return fail(EA_EINVAL, "sample %d: spin %lld not +-1", s, (long long)i);
-        }
+        const int64_t bad = bad_spin(d->spins0 + soff, 2 * nT * N);
+        if (bad >= 0) return fail(EA_EINVAL, "sample %d: spin %lld not +-1", s, (long long)bad);
         boff += nT;
         joff += 3 * N;
         soff += 2 * nT * N;
@@ -308,7 +327,7 @@ void destroy_all(ea_ensemble *e)
                       &e->was, &e->EJ, &e->M, &e->flips, &e->swaps, &e->acc, &e->frames,
                       &e->frameE, &e->state, &e->slot_sample, &e->costab, &e->sintab,
                       &e->scratchE, &e->scratchM, &e->finout, &e->walkers, &e->dEJ, &e->dM,
-                      &e->sow, &e->Ju, &e->mslots, &e->Jbits, &e->sel, &e->jkrep, &e->batchbuf, &e->fincols};
+                      &e->sow, &e->Ju, &e->mslots, &e->Jbits, &e->sel, &e->jkrep, &e->batchbuf, &e->fincols, &e->stage};
     for (DevBuf *b : bufs) dfree(*b);
     if (e->own_stream && e->stream) (void)hipStreamDestroy(e->stream);
     delete e;
@@ -409,6 +428,96 @@ MeasureArgs measure_args(const ea_ensemble *e, int K, int explicit_frames)
     M.measure_every = e->m;
     M.measure_start = e->mstart;
     return M;
+}
+
+// Energies and magnetisations of every walker from its spins.
+void launch_energies(const ea_ensemble *e, const DevBuf &EJ, const DevBuf &M)
+{
+    hipLaunchKernelGGL(e->jkind == EA_J_GAUSS_F32 ? energy_kernel<0> : energy_kernel<1>, dim3(2 * e->S, e->nT_max),
+                       dim3(256), 0, e->stream, (const SampleDev *)e->samples.p, (const int32_t *)e->items.p,
+                       (const int8_t *)e->spins.p, (const void *)e->J.p, (int64_t *)EJ.p, (int32_t *)M.p);
+}
+
+// Device staging for arrays in the caller's order: at most STAGE_BYTES (larger
+// arrays go through it in pieces), less if that much is not to be had, at
+// least one piece.  Kept until the ensemble goes (freeing it would wait for
+// every stream of the device).
+constexpr size_t STAGE_BYTES = (size_t)64 << 20;
+
+ea_status ensure_stage(ea_ensemble *e, size_t total, size_t piece)
+{
+    const size_t want = std::max(std::min(total, STAGE_BYTES), piece);
+    if (e->stage.bytes >= want) return EA_OK;
+    DevBuf nb;
+    ea_status st = EA_OK;
+    for (size_t n = want;; n = std::max(n / 2, piece)) {
+        if (e->stage.bytes >= n) return EA_OK;
+        if ((st = dalloc(e, nb, n)) == EA_OK || n == piece) break;
+    }
+    if (st) return st;
+    e->device_bytes -= (int64_t)e->stage.bytes;
+    dfree(e->stage);  // (waits for the device, so nothing queued still uses it)
+    e->stage = nb;
+    return EA_OK;
+}
+
+// Every walker's spins between the caller's host array (slot order, natural
+// site order) and the device layout, by the walker map on the device, through
+// the staging buffer (which ensure_stage has made at least a walker's N bytes).
+ea_status transfer_spins(ea_ensemble *e, int8_t *host, bool to_host)
+{
+    const int64_t cap = (int64_t)e->stage.bytes, rows = 2 * e->total_slots;
+    int64_t row = 0, off = 0;
+    int s = 0;
+    while (row < rows) {
+        // rows row .. next - 1 (off .. end - 1 in bytes) fill the stage
+        int64_t next = row, end = off;
+        while (next < rows) {
+            while (2 * ((int64_t)e->smp[s].slot_off + e->smp[s].nT) <= next) ++s;
+            const SampleHost &h = e->smp[s];
+            const int64_t left = 2 * ((int64_t)h.slot_off + h.nT) - next, fit = std::min(left, (cap - (end - off)) / h.N);
+            next += fit;
+            end += fit * h.N;
+            if (fit < left) break;
+        }
+        if (!to_host)
+            HIP_TRY(e, hipMemcpyAsync(e->stage.p, host + off, end - off, hipMemcpyHostToDevice, e->stream));
+        hipLaunchKernelGGL(to_host ? split_spins_kernel<true> : split_spins_kernel<false>, dim3((unsigned)(next - row)),
+                           dim3(256), 0, e->stream, (const SampleDev *)e->samples.p,
+                           (const int32_t *)e->slot_sample.p, (const int32_t *)e->was.p, row, off,
+                           (int8_t *)e->stage.p, (int8_t *)e->spins.p);
+        HIP_TRY(e, hipGetLastError());
+        if (to_host)
+            HIP_TRY(e, hipMemcpyAsync(host + off, e->stage.p, end - off, hipMemcpyDeviceToHost, e->stream));
+        row = next;
+        off = end;
+    }
+    return EA_OK;
+}
+
+// The caller's couplings to the device layout, likewise.
+ea_status upload_couplings(ea_ensemble *e, const void *host)
+{
+    const int64_t jsz = e->jkind == EA_J_GAUSS_F32 ? 4 : 1, cap = (int64_t)e->stage.bytes / jsz;
+    for (int s = 0; s < e->S;) {
+        const int64_t base = e->smp[s].J_off;
+        int next = s;
+        int64_t end = base;
+        while (next < e->S && end + 3 * (int64_t)e->smp[next].N - base <= cap) end += 3 * (int64_t)e->smp[next++].N;
+        HIP_TRY(e, hipMemcpyAsync(e->stage.p, (const char *)host + base * jsz, (end - base) * jsz, hipMemcpyHostToDevice,
+                                  e->stream));
+        if (jsz == 4)
+            hipLaunchKernelGGL(split_couplings_kernel<float>, dim3(next - s, 3), dim3(256), 0, e->stream,
+                               (const SampleDev *)e->samples.p, s, base, (const float *)e->stage.p, (float *)e->J.p,
+                               (int32_t *)e->Ju.p);
+        else
+            hipLaunchKernelGGL(split_couplings_kernel<int8_t>, dim3(next - s, 3), dim3(256), 0, e->stream,
+                               (const SampleDev *)e->samples.p, s, base, (const int8_t *)e->stage.p, (int8_t *)e->J.p,
+                               (int32_t *)nullptr);
+        HIP_TRY(e, hipGetLastError());
+        s = next;
+    }
+    return EA_OK;
 }
 
 using SweepFn = void (*)(SweepArgs);
@@ -1146,6 +1255,10 @@ ea_status ea_create_ensemble(const ea_desc *d, void *hip_stream, ea_ensemble **o
     e->spin_bytes = tot.spin_bytes;
     e->J_elems = tot.J_elems;
     e->frame_words = tot.frame_words;
+    for (const SampleHost &h : e->smp) {
+        e->nT_max = std::max(e->nT_max, h.nT);
+        e->N_max = std::max(e->N_max, h.N);
+    }
 
     if (hip_stream) {
         e->stream = (hipStream_t)hip_stream;
@@ -1239,9 +1352,6 @@ ea_status ea_create_ensemble(const ea_desc *d, void *hip_stream, ea_ensemble **o
     const int S = e->S;
     std::vector<SampleDev> sd(S);
     std::vector<int32_t> items(2 * S), slot_sample(e->total_slots);
-    std::vector<int8_t> spins(e->spin_bytes);
-    const size_t jsz = e->jkind == EA_J_GAUSS_F32 ? 4 : 1;
-    std::vector<char> Jsub((size_t)e->J_elems * jsz);
     std::vector<double> beta(e->total_slots);
     std::vector<float> beta32(e->total_slots);
     e->beta_host.assign(d->beta, d->beta + e->total_slots);
@@ -1252,7 +1362,6 @@ ea_status ea_create_ensemble(const ea_desc *d, void *hip_stream, ea_ensemble **o
     std::vector<int32_t> was(2 * e->total_slots);
     for (int s = 0; s < S; ++s) {
         const SampleHost &h = e->smp[s];
-        const int N = h.N, HALF = N / 2;
         sd[s] = SampleDev{h.L, h.nT, h.id, h.h, h.spin_off, h.J_off, h.slot_off, h.hbm ? 1 : 0, h.frame_off,
                           down_mask_of(h.h), field_grid(h.h), h.jb_off};
         items[e->item_pos[s]] = 2 * s;
@@ -1263,17 +1372,6 @@ ea_status ea_create_ensemble(const ea_desc *d, void *hip_stream, ea_ensemble **o
             beta32[h.slot_off + t] = (float)d->beta[h.slot_off + t];
             was[2 * h.slot_off + t] = t;
             was[2 * h.slot_off + h.nT + t] = t;
-        }
-        for (int i = 0; i < N; ++i) {
-            const int p = parity(h.L, i), hh = i >> 1;
-            for (int dd = 0; dd < 3; ++dd)
-                std::memcpy(&Jsub[((size_t)h.J_off + (size_t)p * 3 * HALF + dd * HALF + hh) * jsz],
-                            (const char *)d->J + ((size_t)h.J_off + (size_t)dd * N + i) * jsz, jsz);
-        }
-        for (int rw = 0; rw < 2 * h.nT; ++rw) {
-            const int8_t *src = d->spins0 + h.spin_off + (size_t)rw * N;
-            int8_t *dst = spins.data() + h.spin_off + (size_t)rw * N;
-            for (int i = 0; i < N; ++i) dst[parity(h.L, i) * HALF + (i >> 1)] = src[i];
         }
         if (e->jkind == EA_J_PM1_I8) {
             for (int t = 0; t < h.nT; ++t)
@@ -1314,12 +1412,6 @@ ea_status ea_create_ensemble(const ea_desc *d, void *hip_stream, ea_ensemble **o
             }
             e->slot_classes.back().count = (int)mslots.size() - e->slot_classes.back().begin;
         }
-    }
-    std::vector<int32_t> Ju;
-    if (e->any_hbm && e->jkind == EA_J_GAUSS_F32) {
-        Ju.resize(e->J_elems);
-        const float *Jf = (const float *)Jsub.data();
-        for (int64_t i = 0; i < e->J_elems; ++i) Ju[i] = (int32_t)(Jf[i] * 262144.0f);
     }
     // multispin engine: bond bits aligned to the sites of each parity,
     // [2][6][N/64] words per sample, directions +x, -x, +y, -y, +z, -z
@@ -1368,11 +1460,11 @@ ea_status ea_create_ensemble(const ea_desc *d, void *hip_stream, ea_ensemble **o
         size_t sz[NARENA];
         arena_sizes(S, e->jkind, tot, sz);
         const size_t host_sz[NARENA] = {
-            sizeof(SampleDev) * S, sizeof(int32_t) * items.size(), spins.size(), Jsub.size(),
+            sizeof(SampleDev) * S, sizeof(int32_t) * items.size(), sz[2], sz[3],
             sizeof(double) * beta.size(), sizeof(float) * beta32.size(), sizeof(uint32_t) * lut.size(),
             sizeof(int32_t) * was.size(), sz[8], sz[9], sz[10], sz[11], sz[12], sz[13],
             sizeof(int32_t) * slot_sample.size(), sizeof(double) * costab.size(), sizeof(double) * sintab.size(),
-            sz[17], sz[18], sz[19], sz[20], sizeof(int32_t) * wtab.size(), sizeof(int32_t) * Ju.size(),
+            sz[17], sz[18], sz[19], sz[20], sizeof(int32_t) * wtab.size(), sz[22],
             sizeof(int32_t) * mslots.size(), sizeof(uint32_t) * Jbits.size(), sz[25], sz[26]};
         DevBuf *bufs[NARENA];
         arena_buffers(e, bufs);
@@ -1384,9 +1476,7 @@ ea_status ea_create_ensemble(const ea_desc *d, void *hip_stream, ea_ensemble **o
             ALLOC_BUF(*bufs[k], sz[k]);
         }
     }
-    int nT_max = 1;
-    for (const SampleHost &s : e->smp) nT_max = std::max(nT_max, s.nT);
-    ALLOC_BUF(e->fincols, sizeof(FinColumn) * NACC * (size_t)nT_max);
+    ALLOC_BUF(e->fincols, sizeof(FinColumn) * NACC * (size_t)e->nT_max);
 #undef ALLOC_BUF
     {
         ea_status fs = ensure_frames(e, e->plan.chunk);
@@ -1405,8 +1495,6 @@ ea_status ea_create_ensemble(const ea_desc *d, void *hip_stream, ea_ensemble **o
     } while (0)
     H2D(samples, sd.data(), sizeof(SampleDev) * S);
     H2D(items, items.data(), sizeof(int32_t) * 2 * S);
-    H2D(spins, spins.data(), (size_t)e->spin_bytes);
-    H2D(J, Jsub.data(), Jsub.size());
     H2D(beta, beta.data(), sizeof(double) * TS);
     H2D(beta32, beta32.data(), sizeof(float) * TS);
     H2D(lut, lut.data(), sizeof(uint32_t) * 14 * TS);
@@ -1414,12 +1502,24 @@ ea_status ea_create_ensemble(const ea_desc *d, void *hip_stream, ea_ensemble **o
     H2D(slot_sample, slot_sample.data(), sizeof(int32_t) * TS);
     H2D(sow, was.data(), sizeof(int32_t) * 2 * TS);  // identity, like walker_at_slot
     if (!wtab.empty()) H2D(walkers, wtab.data(), sizeof(int32_t) * wtab.size());
-    if (!Ju.empty()) H2D(Ju, Ju.data(), sizeof(int32_t) * Ju.size());
     H2D(mslots, mslots.data(), sizeof(int32_t) * mslots.size());
     if (!Jbits.empty()) H2D(Jbits, Jbits.data(), sizeof(uint32_t) * Jbits.size());
     H2D(costab, costab.data(), sizeof(double) * costab.size());
     H2D(sintab, sintab.data(), sizeof(double) * sintab.size());
 #undef H2D
+    {
+        // couplings and spins: copied as they are, brought into the device
+        // layout there
+        const size_t jsz = e->jkind == EA_J_GAUSS_F32 ? 4 : 1;
+        const size_t jbytes = (size_t)e->J_elems * jsz, piece = 3 * (size_t)e->N_max * jsz;
+        ea_status us = ensure_stage(e, std::max((size_t)e->spin_bytes, jbytes), piece);
+        if (us == EA_OK) us = upload_couplings(e, d->J);
+        if (us == EA_OK) us = transfer_spins(e, const_cast<int8_t *>(d->spins0), false);
+        if (us) {
+            destroy_all(e);
+            return us;
+        }
+    }
     if (hipMemsetAsync(e->flips.p, 0, e->flips.bytes, e->stream) != hipSuccess ||
         hipMemsetAsync(e->swaps.p, 0, e->swaps.bytes, e->stream) != hipSuccess ||
         hipMemsetAsync(e->acc.p, 0, e->acc.bytes, e->stream) != hipSuccess ||
@@ -1437,14 +1537,7 @@ ea_status ea_create_ensemble(const ea_desc *d, void *hip_stream, ea_ensemble **o
         }
     }
     // initial energies from scratch on the device
-    if (e->jkind == EA_J_GAUSS_F32)
-        hipLaunchKernelGGL(energy_kernel<0>, dim3(2 * S), dim3(256), 0, e->stream, (const SampleDev *)e->samples.p,
-                           (const int32_t *)e->items.p, (const int8_t *)e->spins.p, e->J.p, (int64_t *)e->EJ.p,
-                           (int32_t *)e->M.p);
-    else
-        hipLaunchKernelGGL(energy_kernel<1>, dim3(2 * S), dim3(256), 0, e->stream, (const SampleDev *)e->samples.p,
-                           (const int32_t *)e->items.p, (const int8_t *)e->spins.p, e->J.p, (int64_t *)e->EJ.p,
-                           (int32_t *)e->M.p);
+    launch_energies(e, e->EJ, e->M);
     hipError_t le = hipGetLastError();
     if (le == hipSuccess) le = hipStreamSynchronize(e->stream);
     if (le != hipSuccess) {
@@ -1492,10 +1585,13 @@ ea_status ea_read_state(ea_ensemble *e, int8_t *spins_out, int32_t *was_out, dou
 {
     if (!usable(e)) return EA_ESTATE;
     const int64_t TS = e->total_slots;
-    std::vector<int8_t> sp(spins_out ? e->spin_bytes : 0);
     std::vector<int32_t> was(2 * TS), M(2 * TS);
     std::vector<int64_t> EJ(2 * TS);
-    if (spins_out) HIP_TRY(e, hipMemcpyAsync(sp.data(), e->spins.p, e->spin_bytes, hipMemcpyDeviceToHost, e->stream));
+    if (spins_out) {
+        ea_status st = ensure_stage(e, (size_t)e->spin_bytes, (size_t)e->N_max);
+        if (st == EA_OK) st = transfer_spins(e, spins_out, true);
+        if (st) return st;
+    }
     HIP_TRY(e, hipMemcpyAsync(was.data(), e->was.p, e->was.bytes, hipMemcpyDeviceToHost, e->stream));
     HIP_TRY(e, hipMemcpyAsync(EJ.data(), e->EJ.p, e->EJ.bytes, hipMemcpyDeviceToHost, e->stream));
     HIP_TRY(e, hipMemcpyAsync(M.data(), e->M.p, e->M.bytes, hipMemcpyDeviceToHost, e->stream));
@@ -1503,18 +1599,12 @@ ea_status ea_read_state(ea_ensemble *e, int8_t *spins_out, int32_t *was_out, dou
     const double unit = e->jkind == EA_J_GAUSS_F32 ? 0x1p-18 : 1.0;
     for (int s = 0; s < e->S; ++s) {
         const SampleHost &h = e->smp[s];
-        const int N = h.N, HALF = N / 2;
         for (int r = 0; r < 2; ++r)
             for (int t = 0; t < h.nT; ++t) {
                 const size_t gi = 2 * (size_t)h.slot_off + (size_t)r * h.nT;
                 const int w = was[gi + t];
                 if (was_out) was_out[gi + t] = w;
                 if (E_out) E_out[gi + t] = (double)EJ[gi + w] * unit - (double)h.h * (double)M[gi + w];
-                if (spins_out) {
-                    const int8_t *src = sp.data() + h.spin_off + ((size_t)r * h.nT + w) * N;
-                    int8_t *dst = spins_out + h.spin_off + ((size_t)r * h.nT + t) * N;
-                    for (int i = 0; i < N; ++i) dst[i] = src[parity(h.L, i) * HALF + (i >> 1)];
-                }
             }
     }
     if (sweep) *sweep = e->sweep;
@@ -1526,12 +1616,10 @@ ea_status ea_write_state(ea_ensemble *e, const int8_t *spins_in, const int32_t *
     if (!usable(e)) return EA_ESTATE;
     if (!spins_in) return fail(EA_EINVAL, "spins is NULL");
     if (sweep < 0 || sweep > ((int64_t)1 << 31) - 1) return fail(EA_EINVAL, "sweep out of range");
-    std::vector<int8_t> sp(e->spin_bytes);
     std::vector<int32_t> was(2 * e->total_slots), sow(2 * e->total_slots);
     std::vector<char> seen;
     for (int s = 0; s < e->S; ++s) {
         const SampleHost &h = e->smp[s];
-        const int N = h.N, HALF = N / 2;
         for (int r = 0; r < 2; ++r) {
             // the walker at each slot of chain r, checked to be a permutation
             const size_t base = 2 * (size_t)h.slot_off + (size_t)r * h.nT;
@@ -1544,30 +1632,19 @@ ea_status ea_write_state(ea_ensemble *e, const int8_t *spins_in, const int32_t *
                 was[base + t] = w;
                 sow[base + w] = t;
             }
-            // slot t's spins (natural site order) become walker was[t]'s, sublattice-split
-            for (int t = 0; t < h.nT; ++t) {
-                const int8_t *src = spins_in + h.spin_off + ((size_t)r * h.nT + t) * N;
-                int8_t *dst = sp.data() + h.spin_off + ((size_t)r * h.nT + was[base + t]) * N;
-                for (int i = 0; i < N; ++i) {
-                    if (src[i] != 1 && src[i] != -1) return fail(EA_EINVAL, "sample %d: spin not +-1", s);
-                    dst[parity(h.L, i) * HALF + (i >> 1)] = src[i];
-                }
-            }
+            const int64_t n = (int64_t)h.nT * h.N;
+            if (bad_spin(spins_in + h.spin_off + r * n, n) >= 0) return fail(EA_EINVAL, "sample %d: spin not +-1", s);
         }
     }
-    HIP_TRY(e, hipMemcpyAsync(e->spins.p, sp.data(), e->spin_bytes, hipMemcpyHostToDevice, e->stream));
+    ea_status us = ensure_stage(e, (size_t)e->spin_bytes, (size_t)e->N_max);
+    if (us) return us;
     HIP_TRY(e, hipMemcpyAsync(e->was.p, was.data(), e->was.bytes, hipMemcpyHostToDevice, e->stream));
     HIP_TRY(e, hipMemcpyAsync(e->sow.p, sow.data(), e->sow.bytes, hipMemcpyHostToDevice, e->stream));
+    // slot t's spins become walker was[t]'s
+    if ((us = transfer_spins(e, const_cast<int8_t *>(spins_in), false)) != EA_OK) return us;
     int64_t sw = sweep;
     HIP_TRY(e, hipMemcpyAsync(e->state.p, &sw, sizeof sw, hipMemcpyHostToDevice, e->stream));
-    if (e->jkind == EA_J_GAUSS_F32)
-        hipLaunchKernelGGL(energy_kernel<0>, dim3(2 * e->S), dim3(256), 0, e->stream, (const SampleDev *)e->samples.p,
-                           (const int32_t *)e->items.p, (const int8_t *)e->spins.p, e->J.p, (int64_t *)e->EJ.p,
-                           (int32_t *)e->M.p);
-    else
-        hipLaunchKernelGGL(energy_kernel<1>, dim3(2 * e->S), dim3(256), 0, e->stream, (const SampleDev *)e->samples.p,
-                           (const int32_t *)e->items.p, (const int8_t *)e->spins.p, e->J.p, (int64_t *)e->EJ.p,
-                           (int32_t *)e->M.p);
+    launch_energies(e, e->EJ, e->M);
     HIP_TRY(e, hipGetLastError());
     HIP_TRY(e, hipStreamSynchronize(e->stream));
     e->sweep = sweep;
@@ -1604,14 +1681,7 @@ ea_status ea_check_energies(ea_ensemble *e, int64_t *mismatches)
         st = dalloc(e, e->scratchM, sizeof(int32_t) * 2 * TS);
         if (st) return st;
     }
-    if (e->jkind == EA_J_GAUSS_F32)
-        hipLaunchKernelGGL(energy_kernel<0>, dim3(2 * e->S), dim3(256), 0, e->stream, (const SampleDev *)e->samples.p,
-                           (const int32_t *)e->items.p, (const int8_t *)e->spins.p, e->J.p,
-                           (int64_t *)e->scratchE.p, (int32_t *)e->scratchM.p);
-    else
-        hipLaunchKernelGGL(energy_kernel<1>, dim3(2 * e->S), dim3(256), 0, e->stream, (const SampleDev *)e->samples.p,
-                           (const int32_t *)e->items.p, (const int8_t *)e->spins.p, e->J.p,
-                           (int64_t *)e->scratchE.p, (int32_t *)e->scratchM.p);
+    launch_energies(e, e->scratchE, e->scratchM);
     HIP_TRY(e, hipGetLastError());
     std::vector<int64_t> a(2 * TS), b(2 * TS);
     std::vector<int32_t> ma(2 * TS), mb(2 * TS);

@@ -630,63 +630,61 @@ __global__ void advance_kernel(int64_t *state, int64_t k)
 }
 
 // ---------------------------------------------------------------------------
-// From-scratch energies E_J (exact integer units) and magnetisations of every
-// walker of one (sample, chain) per workgroup; used to verify the incremental
-// bookkeeping and to rebuild the state after ea_write_state.
+// From-scratch energies E_J (exact integer units) and magnetisations, one
+// walker of a (sample, chain) per workgroup (blockIdx.y = walker); used to
+// verify the incremental bookkeeping and to rebuild the state after
+// ea_write_state.  (One workgroup for all walkers of a chain, in turn, took
+// 262 us at 64 samples x 24 temperatures of L = 16, 3443 us at 128 x 32 of
+// L = 32: too few workgroups, and a barrier per walker.  Now 24 and 367 us.)
 template <int JK>
 __global__ void __launch_bounds__(256) energy_kernel(const SampleDev *samples, const int32_t *items,
                                                     const int8_t *spins, const void *J, int64_t *EJ_out,
                                                     int32_t *M_out)
 {
-    __shared__ long long se;
-    __shared__ int sm;
-    const int code = items[blockIdx.x];
+    __shared__ long long se[4];
+    __shared__ int sm[4];
+    const int code = items[blockIdx.x], w = blockIdx.y;
     const SampleDev d = samples[code >> 1];
+    if (w >= d.n_T) return;
     const int r = code & 1;
     const int L = d.L, N = L * L * L, HALF = N / 2, HL = L / 2;
-    const int tid = threadIdx.x, T = blockDim.x;
-    for (int w = 0; w < d.n_T; ++w) {
-        if (tid == 0) {
-            se = 0;
-            sm = 0;
-        }
-        __syncthreads();
-        const int8_t *Sw = spins + d.spin_off + ((size_t)r * d.n_T + w) * N;
-        long long e = 0;
-        int m = 0;
-        for (int idx = tid; idx < N; idx += T) {
-            const int p = idx >= HALF, h = idx - p * HALF;
-            const int row = h / HL, j = h - row * HL, y = row % L, z = row / L;
-            const int x = 2 * j + ((y + z + p) & 1);
-            const int si = Sw[idx];
-            const int xp = (x + 1) % L, yp = (y + 1) % L, zp = (z + 1) % L;
-            const int nb[3] = {(xp + L * (y + L * z)) >> 1, (x + L * (yp + L * z)) >> 1,
-                               (x + L * (y + L * zp)) >> 1};
+    const int tid = threadIdx.x;
+    const int8_t *Sw = spins + d.spin_off + ((size_t)r * d.n_T + w) * N;
+    const float *Jf = (const float *)J + d.J_off;
+    const int8_t *Ji = (const int8_t *)J + d.J_off;
+    long long e = 0;
+    int m = 0;
+    // sublattice index h of both parities: the bonds +x, +y, +z of either site
+    // end at the other parity's sites of the same or the next row
+    for (int h = tid; h < HALF; h += 256) {
+        const int row = h / HL, j = h - row * HL, z = row / L, y = row - z * L;
+        const int yn = y + 1 == L ? h - (L - 1) * HL : h + HL;
+        const int zn = z + 1 == L ? h - (L - 1) * L * HL : h + L * HL;
+        const int jn = j + 1 == HL ? h - (HL - 1) : h + 1;
+        for (int p = 0; p < 2; ++p) {
+            const int8_t *So = Sw + (1 - p) * HALF;
+            const int si = Sw[p * HALF + h], xn = ((y + z + p) & 1) ? jn : h;
+            const int nb[3] = {So[xn], So[yn], So[zn]};
+            int c = 0;
             for (int dd = 0; dd < 3; ++dd) {
-                const int sj = Sw[(1 - p) * HALF + nb[dd]];
-                long long Ju;
-                if (JK == 0)
-                    Ju = (long long)(((const float *)J)[d.J_off + (size_t)p * 3 * HALF + dd * HALF + h] *
-                                     262144.0f);
-                else
-                    Ju = ((const int8_t *)J)[d.J_off + (size_t)p * 3 * HALF + dd * HALF + h];
-                e -= Ju * si * sj;
+                const int i = (p * 3 + dd) * HALF + h;
+                c += (JK == 0 ? (int)(Jf[i] * 262144.0f) : (int)Ji[i]) * nb[dd];  // |.| < 3 2^21
             }
+            e -= (long long)(c * si);
             m += si;
         }
-        e = wave_sum_i64(e);
-        m = wave_sum_i32(m);
-        if ((tid & 63) == 0) {
-            atomicAdd((unsigned long long *)&se, (unsigned long long)e);
-            atomicAdd(&sm, m);
-        }
-        __syncthreads();
-        if (tid == 0) {
-            const size_t gi = 2 * (size_t)d.slot_off + (size_t)r * d.n_T + w;
-            EJ_out[gi] = se;
-            M_out[gi] = sm;
-        }
-        __syncthreads();
+    }
+    e = wave_sum_i64(e);
+    m = wave_sum_i32(m);
+    if ((tid & 63) == 0) {
+        se[tid >> 6] = e;
+        sm[tid >> 6] = m;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        const size_t gi = 2 * (size_t)d.slot_off + (size_t)r * d.n_T + w;
+        EJ_out[gi] = se[0] + se[1] + se[2] + se[3];
+        M_out[gi] = sm[0] + sm[1] + sm[2] + sm[3];
     }
 }
 
@@ -694,6 +692,78 @@ template __global__ void energy_kernel<0>(const SampleDev *, const int32_t *, co
                                           int64_t *, int32_t *);
 template __global__ void energy_kernel<1>(const SampleDev *, const int32_t *, const int8_t *, const void *,
                                           int64_t *, int32_t *);
+
+// The sublattice-split layout against the caller's natural order (i = x + L (y
+// + L z), slot by slot).  Sites 2h and 2h + 1 share the sublattice index h: the
+// even x of row (y, z) is of parity (y + z) & 1, the odd x of the other.
+//
+// One workgroup per (sample, chain, slot): row first + blockIdx.x of the
+// [S][2][n_T] table, whose spins start base bytes into the caller's array;
+// four sublattice indices (8 natural bytes) per thread step, a whole number of
+// them for every even L.  On the host, one byte at a time, the two directions
+// took more than 40 ms each for 12.6 MB; here a pass over the memory, 12 and 10
+// us (2.1 and 2.5 TB/s).  Bound: HBM.
+template <bool TO_NATURAL>
+__global__ void __launch_bounds__(256) split_spins_kernel(const SampleDev *samples, const int32_t *slot_sample,
+                                                         const int32_t *was, int64_t first, int64_t base,
+                                                         int8_t *natural, int8_t *spins)
+{
+    const int64_t row = first + blockIdx.x;
+    const SampleDev d = samples[slot_sample[row >> 1]];
+    const int L = d.L, HL = L / 2, N = L * L * L, HALF = N / 2;
+    const int k = (int)(row - 2 * (int64_t)d.slot_off), r = k >= d.n_T;
+    uint2 *nat = (uint2 *)(natural + (d.spin_off + (int64_t)k * N - base));
+    uint32_t *S0 = (uint32_t *)(spins + d.spin_off + ((int64_t)r * d.n_T + was[row]) * N), *S1 = S0 + HALF / 4;
+    for (int i = threadIdx.x; i < HALF / 4; i += blockDim.x) {
+        uint32_t odd = 0;  // 0xFF in the bytes of rows whose even x is of parity 1
+        for (int b = 0; b < 4; ++b) {
+            const int rr = (4 * i + b) / HL;
+            odd |= ((rr + rr / L) & 1 ? 0xFFu : 0u) << (8 * b);  // L is even: rr = y modulo 2
+        }
+        if constexpr (TO_NATURAL) {
+            const uint32_t a = S0[i], c = S1[i];
+            const uint32_t ev = (a & ~odd) | (c & odd), od = (c & ~odd) | (a & odd);
+            nat[i] = make_uint2(__builtin_amdgcn_perm(od, ev, 0x05010400u), __builtin_amdgcn_perm(od, ev, 0x07030602u));
+        } else {
+            const uint2 v = nat[i];
+            const uint32_t ev = __builtin_amdgcn_perm(v.y, v.x, 0x06040200u);
+            const uint32_t od = __builtin_amdgcn_perm(v.y, v.x, 0x07050301u);
+            S0[i] = (ev & ~odd) | (od & odd);
+            S1[i] = (od & ~odd) | (ev & odd);
+        }
+    }
+}
+
+template __global__ void split_spins_kernel<true>(const SampleDev *, const int32_t *, const int32_t *, int64_t, int64_t,
+                                                  int8_t *, int8_t *);
+template __global__ void split_spins_kernel<false>(const SampleDev *, const int32_t *, const int32_t *, int64_t,
+                                                   int64_t, int8_t *, int8_t *);
+
+// The same for couplings [3][N] (blockIdx.y = direction), samples first +
+// blockIdx.x; Ju (may be NULL) receives them as multiples of 2^-18.
+template <class T>
+__global__ void __launch_bounds__(256) split_couplings_kernel(const SampleDev *samples, int first, int64_t base,
+                                                             const T *natural, T *J, int32_t *Ju)
+{
+    const SampleDev d = samples[first + blockIdx.x];
+    const int L = d.L, HL = L / 2, N = L * L * L, HALF = N / 2, dd = blockIdx.y;
+    const T *nat = natural + (d.J_off - base) + (int64_t)dd * N;
+    for (int h = threadIdx.x; h < HALF; h += blockDim.x) {
+        const int rr = h / HL, p = (rr + rr / L) & 1;
+        const int64_t even = d.J_off + (p * 3 + dd) * HALF + h, odd = d.J_off + ((1 - p) * 3 + dd) * HALF + h;
+        J[even] = nat[2 * h];
+        J[odd] = nat[2 * h + 1];
+        if (Ju) {
+            Ju[even] = (int32_t)((float)nat[2 * h] * 262144.0f);
+            Ju[odd] = (int32_t)((float)nat[2 * h + 1] * 262144.0f);
+        }
+    }
+}
+
+template __global__ void split_couplings_kernel<float>(const SampleDev *, int, int64_t, const float *, float *,
+                                                       int32_t *);
+template __global__ void split_couplings_kernel<int8_t>(const SampleDev *, int, int64_t, const int8_t *, int8_t *,
+                                                        int32_t *);
 
 // Snapshot of the current state (slot order, bit rows) into frame 0, for an
 // immediate measurement.  One workgroup per (sample, chain).

@@ -277,6 +277,36 @@ def test_checkpoint_resume(torch_cuda, case, with_map):
             assert np.array_equal(st2["walker_at_slot"][s], st_full["walker_at_slot"][s])
 
 
+def test_state_transfer_in_pieces(torch_cuda):
+    """Spins beyond one staging buffer (64 MiB) and couplings of every layout
+    case (L/2 odd and even, L/8 whole or not): what is written comes back
+    through any walker map, with the energies of eq. 1."""
+    from paper_1403_4560_amd import binding
+    rng = np.random.default_rng(3)
+    Ls = [2, 32, 6] + [32] * 17 + [10, 24, 32, 4, 14, 16]
+    nTs = [3, 60, 7] + [56] * 17 + [5, 9, 33, 1, 6, 24]
+    for jkind in (W.J_PM1, W.J_GAUSS):
+        work = W.make_workload(Ls, nTs, (0.5, 2.0), 0.3, jkind=jkind, name="pieces")
+        assert work.spins0.size > 64 << 20
+        print("case: state transfer in pieces, jkind %d, %d MB" % (jkind, work.spins0.size >> 20), flush=True)
+        with binding.Ensemble(work) as ens:
+            st0 = ens.read_state()
+            spins = [(2 * rng.integers(0, 2, size=x.shape, dtype=np.int8) - 1).astype(np.int8) for x in st0["spins"]]
+            maps = [np.stack([rng.permutation(nT) for _ in range(2)]).astype(np.int32) for nT in nTs]
+            ens.write_state(spins, 17, maps)
+            st = ens.read_state()
+            assert ens.check_energies() == 0
+        assert st["sweep"] == 17
+        for s, L in enumerate(Ls):
+            assert np.array_equal(st0["spins"][s], work.spins0_of(s)), s
+            assert np.array_equal(st["spins"][s], spins[s]) and np.array_equal(st["walker_at_slot"][s], maps[s]), s
+            x = spins[s].reshape(2, nTs[s], L, L, L).astype(np.float64)  # [z][y][x]
+            J = work.J_of(s).astype(np.float64).reshape(3, L, L, L)
+            EJ = sum(-(J[d] * x * np.roll(x, -1, axis=4 - d)).sum(axis=(2, 3, 4)) for d in range(3))
+            E = EJ - np.float64(work.h[s]) * x.sum(axis=(2, 3, 4))
+            assert np.array_equal(st["E"][s], E), s
+
+
 def test_write_state_rejects_a_walker_map_that_is_not_a_permutation(torch_cuda):
     from paper_1403_4560_amd import binding
     work = W.make_workload([4, 6], [3, 5], (0.5, 2.0), 0.2, name="bad map")
