@@ -16,6 +16,7 @@
 // the compiler hoist every engine's loop invariants out of the queue loop,
 // where they stayed live together and spilled; measured slower.)
 #include "ea_group.hpp"
+#include "ea_groupbits.hpp"
 #include "ea_row.hpp"
 
 namespace ea {
@@ -25,7 +26,10 @@ __device__ __forceinline__ void batch_dispatch(const SweepArgs &A, int kind, con
                                                const Team tm)
 {
 #define EA_G(Lv) \
-    case (BATCH_GROUP << 8) | Lv: run_group_item<Lv, JK>(A, d, r, mem, tm); break;
+    case (BATCH_GROUP << 8) | Lv:                                               \
+        if constexpr (JK == 0) run_group_item<Lv>(A, d, r, mem, tm);            \
+        else run_group_bits_item<Lv>(A, d, r, mem, tm);                         \
+        break;
 #define EA_S(Lv) \
     case (BATCH_SITE << 8) | Lv: run_item<Lv, JK, false>(A, d, r, mem, tm); break;
     switch (kind) {

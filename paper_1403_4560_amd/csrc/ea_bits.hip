@@ -33,6 +33,7 @@
 // 8-entry threshold table directly.
 // Each site still draws its own Philox word: counter (h >> 2, 2n + p,
 // (t << 1) | r, sample), word h & 3, as in every engine.
+#include "ea_bitops.hpp"
 #include "ea_device.hpp"
 #include "ea_item.hpp"
 #include "ea_types.hpp"
@@ -62,53 +63,13 @@ struct BitGeo {
     static constexpr uint32_t TOP = rep_bit(SEG, SEG - 1), BOT = rep_bit(SEG, 0), EVEN = even_rows(SEG);
 };
 
-__device__ __forceinline__ uint32_t sel(uint32_t a, uint32_t b, uint32_t m) { return (a & ~m) | (b & m); }
-__device__ __forceinline__ uint32_t maj3(uint32_t a, uint32_t b, uint32_t c)
-{
-    return __builtin_amdgcn_bitop3_b32(a, b, c, 0xE8);  // truth table of the majority
-}
 // Spreading table and threshold tables sit at fixed LDS offsets, ahead of the
 // spins: byte addresses then come straight from the spread bytes.
 constexpr int SPREAD_OFF = 0, TH_OFF = 256 * 8;
 
-// 2 F + (a < b): the comparison's carry goes straight into the add.
-__device__ __forceinline__ uint32_t shift_in_less(uint32_t F, uint32_t a, uint32_t b)
-{
-    uint32_t r;
-    asm("v_cmp_lt_u32_e32 vcc, %1, %2\n\tv_addc_co_u32_e32 %0, vcc, %3, %3, vcc"
-        : "=v"(r)
-        : "v"(a), "v"(b), "v"(F)
-        : "vcc");
-    return r;
-}
-
-// Loads from an LDS byte address.
-typedef __attribute__((address_space(3))) const uint32_t lds_u32;
-typedef __attribute__((address_space(3))) const uint64_t lds_u64;
-__device__ __forceinline__ uint32_t lds_load(uint32_t addr) { return *(lds_u32 *)(size_t)addr; }
-__device__ __forceinline__ uint2 lds_load2(uint32_t addr)
-{
-    const uint64_t v = *(lds_u64 *)(size_t)addr;
-    return make_uint2((uint32_t)v, (uint32_t)(v >> 32));
-}
-__device__ __forceinline__ uint32_t lds_addr(const void *p)
-{
-    return (uint32_t)(size_t)(__attribute__((address_space(3))) const char *)p;
-}
-
 __device__ __forceinline__ uint32_t funnel(uint32_t hi, uint32_t lo, int s)
 {
     return __builtin_amdgcn_alignbit(hi, lo, s);  // ({hi, lo} >> s) low word
-}
-
-// Spin bits of 32 int8 spins (bit b set iff byte b is -1) and back.
-__device__ __forceinline__ uint32_t pack4(uint32_t v)
-{
-    return ((v >> 7) & 1u) | ((v >> 14) & 2u) | ((v >> 21) & 4u) | ((v >> 28) & 8u);
-}
-__device__ __forceinline__ uint32_t unpack4(uint32_t nib)
-{
-    return 0x01010101u + ((nib * 0x00204081u) & 0x01010101u) * 0xFEu;  // bytes 0x01 / 0xFF
 }
 
 // Row bits of one sublattice row spread to the even bit positions.

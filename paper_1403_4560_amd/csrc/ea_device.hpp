@@ -54,6 +54,21 @@ __device__ __forceinline__ u32x4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_
     return {c0, c1, c2, c3};
 }
 
+// One round with keys k0, k1, for callers that run several calls side by side.
+__device__ __forceinline__ u32x4 philox_round(const u32x4 c, uint32_t k0, uint32_t k1)
+{
+    const uint64_t p0 = (uint64_t)0xD2511F53u * (uint64_t)c.x;
+    const uint64_t p1 = (uint64_t)0xCD9E8D57u * (uint64_t)c.z;
+    return {xor3((uint32_t)(p1 >> 32), c.y, k0), (uint32_t)p1, xor3((uint32_t)(p0 >> 32), c.w, k1), (uint32_t)p0};
+}
+
+// Round 0 multiplies counter words 0 and 2 apart, and round 1 the results of
+// either product apart, so a caller that varies the two words separately can
+// make each side's two products once: with p0 = M0 c0, q1 = M1 (hi(p0) ^ c3 ^
+// k1) of word 0 and p1 = M1 c2, q0 = M0 (hi(p1) ^ c1 ^ k0) of word 2, the state
+// after round 1 is (hi(q1) ^ lo(p1) ^ k0', lo(q1), hi(q0) ^ lo(p0) ^ k1',
+// lo(q0)), k' the key of round 1.
+
 // Counter purposes (bits 28..31 of counter word 2).
 constexpr uint32_t PURPOSE_METROPOLIS = 0u;
 constexpr uint32_t PURPOSE_EXCHANGE = 1u;
@@ -146,31 +161,29 @@ __device__ __forceinline__ double u53_of(uint32_t w0, uint32_t w1)
     return ((double)(w0 >> 5) * 67108864.0 + (double)(w1 >> 6)) * 0x1p-53;
 }
 
-// Replica-exchange test for D < 0: returns u < exp_ea64(D), u a 53-bit
-// uniform (a multiple of 2^-53 in [0, 1)), deciding from the hardware
-// exponential wherever that is safe.
-//   D < -40: exp_ea64(D) < e^-40 (1 + 2^-50) < 2^-57 < 2^-53 <= u unless u = 0.
-//   -40 <= D < 0: e = 2^y, y = fl32(D log2 e) with |t| < 58 for t = D log2 e,
-//     so |y - t| <= 2^-19 (half an ulp at |t| < 64); the hardware exp2 is
-//     within a relative 2^-22 of 2^y on y in [-58, 0] (checked on every
-//     binary32 there by ea_verify_exchange_bracket), and exp_ea64 within 2^-50
-//     of e^D.  So e / exp_ea64(D) lies within 1 +- 1.7e-6, well inside the
-//     margin 2^-16 = 1.5e-5: u < e (1 - 2^-16) implies u < exp_ea64(D), and
-//     u > e (1 + 2^-16) implies u > exp_ea64(D).  Between the two (about 3e-5
-//     of the draws), and for u = 0, exp_ea64 decides.
-constexpr double EXCHANGE_FAST_MIN = -40.0;
-constexpr double EXCHANGE_MARGIN = 0x1p-16;
-
-__device__ __forceinline__ bool exchange_accept(double u, double D)
+// Replica-exchange test: returns D >= 0 or u < exp_ea64(D), u = u53_of(w0, w1),
+// deciding in binary32 from the hardware exponential wherever that is safe.
+// In units of 2^-32: U = fl32(w0) is within 160 of u 2^32 (w0 - 31 <= u 2^32 <
+// w0 + 32, and 128 for the conversion), and A = 2^32 2^y, y = fl32(D log2 e).
+//   -40 <= D < 0: |t| < 58 for t = D log2 e, so |y - t| <= 2^-19 (half an ulp
+//     at |t| < 64); the hardware exp2 is within a relative 2^-22 of 2^y on y
+//     in [-58, 0] (checked on every binary32 there by
+//     ea_verify_exchange_bracket), and exp_ea64 within 2^-50 of e^D, so A is
+//     within a relative 1.7e-6 of T = exp_ea64(D) 2^32.
+//   D < -40: A and T are both below 2^-57 2^32.
+//   D >= 0: A >= 2^32 (1 - 2^-22) (y is cut at 64, which keeps A finite).
+// With the gap g = fl32(U - A) and the margin m = fl32(2^-16 A + 512), g < -m
+// implies u < exp_ea64(D) or D >= 0, and g > m implies D < 0 and u >
+// exp_ea64(D).  Between the two (about 3e-5 of the draws) the exact test
+// decides.
+__device__ __forceinline__ bool exchange_accept(uint32_t w0, uint32_t w1, double D)
 {
-    if (u != 0.0) {
-        if (D < EXCHANGE_FAST_MIN) return false;
-        const float y = (float)(D * __longlong_as_double(0x3FF71547652B82FEll));  // D log2(e)
-        const double e = (double)__builtin_amdgcn_exp2f(y);
-        if (u < e * (1.0 - EXCHANGE_MARGIN)) return true;
-        if (u > e * (1.0 + EXCHANGE_MARGIN)) return false;
-    }
-    return u < exp_ea64(D);
+    const float y = __builtin_fminf((float)(D * __longlong_as_double(0x3FF71547652B82FEll)), 64.0f);  // D log2(e)
+    const float a = __builtin_amdgcn_exp2f(y);
+    const float g = __builtin_fmaf(a, -0x1p32f, (float)w0), m = __builtin_fmaf(a, 0x1p16f, 512.0f);
+    bool accept = g < 0.0f;
+    if (!(__builtin_fabsf(g) > m)) accept = D >= 0.0 || u53_of(w0, w1) < exp_ea64(D);
+    return accept;
 }
 
 }  // namespace ea

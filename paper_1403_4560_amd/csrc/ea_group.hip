@@ -1,6 +1,7 @@
 // ea_group.hip -- per-class kernels of the walker-interleaved LDS engine
-// (ea_group.hpp).
+// (ea_group.hpp: Gaussian couplings; ea_groupbits.hpp: +-1).
 #include "ea_group.hpp"
+#include "ea_groupbits.hpp"
 
 namespace ea {
 
@@ -11,7 +12,9 @@ __global__ void __launch_bounds__(GROUP_MAX_THREADS, 4) group_sweep_kernel(Sweep
     extern __shared__ __attribute__((aligned(16))) char smem[];
     for (int item = blockIdx.x; item < A.n_items; item += gridDim.x) {
         const int code = A.items[item];
-        run_group_item<L, JK>(A, sample_of_item(A.samples, code >> 1), code & 1, smem);
+        const SampleDev d = sample_of_item(A.samples, code >> 1);
+        if constexpr (JK == 0) run_group_item<L>(A, d, code & 1, smem);
+        else run_group_bits_item<L>(A, d, code & 1, smem, whole_block());
     }
 }
 

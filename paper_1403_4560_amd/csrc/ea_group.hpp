@@ -1,6 +1,7 @@
-// ea_group.hpp -- walker-interleaved LDS engine for any even L <= 16 (both
-// coupling kinds): the lattice sizes that the row engine (Gaussian L = 8, 16)
-// and the one-bit engine (+-1 L = 8, 16, 32) do not take.
+// ea_group.hpp -- walker-interleaved LDS engine for any even L <= 16: the
+// lattice sizes that the row engine (Gaussian L = 8, 16) and the one-bit engine
+// (+-1 L = 8, 16, 32) do not take.  This file: Gaussian couplings
+// (ea_groupbits.hpp: +-1 couplings, walkers as bits).
 //
 // Layout: one int8x4 word holds one site of four walkers of a chain (a
 // "quad"), [2 parities][quads][N/2 + 1 sites] (the odd plane stride spreads
@@ -77,7 +78,6 @@ __device__ __forceinline__ uint4 nbr_entry(int h)
 struct GroupLane {
     float ka[4], kb[4];     // per walker: the folded exponent's constants (update_word_gauss)
     uint32_t c2[4];         // Philox counter word 2 of each walker
-    uint32_t thr[4];        // +-1: offset of each walker's threshold table in lut
     uint32_t valid;         // 0xFF in the bytes of real walkers
     float h32;              // the sample's field, held in a vector register
 };
@@ -90,9 +90,9 @@ struct GroupTally {
 };
 
 // Metropolis update of work item (quad q, sites 4 g4 .. 4 g4 + 3) of parity P.
-template <int L, int JK, int P>
-__device__ __forceinline__ void group_item(const SweepArgs &A, const SampleDev &d, uint32_t *SG, const void *Jl,
-                                           const uint32_t *lut, const float *b32, const uint4 *NB, int NQ, int q,
+template <int L, int P>
+__device__ __forceinline__ void group_item(const SweepArgs &A, const SampleDev &d, uint32_t *SG, const int *Jl,
+                                           const float *b32, const uint4 *NB, int NQ, int q,
                                            int g4, uint32_t c1, const GroupLane &ln, GroupTally &ty)
 {
     constexpr int HALF = L * L * L / 2, PS = HALF + 1;
@@ -115,48 +115,22 @@ __device__ __forceinline__ void group_item(const SweepArgs &A, const SampleDev &
                           k == 0 ? rw[1].x : k == 1 ? rw[1].y : k == 2 ? rw[1].z : rw[1].w,
                           k == 0 ? rw[2].x : k == 1 ? rw[2].y : k == 2 ? rw[2].z : rw[2].w,
                           k == 0 ? rw[3].x : k == 1 ? rw[3].y : k == 2 ? rw[3].z : rw[3].w};
-        uint32_t fm;
         int Sus[4];
-        if constexpr (JK == 0) {
-            // bonds +x, -x, +y, -y, +z, -z: own +d bonds, the neighbours' +d bonds for -d
-            const int *Jp = (const int *)Jl + (size_t)P * 3 * HALF, *Jo = (const int *)Jl + (size_t)(1 - P) * 3 * HALF;
-            const char *Jb = (const char *)Jo;
-            const int jx = Jp[h], jxm = *(const int *)(Jb + off[1]), jy = Jp[HALF + h];
-            const int jym = *(const int *)(Jb + 4 * HALF + off[3]);
-            const int jz = Jp[2 * HALF + h], jzm = *(const int *)(Jb + 8 * HALF + off[5]);
-            const int Ja[4] = {jx, jx, jx, jx}, Js[4] = {jxm, jxm, jxm, jxm};
-            const int Jy[4] = {jy, jy, jy, jy}, Jyn[4] = {jym, jym, jym, jym};
-            const int Jz[4] = {jz, jz, jz, jz}, Jzn[4] = {jzm, jzm, jzm, jzm};
-            // the exact path reads 2 beta32 of walker i's slot, t = bits 1 .. 27 of its counter word
-            // Sus = S_u + hgrid (the field's grid part folded into the integer field)
-            fm = update_word_gauss<true>(Sv, X[0], X[1], X[2], X[3], X[4], X[5], Ja, Js, Jy, Jyn, Jz, Jzn, rk,
-                                         ln.ka, ln.kb, [&](int i) { return 2.0f * b32[(ln.c2[i] >> 1) & 0x7FFFFFFu]; },
-                                         ln.h32, d.hgrid, Sus) &
-                 ln.valid;
-        } else {
-            // bond-spin product bytes J s_j: 0x01 (+1) or 0xFF (-1); c counts the -1
-            const int8_t *Jp = (const int8_t *)Jl + (size_t)P * 3 * HALF;
-            const int8_t *Jo = (const int8_t *)Jl + (size_t)(1 - P) * 3 * HALF;
-            const int8_t jb[6] = {Jp[h], Jo[off[1] >> 2], Jp[HALF + h], Jo[HALF + (off[3] >> 2)], Jp[2 * HALF + h],
-                                  Jo[2 * HALF + (off[5] >> 2)]};
-            constexpr uint32_t LOW = 0x01010101u;
-            uint32_t cnt = 0;
-#pragma unroll
-            for (int j = 0; j < 6; ++j) cnt += ((X[j] ^ (jb[j] < 0 ? 0xFEFEFEFEu : 0u)) >> 7) & LOW;
-            const uint32_t words[4] = {rk.x, rk.y, rk.z, rk.w};
-            fm = 0;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int sh = 8 * i;
-                const int b = 6 - (int)((cnt >> sh) & 0xFFu);               // (S_J + 6) / 2
-                const int m = __builtin_amdgcn_sbfe((int)Sv, sh + 7, 1);  // 0: s_i = +1, -1: s_i = -1
-                const int idx = (m + 1) * 7 + b;
-                Sus[i] = 2 * b - 6;  // S_J
-                const bool accept = ((d.down_mask >> idx) & 1u) | (words[i] < lut[ln.thr[i] + idx]);
-                fm |= accept ? 0xFEu << sh : 0u;
-            }
-            fm &= ln.valid;
-        }
+        // bonds +x, -x, +y, -y, +z, -z: own +d bonds, the neighbours' +d bonds for -d
+        const int *Jp = Jl + (size_t)P * 3 * HALF, *Jo = Jl + (size_t)(1 - P) * 3 * HALF;
+        const char *Jb = (const char *)Jo;
+        const int jx = Jp[h], jxm = *(const int *)(Jb + off[1]), jy = Jp[HALF + h];
+        const int jym = *(const int *)(Jb + 4 * HALF + off[3]);
+        const int jz = Jp[2 * HALF + h], jzm = *(const int *)(Jb + 8 * HALF + off[5]);
+        const int Ja[4] = {jx, jx, jx, jx}, Js[4] = {jxm, jxm, jxm, jxm};
+        const int Jy[4] = {jy, jy, jy, jy}, Jyn[4] = {jym, jym, jym, jym};
+        const int Jz[4] = {jz, jz, jz, jz}, Jzn[4] = {jzm, jzm, jzm, jzm};
+        // the exact path reads 2 beta32 of walker i's slot, t = bits 1 .. 27 of its counter word
+        // Sus = S_u + hgrid (the field's grid part folded into the integer field)
+        const uint32_t fm = update_word_gauss<true>(Sv, X[0], X[1], X[2], X[3], X[4], X[5], Ja, Js, Jy, Jyn, Jz, Jzn, rk,
+                                     ln.ka, ln.kb, [&](int i) { return 2.0f * b32[(ln.c2[i] >> 1) & 0x7FFFFFFu]; },
+                                     ln.h32, d.hgrid, Sus) &
+             ln.valid;
         Sp[h] = Sv ^ fm;
         ty.flips += (fm >> 7) & 0x01010101u;
         ty.fdown += ((fm & Sv) >> 7) & 0x01010101u;
@@ -169,17 +143,16 @@ __device__ __forceinline__ void group_item(const SweepArgs &A, const SampleDev &
     }
 }
 
-template <int L, int JK>
+template <int L>
 __device__ __forceinline__ void run_group_item(const SweepArgs &A, const SampleDev &d, int r, char *smem,
                                                const Team tm = whole_block())
 {
     constexpr int N = L * L * L, HALF = N / 2, G4 = HALF / 4;
     const int nT = d.n_T, NQ = (nT + 3) / 4;
     const int T = tm.T, tid = tm.tid;
-    const GroupLdsOff o = group_lds_offsets(L, nT, JK);
+    const GroupLdsOff o = group_lds_offsets(L, nT);
     uint32_t *SG = (uint32_t *)(smem + o.spins);
-    void *Jl = (void *)(smem + o.J);
-    uint32_t *lut = (uint32_t *)(smem + o.lut);
+    int *Jl = (int *)(smem + o.J);
     uint4 *NB = (uint4 *)(smem + o.nb);
     ItemLds I{};
     I.was = (int32_t *)(smem + o.was);
@@ -207,7 +180,7 @@ __device__ __forceinline__ void run_group_item(const SweepArgs &A, const SampleD
         SG[gidx<L>(ph / HALF, ph % HALF, q, NQ)] = wv;
     }
     for (int h = tid; h < HALF; h += T) NB[(h & 3) * G4 + (h >> 2)] = nbr_entry<L>(h);
-    if constexpr (JK == 0) {
+    {
         // couplings as exact int32 multiples of 2^-18
         const float4 *src = (const float4 *)((const float *)A.J + d.J_off);  // J_off is a multiple of 4
         int4 *dst = (int4 *)Jl;
@@ -216,9 +189,6 @@ __device__ __forceinline__ void run_group_item(const SweepArgs &A, const SampleD
             dst[i] = make_int4((int)(v.x * 262144.0f), (int)(v.y * 262144.0f), (int)(v.z * 262144.0f),
                                (int)(v.w * 262144.0f));
         }
-    } else {
-        block_copy(Jl, (const int8_t *)A.J + d.J_off, (size_t)3 * N, tm);
-        for (int i = tid; i < nT * 14; i += T) lut[i] = A.lut[(size_t)d.slot_off * 14 + i];
     }
     for (int i = tid; i < nT; i += T) {
         I.was[i] = A.was[gi + i];
@@ -268,9 +238,8 @@ __device__ __forceinline__ void run_group_item(const SweepArgs &A, const SampleD
     const bool on = gs < TPQ;
     uint32_t valid = 0;
     for (int i = 0; i < 4; ++i) valid |= (4 * q + i < nT ? 0xFFu : 0u) << (8 * i);
-    const double unit = JK == 0 ? 0x1p-18 : 1.0;
     const double hd = (double)d.h32;
-    const int hg = JK == 0 ? d.hgrid : 0;  // the field's grid part folded into S_u
+    const int hg = d.hgrid;  // the field's grid part folded into S_u
     const int64_t n0 = A.state[0];
     int64_t next_meas = next_measurement(n0, A.measure_every, A.measure_start);
     int64_t f = 0;  // frame of the next measurement within this chunk
@@ -278,7 +247,7 @@ __device__ __forceinline__ void run_group_item(const SweepArgs &A, const SampleD
     // minus E_J in dEJ and the magnetisation change in dM; both are folded in
     // at the start of the next sweep, before its own tallies (which follow the
     // first half-sweep's barrier), so no pass of their own is needed.
-    const auto energy = [&](int w) { return (double)(-I.dEJ[w]) * unit - hd * (double)(I.M[w] + I.dM[w]); };
+    const auto energy = [&](int w) { return (double)(-I.dEJ[w]) * 0x1p-18 - hd * (double)(I.M[w] + I.dM[w]); };
     for (int it = 0; it < A.K; ++it) {
         const int64_t n = n0 + it;
 #pragma unroll 1
@@ -296,7 +265,6 @@ __device__ __forceinline__ void run_group_item(const SweepArgs &A, const SampleD
             ln.ka[i] = cp * 0x1p-18f;
             ln.kb[i] = cp * (d.h32 - (float)d.hgrid * 0x1p-18f);
             ln.c2[i] = (PURPOSE_METROPOLIS << 28) | ((uint32_t)ts[i] << 1) | (uint32_t)r;
-            ln.thr[i] = 14 * ts[i];
         }
         ln.valid = valid;
         ln.h32 = d.h32;
@@ -306,20 +274,19 @@ __device__ __forceinline__ void run_group_item(const SweepArgs &A, const SampleD
             const uint32_t c1 = (uint32_t)(2 * n);
 #pragma unroll 1
             for (int g4 = gs; g4 < G4; g4 += TPQ)
-                group_item<L, JK, 0>(A, d, SG, Jl, lut, I.b32, NB, NQ, q, g4, c1, ln, ty);
+                group_item<L, 0>(A, d, SG, Jl, I.b32, NB, NQ, q, g4, c1, ln, ty);
         }
         __syncthreads();
         if (on) {
             const uint32_t c1 = (uint32_t)(2 * n + 1);
 #pragma unroll 1
             for (int g4 = gs; g4 < G4; g4 += TPQ)
-                group_item<L, JK, 1>(A, d, SG, Jl, lut, I.b32, NB, NQ, q, g4, c1, ln, ty);
+                group_item<L, 1>(A, d, SG, Jl, I.b32, NB, NQ, q, g4, c1, ln, ty);
         }
         // Per-walker tallies (idle lanes hold zeros).  dEJ collects minus the
         // new E_J: the second half-sweep summed (S_u + hgrid) XOR m' = s'(S_u +
         // hgrid) - [s' = -1] over the odd sites, so a thread adds accE +
-        // (1 + 2 hgrid) nd and dEJ starts the sweep at -hgrid N/2 (+-1
-        // couplings: hgrid = 0).  Per thread a byte counter holds at most 128
+        // (1 + 2 hgrid) nd and dEJ starts the sweep at -hgrid N/2 .  Per thread a byte counter holds at most 128
         // (at most 16 site groups per half-sweep), so a sum over 16 lanes fits
         // a 16-bit lane.  Teams of four or more waves with NQ = 1, 2 or 4 sum
         // the lanes of a row of 16 that share a quad (lane = quad mod NQ)

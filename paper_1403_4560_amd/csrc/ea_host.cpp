@@ -657,7 +657,29 @@ int bits_threads(int L, int nT) { return ((nT * bits_tpw(L, nT) + 63) / 64) * 64
 // GROUP_MAX_THREADS; the launch takes the smaller of this and the plan's size.
 int group_items(int L, int nT) { return ((nT + 3) / 4) * (L * L * L / 8); }
 
-int group_threads(int L, int nT) { return std::min(GROUP_MAX_THREADS, ((group_items(L, nT) + 63) / 64) * 64); }
+int group_threads(int L, int nT, int jk)
+{
+    if (jk == EA_J_PM1_I8) {
+        // One site group per thread and set on two to eight waves, and, as
+        // long as the team stays within four waves, as many sets as leave
+        // eight walkers each: more waves hide more of a sweep's latency until
+        // the work done per set (the field, the tallies) outweighs it.  attempts/ns at 512, 256,
+        // 128, 64 threads: L = 6 x 56 temperatures 237, 269, 187 (64
+        // samples) and 701, 1099, 902 (1024); L = 6 x 16 250, 424, 727, 739;
+        // L = 10 x 56 1414, 1648 (256); L = 10 x 20 814, 998, 794; L = 12 x
+        // 16 1159, 1542, 1060.
+        int T = 128;
+        while (T < GROUP_MAX_THREADS && group_sets(L, nT, T).TPS < L * L * L / 8) T *= 2;
+        while (T < 256 && group_sets(L, nT, T).WS > 8) T *= 2;
+        return T;
+    }
+    return std::min(GROUP_MAX_THREADS, ((group_items(L, nT) + 63) / 64) * 64);
+}
+
+size_t group_lds(int L, int nT, int jk)
+{
+    return jk == EA_J_PM1_I8 ? group_bits_lds_offsets(L, nT).total : group_lds_offsets(L, nT).total;
+}
 
 bool bits_engine(int L, int nT, int jk, float h, size_t lds_max)
 {
@@ -898,7 +920,7 @@ ea_status plan_samples(const ea_desc *d, size_t lds_max, std::vector<SampleHost>
         // spreads them over more lanes
         h.group = !h.hbm && !h.bits && d->tier != EA_TIER_SITE && !row_engine(h.L, h.nT, jk) &&
                   h.L <= LDS_MAX_L && group_items(h.L, h.nT) >= 64 &&
-                  group_lds_offsets(h.L, h.nT, jk).total <= lds_max;
+                  group_lds(h.L, h.nT, jk) <= lds_max;
         if (h.hbm && !hbm_size(h.L))
             return fail(EA_EUNSUPPORTED,
                         "sample %d: L=%d with %d temperatures does not fit LDS (%zu of %zu B) and the HBM tier "
@@ -1301,8 +1323,8 @@ ea_status ea_create_ensemble(const ea_desc *d, void *hip_stream, ea_ensemble **o
                 c.lds = std::max(c.lds, bits_lds_offsets(h.L, h.nT).total);
                 c.threads = std::max(c.threads, bits_threads(h.L, h.nT));
             } else if (h.group) {
-                c.lds = std::max(c.lds, group_lds_offsets(h.L, h.nT, e->jkind).total);
-                c.threads = std::max(c.threads, group_threads(h.L, h.nT));
+                c.lds = std::max(c.lds, group_lds(h.L, h.nT, e->jkind));
+                c.threads = std::max(c.threads, group_threads(h.L, h.nT, e->jkind));
                 c.group_min_threads = std::max(c.group_min_threads, (group_items(h.L, h.nT) / 16 + 63) / 64 * 64);
             } else {
                 c.lds = std::max(c.lds, lds_offsets(h.L, h.nT, e->jkind).total);

@@ -151,7 +151,7 @@ __device__ __forceinline__ void exchange_pass_e(const SweepArgs &A, const Sample
             const u32x4 q = philox4x32_10(0u, (uint32_t)n,
                                           (PURPOSE_EXCHANGE << 28) | ((uint32_t)t << 1) | (uint32_t)r,
                                           d.sample_id, A.key0, A.key1);
-            acc = exchange_accept(u53_of(q.x, q.y), D);
+            acc = exchange_accept(q.x, q.y, D);
         }
         if (acc) {
             I.was[t] = w1;
@@ -237,6 +237,51 @@ __device__ __forceinline__ V row_residue_sum(V v, int S)
     if (S <= 4) v += row_rotate<4>(v);
     if (S <= 8) v += row_rotate<8>(v);
     return v;
+}
+
+// v of the other lane of a pair of neighbouring lanes: (0, 1), (2, 3), .. or,
+// with odd set, (1, 2), (3, 4), ..
+__device__ __forceinline__ int pair_other(int v, int lane, bool odd)
+{
+    const int a = quad_xor<1>(v);
+    const int l = __builtin_amdgcn_mov_dpp(v, 0x130, 0xF, 0xF, true);  // of lane + 1
+    const int r = __builtin_amdgcn_mov_dpp(v, 0x138, 0xF, 0xF, true);  // of lane - 1
+    return !odd ? a : (lane & 1) ? l : r;
+}
+
+// The exchange pass after sweep n (see exchange_pass_e) by one whole wave, lane
+// t for slot t: both lanes of a pair form its decision from the same operands,
+// and the slots' walkers and energies cross between the lanes in registers.
+// Nothing is kept between sweeps (it would be spilled); two dependent LDS
+// reads, hidden in part behind the random words.  Returns the walker now at
+// slot t (t itself from n_T on).
+template <class Energy>
+__device__ __forceinline__ int exchange_slots(const SweepArgs &A, const SampleDev &d, int r, int64_t n, const ItemLds &I,
+                                              int t, Energy energy)
+{
+    const int nT = d.n_T;
+    const bool odd = n & 1, slot = t < nT;
+    const int lo = odd ? (t - 1) | 1 : t & ~1;  // the pair's lower slot
+    const bool pair = lo >= 0 && lo + 1 < nT;
+    int w = slot ? I.was[t] : t;
+    const double db = pair ? I.b64[lo] - I.b64[lo + 1] : 0.0;
+    const double E = slot ? energy(w) : 0.0;
+    const u32x4 q = philox4x32_10(0u, (uint32_t)n, (PURPOSE_EXCHANGE << 28) | ((uint32_t)lo << 1) | (uint32_t)r,
+                                  d.sample_id, A.key0, A.key1);
+    typedef int int2v __attribute__((ext_vector_type(2)));
+    int2v e = __builtin_bit_cast(int2v, E);
+    e.x = pair_other(e.x, t, odd);
+    e.y = pair_other(e.y, t, odd);
+    const double Eo = __builtin_bit_cast(double, e);
+    const int wo = pair_other(w, t, odd);
+    const double D = db * (t == lo ? E - Eo : Eo - E);
+    if (pair && exchange_accept(q.x, q.y, D)) {
+        w = wo;
+        if (t == lo) atomicAdd(&I.sw[t], 1);
+        I.was[t] = w;
+        I.sow[w] = t;
+    }
+    return w;
 }
 
 }  // namespace ea

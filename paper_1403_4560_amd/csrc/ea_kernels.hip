@@ -245,7 +245,7 @@ __global__ void __launch_bounds__(64) hbm_exchange_kernel(SweepArgs A)
             const u32x4 q = philox4x32_10(0u, (uint32_t)n,
                                           (PURPOSE_EXCHANGE << 28) | ((uint32_t)t << 1) | (uint32_t)r,
                                           d.sample_id, A.key0, A.key1);
-            acc = exchange_accept(u53_of(q.x, q.y), D);
+            acc = exchange_accept(q.x, q.y, D);
         }
         if (acc) {
             A.was[gi + t] = w1;
@@ -601,9 +601,10 @@ __global__ void exp_bracket_kernel(uint32_t first_bits, uint32_t count, unsigned
 // reference) and exp_ea64(y) within 2^-49 of e^y (binary64 exp, itself within
 // an ulp); records the largest |2^y (hardware) / 2^y - 1|.  With D = 1.5 y
 // (down to -87, past the cut at -40) it also compares the decision itself
-// with u < exp_ea64(D) for uniforms on the 2^-53 grid at relative distances
-// k 2^-17 (k = -6 .. 6) from exp_ea64(D), both sides of the margin, and for
-// u = 0 and u = 1 - 2^-53.
+// with u < exp_ea64(D) for uniforms on the 2^-53 grid at distances k (2^-17
+// exp_ea64(D) + 2^-24) (k = -6 .. 6) from exp_ea64(D), both sides of the
+// margin, and for u = 0 and u = 1 - 2^-53, each with the random words' unused
+// low bits clear and set; and that D = -1.5 y >= 0 accepts the same uniforms.
 __global__ void exchange_bracket_kernel(uint32_t first_bits, uint32_t count, unsigned long long *violations,
                                         unsigned long long *max_dev_bits)
 {
@@ -614,11 +615,16 @@ __global__ void exchange_bracket_kernel(uint32_t first_bits, uint32_t count, uns
     bool ok = dev <= 0x1p-22 && fabs(exp_ea64((double)y) / exp((double)y) - 1.0) <= 0x1p-49;
     if (y < 0.0f) {
         const double D = 1.5 * (double)y, E = exp_ea64(D);
-        ok = ok && exchange_accept(0.0, D) == (0.0 < E) && exchange_accept(1.0 - 0x1p-53, D) == (1.0 - 0x1p-53 < E);
-        for (int k = -6; k <= 6; ++k) {
-            const double u = fmin(floor(E * (1.0 + k * 0x1p-17) * 0x1p53) * 0x1p-53, 1.0 - 0x1p-53);
-            ok = ok && exchange_accept(u, D) == (u < E);
-        }
+        const auto decides = [&](double u) {
+            const uint64_t n = (uint64_t)(u * 0x1p53);
+            const uint32_t w0 = (uint32_t)(n >> 26) << 5, w1 = (uint32_t)(n & 0x3FFFFFFu) << 6;
+            return exchange_accept(w0, w1, D) == (u < E) && exchange_accept(w0 | 31u, w1 | 63u, D) == (u < E) &&
+                   exchange_accept(w0 | 31u, w1 | 63u, -D);
+        };
+        ok = ok && decides(0.0) && decides(1.0 - 0x1p-53);
+        for (int k = -6; k <= 6; ++k)
+            ok = ok && decides(fmax(0.0, fmin(floor((E + k * (E * 0x1p-17 + 0x1p-24)) * 0x1p53) * 0x1p-53,
+                                              1.0 - 0x1p-53)));
     }
     atomicMax(max_dev_bits, (unsigned long long)__double_as_longlong(dev));
     if (!ok) atomicAdd(violations, 1ull);

@@ -235,24 +235,23 @@ __host__ __device__ inline BitsLdsOff bits_lds_offsets(int L, int nT)
     return o;
 }
 
-// LDS layout of one group-engine work item (bytes): quad words
-// [2][ceil(n_T/4)][N/2 + 1], couplings (int32 units of 2^-18, or int8 +-1)
-// [2][3][N/2], the neighbour table [N/2] (16 B per site), +-1 threshold
-// tables [n_T][14], then the per-walker/slot arrays of the common frame.
+// LDS layout of one group-engine work item with Gaussian couplings (bytes):
+// quad words [2][ceil(n_T/4)][N/2 + 1], couplings (int32 units of 2^-18)
+// [2][3][N/2], the neighbour table [N/2] (16 B per site), then the
+// per-walker/slot arrays of the common frame.
 struct GroupLdsOff {
-    size_t spins, J, nb, lut, was, sow, M, dM, fl, sw, EJ, dEJ, b32, b64, total;
+    size_t spins, J, nb, was, sow, M, dM, fl, sw, EJ, dEJ, b32, b64, total;
 };
 
-__host__ __device__ inline GroupLdsOff group_lds_offsets(int L, int nT, int jkind)
+__host__ __device__ inline GroupLdsOff group_lds_offsets(int L, int nT)
 {
     const size_t N = (size_t)L * L * L, NQ = (size_t)(nT + 3) / 4;
     const size_t T4 = (size_t)((nT + 3) & ~3);
     GroupLdsOff o;
     o.spins = 0;
     o.J = align16(2 * NQ * (N / 2 + 1) * 4);
-    o.nb = align16(o.J + 3 * N * (jkind == 0 ? 4 : 1));
-    o.lut = o.nb + (N / 2) * 16;
-    o.was = o.lut + (jkind == 1 ? 4 * 14 * T4 : 0);
+    o.nb = align16(o.J + 3 * N * 4);
+    o.was = o.nb + (N / 2) * 16;
     o.sow = o.was + 4 * T4;
     o.M = o.sow + 4 * T4;
     o.dM = o.M + 4 * T4;
@@ -262,6 +261,60 @@ __host__ __device__ inline GroupLdsOff group_lds_offsets(int L, int nT, int jkin
     o.dEJ = o.EJ + 8 * T4;
     o.b32 = o.dEJ + 8 * T4;
     o.b64 = align16(o.b32 + 4 * T4);
+    o.total = align16(o.b64 + 8 * T4);
+    return o;
+}
+
+// The group engine's +-1 form (ea_groupbits.hpp) on a team of T threads: NS
+// sets of WS walkers (a multiple of 4, at most 32), TPS threads a set (16, 32
+// or whole waves).  More sets than the walkers need, as far as threads are
+// left to take them (a thread per site group and set), so that small lattices
+// fill the team.
+struct GroupSets {
+    int NS, WS, TPS;
+};
+
+__host__ __device__ inline GroupSets group_sets(int L, int nT, int T)
+{
+    const int G4 = L * L * L / 8, want = G4 <= 16 ? 16 : G4 <= 32 ? 32 : (G4 + 63) & ~63;
+    const int least = (nT + 31) / 32, fill = T / want;
+    GroupSets g;
+    g.NS = fill > least ? fill : least;
+    g.WS = ((nT + g.NS - 1) / g.NS + 3) & ~3;
+    g.NS = (nT + g.WS - 1) / g.WS;
+    g.TPS = T / g.NS;
+    g.TPS = g.TPS >= 64 ? g.TPS & ~63 : g.TPS >= 32 ? 32 : 16;
+    return g;
+}
+
+// Its LDS layout (bytes): set words [2][NS][N/2] (NS of the largest team),
+// bond bits [2][N/2], the neighbour table, the walkers' Philox words
+// [2][MAX_T], thresholds, then the per-walker/slot arrays.
+struct GroupBitsLdsOff {
+    size_t spins, J, nb, pw, th, was, sow, U, ND, fl, sw, b64, total;
+};
+
+__host__ __device__ inline GroupBitsLdsOff group_bits_lds_offsets(int L, int nT)
+{
+    const size_t HALF = (size_t)L * L * L / 2, T4 = (size_t)((nT + 3) & ~3);
+    int ns = 1;
+    for (int T = 64; T <= GROUP_MAX_THREADS; T *= 2) {
+        const GroupSets g = group_sets(L, nT, T);
+        ns = g.NS > ns ? g.NS : ns;
+    }
+    GroupBitsLdsOff o;
+    o.spins = 0;
+    o.nb = align16((size_t)2 * ns * HALF * 4);
+    o.J = o.nb + HALF * 16;
+    o.pw = align16(o.J + 2 * HALF);
+    o.th = o.pw + (size_t)2 * MAX_T * 16;
+    o.was = o.th + (size_t)nT * 32;
+    o.sow = o.was + 4 * T4;
+    o.U = o.sow + 4 * T4;
+    o.ND = o.U + 4 * T4;
+    o.fl = o.ND + 4 * T4;
+    o.sw = o.fl + 4 * T4;
+    o.b64 = align16(o.sw + 4 * T4);
     o.total = align16(o.b64 + 8 * T4);
     return o;
 }

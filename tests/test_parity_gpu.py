@@ -199,6 +199,36 @@ def test_group_engine_tally_forms(torch_cuda):
         assert_same(work, st, ms, ref)
 
 
+@pytest.mark.parametrize("L,nT", [(4, 29), (6, 9), (6, 33), (6, 64), (8, 1), (8, 64), (10, 1), (10, 20), (10, 57),
+                                  (12, 17), (14, 4), (14, 40), (16, 4), (16, 33)])
+def test_group_engine_pm1_sets(torch_cuda, L, nT):
+    """The group engine's +-1 form: every team size the class allows splits the
+    walkers into other sets (4 to 32 walkers, the last one partly filled) and
+    gives a thread one to eight site groups of a half-sweep, sets sharing a
+    wave or spanning several; each equals the oracle bit for bit."""
+    from paper_1403_4560_amd import binding
+    hs = [0.1, -0.4, 7.0]
+    work = W.make_workload([L] * 3, nT, None, hs, jkind=W.J_PM1, measure_every=2, beta_range=(0.1, 1.8),
+                           name="pm1 sets")
+    sweeps = 5
+    ref = O.OracleEnsemble(work).run(sweeps)
+    for P in (1, 2, 4, 8):
+        with binding.Ensemble(work, tier=binding.TIER_BYTES) as ens:
+            assert ens.engines() == ["group"] * 3
+            try:
+                ens.set_batch_plan([P])
+            except binding.EAError:
+                assert P > 1
+                continue
+            print("case: pm1 sets L=%d n_T=%d teams=%d" % (L, nT, P), flush=True)
+            ens.set_plan(chunk=3)
+            ens.sweep_pt(sweeps)
+            st = ens.read_state()
+            ms = ens.measure()
+            assert ens.check_energies() == 0
+        assert_same(work, st, ms, ref)
+
+
 def test_group_engine_unbatched(torch_cuda):
     work = W.config_workload("mixed_L6_12", samples=[0, 2, 3], measure_start=4)
     check(work, 16, unbatched=True)
