@@ -65,7 +65,7 @@ struct BitGeo {
 
 // Spreading table and threshold tables sit at fixed LDS offsets, ahead of the
 // spins: byte addresses then come straight from the spread bytes.
-constexpr int SPREAD_OFF = 0, TH_OFF = 256 * 8;
+constexpr int SPREAD_OFF = 0, TH_OFF = 3 * 256 * 8;
 
 __device__ __forceinline__ uint32_t funnel(uint32_t hi, uint32_t lo, int s)
 {
@@ -85,15 +85,78 @@ __device__ __forceinline__ uint32_t spread2(uint32_t x)
 
 // Bytes 8M .. 8M + 7 of the class planes spread to byte offsets 4 e (sites
 // 8M .. 8M + 3 in Q[2M], 8M + 4 .. 8M + 7 in Q[2M + 1]); sp = LDS address of
-// the spreading table.
-template <int M>
-__device__ __forceinline__ void spread3(uint32_t sp, uint32_t E0, uint32_t E1, uint32_t E2, uint32_t Q[8])
+// the spreading tables, t: the six loads, issued ahead.
+struct Spread3 {
+    uint2 t[3];
+    template <int M>
+    __device__ __forceinline__ void load(uint32_t sp, const uint32_t E[3])
+    {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) t[k] = lds_load2(sp + 2048 * k + 8 * ((E[k] >> (8 * M)) & 0xFFu));
+    }
+    __device__ __forceinline__ void join(uint32_t *Q) const
+    {
+        Q[0] = xor3(t[0].x, t[1].x, t[2].x);
+        Q[1] = xor3(t[0].y, t[1].y, t[2].y);
+    }
+};
+
+// What a walker's slot gives its Philox calls of one half-sweep (rounds 0 and
+// 1, see ea_device.hpp), and the LDS address of its threshold table.
+struct BitsSlot {
+    uint32_t x, y, z, th;
+    __device__ __forceinline__ void init(uint32_t c1, uint32_t c2, uint32_t k0, uint32_t k1, uint32_t th_base)
+    {
+        const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
+        const uint64_t p0 = (uint64_t)0xD2511F53u * ((uint32_t)(p1 >> 32) ^ c1 ^ k0);
+        x = (uint32_t)p1 ^ (k0 + 0x9E3779B9u);
+        y = (uint32_t)(p0 >> 32) ^ (k1 + 0xBB67AE85u);
+        z = (uint32_t)p0;
+        th = th_base;
+    }
+};
+
+// The accept bits of 16 sites (bytes of Q[0 .. 3]; site groups g0 .. g0 + 3),
+// shifted into F from the highest down.  The scheduling barriers keep the
+// order written: the threshold loads ahead of the rounds that hide them, and
+// the four calls side by side, round by round.  (Left to itself the compiler
+// runs the calls one after the other and waits for each threshold where it
+// compares it.)  Bound: VALU issue, 1880 cycles of a wave per word of 32 sites
+// (59 an attempt).  With this order, round keys in vector registers, the
+// Philox products of the slot made once per half-sweep and a spreading table
+// per class plane, attempts/ns: L = 32 x 32 temperatures 2000 -> 2341 (one
+// chain per CU), L = 16 x 24 1645 -> 1965, L = 8 x 56 1346 -> 1564; one
+// sweep of few chains at L = 8 x 56 7.1 -> 5.9 us.
+__device__ __forceinline__ uint32_t bits_accept16(uint32_t F, const uint32_t *Q, const BitsSlot &w, uint32_t g0,
+                                                  uint32_t c3k1, const RoundKeys &key)
 {
-    const uint2 t0 = lds_load2(sp + 8 * ((E0 >> (8 * M)) & 0xFFu));
-    const uint2 t1 = lds_load2(sp + 8 * ((E1 >> (8 * M)) & 0xFFu));
-    const uint2 t2 = lds_load2(sp + 8 * ((E2 >> (8 * M)) & 0xFFu));
-    Q[2 * M] = t0.x | (t1.x << 1) | (t2.x << 2);
-    Q[2 * M + 1] = t0.y | (t1.y << 1) | (t2.y << 2);
+    uint32_t thr[4][4];
+    u32x4 c[4];
+#pragma unroll
+    for (int j = 3; j >= 0; --j)
+#pragma unroll
+        for (int k = 3; k >= 0; --k) thr[j][k] = lds_load(w.th + ((Q[j] >> (8 * k)) & 0xFFu));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const uint64_t p0 = (uint64_t)0xD2511F53u * (g0 + (uint32_t)j);
+        const uint64_t p1 = (uint64_t)0xCD9E8D57u * ((uint32_t)(p0 >> 32) ^ c3k1);
+        c[j] = u32x4{(uint32_t)(p1 >> 32) ^ w.x, (uint32_t)p1, (uint32_t)p0 ^ w.y, w.z};
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) c[j] = philox_round(c[j], key.a[k], key.b[k]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int j = 3; j >= 0; --j) {
+        F = shift_in_less(F, c[j].w, thr[j][3]);
+        F = shift_in_less(F, c[j].z, thr[j][2]);
+        F = shift_in_less(F, c[j].y, thr[j][1]);
+        F = shift_in_less(F, c[j].x, thr[j][0]);
+    }
+    return F;
 }
 
 struct BitTally {
@@ -103,14 +166,14 @@ struct BitTally {
 };
 
 // Metropolis update of word g (32 sites of sublattice P) of one walker.
-// Sw: the walker's bits [2][G]; JB: bond bits [2][6][G]; th_base: LDS byte
-// address of the slot's threshold table (8 entries, entry e); smem: the work
-// item's LDS; kb0/kb1: bits of k_s as all-zero/all-one masks for
+// Sw: the walker's bits [2][G]; JB: bond bits [2][6][G]; w: the walker's slot
+// (its threshold table has 8 entries, entry e); smem: the work item's LDS;
+// c3k1: sample id ^ Philox key word 1; kb0/kb1: bits of k_s as all-zero/all-one masks for
 // s = +1 / -1.
 template <int L, int P>
-__device__ __forceinline__ void bits_word(const SweepArgs &A, const SampleDev &d, uint32_t *Sw,
-                                          const uint32_t *JB, const char *smem, uint32_t th_base, uint32_t g,
-                                          uint32_t c1, uint32_t c2, const uint32_t kb0[3],
+__device__ __forceinline__ void bits_word(uint32_t *Sw,
+                                          const uint32_t *JB, const char *smem, const BitsSlot &w, uint32_t g,
+                                          uint32_t c3k1, const RoundKeys &key, const uint32_t kb0[3],
                                           const uint32_t kb1[3], BitTally &ty)
 {
     using B = BitGeo<L>;
@@ -150,25 +213,22 @@ __device__ __forceinline__ void bits_word(const SweepArgs &A, const SampleDev &d
     const uint32_t w2 = (~C2 & K2) | (~C2 & w1) | (K2 & w1);
     const uint32_t D = ~w2;
     // class numbers e (c, or 7 - c for s = +1) as byte offsets 4 e, 8 sites per pair
-    const uint32_t E0 = ~(C0 ^ s), E1 = ~(C1 ^ s), E2 = ~(C2 ^ s);
+    const uint32_t E[3] = {~(C0 ^ s), ~(C1 ^ s), ~(C2 ^ s)};
     uint32_t Q[8];
     const uint32_t sp = lds_addr(smem + SPREAD_OFF);
-    spread3<0>(sp, E0, E1, E2, Q);
-    spread3<1>(sp, E0, E1, E2, Q);
-    spread3<2>(sp, E0, E1, E2, Q);
-    spread3<3>(sp, E0, E1, E2, Q);
+    Spread3 t[4];
+    t[0].load<0>(sp, E);
+    t[1].load<1>(sp, E);
+    t[2].load<2>(sp, E);
+    t[3].load<3>(sp, E);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int m = 0; m < 4; ++m) t[m].join(Q + 2 * m);
     // sites 31 .. 0, one Philox call per four (counter word 0 = 8 g + q); F
     // collects the accept bits (w < thr), each shifted in as the carry of F + F
     uint32_t F = 0;
-#pragma unroll
-    for (int q = 7; q >= 0; --q) {
-        const u32x4 rw = philox4x32_10(8u * g + (uint32_t)q, c1, c2, d.sample_id, A.key0, A.key1);
-        const uint32_t Qq = Q[q];
-        F = shift_in_less(F, rw.w, lds_load(th_base + (Qq >> 24)));
-        F = shift_in_less(F, rw.z, lds_load(th_base + ((Qq >> 16) & 0xFFu)));
-        F = shift_in_less(F, rw.y, lds_load(th_base + ((Qq >> 8) & 0xFFu)));
-        F = shift_in_less(F, rw.x, lds_load(th_base + (Qq & 0xFFu)));
-    }
+    F = bits_accept16(F, Q + 4, w, 8u * g + 4u, c3k1, key);
+    F = bits_accept16(F, Q, w, 8u * g, c3k1, key);
     F |= D;
     own[g] = s ^ F;
     ty.flips += __builtin_popcount(F);
@@ -180,9 +240,22 @@ __device__ __forceinline__ void bits_word(const SweepArgs &A, const SampleDev &d
     }
 }
 
+// Sum over aligned groups of width lanes (a power of two, uniform; every lane
+// of a group active or none).
 __device__ __forceinline__ int lane_group_sum(int v, int width)
 {
-    for (int m = width >> 1; m >= 1; m >>= 1) v += __shfl_xor(v, m);
+    if (width >= 2) v += quad_xor<1>(v);
+    if (width >= 4) v += quad_xor<2>(v);
+    if (width >= 8) v += __builtin_amdgcn_mov_dpp(v, 0x141, 0xF, 0xF, true);   // lane ^ 7
+    if (width >= 16) v += __builtin_amdgcn_mov_dpp(v, 0x140, 0xF, 0xF, true);  // lane ^ 15
+    if (width >= 32) {
+        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);  // rows 0 and 1, 2 and 3
+        v = (int)(r[0] + r[1]);
+    }
+    if (width >= 64) {
+        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        v = (int)(r[0] + r[1]);
+    }
     return v;
 }
 
@@ -201,11 +274,9 @@ __device__ __forceinline__ void run_bits_item(const SweepArgs &A, const SampleDe
     I.was = (int32_t *)(smem + o.was);
     I.sow = (int32_t *)(smem + o.sow);
     I.M = (int32_t *)(smem + o.M);
-    I.dM = (int32_t *)(smem + o.dM);
     I.fl = (int32_t *)(smem + o.fl);
     I.sw = (int32_t *)(smem + o.sw);
-    I.EJ = (long long *)(smem + o.EJ);
-    I.dEJ = (long long *)(smem + o.dEJ);
+    int32_t *EJ = (int32_t *)(smem + o.EJ);
     I.b64 = (double *)(smem + o.b64);
 
     const size_t sbase = (size_t)d.spin_off + (size_t)r * nT * N;
@@ -237,12 +308,12 @@ __device__ __forceinline__ void run_bits_item(const SweepArgs &A, const SampleDe
             lo |= ((v >> k) & 1u) * 4u << (8 * k);
             hi |= ((v >> (k + 4)) & 1u) * 4u << (8 * k);
         }
-        SP[v] = make_uint2(lo, hi);
+        for (int k = 0; k < 3; ++k) SP[256 * k + v] = make_uint2(lo << k, hi << k);
     }
     for (int i = tid; i < nT; i += T) {
         I.was[i] = A.was[gi + i];
         I.sow[A.was[gi + i]] = i;  // kept by exchange_pass from here on
-        I.EJ[i] = A.EJ[gi + i];
+        EJ[i] = (int32_t)A.EJ[gi + i];  // at most 3 N in size
         I.M[i] = A.M[gi + i];
         I.fl[i] = 0;
         I.sw[i] = 0;
@@ -260,6 +331,10 @@ __device__ __forceinline__ void run_bits_item(const SweepArgs &A, const SampleDe
     const bool on = w < nT;
     uint32_t *Sw = SB + (size_t)(on ? w : 0) * 2 * G;
     const double hd = (double)d.h32;
+    RoundKeys key;
+    key.init(A.key0, A.key1);
+    uint32_t c3k1 = d.sample_id ^ A.key1;
+    asm volatile("" : "+v"(c3k1));
     const int64_t n0 = A.state[0];
     int64_t next_meas = next_measurement(n0, A.measure_every, A.measure_start);
     int64_t f = 0;  // frame of the next measurement within this chunk
@@ -268,28 +343,30 @@ __device__ __forceinline__ void run_bits_item(const SweepArgs &A, const SampleDe
         const int t = on ? I.sow[w] : 0;
         const uint32_t th_base = lds_addr(smem + TH_OFF + 32 * t);
         const uint32_t c2 = (PURPOSE_METROPOLIS << 28) | ((uint32_t)t << 1) | (uint32_t)r;
+        BitsSlot bs;
         BitTally ty;
         if (on) {
-            const uint32_t c1 = (uint32_t)(2 * n);
+            bs.init((uint32_t)(2 * n), c2, A.key0, A.key1, th_base);
 #pragma unroll 1
-            for (uint32_t g = lane; g < G; g += tpw) bits_word<L, 0>(A, d, Sw, JB, smem, th_base, g, c1, c2, kb0, kb1, ty);
+            for (uint32_t g = lane; g < G; g += tpw) bits_word<L, 0>(Sw, JB, smem, bs, g, c3k1, key, kb0, kb1, ty);
         }
         __syncthreads();
         if (on) {
-            const uint32_t c1 = (uint32_t)(2 * n + 1);
+            bs.init((uint32_t)(2 * n + 1), c2, A.key0, A.key1, th_base);
 #pragma unroll 1
-            for (uint32_t g = lane; g < G; g += tpw) bits_word<L, 1>(A, d, Sw, JB, smem, th_base, g, c1, c2, kb0, kb1, ty);
+            for (uint32_t g = lane; g < G; g += tpw) bits_word<L, 1>(Sw, JB, smem, bs, g, c3k1, key, kb0, kb1, ty);
             const int sf = lane_group_sum(ty.flips, tpw), sd = lane_group_sum(ty.fdown, tpw);
             const int su = lane_group_sum(ty.u, tpw);
             if (lane == 0) {
                 // every bond has one odd end: E_J = (unsatisfied) - (satisfied) = 2 U - 3 N
-                I.EJ[w] = 2 * (long long)su - 3 * (long long)N;
+                EJ[w] = 2 * su - 3 * N;
                 I.M[w] += -2 * (sf - 2 * sd);
                 I.fl[t] += sf;
             }
         }
         __syncthreads();
-        exchange_pass(A, d, r, n, I, 1.0, hd);
+        if (tid < 64)
+            exchange_slots(A, d, r, n, I, tid, [&](int w) { return (double)EJ[w] - hd * (double)I.M[w]; });
         __syncthreads();
         // Snapshot for the overlap measurement, in slot order: row (y, z) of
         // L bits interleaves the two sublattices' rows.
@@ -309,7 +386,7 @@ __device__ __forceinline__ void run_bits_item(const SweepArgs &A, const SampleDe
             }
             for (int ts = tid; ts < nT; ts += T) {
                 const int ww = I.was[ts];
-                A.frameE[f * 2 * A.total_slots + gi + ts] = (double)I.EJ[ww] - hd * (double)I.M[ww];
+                A.frameE[f * 2 * A.total_slots + gi + ts] = (double)EJ[ww] - hd * (double)I.M[ww];
             }
             ++f;
             __syncthreads();  // the next sweep changes the spins read here
@@ -326,7 +403,7 @@ __device__ __forceinline__ void run_bits_item(const SweepArgs &A, const SampleDe
     }
     for (int i = tid; i < nT; i += T) {
         A.was[gi + i] = I.was[i];
-        A.EJ[gi + i] = I.EJ[i];
+        A.EJ[gi + i] = EJ[i];
         A.M[gi + i] = I.M[i];
         A.flips[gi + i] += I.fl[i];
         A.swaps[gi + i] += I.sw[i];

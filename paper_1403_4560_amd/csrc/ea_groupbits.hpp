@@ -211,22 +211,6 @@ __device__ __forceinline__ uint2 *spread_tables()
     return tab;
 }
 
-// The round keys of Philox rounds 2 .. 9, held in vector registers: a
-// three-input xor with a scalar operand issues at 4.4 cycles a wave, from
-// vector registers at 2.6.
-struct RoundKeys {
-    uint32_t a[8], b[8];
-    __device__ __forceinline__ void init(uint32_t k0, uint32_t k1)
-    {
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            a[k] = k0 + (uint32_t)(k + 2) * 0x9E3779B9u;
-            b[k] = k1 + (uint32_t)(k + 2) * 0xBB67AE85u;
-            asm volatile("" : "+v"(a[k]), "+v"(b[k]));
-        }
-    }
-};
-
 // What a chain's sweep needs of the walkers' slots: the Philox state words that
 // depend on the slot alone (rounds 0 and 1), and the LDS address of the slot's
 // threshold table.

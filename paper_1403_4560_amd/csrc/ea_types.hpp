@@ -205,12 +205,12 @@ __host__ __device__ inline LdsOff lds_offsets(int L, int nT, int jkind)
     return o;
 }
 
-// LDS layout of one bit-engine work item (bytes): the 256-entry
-// bit-to-byte spreading table and the per-slot threshold tables [n_T][8] at
+// LDS layout of one bit-engine work item (bytes): the three 256-entry
+// bit-to-byte spreading tables and the per-slot threshold tables [n_T][8] at
 // fixed offsets, then spin bits [n_T][2][N/64] words, bond bits [2][6][N/64],
 // then the per-walker/slot arrays of the common frame.
 struct BitsLdsOff {
-    size_t spread, th, spins, J, was, sow, M, dM, fl, sw, EJ, dEJ, b64, total;
+    size_t spread, th, spins, J, was, sow, M, fl, sw, EJ, b64, total;
 };
 
 __host__ __device__ inline BitsLdsOff bits_lds_offsets(int L, int nT)
@@ -219,18 +219,16 @@ __host__ __device__ inline BitsLdsOff bits_lds_offsets(int L, int nT)
     const size_t T4 = (size_t)((nT + 3) & ~3);
     BitsLdsOff o;
     o.spread = 0;
-    o.th = 256 * 8;
+    o.th = 3 * 256 * 8;
     o.spins = align16(o.th + (size_t)nT * 8 * 4);
     o.J = o.spins + (size_t)nT * 2 * G * 4;
     o.was = o.J + 12 * G * 4;
     o.sow = o.was + 4 * T4;
     o.M = o.sow + 4 * T4;
-    o.dM = o.M + 4 * T4;
-    o.fl = o.dM + 4 * T4;
+    o.fl = o.M + 4 * T4;
     o.sw = o.fl + 4 * T4;
-    o.EJ = align16(o.sw + 4 * T4);
-    o.dEJ = o.EJ + 8 * T4;
-    o.b64 = o.dEJ + 8 * T4;
+    o.EJ = o.sw + 4 * T4;
+    o.b64 = align16(o.EJ + 4 * T4);
     o.total = align16(o.b64 + 8 * T4);
     return o;
 }
