@@ -101,21 +101,6 @@ struct Spread3 {
     }
 };
 
-// What a walker's slot gives its Philox calls of one half-sweep (rounds 0 and
-// 1, see ea_device.hpp), and the LDS address of its threshold table.
-struct BitsSlot {
-    uint32_t x, y, z, th;
-    __device__ __forceinline__ void init(uint32_t c1, uint32_t c2, uint32_t k0, uint32_t k1, uint32_t th_base)
-    {
-        const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
-        const uint64_t p0 = (uint64_t)0xD2511F53u * ((uint32_t)(p1 >> 32) ^ c1 ^ k0);
-        x = (uint32_t)p1 ^ (k0 + 0x9E3779B9u);
-        y = (uint32_t)(p0 >> 32) ^ (k1 + 0xBB67AE85u);
-        z = (uint32_t)p0;
-        th = th_base;
-    }
-};
-
 // The accept bits of 16 sites (bytes of Q[0 .. 3]; site groups g0 .. g0 + 3),
 // shifted into F from the highest down.  The scheduling barriers keep the
 // order written: the threshold loads ahead of the rounds that hide them, and
@@ -127,21 +112,17 @@ struct BitsSlot {
 // per class plane, attempts/ns: L = 32 x 32 temperatures 2000 -> 2341 (one
 // chain per CU), L = 16 x 24 1645 -> 1965, L = 8 x 56 1346 -> 1564; one
 // sweep of few chains at L = 8 x 56 7.1 -> 5.9 us.
-__device__ __forceinline__ uint32_t bits_accept16(uint32_t F, const uint32_t *Q, const BitsSlot &w, uint32_t g0,
-                                                  uint32_t c3k1, const RoundKeys &key)
+__device__ __forceinline__ uint32_t bits_accept16(uint32_t F, const uint32_t *Q, const PhiloxSlot &w, uint32_t th,
+                                                  uint32_t g0, uint32_t c3k1, const RoundKeys &key)
 {
     uint32_t thr[4][4];
     u32x4 c[4];
 #pragma unroll
     for (int j = 3; j >= 0; --j)
 #pragma unroll
-        for (int k = 3; k >= 0; --k) thr[j][k] = lds_load(w.th + ((Q[j] >> (8 * k)) & 0xFFu));
+        for (int k = 3; k >= 0; --k) thr[j][k] = lds_load(th + ((Q[j] >> (8 * k)) & 0xFFu));
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const uint64_t p0 = (uint64_t)0xD2511F53u * (g0 + (uint32_t)j);
-        const uint64_t p1 = (uint64_t)0xCD9E8D57u * ((uint32_t)(p0 >> 32) ^ c3k1);
-        c[j] = u32x4{(uint32_t)(p1 >> 32) ^ w.x, (uint32_t)p1, (uint32_t)p0 ^ w.y, w.z};
-    }
+    for (int j = 0; j < 4; ++j) c[j] = w.start(philox_group(g0 + (uint32_t)j, c3k1, 0u));
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
@@ -166,14 +147,15 @@ struct BitTally {
 };
 
 // Metropolis update of word g (32 sites of sublattice P) of one walker.
-// Sw: the walker's bits [2][G]; JB: bond bits [2][6][G]; w: the walker's slot
-// (its threshold table has 8 entries, entry e); smem: the work item's LDS;
+// Sw: the walker's bits [2][G]; JB: bond bits [2][6][G]; w: the Philox words of
+// the walker's slot, th: the LDS address of its threshold table (8 entries,
+// entry e); smem: the work item's LDS;
 // c3k1: sample id ^ Philox key word 1; kb0/kb1: bits of k_s as all-zero/all-one masks for
 // s = +1 / -1.
 template <int L, int P>
 __device__ __forceinline__ void bits_word(uint32_t *Sw,
-                                          const uint32_t *JB, const char *smem, const BitsSlot &w, uint32_t g,
-                                          uint32_t c3k1, const RoundKeys &key, const uint32_t kb0[3],
+                                          const uint32_t *JB, const char *smem, const PhiloxSlot &w, uint32_t th,
+                                          uint32_t g, uint32_t c3k1, const RoundKeys &key, const uint32_t kb0[3],
                                           const uint32_t kb1[3], BitTally &ty)
 {
     using B = BitGeo<L>;
@@ -227,8 +209,8 @@ __device__ __forceinline__ void bits_word(uint32_t *Sw,
     // sites 31 .. 0, one Philox call per four (counter word 0 = 8 g + q); F
     // collects the accept bits (w < thr), each shifted in as the carry of F + F
     uint32_t F = 0;
-    F = bits_accept16(F, Q + 4, w, 8u * g + 4u, c3k1, key);
-    F = bits_accept16(F, Q, w, 8u * g, c3k1, key);
+    F = bits_accept16(F, Q + 4, w, th, 8u * g + 4u, c3k1, key);
+    F = bits_accept16(F, Q, w, th, 8u * g, c3k1, key);
     F |= D;
     own[g] = s ^ F;
     ty.flips += __builtin_popcount(F);
@@ -312,7 +294,7 @@ __device__ __forceinline__ void run_bits_item(const SweepArgs &A, const SampleDe
     }
     for (int i = tid; i < nT; i += T) {
         I.was[i] = A.was[gi + i];
-        I.sow[A.was[gi + i]] = i;  // kept by exchange_pass from here on
+        I.sow[A.was[gi + i]] = i;  // kept by the exchange from here on
         EJ[i] = (int32_t)A.EJ[gi + i];  // at most 3 N in size
         I.M[i] = A.M[gi + i];
         I.fl[i] = 0;
@@ -343,18 +325,18 @@ __device__ __forceinline__ void run_bits_item(const SweepArgs &A, const SampleDe
         const int t = on ? I.sow[w] : 0;
         const uint32_t th_base = lds_addr(smem + TH_OFF + 32 * t);
         const uint32_t c2 = (PURPOSE_METROPOLIS << 28) | ((uint32_t)t << 1) | (uint32_t)r;
-        BitsSlot bs;
+        PhiloxSlot ps;
         BitTally ty;
         if (on) {
-            bs.init((uint32_t)(2 * n), c2, A.key0, A.key1, th_base);
+            ps.init((uint32_t)(2 * n), c2, A.key0, A.key1);
 #pragma unroll 1
-            for (uint32_t g = lane; g < G; g += tpw) bits_word<L, 0>(Sw, JB, smem, bs, g, c3k1, key, kb0, kb1, ty);
+            for (uint32_t g = lane; g < G; g += tpw) bits_word<L, 0>(Sw, JB, smem, ps, th_base, g, c3k1, key, kb0, kb1, ty);
         }
         __syncthreads();
         if (on) {
-            bs.init((uint32_t)(2 * n + 1), c2, A.key0, A.key1, th_base);
+            ps.init((uint32_t)(2 * n + 1), c2, A.key0, A.key1);
 #pragma unroll 1
-            for (uint32_t g = lane; g < G; g += tpw) bits_word<L, 1>(Sw, JB, smem, bs, g, c3k1, key, kb0, kb1, ty);
+            for (uint32_t g = lane; g < G; g += tpw) bits_word<L, 1>(Sw, JB, smem, ps, th_base, g, c3k1, key, kb0, kb1, ty);
             const int sf = lane_group_sum(ty.flips, tpw), sd = lane_group_sum(ty.fdown, tpw);
             const int su = lane_group_sum(ty.u, tpw);
             if (lane == 0) {

@@ -85,6 +85,37 @@ struct RoundKeys {
     }
 };
 
+// A site group's part of the state after round 1 (word 0 = g, word 3 = the
+// sample): {hi(q1), lo(p0), lo(q1)}.
+__device__ __forceinline__ uint4 philox_group(uint32_t g, uint32_t sample, uint32_t k1)
+{
+    const uint64_t p0 = (uint64_t)0xD2511F53u * g;
+    const uint64_t q1 = (uint64_t)0xCD9E8D57u * ((uint32_t)(p0 >> 32) ^ sample ^ k1);
+    return make_uint4((uint32_t)(q1 >> 32), (uint32_t)p0, (uint32_t)q1, 0u);
+}
+
+// The slot's part for one half-sweep (word 2 = c2, word 1 = c1), round keys
+// folded in.
+struct PhiloxSlot {
+    uint32_t x, y, z;
+    __device__ __forceinline__ void init(uint32_t c1, uint32_t c2, uint32_t k0, uint32_t k1)
+    {
+        const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
+        const uint64_t q0 = (uint64_t)0xD2511F53u * ((uint32_t)(p1 >> 32) ^ c1 ^ k0);
+        x = (uint32_t)p1 ^ (k0 + 0x9E3779B9u);
+        y = (uint32_t)(q0 >> 32) ^ (k1 + 0xBB67AE85u);
+        z = (uint32_t)q0;
+    }
+    __device__ __forceinline__ u32x4 start(const uint4 g) const { return {g.x ^ x, g.z, g.y ^ y, z}; }
+    __device__ __forceinline__ u32x4 call(const uint4 g, const RoundKeys &key) const
+    {
+        u32x4 c = start(g);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) c = philox_round(c, key.a[k], key.b[k]);
+        return c;
+    }
+};
+
 // Counter purposes (bits 28..31 of counter word 2).
 constexpr uint32_t PURPOSE_METROPOLIS = 0u;
 constexpr uint32_t PURPOSE_EXCHANGE = 1u;

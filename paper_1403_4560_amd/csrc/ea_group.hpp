@@ -77,7 +77,8 @@ __device__ __forceinline__ uint4 nbr_entry(int h)
 
 struct GroupLane {
     float ka[4], kb[4];     // per walker: the folded exponent's constants (update_word_gauss)
-    uint32_t c2[4];         // Philox counter word 2 of each walker
+    PhiloxSlot ps[4];       // per walker: its slot's Philox words of this half-sweep
+    int t[4];               // per walker: its slot
     uint32_t valid;         // 0xFF in the bytes of real walkers
     float h32;              // the sample's field, held in a vector register
 };
@@ -93,14 +94,19 @@ struct GroupTally {
 template <int L, int P>
 __device__ __forceinline__ void group_item(const SweepArgs &A, const SampleDev &d, uint32_t *SG, const int *Jl,
                                            const float *b32, const uint4 *NB, int NQ, int q,
-                                           int g4, uint32_t c1, const GroupLane &ln, GroupTally &ty)
+                                           int g4, const RoundKeys &key, const GroupLane &ln, GroupTally &ty)
 {
     constexpr int HALF = L * L * L / 2, PS = HALF + 1;
     uint32_t *Sp = SG + (P * NQ + q) * PS;
     const uint32_t *So = SG + ((1 - P) * NQ + q) * PS;
+    const uint4 pg = philox_group((uint32_t)g4, d.sample_id, A.key1);
     u32x4 rw[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) rw[i] = philox4x32_10((uint32_t)g4, c1, ln.c2[i], d.sample_id, A.key0, A.key1);
+    for (int i = 0; i < 4; ++i) rw[i] = ln.ps[i].start(pg);
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) rw[i] = philox_round(rw[i], key.a[k], key.b[k]);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const int h = 4 * g4 + k;
@@ -125,10 +131,10 @@ __device__ __forceinline__ void group_item(const SweepArgs &A, const SampleDev &
         const int Ja[4] = {jx, jx, jx, jx}, Js[4] = {jxm, jxm, jxm, jxm};
         const int Jy[4] = {jy, jy, jy, jy}, Jyn[4] = {jym, jym, jym, jym};
         const int Jz[4] = {jz, jz, jz, jz}, Jzn[4] = {jzm, jzm, jzm, jzm};
-        // the exact path reads 2 beta32 of walker i's slot, t = bits 1 .. 27 of its counter word
+        // the exact path reads 2 beta32 of walker i's slot
         // Sus = S_u + hgrid (the field's grid part folded into the integer field)
         const uint32_t fm = update_word_gauss<true>(Sv, X[0], X[1], X[2], X[3], X[4], X[5], Ja, Js, Jy, Jyn, Jz, Jzn, rk,
-                                     ln.ka, ln.kb, [&](int i) { return 2.0f * b32[(ln.c2[i] >> 1) & 0x7FFFFFFu]; },
+                                     ln.ka, ln.kb, [&](int i) { return 2.0f * b32[ln.t[i]]; },
                                      ln.h32, d.hgrid, Sus) &
              ln.valid;
         Sp[h] = Sv ^ fm;
@@ -192,7 +198,7 @@ __device__ __forceinline__ void run_group_item(const SweepArgs &A, const SampleD
     }
     for (int i = tid; i < nT; i += T) {
         I.was[i] = A.was[gi + i];
-        I.sow[A.was[gi + i]] = i;  // kept by exchange_pass from here on
+        I.sow[A.was[gi + i]] = i;  // kept by the exchange from here on
         // walker totals: E_J = -dEJ, magnetisation M + dM (see the sweep loop)
         I.dEJ[i] = -A.EJ[gi + i];
         I.dM[i] = 0;
@@ -248,6 +254,8 @@ __device__ __forceinline__ void run_group_item(const SweepArgs &A, const SampleD
     // at the start of the next sweep, before its own tallies (which follow the
     // first half-sweep's barrier), so no pass of their own is needed.
     const auto energy = [&](int w) { return (double)(-I.dEJ[w]) * 0x1p-18 - hd * (double)(I.M[w] + I.dM[w]); };
+    RoundKeys key;
+    key.init(A.key0, A.key1);
     for (int it = 0; it < A.K; ++it) {
         const int64_t n = n0 + it;
 #pragma unroll 1
@@ -264,24 +272,29 @@ __device__ __forceinline__ void run_group_item(const SweepArgs &A, const SampleD
             const float cp = two_beta_log2e(I.b32[ts[i]]);
             ln.ka[i] = cp * 0x1p-18f;
             ln.kb[i] = cp * (d.h32 - (float)d.hgrid * 0x1p-18f);
-            ln.c2[i] = (PURPOSE_METROPOLIS << 28) | ((uint32_t)ts[i] << 1) | (uint32_t)r;
+            ln.t[i] = ts[i];
         }
         ln.valid = valid;
         ln.h32 = d.h32;
         asm volatile("" : "+v"(ln.h32));
         GroupTally ty;
+        const auto slot_words = [&](int p) {
+            for (int i = 0; i < 4; ++i)
+                ln.ps[i].init((uint32_t)(2 * n + p), (PURPOSE_METROPOLIS << 28) | ((uint32_t)ts[i] << 1) | (uint32_t)r,
+                              A.key0, A.key1);
+        };
         if (on) {
-            const uint32_t c1 = (uint32_t)(2 * n);
+            slot_words(0);
 #pragma unroll 1
             for (int g4 = gs; g4 < G4; g4 += TPQ)
-                group_item<L, 0>(A, d, SG, Jl, I.b32, NB, NQ, q, g4, c1, ln, ty);
+                group_item<L, 0>(A, d, SG, Jl, I.b32, NB, NQ, q, g4, key, ln, ty);
         }
         __syncthreads();
         if (on) {
-            const uint32_t c1 = (uint32_t)(2 * n + 1);
+            slot_words(1);
 #pragma unroll 1
             for (int g4 = gs; g4 < G4; g4 += TPQ)
-                group_item<L, 1>(A, d, SG, Jl, I.b32, NB, NQ, q, g4, c1, ln, ty);
+                group_item<L, 1>(A, d, SG, Jl, I.b32, NB, NQ, q, g4, key, ln, ty);
         }
         // Per-walker tallies (idle lanes hold zeros).  dEJ collects minus the
         // new E_J: the second half-sweep summed (S_u + hgrid) XOR m' = s'(S_u +
@@ -363,7 +376,7 @@ __device__ __forceinline__ void run_group_item(const SweepArgs &A, const SampleD
             }
         }
         __syncthreads();
-        exchange_pass_e(A, d, r, n, I, energy, tm);
+        if (tid < 64) exchange_slots(A, d, r, n, I, tid, energy);
         __syncthreads();
         // Snapshot for the overlap measurement, in slot order.
         const int64_t done = n + 1;

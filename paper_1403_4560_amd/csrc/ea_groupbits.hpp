@@ -232,8 +232,8 @@ struct GroupBitsItem {
 // to itself the compiler orders by register pressure, one walker after the
 // other and each threshold waited for where it is used: 2500 cycles a quad
 // instead of 1800 with one wave per SIMD.
-__device__ __forceinline__ void group_bits_quad(const uint4 (&w)[4], const uint32_t Q[4], uint32_t sa, uint32_t sb,
-                                                uint32_t sc, const RoundKeys &key, uint32_t F[4])
+__device__ __forceinline__ void group_bits_quad(const uint4 (&w)[4], const uint32_t Q[4], const uint4 pg,
+                                                const RoundKeys &key, uint32_t F[4])
 {
     uint32_t thr[4][4];
 #pragma unroll
@@ -242,7 +242,7 @@ __device__ __forceinline__ void group_bits_quad(const uint4 (&w)[4], const uint3
         for (int k = 0; k < 4; ++k) thr[j][k] = lds_load(w[j].w + ((Q[k] >> (8 * j)) & 0xFFu));
     u32x4 c[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) c[j] = u32x4{sa ^ w[j].x, sc, sb ^ w[j].y, w[j].z};
+    for (int j = 0; j < 4; ++j) c[j] = PhiloxSlot{w[j].x, w[j].y, w[j].z}.start(pg);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
@@ -317,10 +317,7 @@ __device__ __forceinline__ void group_bits_item(const SweepArgs &A, const Sample
         F[k] = 0;
     }
     // the site group's part of Philox rounds 0 and 1
-    constexpr uint32_t M0 = 0xD2511F53u, M1 = 0xCD9E8D57u;
-    const uint64_t p0 = (uint64_t)M0 * (uint32_t)g4;
-    const uint64_t p1 = (uint64_t)M1 * ((uint32_t)(p0 >> 32) ^ d.sample_id ^ A.key1);
-    const uint32_t sa = (uint32_t)(p1 >> 32), sb = (uint32_t)p0, sc = (uint32_t)p1;
+    const uint4 pg = philox_group((uint32_t)g4, d.sample_id, A.key1);
     uint32_t pw = G.pw + P * G.pws + 16 * (s * G.WS);
     const uint32_t sp = lds_addr(spread_tables());
     uint32_t e[4][3];
@@ -348,10 +345,10 @@ __device__ __forceinline__ void group_bits_item(const SweepArgs &A, const Sample
         for (int k = 0; k < 4; ++k)
 #pragma unroll
             for (int b = 0; b < 3; ++b) e[k][b] >>= 8;
-        group_bits_quad(w, Ql, sa, sb, sc, key, F);
+        group_bits_quad(w, Ql, pg, key, F);
         if (left > 4) {
             load_walkers(pw + 64, w);
-            group_bits_quad(w, Qh, sa, sb, sc, key, F);
+            group_bits_quad(w, Qh, pg, key, F);
         }
     }
 #pragma unroll
@@ -533,14 +530,13 @@ __device__ __forceinline__ void run_group_bits_item(const SweepArgs &A, const Sa
     // (from n_T on: the padding of the last set, whose bits are never used;
     // whole sets never reach past 64 walkers)
     const auto slot_words = [&](int64_t n, int w) {
-        constexpr uint32_t M0 = 0xD2511F53u, M1 = 0xCD9E8D57u, W0 = 0x9E3779B9u, W1 = 0xBB67AE85u;
         const uint32_t th = lds_addr(TH + 8 * min(tid, nT - 1));
-        const uint64_t p1 = (uint64_t)M1 * ((PURPOSE_METROPOLIS << 28) | ((uint32_t)tid << 1) | (uint32_t)r);
+        const uint32_t c2 = (PURPOSE_METROPOLIS << 28) | ((uint32_t)tid << 1) | (uint32_t)r;
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
-            const uint64_t p0 = (uint64_t)M0 * ((uint32_t)(p1 >> 32) ^ (uint32_t)(2 * n + p) ^ A.key0);
-            PW[p * MAX_T + w] = make_uint4((uint32_t)p1 ^ (A.key0 + W0), (uint32_t)(p0 >> 32) ^ (A.key1 + W1),
-                                           (uint32_t)p0, th);
+            PhiloxSlot ps;
+            ps.init((uint32_t)(2 * n + p), c2, A.key0, A.key1);
+            PW[p * MAX_T + w] = make_uint4(ps.x, ps.y, ps.z, th);
         }
     };
     if (tid < 64) slot_words(n0, tid < nT ? I.was[tid] : tid);

@@ -24,7 +24,7 @@
 
 namespace ea {
 template <int L, int JK, int VAR> __global__ void site_sweep_kernel(SweepArgs A);
-template <int L, int VAR> __global__ void row_sweep_kernel(SweepArgs A);
+template <int L, int VAR, bool TAB> __global__ void row_sweep_kernel(SweepArgs A);
 template <int L, int VAR> __global__ void bits_sweep_kernel(SweepArgs A);
 template <int L, int JK, int VAR> __global__ void group_sweep_kernel(SweepArgs A);
 template <int L, int JK, int VAR> __global__ void hbm_half_kernel(SweepArgs A);
@@ -165,6 +165,7 @@ struct ea_ensemble {
         bool bits;           // multispin engine
         bool group;          // walker-interleaved engine
         int group_min_threads = 64;
+        bool row_table = true;  // row engine: the site groups' Philox words in LDS
     };
     std::vector<Class> classes;
     std::vector<int> item_pos;  // sample -> index of its chain-a item in the sorted item list
@@ -575,7 +576,7 @@ SweepFn group_fn(int L, int jk)
 #undef EA_CASE
 }
 
-SweepFn sweep_fn(int L, int jk, bool row, bool bits, bool group, bool unbatched)
+SweepFn sweep_fn(int L, int jk, bool row, bool table, bool bits, bool group, bool unbatched)
 {
     if (group) return unbatched ? group_fn<1>(L, jk) : group_fn<0>(L, jk);
     if (bits) {
@@ -585,8 +586,9 @@ SweepFn sweep_fn(int L, int jk, bool row, bool bits, bool group, bool unbatched)
         return nullptr;
     }
     if (row) {
-        if (L == 8) return unbatched ? row_sweep_kernel<8, 1> : row_sweep_kernel<8, 0>;
-        if (L == 16) return unbatched ? row_sweep_kernel<16, 1> : row_sweep_kernel<16, 0>;
+        if (L == 8) return unbatched ? row_sweep_kernel<8, 1, true> : row_sweep_kernel<8, 0, true>;
+        if (L == 16 && table) return unbatched ? row_sweep_kernel<16, 1, true> : row_sweep_kernel<16, 0, true>;
+        if (L == 16) return unbatched ? row_sweep_kernel<16, 1, false> : row_sweep_kernel<16, 0, false>;
         return nullptr;
     }
     return unbatched ? site_fn<1>(L, jk) : site_fn<0>(L, jk);
@@ -605,6 +607,18 @@ int row_threads(int L, int nT)
 bool row_engine(int L, int nT, int jk)
 {
     return jk == 0 && (L == 8 || L == 16) && row_threads(L, nT) <= ROW_MAX_THREADS;
+}
+
+// The row engine's table of the site groups' Philox words (two multiply-adds
+// and two xors less per word) costs 2 N bytes of LDS.  L = 16 chains go without
+// it where it would cost a resident workgroup: at 7 temperatures (2 workgroups
+// per CU without, 1 with) 651 attempts/ns with it, 868 without; at 24 (one
+// either way) 1150 with it, 1090 without.  (L = 8: 1 KB, never decisive, its
+// residency is bound by registers.)
+bool row_table(int L, int nT, size_t lds_max)
+{
+    const size_t with = lds_offsets(L, nT, EA_J_GAUSS_F32, true).total, without = lds_offsets(L, nT, EA_J_GAUSS_F32).total;
+    return L == 8 || lds_max / with == lds_max / without;
 }
 
 // The field's nearest point on the coupling grid, round(h 2^18), kept within
@@ -730,7 +744,7 @@ hipError_t launch_hbm_sweep(ea_ensemble *e, int L, int it, int item_first, int n
 hipError_t launch_class(ea_ensemble *e, const ea_ensemble::Class &c, int K, int first, int n_items, bool unbatched)
 {
     SweepArgs A = sweep_args(e, K, (const int32_t *)e->items.p + first, n_items);
-    SweepFn fn = sweep_fn(c.L, e->jkind, c.row, c.bits, c.group, unbatched);
+    SweepFn fn = sweep_fn(c.L, e->jkind, c.row, c.row_table, c.bits, c.group, unbatched);
     if (!fn) return hipErrorInvalidDeviceFunction;
     // the group engine runs the team size the plan gives its class (the batch
     // launch's teams: BATCH_THREADS / teams per workgroup), which keeps a
@@ -1327,8 +1341,9 @@ ea_status ea_create_ensemble(const ea_desc *d, void *hip_stream, ea_ensemble **o
                 c.threads = std::max(c.threads, group_threads(h.L, h.nT, e->jkind));
                 c.group_min_threads = std::max(c.group_min_threads, (group_items(h.L, h.nT) / 16 + 63) / 64 * 64);
             } else {
-                c.lds = std::max(c.lds, lds_offsets(h.L, h.nT, e->jkind).total);
                 const bool row = d->tier != EA_TIER_SITE && row_engine(h.L, h.nT, e->jkind);
+                if (row) c.row_table = c.row_table && row_table(h.L, h.nT, lds_max);
+                c.lds = std::max(c.lds, lds_offsets(h.L, h.nT, e->jkind, row && row_table(h.L, h.nT, lds_max)).total);
                 c.row = c.row && row;
                 if (row) c.threads = std::max(c.threads, row_threads(h.L, h.nT));
             }
@@ -1338,7 +1353,7 @@ ea_status ea_create_ensemble(const ea_desc *d, void *hip_stream, ea_ensemble **o
         for (const auto &c : e->classes) {
             if (c.hbm) continue;
             for (int v = 0; v < 2; ++v) {
-                SweepFn fn = sweep_fn(c.L, e->jkind, c.row, c.bits, c.group, v == 1);
+                SweepFn fn = sweep_fn(c.L, e->jkind, c.row, c.row_table, c.bits, c.group, v == 1);
                 if (fn) (void)hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
                                                   (int)lds_max);
             }

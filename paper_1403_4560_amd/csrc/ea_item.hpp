@@ -90,6 +90,7 @@ struct ItemLds {
     uint32_t *lut;
     float *b32;
     double *b64;
+    uint4 *ph;  // row engine: the site groups' Philox words (philox_group)
 };
 
 // The descriptor of a workgroup's sample, read into scalar registers: the
@@ -125,50 +126,8 @@ __device__ __forceinline__ ItemLds item_lds(char *smem, int L, int nT, int jkind
     p.lut = (uint32_t *)(smem + o.lut);
     p.b32 = (float *)(smem + o.b32);
     p.b64 = (double *)(smem + o.b64);
+    p.ph = (uint4 *)(smem + o.ph);
     return p;
-}
-
-// Replica exchange of neighbouring slots (t, t+1), t = n&1, n&1 + 2, ...
-// (Methods: parallel tempering; even-odd pairs alternate with the sweep
-// parity).  D = (beta_t - beta_{t+1}) (E_t - E_{t+1}) in binary64, E_w =
-// energy(w); accepted iff D >= 0 or u53 < exp_ea64(D) (decided by
-// exchange_accept), u53 from the exchange counter (0, n, (1 << 28) | (t << 1)
-// | r, sample).  Swaps walker labels only, in both maps (was: slot -> walker,
-// sow: walker -> slot), so the sweep that follows reads its temperatures
-// without rebuilding sow.
-template <class Energy>
-__device__ __forceinline__ void exchange_pass_e(const SweepArgs &A, const SampleDev &d, int r, int64_t n,
-                                                const ItemLds &I, Energy energy, const Team tm)
-{
-    const int nT = d.n_T, T = tm.T;
-    for (int j = tm.tid;; j += T) {
-        const int t = (int)(n & 1) + 2 * j;
-        if (t + 1 >= nT) break;
-        const int w0 = I.was[t], w1 = I.was[t + 1];
-        const double D = (I.b64[t] - I.b64[t + 1]) * (energy(w0) - energy(w1));
-        bool acc = D >= 0.0;
-        if (!acc) {
-            const u32x4 q = philox4x32_10(0u, (uint32_t)n,
-                                          (PURPOSE_EXCHANGE << 28) | ((uint32_t)t << 1) | (uint32_t)r,
-                                          d.sample_id, A.key0, A.key1);
-            acc = exchange_accept(q.x, q.y, D);
-        }
-        if (acc) {
-            I.was[t] = w1;
-            I.was[t + 1] = w0;
-            I.sow[w1] = t;
-            I.sow[w0] = t + 1;
-            I.sw[t] += 1;
-        }
-    }
-}
-
-// The same with E_w = EJ_w unit - h M_w from the walker arrays.
-__device__ __forceinline__ void exchange_pass(const SweepArgs &A, const SampleDev &d, int r, int64_t n,
-                                              const ItemLds &I, double unit, double hd, const Team tm = whole_block())
-{
-    exchange_pass_e(
-        A, d, r, n, I, [&](int w) { return (double)I.EJ[w] * unit - hd * (double)I.M[w]; }, tm);
 }
 
 // v of the lane K places along in the same row of 16 lanes (rotation).
@@ -249,12 +208,20 @@ __device__ __forceinline__ int pair_other(int v, int lane, bool odd)
     return !odd ? a : (lane & 1) ? l : r;
 }
 
-// The exchange pass after sweep n (see exchange_pass_e) by one whole wave, lane
-// t for slot t: both lanes of a pair form its decision from the same operands,
-// and the slots' walkers and energies cross between the lanes in registers.
-// Nothing is kept between sweeps (it would be spilled); two dependent LDS
-// reads, hidden in part behind the random words.  Returns the walker now at
-// slot t (t itself from n_T on).
+// Replica exchange of neighbouring slots (t, t+1), t = n&1, n&1 + 2, ..., after
+// sweep n (Methods: parallel tempering; even-odd pairs alternate with the sweep
+// parity).  D = (beta_t - beta_{t+1}) (E_t - E_{t+1}) in binary64, E_w =
+// energy(w); accepted iff D >= 0 or u53 < exp_ea64(D) (decided by
+// exchange_accept), u53 from the exchange counter (0, n, (1 << 28) | (t << 1)
+// | r, sample).  Swaps walker labels only, in both maps (was: slot -> walker,
+// sow: walker -> slot), so the sweep that follows reads its temperatures
+// without rebuilding sow.
+//
+// By one whole wave, lane t for slot t: both lanes of a pair form its decision
+// from the same operands, and the slots' walkers and energies cross between
+// the lanes in registers (two dependent LDS reads, hidden in part behind the
+// random words).  Nothing is kept between sweeps: held in registers, it would
+// be spilled.  Returns the walker now at slot t (t itself from n_T on).
 template <class Energy>
 __device__ __forceinline__ int exchange_slots(const SweepArgs &A, const SampleDev &d, int r, int64_t n, const ItemLds &I,
                                               int t, Energy energy)

@@ -48,13 +48,13 @@ __global__ void __launch_bounds__(1024) site_sweep_kernel(SweepArgs A)
 
 // L = 8 chains are small (two waves for 16 walkers), so their workgroups are
 // held to 128 VGPRs to keep four waves per SIMD resident.
-template <int L, int VAR>
+template <int L, int VAR, bool TAB>
 __global__ void __launch_bounds__(ROW_MAX_THREADS, L == 8 ? 4 : 1) row_sweep_kernel(SweepArgs A)
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     for (int item = blockIdx.x; item < A.n_items; item += gridDim.x) {
         const int code = A.items[item];
-        run_item<L, 0, true>(A, sample_of_item(A.samples, code >> 1), code & 1, smem);
+        run_item<L, 0, true, TAB>(A, sample_of_item(A.samples, code >> 1), code & 1, smem);
     }
 }
 
@@ -72,10 +72,12 @@ EA_SITE(12)
 EA_SITE(14)
 EA_SITE(16)
 #undef EA_SITE
-template __global__ void row_sweep_kernel<8, 0>(SweepArgs);
-template __global__ void row_sweep_kernel<8, 1>(SweepArgs);
-template __global__ void row_sweep_kernel<16, 0>(SweepArgs);
-template __global__ void row_sweep_kernel<16, 1>(SweepArgs);
+template __global__ void row_sweep_kernel<8, 0, true>(SweepArgs);
+template __global__ void row_sweep_kernel<8, 1, true>(SweepArgs);
+template __global__ void row_sweep_kernel<16, 0, true>(SweepArgs);
+template __global__ void row_sweep_kernel<16, 1, true>(SweepArgs);
+template __global__ void row_sweep_kernel<16, 0, false>(SweepArgs);
+template __global__ void row_sweep_kernel<16, 1, false>(SweepArgs);
 
 // ---------------------------------------------------------------------------
 // HBM-resident tier (chains too large for LDS, e.g. L = 32).  Spins stay in

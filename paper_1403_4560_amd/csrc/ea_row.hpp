@@ -160,10 +160,10 @@ __device__ __forceinline__ uint32_t update_word_pm1(uint32_t Sv, uint32_t Xa, ui
 // the words of the same index in the adjacent rows.
 //
 // Tallies per thread and sweep: the first half-sweep tallies no energy; the
-// second gives accE + nd = sum of s_i S_u over the thread's odd sites after
-// the update (tally_final), i.e. minus its share of the walker's new E_J;
-// bf and bd count the set bits of the flip masks (7 per flipped byte) and of
-// (spins AND flip mask) over both halves.
+// second gives accE + (down spins of the odd sites) = sum of s_i S_u over the
+// thread's odd sites after the update (tally_final), i.e. minus its share of
+// the walker's new E_J; bf counts the set bits of the flip masks (7 per
+// flipped byte) over both halves, nd the down spins of either half.
 //
 // Lane map: a walker's L*L/8 columns (k, y) are split by the parity of y over
 // two waves, and a wave holds the columns of WPW walkers with y of one parity.
@@ -187,11 +187,14 @@ __device__ __forceinline__ int row_slot(int y)
 
 // j_y0, j_ym, je_prev: the coupling offsets of the word and of its -y neighbour
 // word, and the coupling element before the word, in that layout.
-template <int L, int P, int EPS>
+// ph: the Philox words of the site groups (TAB), or they are formed here; w:
+// those of the walker's slot, with t the slot; nd: down spins after the update.
+template <int L, int P, int EPS, bool TAB>
 __device__ __forceinline__ void row_word(const SweepArgs &A, const SampleDev &d, uint8_t *Sw, const int *J,
-                                         int o_y0, int o_yp, int o_ym, int o_x, int j_y0, int j_ym, int je_prev,
-                                         int z, int zp, int zm, uint32_t c1, uint32_t c2, float ka, float kb,
-                                         float h32, int &accE, int &nd, int &bf, int &bd)
+                                         const uint4 *ph, int o_y0, int o_yp, int o_ym, int o_x, int j_y0, int j_ym,
+                                         int je_prev, int z, int zp, int zm, const PhiloxSlot &w, int t,
+                                         const RoundKeys &key, float ka, float kb, float h32, int &accE, int &nd,
+                                         int &bf)
 {
     constexpr int HALF = L * L * L / 2, HL = L / 2, PLANE = L * HL;
     const uint8_t *own = Sw + P * HALF, *oth = Sw + (1 - P) * HALF;
@@ -204,13 +207,17 @@ __device__ __forceinline__ void row_word(const SweepArgs &A, const SampleDev &d,
     const uint32_t Ym = *(const uint32_t *)(oth + o_ym + zo);
     const uint32_t Zp = *(const uint32_t *)(oth + o_y0 + zp * PLANE);
     const uint32_t Zm = *(const uint32_t *)(oth + o_y0 + zm * PLANE);
-    const uint32_t Xs = __builtin_amdgcn_perm(Xa, Xo, EPS ? 0x00070605u : 0x06050403u);
+    uint4 pg;
+    if constexpr (TAB) pg = ph[o_y0 / 4 + z * (PLANE / 4)];
+    else pg = philox_group((uint32_t)(o_y0 / 4 + z * (PLANE / 4)), d.sample_id, A.key1);
     const int4 Jpx = *(const int4 *)(Jp + j_y0 + zo);
     const int4 Jpy = *(const int4 *)(Jp + HALF + j_y0 + zo);
     const int4 Jpz = *(const int4 *)(Jp + 2 * HALF + j_y0 + zo);
     const int4 V = *(const int4 *)(Jo + j_y0 + zo);
     const int4 Jym = *(const int4 *)(Jo + HALF + j_ym + zo);
     const int4 Jzm = *(const int4 *)(Jo + 2 * HALF + j_y0 + zm * PLANE);
+    const u32x4 rw = w.call(pg, key);
+    const uint32_t Xs = __builtin_amdgcn_perm(Xa, Xo, EPS ? 0x00070605u : 0x06050403u);
     // bonds to the aligned x-neighbour (x+1 if eps = 0, else x-1) and the shifted one
     int Ja[4], Js[4];
     if constexpr (EPS) {
@@ -223,24 +230,23 @@ __device__ __forceinline__ void row_word(const SweepArgs &A, const SampleDev &d,
     }
     const int Jy[4] = {Jpy.x, Jpy.y, Jpy.z, Jpy.w}, Jyn[4] = {Jym.x, Jym.y, Jym.z, Jym.w};
     const int Jz[4] = {Jpz.x, Jpz.y, Jpz.z, Jpz.w}, Jzn[4] = {Jzm.x, Jzm.y, Jzm.z, Jzm.w};
-    const uint32_t g = (uint32_t)(o_y0 / 4 + z * (PLANE / 4));
-    const u32x4 rw = philox4x32_10(g, c1, c2, d.sample_id, A.key0, A.key1);
     const float kav[4] = {ka, ka, ka, ka}, kbv[4] = {kb, kb, kb, kb};
     int Sus[4];
     const uint32_t fm = update_word_gauss<true>(
         Sv, Xa, Xs, Yp, Ym, Zp, Zm, Ja, Js, Jy, Jyn, Jz, Jzn, rw, kav, kbv,
-        [&](int) { return 2.0f * A.beta32[d.slot_off + ((c2 >> 1) & 0x7FFFFFFu)]; }, h32, d.hgrid, Sus);
-    if constexpr (P == 1) tally_final(Sv, fm, Sus, accE, nd);
-    *(uint32_t *)(Sw + P * HALF + o_y0 + zo) = Sv ^ fm;
+        [&](int) { return 2.0f * A.beta32[d.slot_off + t]; }, h32, d.hgrid, Sus);
+    if constexpr (P == 1) tally_final(Sv, fm, Sus, accE);
+    const uint32_t Sn = Sv ^ fm;
+    *(uint32_t *)(Sw + P * HALF + o_y0 + zo) = Sn;
     bf += __builtin_popcount(fm);
-    bd += __builtin_popcount(Sv & fm);
+    nd += __builtin_popcount(Sn & 0x80808080u);
 }
 
 // Half-sweep P of one walker's column (k, y); E0 = eps of the even z planes.
-template <int L, int P, int E0>
+template <int L, int P, int E0, bool TAB>
 __device__ __forceinline__ void row_half_sweep(const SweepArgs &A, const SampleDev &d, int r, int64_t n,
-                                               const ItemLds &I, int w, int y, int k, int t, int &accE,
-                                               int &nd, int &bf, int &bd)
+                                               const ItemLds &I, const RoundKeys &key, int w, int y, int k, int t,
+                                               int &accE, int &nd, int &bf)
 {
     constexpr int WPR = L / 8, HL = L / 2;
     const int yp = (y + 1) & (L - 1), ym = (y - 1) & (L - 1);
@@ -251,8 +257,8 @@ __device__ __forceinline__ void row_half_sweep(const SweepArgs &A, const SampleD
     const int je_prev = row_slot<L>(y) * HL + (k == 0 ? HL - 1 : 4 * k - 1);  // element before the word, cyclic
     uint8_t *Sw = (uint8_t *)I.S + (size_t)w * item_walker_stride(L);
     const int *J = (const int *)I.J;
-    const uint32_t c1 = (uint32_t)(2 * n + P);
-    const uint32_t c2 = (PURPOSE_METROPOLIS << 28) | ((uint32_t)t << 1) | (uint32_t)r;
+    PhiloxSlot ps;
+    ps.init((uint32_t)(2 * n + P), (PURPOSE_METROPOLIS << 28) | ((uint32_t)t << 1) | (uint32_t)r, A.key0, A.key1);
     // the exponent's two per-slot constants (see update_word_gauss)
     const float cp = two_beta_log2e(I.b32[t]);
     const float ka = cp * 0x1p-18f, kb = cp * (d.h32 - (float)d.hgrid * 0x1p-18f);
@@ -260,14 +266,14 @@ __device__ __forceinline__ void row_half_sweep(const SweepArgs &A, const SampleD
 #pragma unroll 1
     for (int z = 0; z < L; z += 4) {
         const int zm = z == 0 ? L - 1 : z - 1, z4 = z + 4 == L ? 0 : z + 4;
-        row_word<L, P, E0>(A, d, Sw, J, o_y0, o_yp, o_ym, o_x, j_y0, j_ym, je_prev, z, z + 1, zm, c1, c2, ka, kb,
-                           h32, accE, nd, bf, bd);
-        row_word<L, P, 1 - E0>(A, d, Sw, J, o_y0, o_yp, o_ym, o_x, j_y0, j_ym, je_prev, z + 1, z + 2, z, c1, c2,
-                               ka, kb, h32, accE, nd, bf, bd);
-        row_word<L, P, E0>(A, d, Sw, J, o_y0, o_yp, o_ym, o_x, j_y0, j_ym, je_prev, z + 2, z + 3, z + 1, c1, c2,
-                           ka, kb, h32, accE, nd, bf, bd);
-        row_word<L, P, 1 - E0>(A, d, Sw, J, o_y0, o_yp, o_ym, o_x, j_y0, j_ym, je_prev, z + 3, z4, z + 2, c1, c2,
-                               ka, kb, h32, accE, nd, bf, bd);
+        row_word<L, P, E0, TAB>(A, d, Sw, J, I.ph, o_y0, o_yp, o_ym, o_x, j_y0, j_ym, je_prev, z, z + 1, zm, ps, t, key, ka,
+                           kb, h32, accE, nd, bf);
+        row_word<L, P, 1 - E0, TAB>(A, d, Sw, J, I.ph, o_y0, o_yp, o_ym, o_x, j_y0, j_ym, je_prev, z + 1, z + 2, z, ps, t,
+                               key, ka, kb, h32, accE, nd, bf);
+        row_word<L, P, E0, TAB>(A, d, Sw, J, I.ph, o_y0, o_yp, o_ym, o_x, j_y0, j_ym, je_prev, z + 2, z + 3, z + 1, ps, t,
+                           key, ka, kb, h32, accE, nd, bf);
+        row_word<L, P, 1 - E0, TAB>(A, d, Sw, J, I.ph, o_y0, o_yp, o_ym, o_x, j_y0, j_ym, je_prev, z + 3, z4, z + 2, ps, t,
+                               key, ka, kb, h32, accE, nd, bf);
     }
 }
 
@@ -308,8 +314,9 @@ __device__ __forceinline__ uint32_t pack_row_lds(const int8_t *Sw, int row)
 }
 
 // ---------------------------------------------------------------------------
-// The per-item frame shared by both engines.
-template <int L, int JK, bool ROW>
+// The per-item frame shared by both engines (TAB: the row engine keeps the
+// site groups' Philox words in LDS, 2 N bytes).
+template <int L, int JK, bool ROW, bool TAB = ROW>
 __device__ __forceinline__ void run_item(const SweepArgs &A, const SampleDev &d, int r, char *smem,
                                          const Team tm = whole_block())
 {
@@ -335,16 +342,19 @@ __device__ __forceinline__ void run_item(const SweepArgs &A, const SampleDev &d,
                 make_int4((int)(v.x * 262144.0f), (int)(v.y * 262144.0f), (int)(v.z * 262144.0f),
                           (int)(v.w * 262144.0f));
         }
+        if constexpr (TAB)
+            for (int g = tid; g < HALF / 4; g += T) I.ph[g] = philox_group((uint32_t)g, d.sample_id, A.key1);
     } else {
         block_copy(I.J, (const char *)A.J + (size_t)d.J_off * (JK == 0 ? 4 : 1),
                    (size_t)3 * N * (JK == 0 ? 4 : 1), tm);
     }
     for (int i = tid; i < nT; i += T) {
         I.was[i] = A.was[gi + i];
-        I.sow[A.was[gi + i]] = i;  // kept by exchange_pass from here on
-        // row engine: E_J = -dEJ (see the sweep loop); site engine: EJ + dEJ
+        I.sow[A.was[gi + i]] = i;  // kept by the exchange from here on
+        // row engine: E_J = -dEJ and dM the number of down spins (see the
+        // sweep loop); site engine: EJ + dEJ, M + dM
         I.dEJ[i] = ROW ? -A.EJ[gi + i] : 0;
-        I.dM[i] = 0;
+        I.dM[i] = ROW ? (N - A.M[gi + i]) / 2 : 0;
         I.EJ[i] = A.EJ[gi + i];
         I.M[i] = A.M[gi + i];
         I.fl[i] = 0;
@@ -380,20 +390,21 @@ __device__ __forceinline__ void run_item(const SweepArgs &A, const SampleDev &d,
     int64_t next_meas = next_measurement(n0, every, A.measure_start);
     int64_t f = 0;  // frame of the next measurement within this chunk
     // Energy of walker w after a sweep.  Row engine: the second half-sweep's
-    // tallies leave minus E_J in dEJ and the magnetisation change in dM; both
-    // are folded in at the start of the next sweep, before its own tallies
+    // tallies leave minus E_J in dEJ and the number of down spins in dM; both
+    // are cleared at the start of the next sweep, before its own tallies
     // (which follow the first half-sweep's barrier), so no pass of their own
     // is needed.  Site engine: a pass after the sweep folds them in.
     const auto energy = [&](int w) {
-        return ROW ? (double)(-I.dEJ[w]) * unit - hd * (double)(I.M[w] + I.dM[w])
+        return ROW ? (double)(-I.dEJ[w]) * unit - hd * (double)(N - 2 * I.dM[w])
                    : (double)I.EJ[w] * unit - hd * (double)I.M[w];
     };
+    RoundKeys key;
+    if constexpr (ROW) key.init(A.key0, A.key1);
     for (int it = 0; it < A.K; ++it) {
         const int64_t n = n0 + it;
         if constexpr (ROW) {
 #pragma unroll 1
             for (int i = tid; i < nT; i += T) {
-                I.M[i] += I.dM[i];
                 I.dM[i] = 0;
                 I.dEJ[i] = 0;
             }
@@ -403,15 +414,15 @@ __device__ __forceinline__ void run_item(const SweepArgs &A, const SampleDev &d,
             // its lanes; the two waves of a walker add into LDS.
             const bool on = rw_w < nT;
             const int t = on ? I.sow[rw_w] : 0;
-            int accE = 0, nd = 0, bf = 0, bd = 0;
+            int accE = 0, nd0 = 0, nd = 0, bf = 0;
             if (on) {
-                if (rw_par) row_half_sweep<L, 0, 1>(A, d, r, n, I, rw_w, rw_y, rw_k, t, accE, nd, bf, bd);
-                else row_half_sweep<L, 0, 0>(A, d, r, n, I, rw_w, rw_y, rw_k, t, accE, nd, bf, bd);
+                if (rw_par) row_half_sweep<L, 0, 1, TAB>(A, d, r, n, I, key, rw_w, rw_y, rw_k, t, accE, nd0, bf);
+                else row_half_sweep<L, 0, 0, TAB>(A, d, r, n, I, key, rw_w, rw_y, rw_k, t, accE, nd0, bf);
             }
             __syncthreads();
             if (on) {
-                if (rw_par) row_half_sweep<L, 1, 0>(A, d, r, n, I, rw_w, rw_y, rw_k, t, accE, nd, bf, bd);
-                else row_half_sweep<L, 1, 1>(A, d, r, n, I, rw_w, rw_y, rw_k, t, accE, nd, bf, bd);
+                if (rw_par) row_half_sweep<L, 1, 0, TAB>(A, d, r, n, I, key, rw_w, rw_y, rw_k, t, accE, nd, bf);
+                else row_half_sweep<L, 1, 1, TAB>(A, d, r, n, I, key, rw_w, rw_y, rw_k, t, accE, nd, bf);
                 // accE + nd = sum of s' (S_u + hgrid) over this thread's 4 L odd
                 // sites, |accE| <= 64 sites x 12 2^21 < 2^31; less hgrid sum s'
                 // leaves sum s' S_u, at most 4 L x 6 2^21 in size per thread:
@@ -421,13 +432,14 @@ __device__ __forceinline__ void run_item(const SweepArgs &A, const SampleDev &d,
                 long long sE;
                 if constexpr (CPW == 4) sE = group_sum_dpp<CPW>((int)own);
                 else sE = group_sum_dpp<CPW>(own);
-                const int sf = group_sum_dpp<CPW>(bf), sd = group_sum_dpp<CPW>(bd);
+                // flips (bits) and down spins in one word: at most 16 lanes x
+                // 128 sites x 7 < 2^15 and 16 x 128 < 2^12
+                const int s2 = group_sum_dpp<CPW>(bf + ((nd0 + nd) << 16));
                 if (rw_rem == 0) {
-                    const int flips = (int)((unsigned)sf / 7u), ndown = (int)((unsigned)sd / 7u);
                     // dEJ collects minus the new E_J (both waves of the walker add)
                     atomicAdd((unsigned long long *)&I.dEJ[rw_w], (unsigned long long)sE);
-                    atomicAdd(&I.dM[rw_w], -2 * (flips - 2 * ndown));
-                    atomicAdd(&I.fl[t], flips);
+                    atomicAdd(&I.dM[rw_w], s2 >> 16);
+                    atomicAdd(&I.fl[t], (int)((unsigned)(s2 & 0xFFFF) / 7u));
                 }
             }
         } else {
@@ -445,7 +457,7 @@ __device__ __forceinline__ void run_item(const SweepArgs &A, const SampleDev &d,
             }
             __syncthreads();
         }
-        exchange_pass_e(A, d, r, n, I, energy, tm);
+        if (tid < 64) exchange_slots(A, d, r, n, I, tid, energy);
         __syncthreads();
         // Snapshot for the overlap measurement, in slot order.
         const int64_t done = n + 1;
@@ -475,7 +487,7 @@ __device__ __forceinline__ void run_item(const SweepArgs &A, const SampleDev &d,
     for (int i = tw.tid; !tw.ghost && i < nT; i += T) {
         A.was[gi + i] = I.was[i];
         A.EJ[gi + i] = ROW ? -I.dEJ[i] : I.EJ[i];
-        A.M[gi + i] = ROW ? I.M[i] + I.dM[i] : I.M[i];
+        A.M[gi + i] = ROW ? N - 2 * I.dM[i] : I.M[i];
         A.flips[gi + i] += I.fl[i];
         A.swaps[gi + i] += I.sw[i];
     }

@@ -174,7 +174,7 @@ __host__ __device__ inline size_t align16(size_t x) { return (x + 15) & ~(size_t
 // LDS layout of one LDS-tier work item (bytes).  Shared with the host, which
 // sizes the dynamic LDS of a launch with lds_total().
 struct LdsOff {
-    size_t spins, J, was, sow, M, dM, fl, sw, EJ, dEJ, lut, b32, b64, total;
+    size_t spins, J, was, sow, M, dM, fl, sw, EJ, dEJ, lut, b32, b64, ph, total;
 };
 
 // Bytes between consecutive walkers of the per-item frame's LDS spins: N plus
@@ -183,7 +183,7 @@ struct LdsOff {
 // disjoint LDS banks.
 __host__ __device__ inline size_t item_walker_stride(int L) { return (size_t)L * L * L + 8; }
 
-__host__ __device__ inline LdsOff lds_offsets(int L, int nT, int jkind)
+__host__ __device__ inline LdsOff lds_offsets(int L, int nT, int jkind, bool row = false)
 {
     const size_t N = (size_t)L * L * L;
     const size_t T4 = (size_t)((nT + 3) & ~3);
@@ -201,7 +201,8 @@ __host__ __device__ inline LdsOff lds_offsets(int L, int nT, int jkind)
     o.lut = o.dEJ + 8 * T4;
     o.b32 = o.lut + (jkind == 1 ? 4 * 14 * T4 : 0);
     o.b64 = align16(o.b32 + 4 * T4);
-    o.total = align16(o.b64 + 8 * T4);
+    o.ph = align16(o.b64 + 8 * T4);
+    o.total = o.ph + (row ? (N / 8) * 16 : 0);  // row engine: a table entry per site group
     return o;
 }
 

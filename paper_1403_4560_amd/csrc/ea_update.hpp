@@ -128,32 +128,17 @@ __device__ __forceinline__ int tally_delta(uint32_t Sv, uint32_t fm, const int S
     return a;
 }
 
-// After the update: accE += (S_u XOR m') over all four bytes and nd += the
-// number of -1 spins, m' from the updated spin, so that accE + nd is the sum of
-// s_i' S_u with the updated spins.  On the second half-sweep that sum over a
-// walker's odd sites is minus its whole coupling energy: every bond joins one
-// even and one odd site, and the even spins no longer change.  S_u can reach
-// 6 (2^21 - 1) in magnitude, beyond a 24-bit multiplier, so the sign is
-// applied by XOR.
-__device__ __forceinline__ void tally_final(uint32_t Sv, uint32_t fm, const int Sus[4], int &accE, int &nd)
+// After the update: accE += (S_u XOR m') over all four bytes, m' from the
+// updated spin, so that accE plus the number of -1 spins is the sum of s_i' S_u
+// with the updated spins.  On the second half-sweep that sum over a walker's
+// odd sites is minus its whole coupling energy: every bond joins one even and
+// one odd site, and the even spins no longer change.  S_u can reach 6 (2^21 -
+// 1) in magnitude, beyond a 24-bit multiplier, so the sign is applied by XOR.
+__device__ __forceinline__ void tally_final(uint32_t Sv, uint32_t fm, const int Sus[4], int &accE)
 {
     const uint32_t Sn = Sv ^ fm;
 #pragma unroll
     for (int i = 0; i < 4; ++i) accE += Sus[i] ^ __builtin_amdgcn_sbfe((int)Sn, 8 * i + 7, 1);
-    nd += __builtin_popcount(Sn & 0x80808080u);
-}
-
-// The same per byte (group engine: byte i is walker i of the word's quad).
-__device__ __forceinline__ void tally_final_lanes(uint32_t Sv, uint32_t fm, const int Sus[4], int accE[4],
-                                                  int nd[4])
-{
-    const uint32_t Sn = Sv ^ fm;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int m = __builtin_amdgcn_sbfe((int)Sn, 8 * i + 7, 1);
-        accE[i] += Sus[i] ^ m;
-        nd[i] -= m;
-    }
 }
 
 }  // namespace ea
