@@ -165,6 +165,14 @@ __device__ __forceinline__ uint32_t update_word_pm1(uint32_t Sv, uint32_t Xa, ui
 // the walker's new E_J; bf counts the set bits of the flip masks (7 per
 // flipped byte) over both halves, nd the down spins of either half.
 //
+// Bound: VALU issue.  A word's Philox call starts after round 1 (the site
+// groups' words from an LDS table, the slot's from registers) with its round
+// keys in vector registers, because a three-input xor with a scalar operand
+// issues at 4.4 cycles a wave, from vector registers at 2.6; with the down
+// spins counted once instead of the flipped ones a word takes about 470 issue
+// cycles instead of 525.  Attempts/ns: L = 16 x 24 temperatures 1101 -> 1158,
+// L = 8 x 16 918 -> 970 (1024 samples), 1083 -> 1139 (4096).
+//
 // Lane map: a walker's L*L/8 columns (k, y) are split by the parity of y over
 // two waves, and a wave holds the columns of WPW walkers with y of one parity.
 // eps = (y + z + p) & 1 is then the same for every lane of a wave, so each

@@ -841,6 +841,15 @@ def test_row_engine_partial_waves(torch_cuda):
     check(work, 18, plan=dict(chunk=6))
 
 
+@pytest.mark.parametrize("nTs", [[5], [6], [7, 24], [1], [24]])
+def test_row_engine_with_and_without_the_site_group_table(torch_cuda, nTs):
+    # L = 16: the table of Philox words fits beside the chain (5, 24) or would
+    # cost a resident workgroup and is left out (1, 6, 7; a class goes without
+    # it as soon as one of its chains does)
+    work = W.make_workload([16] * len(nTs), nTs, (0.4, 1.5), 0.1, measure_every=2, name="row table")
+    check(work, 5, plan=dict(chunk=3))
+
+
 def test_engine_routing(torch_cuda):
     """Which engine each sample runs on, by size, coupling kind, field and tier."""
     from paper_1403_4560_amd import binding
