@@ -91,9 +91,8 @@ VALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 MEASURED_TRAFFIC = {"L16_gauss": ("bbc1b9be80475284", 2.0324e9), "L32_pm1": ("bbc1b9be80475284", 3.5397e9),
                     "mixed_L6_12": ("bbc1b9be80475284", 0.7665e9), "L8_gauss": ("bbc1b9be80475284", 0.1367e9)}
 KERNEL_SOURCES = tuple("paper_1403_4560_amd/csrc/" + f for f in (
-    "ea_kernels.hip", "ea_bits.hip", "ea_group.hip", "ea_batch.hip", "ea_row.hpp", "ea_group.hpp", "ea_groupbits.hpp",
-    "ea_bitops.hpp", "ea_item.hpp",
-    "ea_update.hpp", "ea_device.hpp", "ea_types.hpp"))
+    "ea_kernels.hip", "ea_bits.hip", "ea_group.hip", "ea_hbm.hip", "ea_batch.hip", "ea_row.hpp", "ea_group.hpp",
+    "ea_groupbits.hpp", "ea_bitops.hpp", "ea_item.hpp", "ea_update.hpp", "ea_device.hpp", "ea_types.hpp"))
 
 
 def kernel_fingerprint():

@@ -27,7 +27,7 @@ template <int L, int JK, int VAR> __global__ void site_sweep_kernel(SweepArgs A)
 template <int L, int VAR, bool TAB> __global__ void row_sweep_kernel(SweepArgs A);
 template <int L, int VAR> __global__ void bits_sweep_kernel(SweepArgs A);
 template <int L, int JK, int VAR> __global__ void group_sweep_kernel(SweepArgs A);
-template <int L, int JK, int VAR> __global__ void hbm_half_kernel(SweepArgs A);
+template <int L, int JK, int VAR> __global__ void hbm_sweep_kernel(SweepArgs A);
 __global__ void hbm_exchange_kernel(SweepArgs A);
 __global__ void hbm_snapshot_kernel(SweepArgs A);
 template <int L> __global__ void measure_kernel(MeasureArgs A);
@@ -141,7 +141,7 @@ struct ea_ensemble {
     // device buffers
     DevBuf samples, items, spins, J, beta, beta32, lut, was, EJ, M, flips, swaps, acc, frames, frameE,
         state, slot_sample, costab, sintab, scratchE, scratchM, finout, walkers, dEJ, dM, sow, Ju, mslots, Jbits,
-        sel, fincols, stage;
+        sel, fincols, stage, hbm_was;
     int64_t frames_cap = 0;  // frames allocated
     std::vector<double> beta_host;  // [total_slots], to check that a finalize selection is one system
     std::vector<int32_t> sel_idx;   // [S] a finalize call's selection (no allocation per call)
@@ -328,7 +328,7 @@ void destroy_all(ea_ensemble *e)
                       &e->was, &e->EJ, &e->M, &e->flips, &e->swaps, &e->acc, &e->frames,
                       &e->frameE, &e->state, &e->slot_sample, &e->costab, &e->sintab,
                       &e->scratchE, &e->scratchM, &e->finout, &e->walkers, &e->dEJ, &e->dM,
-                      &e->sow, &e->Ju, &e->mslots, &e->Jbits, &e->sel, &e->jkrep, &e->batchbuf, &e->fincols, &e->stage};
+                      &e->sow, &e->Ju, &e->mslots, &e->Jbits, &e->sel, &e->jkrep, &e->batchbuf, &e->fincols, &e->stage, &e->hbm_was};
     for (DevBuf *b : bufs) dfree(*b);
     if (e->own_stream && e->stream) (void)hipStreamDestroy(e->stream);
     delete e;
@@ -402,9 +402,7 @@ SweepArgs sweep_args(const ea_ensemble *e, int K, const int32_t *items, int n_it
     A.key1 = (uint32_t)(e->seed >> 32);
     A.measure_every = e->m;
     A.measure_start = e->mstart;
-    A.dEJ = (int64_t *)e->dEJ.p;
-    A.dM = (int32_t *)e->dM.p;
-    A.sow = (int32_t *)e->sow.p;
+    A.sow = (const int32_t *)e->sow.p;
     A.Ju = (const int32_t *)e->Ju.p;
     A.Jbits = (const uint32_t *)e->Jbits.p;
     A.jkind = e->jkind;
@@ -706,8 +704,8 @@ SweepFn hbm_fn(int L, int jk, bool unbatched)
 {
 #define EA_CASE(Lv)                                                                                \
     case Lv:                                                                                       \
-        if (unbatched) return jk == 0 ? hbm_half_kernel<Lv, 0, 1> : hbm_half_kernel<Lv, 1, 1>;    \
-        return jk == 0 ? hbm_half_kernel<Lv, 0, 0> : hbm_half_kernel<Lv, 1, 0>;
+        if (unbatched) return jk == 0 ? hbm_sweep_kernel<Lv, 0, 1> : hbm_sweep_kernel<Lv, 1, 1>;    \
+        return jk == 0 ? hbm_sweep_kernel<Lv, 0, 0> : hbm_sweep_kernel<Lv, 1, 0>;
     switch (L) {
         EA_CASE(8) EA_CASE(16) EA_CASE(24) EA_CASE(32)
     default: return nullptr;
@@ -717,26 +715,37 @@ SweepFn hbm_fn(int L, int jk, bool unbatched)
 
 bool hbm_size(int L) { return L == 8 || L == 16 || L == 24 || L == 32; }
 
-// One sweep of an HBM-tier range: half-sweep p = 0, p = 1, exchange, snapshot.
-hipError_t launch_hbm_sweep(ea_ensemble *e, int L, int it, int item_first, int n_items, int w_first, int n_walk,
-                            bool unbatched)
+// K sweeps of an HBM-tier range: a launch per sweep, which also decides the
+// exchange and takes the snapshot of the sweep before; then those of the last
+// sweep.  The map, the energies and the magnetisations alternate between the
+// ensemble's buffers (in which a chunk starts and ends) and a second set.
+hipError_t launch_hbm(ea_ensemble *e, int L, int K, int item_first, int n_items, int w_first, int n_walk, bool unbatched)
 {
-    SweepArgs A = sweep_args(e, 0, (const int32_t *)e->items.p + item_first, n_items);
+    SweepArgs A = sweep_args(e, K, (const int32_t *)e->items.p + item_first, n_items);
     A.walkers = (const int32_t *)e->walkers.p + w_first;
-    A.n_walkers = n_walk;
-    A.it = it;
     SweepFn fn = hbm_fn(L, e->jkind, unbatched);
     if (!fn) return hipErrorInvalidDeviceFunction;
-    const int G = L * L * L / 8, TILE = G < 1024 ? G : 1024, TPW = (G + TILE - 1) / TILE;
-    for (int p = 0; p < 2; ++p) {
-        A.p = p;
-        hipLaunchKernelGGL(fn, dim3(n_walk * TPW), dim3(256), 0, e->stream, A);
-        hipError_t st = hipGetLastError();
-        if (st != hipSuccess) return st;
+    const auto buffers = [&](int read, int write) {
+        A.EJ = (int64_t *)(read ? e->dEJ.p : e->EJ.p);
+        A.M = (int32_t *)(read ? e->dM.p : e->M.p);
+        A.was = (int32_t *)(read ? e->hbm_was.p : e->was.p);
+        A.EJ_next = (int64_t *)(write ? e->dEJ.p : e->EJ.p);
+        A.M_next = (int32_t *)(write ? e->dM.p : e->M.p);
+        A.was_next = (int32_t *)(write ? e->hbm_was.p : e->was.p);
+        A.sow_next = (int32_t *)e->sow.p;
+    };
+    hipError_t st;
+    for (int it = 0; it < K; ++it) {
+        A.it = it;
+        buffers(it & 1, (it + 1) & 1);
+        hipLaunchKernelGGL(fn, dim3(n_walk), dim3(hbm_threads(L)), 0, e->stream, A);
+        if ((st = hipGetLastError()) != hipSuccess) return st;
     }
+    A.it = K - 1;
+    buffers(K & 1, 0);
     hipLaunchKernelGGL(hbm_exchange_kernel, dim3(n_items), dim3(64), 0, e->stream, A);
-    hipError_t st = hipGetLastError();
-    if (st != hipSuccess) return st;
+    if ((st = hipGetLastError()) != hipSuccess) return st;
+    buffers(0, 0);
     hipLaunchKernelGGL(hbm_snapshot_kernel, dim3(n_walk), dim3(256), 0, e->stream, A);
     return hipGetLastError();
 }
@@ -866,10 +875,9 @@ hipError_t enqueue_chunk(ea_ensemble *e, int K, bool unbatched)
         for (int s = 0; s < e->S; ++s) {
             const auto &c = e->classes[e->sample_class[s]];
             if (c.hbm) {
-                for (int it = 0; it < K; ++it)
-                    if ((st = launch_hbm_sweep(e, c.L, it, e->item_pos[s], 2, e->walker_pos[s], 2 * e->smp[s].nT,
-                                               true)) != hipSuccess)
-                        return st;
+                if ((st = launch_hbm(e, c.L, K, e->item_pos[s], 2, e->walker_pos[s], 2 * e->smp[s].nT, true)) !=
+                    hipSuccess)
+                    return st;
             } else if ((st = launch_class(e, c, K, e->item_pos[s], 2, true)) != hipSuccess) {
                 return st;
             }
@@ -882,11 +890,9 @@ hipError_t enqueue_chunk(ea_ensemble *e, int K, bool unbatched)
             if (c.hbm || (batch && e->class_P[ci] > 0)) continue;
             if ((st = launch_class(e, c, K, c.begin, c.count, false)) != hipSuccess) return st;
         }
-        for (int it = 0; it < K && e->any_hbm; ++it)
-            for (const auto &c : e->classes)
-                if (c.hbm &&
-                    (st = launch_hbm_sweep(e, c.L, it, c.begin, c.count, c.wbegin, c.wcount, false)) != hipSuccess)
-                    return st;
+        for (const auto &c : e->classes)
+            if (c.hbm && (st = launch_hbm(e, c.L, K, c.begin, c.count, c.wbegin, c.wcount, false)) != hipSuccess)
+                return st;
     }
     if (e->timing && (st = hipEventRecord(ev.second, e->stream)) != hipSuccess) return st;
     const int64_t nmeas = measurements_upto(e->sweep + K, e->m, e->mstart) - measurements_upto(e->sweep, e->m, e->mstart);
@@ -1513,6 +1519,7 @@ ea_status ea_create_ensemble(const ea_desc *d, void *hip_stream, ea_ensemble **o
             ALLOC_BUF(*bufs[k], sz[k]);
         }
     }
+    if (e->any_hbm) ALLOC_BUF(e->hbm_was, sizeof(int32_t) * 2 * TS);
     ALLOC_BUF(e->fincols, sizeof(FinColumn) * NACC * (size_t)e->nT_max);
 #undef ALLOC_BUF
     {

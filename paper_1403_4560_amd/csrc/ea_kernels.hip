@@ -23,8 +23,8 @@
 //    its sites one by one.
 // The group engine (ea_group.hip: one word = one site of four walkers) and the
 // one-bit engine (ea_bits.hip: +-1 couplings) use the same frame with their
-// own LDS layouts.  This file also holds the HBM-resident tier, the overlap
-// measurement and the setup and check kernels (finalize: ea_finalize.hip).
+// own LDS layouts.  This file also holds the overlap measurement and the setup
+// and check kernels (HBM-resident tier: ea_hbm.hip; finalize: ea_finalize.hip).
 #include "ea_device.hpp"
 #include "ea_item.hpp"
 #include "ea_row.hpp"
@@ -78,233 +78,6 @@ template __global__ void row_sweep_kernel<16, 0, true>(SweepArgs);
 template __global__ void row_sweep_kernel<16, 1, true>(SweepArgs);
 template __global__ void row_sweep_kernel<16, 0, false>(SweepArgs);
 template __global__ void row_sweep_kernel<16, 1, false>(SweepArgs);
-
-// ---------------------------------------------------------------------------
-// HBM-resident tier (chains too large for LDS, e.g. L = 32).  Spins stay in
-// HBM in the same sublattice layout; each sweep is four launches: half-sweep
-// p = 0, half-sweep p = 1, exchange, snapshot.  A half-sweep workgroup takes a
-// tile of up to 1024 int8x4 words of one walker (4 per thread); energy,
-// magnetisation and flip tallies are reduced per workgroup and added to the
-// walker's per-sweep change with integer atomics (order-free).  Blocks of one
-// sample are kept on one XCD (blocks are dealt to the 8 XCDs round-robin) so
-// the sample's couplings stay in that XCD's L2.
-__device__ __forceinline__ int xcd_block(int b, int nb)
-{
-    const int nb8 = nb & ~7;
-    return b < nb8 ? (b & 7) * (nb8 >> 3) + (b >> 3) : b;
-}
-
-template <int W>
-__device__ __forceinline__ void block_sum3(long long &a, int &b, int &c)
-{
-    __shared__ long long sa[W / 64];
-    __shared__ int sb[W / 64], sc[W / 64];
-    a = wave_sum_i64(a);
-    b = wave_sum_i32(b);
-    c = wave_sum_i32(c);
-    const int wv = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) {
-        sa[wv] = a;
-        sb[wv] = b;
-        sc[wv] = c;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int i = 1; i < W / 64; ++i) {
-            a += sa[i];
-            b += sb[i];
-            c += sc[i];
-        }
-    }
-}
-
-template <int L, int JK, int VAR>
-__global__ void __launch_bounds__(256) hbm_half_kernel(SweepArgs A)
-{
-    constexpr int N = L * L * L, HALF = N / 2, WPR = L / 8, HL = L / 2, G = HALF / 4;
-    constexpr int TILE = G < 1024 ? G : 1024, TPW = (G + TILE - 1) / TILE;
-    __shared__ uint32_t thr[14];
-    const int b = xcd_block(blockIdx.x, gridDim.x);
-    const int wi = b / TPW, tile = b - wi * TPW;
-    if (wi >= A.n_walkers) return;
-    const int code = A.walkers[wi];
-    const SampleDev d = A.samples[code >> 7];
-    const int r = (code >> 6) & 1, w = code & 63;
-    const int nT = d.n_T, gi = 2 * d.slot_off + r * nT;
-    const int t = A.sow[gi + w];
-    const int p = A.p;
-    const int64_t n = A.state[0] + A.it;
-    const int tid = threadIdx.x;
-    if (JK == 1 && tid < 14) thr[tid] = A.lut[((size_t)d.slot_off + t) * 14 + tid];
-    __syncthreads();
-    uint8_t *Sw = (uint8_t *)A.spins + d.spin_off + ((size_t)r * nT + w) * N;
-    uint8_t *own = Sw + p * HALF;
-    const uint8_t *oth = Sw + (1 - p) * HALF;
-    const uint32_t c1 = (uint32_t)(2 * n + p);
-    const uint32_t c2 = (PURPOSE_METROPOLIS << 28) | ((uint32_t)t << 1) | (uint32_t)r;
-    const float b32 = A.beta32[d.slot_off + t];
-    const float cp = two_beta_log2e(b32);
-    const float ka = cp * 0x1p-18f, kb = cp * (d.h32 - (float)d.hgrid * 0x1p-18f);
-    int accE = 0, bf = 0, bd = 0;
-    for (int j = 0; j < (TILE + 255) / 256; ++j) {
-        const int g = tile * TILE + j * 256 + tid;
-        if (j * 256 + tid >= TILE || g >= G) break;
-        const int k = g % WPR, row = g / WPR, y = row % L, z = row / L;
-        const int eps = (y + z + p) & 1;
-        const int kx = eps ? (k + 1) % WPR : (k + WPR - 1) % WPR;
-        const int yp = (y + 1) % L, ym = (y + L - 1) % L, zp = (z + 1) % L, zm = (z + L - 1) % L;
-        const int g_x = row * WPR + kx;
-        const int g_yp = (yp + L * z) * WPR + k, g_ym = (ym + L * z) * WPR + k;
-        const int g_zp = (y + L * zp) * WPR + k, g_zm = (y + L * zm) * WPR + k;
-        const uint32_t Sv = *(const uint32_t *)(own + 4 * g);
-        const uint32_t Xa = *(const uint32_t *)(oth + 4 * g);
-        const uint32_t Xo = *(const uint32_t *)(oth + 4 * g_x);
-        const uint32_t Yp = *(const uint32_t *)(oth + 4 * g_yp);
-        const uint32_t Ym = *(const uint32_t *)(oth + 4 * g_ym);
-        const uint32_t Zp = *(const uint32_t *)(oth + 4 * g_zp);
-        const uint32_t Zm = *(const uint32_t *)(oth + 4 * g_zm);
-        const uint32_t sel = eps ? 0x00070605u : 0x06050403u;
-        const uint32_t Xs = __builtin_amdgcn_perm(Xa, Xo, sel);
-        const u32x4 rw = philox4x32_10((uint32_t)g, c1, c2, d.sample_id, A.key0, A.key1);
-        uint32_t fm;
-        if constexpr (JK == 0) {
-            const int *Jp = A.Ju + d.J_off + (size_t)p * 3 * HALF;
-            const int *Jo = A.Ju + d.J_off + (size_t)(1 - p) * 3 * HALF;
-            const int4 Jpx = *(const int4 *)(Jp + 4 * g);
-            const int4 Jpy = *(const int4 *)(Jp + HALF + 4 * g);
-            const int4 Jpz = *(const int4 *)(Jp + 2 * HALF + 4 * g);
-            const int4 V = *(const int4 *)(Jo + 4 * g);
-            const int4 Jym = *(const int4 *)(Jo + HALF + 4 * g_ym);
-            const int4 Jzm = *(const int4 *)(Jo + 2 * HALF + 4 * g_zm);
-            const int Ep = Jo[row * HL + (k == 0 ? HL - 1 : 4 * k - 1)];
-            const int Ja[4] = {eps ? V.x : Jpx.x, eps ? V.y : Jpx.y, eps ? V.z : Jpx.z, eps ? V.w : Jpx.w};
-            const int Js[4] = {eps ? Jpx.x : Ep, eps ? Jpx.y : V.x, eps ? Jpx.z : V.y, eps ? Jpx.w : V.z};
-            const int Jy[4] = {Jpy.x, Jpy.y, Jpy.z, Jpy.w}, Jyn[4] = {Jym.x, Jym.y, Jym.z, Jym.w};
-            const int Jz[4] = {Jpz.x, Jpz.y, Jpz.z, Jpz.w}, Jzn[4] = {Jzm.x, Jzm.y, Jzm.z, Jzm.w};
-            const float kav[4] = {ka, ka, ka, ka}, kbv[4] = {kb, kb, kb, kb};
-            int Sus[4];
-            fm = update_word_gauss<true>(Sv, Xa, Xs, Yp, Ym, Zp, Zm, Ja, Js, Jy, Jyn, Jz, Jzn, rw, kav, kbv,
-                                         [=](int) { return 2.0f * b32; }, d.h32, d.hgrid, Sus);
-            accE += tally_delta(Sv, fm, Sus);
-        } else {
-            const uint8_t *J8 = (const uint8_t *)A.J + d.J_off;
-            const uint8_t *Jp = J8 + (size_t)p * 3 * HALF, *Jo = J8 + (size_t)(1 - p) * 3 * HALF;
-            const uint32_t Jpx = *(const uint32_t *)(Jp + 4 * g);
-            const uint32_t Jpy = *(const uint32_t *)(Jp + HALF + 4 * g);
-            const uint32_t Jpz = *(const uint32_t *)(Jp + 2 * HALF + 4 * g);
-            const uint32_t V = *(const uint32_t *)(Jo + 4 * g);
-            const uint32_t Vo = *(const uint32_t *)(Jo + 4 * g_x);
-            const uint32_t Jym = *(const uint32_t *)(Jo + HALF + 4 * g_ym);
-            const uint32_t Jzm = *(const uint32_t *)(Jo + 2 * HALF + 4 * g_zm);
-            const uint32_t Ja = eps ? V : Jpx;
-            const uint32_t Js = eps ? Jpx : __builtin_amdgcn_perm(V, Vo, 0x06050403u);
-            fm = update_word_pm1(Sv, Xa, Xs, Yp, Ym, Zp, Zm, Ja, Js, Jpy, Jym, Jpz, Jzm, rw, thr, d.down_mask,
-                                 accE);
-        }
-        *(uint32_t *)(own + 4 * g) = Sv ^ fm;
-        bf += __builtin_popcount(fm);
-        bd += __builtin_popcount(Sv & fm);
-    }
-    long long sE = accE;
-    block_sum3<256>(sE, bf, bd);
-    if (tid == 0) {
-        const int flips = bf / 7, ndown = bd / 7;
-        // sE + ndown = sum over accepted sites of s (S_u + hgrid) (Gaussian), less hgrid sum s
-        const long long corr = JK == 0 ? (long long)d.hgrid * (flips - 2 * ndown) : 0;
-        atomicAdd((unsigned long long *)&A.dEJ[gi + w], (unsigned long long)(2 * (sE + ndown - corr)));
-        atomicAdd(&A.dM[gi + w], -2 * (flips - 2 * ndown));
-        atomicAdd((unsigned long long *)&A.flips[gi + t], (unsigned long long)flips);
-    }
-}
-
-// Exchange pass of one sweep for the HBM tier: one wave per (sample, chain).
-__global__ void __launch_bounds__(64) hbm_exchange_kernel(SweepArgs A)
-{
-    const int code = A.items[blockIdx.x];
-    const SampleDev d = A.samples[code >> 1];
-    const int r = code & 1;
-    const int nT = d.n_T, gi = 2 * d.slot_off + r * nT;
-    const int tid = threadIdx.x;
-    const int64_t n = A.state[0] + A.it;
-    const double unit = A.jkind == 0 ? 0x1p-18 : 1.0;
-    const double hd = (double)d.h32;
-    if (tid < nT) {
-        A.EJ[gi + tid] += A.dEJ[gi + tid];
-        A.M[gi + tid] += A.dM[gi + tid];
-        A.dEJ[gi + tid] = 0;
-        A.dM[gi + tid] = 0;
-    }
-    __syncthreads();
-    for (int j = tid;; j += blockDim.x) {
-        const int t = (int)(n & 1) + 2 * j;
-        if (t + 1 >= nT) break;
-        const int w0 = A.was[gi + t], w1 = A.was[gi + t + 1];
-        const double E0 = (double)A.EJ[gi + w0] * unit - hd * (double)A.M[gi + w0];
-        const double E1 = (double)A.EJ[gi + w1] * unit - hd * (double)A.M[gi + w1];
-        const double D = (A.beta[d.slot_off + t] - A.beta[d.slot_off + t + 1]) * (E0 - E1);
-        bool acc = D >= 0.0;
-        if (!acc) {
-            const u32x4 q = philox4x32_10(0u, (uint32_t)n,
-                                          (PURPOSE_EXCHANGE << 28) | ((uint32_t)t << 1) | (uint32_t)r,
-                                          d.sample_id, A.key0, A.key1);
-            acc = exchange_accept(q.x, q.y, D);
-        }
-        if (acc) {
-            A.was[gi + t] = w1;
-            A.was[gi + t + 1] = w0;
-            A.swaps[gi + t] += 1;
-        }
-    }
-    __syncthreads();
-    if (tid < nT) {
-        const int w = A.was[gi + tid];
-        A.sow[gi + w] = tid;
-        const int64_t done = n + 1;
-        if (A.measure_every > 0 && done > A.measure_start && (done - A.measure_start) % A.measure_every == 0) {
-            const int64_t f = measurements_upto(done, A.measure_every, A.measure_start) -
-                              measurements_upto(A.state[0], A.measure_every, A.measure_start) - 1;
-            A.frameE[f * 2 * A.total_slots + gi + tid] = (double)A.EJ[gi + w] * unit - hd * (double)A.M[gi + w];
-        }
-    }
-}
-
-// Snapshot of one (sample, chain, slot) for the HBM tier, when a measurement
-// is due after this sweep (the launch returns at once otherwise).
-__global__ void __launch_bounds__(256) hbm_snapshot_kernel(SweepArgs A)
-{
-    const int64_t n = A.state[0] + A.it, done = n + 1;
-    if (!(A.measure_every > 0 && done > A.measure_start && (done - A.measure_start) % A.measure_every == 0))
-        return;
-    const int code = A.walkers[blockIdx.x];
-    const SampleDev d = A.samples[code >> 7];
-    const int r = (code >> 6) & 1, t = code & 63;
-    const int L = d.L, L2 = L * L, N = L2 * L, HALF = N / 2;
-    const int nT = d.n_T, gi = 2 * d.slot_off + r * nT;
-    const int64_t f = measurements_upto(done, A.measure_every, A.measure_start) -
-                      measurements_upto(A.state[0], A.measure_every, A.measure_start) - 1;
-    const int8_t *Sw = A.spins + d.spin_off + ((size_t)r * nT + A.was[gi + t]) * N;
-    uint32_t *dst = A.frames + f * A.frame_words + d.frame_off + ((size_t)r * nT + t) * L2;
-    for (int row = threadIdx.x; row < L2; row += blockDim.x) {
-        const int yz = (row % L) + row / L;
-        uint32_t bits = 0;
-        for (int x = 0; x < L; ++x) {
-            const int p = (x + yz) & 1;
-            bits |= (uint32_t)(Sw[p * HALF + ((x + L * row) >> 1)] < 0) << x;
-        }
-        dst[row] = bits;
-    }
-}
-
-#define EA_HBM(Lv)                                                  \
-    template __global__ void hbm_half_kernel<Lv, 0, 0>(SweepArgs); \
-    template __global__ void hbm_half_kernel<Lv, 1, 0>(SweepArgs); \
-    template __global__ void hbm_half_kernel<Lv, 0, 1>(SweepArgs); \
-    template __global__ void hbm_half_kernel<Lv, 1, 1>(SweepArgs);
-EA_HBM(8)
-EA_HBM(16)
-EA_HBM(24)
-EA_HBM(32)
-#undef EA_HBM
 
 // ---------------------------------------------------------------------------
 // Overlap measurement (eq. 2).  One wave per (sample, slot).  For each snapshot

@@ -119,36 +119,6 @@ __device__ __forceinline__ void site_half_sweep(const SweepArgs &A, const Sample
     }
 }
 
-// The same for +-1 couplings (int8x4 bond words Ja..Jzn): a bond-spin product
-// byte n ^ J is 0x00 for +1 and 0xFE for -1, so per byte c = number of -1
-// products and S_J = 6 - 2c.  Acceptance uses the slot's threshold table
-// thr[a*7 + b] (a = (s_i+1)/2, b = (S_J+6)/2): accept iff dE <= 0 (bit a*7+b of
-// down_mask, set on the host from 2 s (S_J + h) <= 0) or w < thr.  S_u = S_J.
-__device__ __forceinline__ uint32_t update_word_pm1(uint32_t Sv, uint32_t Xa, uint32_t Xs, uint32_t Yp, uint32_t Ym,
-                                                    uint32_t Zp, uint32_t Zm, uint32_t Ja, uint32_t Js, uint32_t Jy,
-                                                    uint32_t Jyn, uint32_t Jz, uint32_t Jzn, const u32x4 rw,
-                                                    const uint32_t *thr, uint32_t down_mask, int &accE)
-{
-    constexpr uint32_t LOW = 0x01010101u;
-    const uint32_t cnt = (((Xa ^ Ja) >> 1) & LOW) + (((Xs ^ Js) >> 1) & LOW) + (((Yp ^ Jy) >> 1) & LOW) +
-                         (((Ym ^ Jyn) >> 1) & LOW) + (((Zp ^ Jz) >> 1) & LOW) + (((Zm ^ Jzn) >> 1) & LOW);
-    const uint32_t words[4] = {rw.x, rw.y, rw.z, rw.w};
-    uint32_t fm = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int sh = 8 * i;
-        const int b = 6 - (int)((cnt >> sh) & 0xFFu);               // (S_J + 6) / 2
-        const int m = __builtin_amdgcn_sbfe((int)Sv, sh + 7, 1);  // 0: s_i = +1, -1: s_i = -1
-        const int idx = (m + 1) * 7 + b;
-        const bool accept = ((down_mask >> idx) & 1u) | (words[i] < thr[idx]);
-        if (accept) {
-            fm |= 0xFEu << sh;
-            accE += (2 * b - 6) ^ m;
-        }
-    }
-    return fm;
-}
-
 // ---------------------------------------------------------------------------
 // Row engine (L = 8 or 16, Gaussian couplings held as int32 multiples of
 // 2^-18).  Sublattice p's row (y, z) holds L/2 sites, i.e. L/8 int8x4 words;

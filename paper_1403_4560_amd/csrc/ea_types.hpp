@@ -38,6 +38,13 @@ constexpr int LDS_MAX_L = 16; // largest lattice of the LDS-resident tier
 constexpr int ROW_MAX_THREADS = 768;  // row engine: one thread per (walker, column)
 constexpr int GROUP_MAX_THREADS = 512;  // group engine workgroup size cap
 
+// Threads of an HBM-tier workgroup: half of what the words of one class of rows
+// (half a sublattice, L L / 2 rows of L / 8 words) take in as few steps as 1024
+// threads allow.  The whole count was slower everywhere (50 sweeps, Gaussian:
+// L = 24, 16 temperatures, 8 samples 723 us against 681, 64 samples 4404 against
+// 3392), a quarter faster only at many walkers (809 and 3066).
+constexpr int hbm_threads(int L) { return L == 32 ? 512 : L == 24 ? 448 : L == 16 ? 128 : 64; }
+
 struct SampleDev {
     int32_t L;
     int32_t n_T;
@@ -77,15 +84,16 @@ struct SweepArgs {
     int32_t measure_every;
     int32_t pad;
     int64_t measure_start;
-    // HBM-resident tier (one launch per half-sweep / exchange / snapshot)
+    // HBM-resident tier (one launch per sweep): EJ, M, was, sow as the launch
+    // before left them, and the buffers this launch writes
     const int32_t *walkers;     // (sample << 7) | (chain << 6) | walker-or-slot
-    int32_t n_walkers;
-    int32_t p;                  // parity of this half-sweep
     int32_t it;                 // sweep index within the chunk: n = state[0] + it
     int32_t jkind;              // 0 Gaussian (energy unit 2^-18), 1 +-1 (unit 1)
-    int64_t *dEJ;               // per walker: coupling-energy change of this sweep
-    int32_t *dM;                // per walker: magnetisation change of this sweep
-    int32_t *sow;               // per walker: its slot during this sweep
+    const int32_t *sow;         // per walker: its slot during the sweep before
+    int64_t *EJ_next;
+    int32_t *M_next;
+    int32_t *was_next;
+    int32_t *sow_next;
     const int32_t *Ju;          // Gaussian couplings as int32 multiples of 2^-18, Jsub layout
     const uint32_t *Jbits;      // bit engine: per sample [2 parities][6 bonds][N/64] words
 };

@@ -116,18 +116,6 @@ __device__ __forceinline__ uint32_t update_word_gauss(uint32_t Sv, uint32_t Xa, 
     return fm;
 }
 
-// Sum over accepted bytes of (S_u XOR m), m = 0 for s_i = +1 and -1 for
-// s_i = -1: the sum of s_i S_u over accepted sites is this plus the number of
-// accepted down spins.
-__device__ __forceinline__ int tally_delta(uint32_t Sv, uint32_t fm, const int Sus[4])
-{
-    int a = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-        if ((fm >> (8 * i)) & 0xFFu) a += Sus[i] ^ __builtin_amdgcn_sbfe((int)Sv, 8 * i + 7, 1);
-    return a;
-}
-
 // After the update: accE += (S_u XOR m') over all four bytes, m' from the
 // updated spin, so that accE plus the number of -1 spins is the sum of s_i' S_u
 // with the updated spins.  On the second half-sweep that sum over a walker's

@@ -810,6 +810,17 @@ def test_hbm_mixed_tiers_pm1(torch_cuda):
     check(work, 12, splits=[5, 7], plan=dict(chunk=4))
 
 
+@pytest.mark.parametrize("jk", [W.J_GAUSS, W.J_PM1])
+@pytest.mark.parametrize("chunk", [1, 2, 5])
+def test_hbm_chunk_edges(torch_cuda, jk, chunk):
+    # an odd and an even number of launches a chunk (the buffers that alternate
+    # end in either set), snapshots within and at the end of one, ladders with
+    # no pair, one pair and an idle end slot
+    work = W.make_workload([24, 8, 16, 8], [1, 2, 5, 3], (0.4, 1.5), 0.1, jkind=jk, measure_every=2, measure_start=1,
+                           name="hbm chunks")
+    check(work, 11, plan=dict(chunk=chunk), tier=1)
+
+
 def test_hbm_unbatched_equals_oracle(torch_cuda):
     work = W.make_workload([32, 32], 4, (0.5, 2.0), 0.4, jkind=W.J_PM1, sample_ids=[5, 6], measure_every=3,
                            measure_start=0, name="pm1 unbatched")
