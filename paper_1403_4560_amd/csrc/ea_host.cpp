@@ -24,6 +24,7 @@
 
 namespace ea {
 template <int L, int JK, int VAR> __global__ void site_sweep_kernel(SweepArgs A);
+template <int L, int JK, int VAR> __global__ void tiny_sweep_kernel(SweepArgs A);
 template <int L, int VAR, bool TAB> __global__ void row_sweep_kernel(SweepArgs A);
 template <int L, int VAR> __global__ void bits_sweep_kernel(SweepArgs A);
 template <int L, int JK, int VAR> __global__ void group_sweep_kernel(SweepArgs A);
@@ -166,6 +167,7 @@ struct ea_ensemble {
         bool group;          // walker-interleaved engine
         int group_min_threads = 64;
         bool row_table = true;  // row engine: the site groups' Philox words in LDS
+        bool tiny = false;      // site engine: a lane per odd site of the ladder
     };
     std::vector<Class> classes;
     std::vector<int> item_pos;  // sample -> index of its chain-a item in the sorted item list
@@ -574,8 +576,32 @@ SweepFn group_fn(int L, int jk)
 #undef EA_CASE
 }
 
-SweepFn sweep_fn(int L, int jk, bool row, bool table, bool bits, bool group, bool unbatched)
+SweepFn tiny_fn(int L, int jk, bool unbatched)
 {
+#define EA_CASE(Lv)                                                                                  \
+    case Lv:                                                                                         \
+        if (unbatched) return jk == 0 ? tiny_sweep_kernel<Lv, 0, 1> : tiny_sweep_kernel<Lv, 1, 1>;    \
+        return jk == 0 ? tiny_sweep_kernel<Lv, 0, 0> : tiny_sweep_kernel<Lv, 1, 0>;
+    switch (L) {
+        EA_CASE(2) EA_CASE(4)
+    default: return nullptr;
+    }
+#undef EA_CASE
+}
+
+// Threads of a tiny chain's workgroup (a lane per odd site of the ladder, as
+// many as a workgroup can hold), or 0 if the chain is not one.  The site
+// engine's kernel is four to nine times slower at every number of chains up to
+// 4096 (figures at the kernel).
+int tiny_threads(int L, int nT)
+{
+    const int lanes = nT * L * L * L / 2;
+    return (L == 2 || L == 4) && lanes <= 1024 ? (lanes + 63) / 64 * 64 : 0;
+}
+
+SweepFn sweep_fn(int L, int jk, bool row, bool table, bool bits, bool group, bool tiny, bool unbatched)
+{
+    if (tiny) return tiny_fn(L, jk, unbatched);
     if (group) return unbatched ? group_fn<1>(L, jk) : group_fn<0>(L, jk);
     if (bits) {
         if (L == 8) return unbatched ? bits_sweep_kernel<8, 1> : bits_sweep_kernel<8, 0>;
@@ -753,19 +779,19 @@ hipError_t launch_hbm(ea_ensemble *e, int L, int K, int item_first, int n_items,
 hipError_t launch_class(ea_ensemble *e, const ea_ensemble::Class &c, int K, int first, int n_items, bool unbatched)
 {
     SweepArgs A = sweep_args(e, K, (const int32_t *)e->items.p + first, n_items);
-    SweepFn fn = sweep_fn(c.L, e->jkind, c.row, c.row_table, c.bits, c.group, unbatched);
+    SweepFn fn = sweep_fn(c.L, e->jkind, c.row, c.row_table, c.bits, c.group, c.tiny, unbatched);
     if (!fn) return hipErrorInvalidDeviceFunction;
     // the group engine runs the team size the plan gives its class (the batch
     // launch's teams: BATCH_THREADS / teams per workgroup), which keeps a
     // thread's share within 16 site groups per half-sweep (its int32 energy
     // tallies); the site engine runs the plan's workgroup size
     const size_t ci = (size_t)(&c - e->classes.data());
-    const int threads = c.row || c.bits ? c.threads
+    const int threads = c.row || c.bits || c.tiny ? c.threads
                         : c.group ? (e->class_P[ci] > 0 ? BATCH_THREADS / e->class_P[ci]
                                                         : std::max(std::min(c.threads, e->plan.threads),
                                                                    c.group_min_threads))
                                   : e->plan.threads;
-    hipLaunchKernelGGL(fn, dim3(n_items), dim3(threads), c.lds, e->stream, A);
+    hipLaunchKernelGGL(fn, dim3(n_items), dim3(threads), c.tiny ? 0 : c.lds, e->stream, A);
     return hipGetLastError();
 }
 
@@ -1329,9 +1355,11 @@ ea_status ea_create_ensemble(const ea_desc *d, void *hip_stream, ea_ensemble **o
         for (int i = 0; i < e->S; ++i) {
             const SampleHost &h = e->smp[order[i]];
             if (e->classes.empty() || e->classes.back().L != h.L || e->classes.back().hbm != h.hbm ||
-                e->classes.back().bits != h.bits || e->classes.back().group != h.group)
+                e->classes.back().bits != h.bits || e->classes.back().group != h.group) {
                 e->classes.push_back(
                     {h.L, 2 * i, 0, 0, !h.hbm && !h.bits && !h.group, 0, h.hbm, wtotal, 0, h.bits, h.group});
+                e->classes.back().tiny = e->classes.back().row;
+            }
             ea_ensemble::Class &c = e->classes.back();
             c.count += 2;
             if (h.hbm) {
@@ -1351,7 +1379,9 @@ ea_status ea_create_ensemble(const ea_desc *d, void *hip_stream, ea_ensemble **o
                 if (row) c.row_table = c.row_table && row_table(h.L, h.nT, lds_max);
                 c.lds = std::max(c.lds, lds_offsets(h.L, h.nT, e->jkind, row && row_table(h.L, h.nT, lds_max)).total);
                 c.row = c.row && row;
+                c.tiny = c.tiny && tiny_threads(h.L, h.nT) > 0;
                 if (row) c.threads = std::max(c.threads, row_threads(h.L, h.nT));
+                else if (c.tiny) c.threads = std::max(c.threads, tiny_threads(h.L, h.nT));
             }
             e->item_pos[order[i]] = 2 * i;
             e->sample_class[order[i]] = (int)e->classes.size() - 1;
@@ -1359,7 +1389,7 @@ ea_status ea_create_ensemble(const ea_desc *d, void *hip_stream, ea_ensemble **o
         for (const auto &c : e->classes) {
             if (c.hbm) continue;
             for (int v = 0; v < 2; ++v) {
-                SweepFn fn = sweep_fn(c.L, e->jkind, c.row, c.row_table, c.bits, c.group, v == 1);
+                SweepFn fn = sweep_fn(c.L, e->jkind, c.row, c.row_table, c.bits, c.group, c.tiny, v == 1);
                 if (fn) (void)hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
                                                   (int)lds_max);
             }
@@ -1932,7 +1962,7 @@ ea_status ea_autotune(ea_ensemble *e, int32_t trial_sweeps)
     bool site_launch = false;
     for (size_t ci = 0; ci < e->classes.size(); ++ci) {
         const auto &c = e->classes[ci];
-        site_launch |= !c.hbm && !c.bits && !c.row && !c.group && !(e->plan.batch && e->class_P[ci] > 0);
+        site_launch |= !c.hbm && !c.bits && !c.row && !c.group && !c.tiny && !(e->plan.batch && e->class_P[ci] > 0);
     }
     if (result == EA_OK && site_launch) {
         const int keepT = e->plan.threads;

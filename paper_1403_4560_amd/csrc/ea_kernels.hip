@@ -20,11 +20,14 @@
 //    walker's energy/flip tallies in registers for the whole sweep;
 //  * site engine (any even L <= 16, either coupling kind; chains too small for
 //    the group engine): a thread takes a 4-site group of any walker and updates
-//    its sites one by one.
+//    its sites one by one.  Outside the batch launch the tiny kernel takes its
+//    place up to 1024 odd sites (L = 2, and L = 4 with up to 32 temperatures).
 // The group engine (ea_group.hip: one word = one site of four walkers) and the
 // one-bit engine (ea_bits.hip: +-1 couplings) use the same frame with their
 // own LDS layouts.  This file also holds the overlap measurement and the setup
 // and check kernels (HBM-resident tier: ea_hbm.hip; finalize: ea_finalize.hip).
+#include <type_traits>
+
 #include "ea_device.hpp"
 #include "ea_item.hpp"
 #include "ea_row.hpp"
@@ -43,6 +46,187 @@ __global__ void __launch_bounds__(1024) site_sweep_kernel(SweepArgs A)
     for (int item = blockIdx.x; item < A.n_items; item += gridDim.x) {
         const int code = A.items[item];
         run_item<L, JK, false>(A, A.samples[code >> 1], code & 1, smem);
+    }
+}
+
+// Tiny chains (L = 2 or 4, at most 1024 odd sites over the ladder): a lane per
+// (walker, site pair), which keeps its even and its odd site's spin, couplings
+// and neighbour addresses in registers for the whole chunk; only neighbour
+// spins are read from LDS.  A walker's lanes lie in one wave, so energy, down
+// spins and flips are a lane reduction and two counts of a ballot, once a
+// sweep, and every walker decides its own exchange from the energies of its
+// slot and the other's: two barriers a sweep.
+//
+// Bound: one wave's chain of instructions, about 5 cycles each (a Philox call
+// per half-sweep and one for the exchange, the field, the exponential); a
+// quarter of the Philox calls would do, at four sites in a row per lane.
+// 100 sweeps, by the site engine in workgroups of 1024 threads and now: L = 4,
+// 8 temperatures, 16 / 512 / 4096 samples 424 / 1639 / 13024 us and 111 / 230 /
+// 1449; +-1 16 / 4096 samples 376 / 11582 and 105 / 1268; L = 2, 16
+// temperatures, 4096 samples 9240 and 389.
+template <int L, int JK, int VAR>
+__global__ void __launch_bounds__(1024) tiny_sweep_kernel(SweepArgs A)
+{
+    constexpr int N = L * L * L, HALF = N / 2, HL = L / 2;
+    __shared__ int8_t S[2 * 1024];
+    __shared__ double Es[2][MAX_T], b64[MAX_T];
+    __shared__ int32_t map[MAX_T], fl[MAX_T], sw[MAX_T];
+    __shared__ uint32_t lut[JK == 1 ? 14 * MAX_T : 1];
+    const int code = A.items[blockIdx.x];
+    const SampleDev d = sample_of_item(A.samples, code >> 1);
+    const int r = code & 1, nT = d.n_T, gi = 2 * d.slot_off + r * nT;
+    const int tid = threadIdx.x, w = tid / HALF, h = tid % HALF;
+    const bool on = w < nT;
+    for (int i = tid; i < nT; i += blockDim.x) {
+        map[A.was[gi + i]] = i;
+        fl[i] = 0;
+        sw[i] = 0;
+        b64[i] = A.beta[d.slot_off + i];
+    }
+    if (JK == 1)
+        for (int i = tid; i < 14 * nT; i += blockDim.x) lut[i] = A.lut[(size_t)d.slot_off * 14 + i];
+
+    // the lane's two sites (sublattice index h): spin, neighbours in LDS, bonds
+    // in the order x+, x-, y+, y-, z+, z-
+    const int row = h / HL, j = h - row * HL, y = row % L, z = row / L;
+    typedef typename std::conditional<JK == 0, float, int>::type Bond;
+    int8_t *glob = A.spins + d.spin_off + (size_t)r * nT * N + (size_t)w * N;
+    int s[2], nb[2][6];
+    Bond J[2][6];
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        const int x = 2 * j + ((y + z + p) & 1);
+        const int xp = x + 1 == L ? 0 : x + 1, xm = x == 0 ? L - 1 : x - 1;
+        const int yp = y + 1 == L ? 0 : y + 1, ym = y == 0 ? L - 1 : y - 1;
+        const int zp = z + 1 == L ? 0 : z + 1, zm = z == 0 ? L - 1 : z - 1;
+        const int q[6] = {(xp + L * row) >> 1,           (xm + L * row) >> 1,           (x + L * (yp + L * z)) >> 1,
+                          (x + L * (ym + L * z)) >> 1,   (x + L * (y + L * zp)) >> 1,   (x + L * (y + L * zm)) >> 1};
+        s[p] = on ? glob[p * HALF + h] : 0;
+        if (on) S[w * N + p * HALF + h] = (int8_t)s[p];
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            nb[p][k] = (on ? w * N : 0) + (1 - p) * HALF + q[k];
+            // a bond is stored with the site at its lower end along the axis
+            const int e = (k & 1) ? ((1 - p) * 3 + k / 2) * HALF + q[k] : (p * 3 + k / 2) * HALF + h;
+            if constexpr (JK == 0) J[p][k] = ((const float *)A.J)[d.J_off + e];
+            else J[p][k] = ((const int8_t *)A.J)[d.J_off + e];
+        }
+    }
+    __syncthreads();
+    int t = on ? map[w] : 0;
+    // the walker's lanes within the wave
+    const int lane = tid & 63;
+    const uint64_t lanes = (HALF >= 64 ? ~0ull : (1ull << HALF) - 1) << (lane / HALF * HALF);
+    const bool lead = on && h == HALF - 1;
+    const double unit = JK == 0 ? 0x1p-18 : 1.0, hd = (double)d.h32;
+    const int64_t n0 = A.state[0];
+    int64_t next_meas = next_measurement(n0, A.measure_every, A.measure_start), f = 0;
+    RoundKeys key;
+    key.init(A.key0, A.key1);
+    const uint4 pg = philox_group((uint32_t)(h >> 2), d.sample_id, A.key1);
+    float b32 = A.beta32[d.slot_off + t];
+    int ej = 0, down = 0;
+    for (int it = 0; it < A.K; ++it) {
+        const int64_t n = n0 + it;
+        const uint32_t c2 = (PURPOSE_METROPOLIS << 28) | ((uint32_t)t << 1) | (uint32_t)r;
+        int flips = 0;
+        down = 0;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            int v[6];
+#pragma unroll
+            for (int k = 0; k < 6; ++k) v[k] = S[nb[p][k]];
+            PhiloxSlot ps;
+            ps.init((uint32_t)(2 * n + p), c2, A.key0, A.key1);
+            const u32x4 rw = ps.call(pg, key);
+            const uint32_t word = (h & 2) ? ((h & 1) ? rw.w : rw.z) : ((h & 1) ? rw.y : rw.x);
+            const int si = s[p];
+            bool accept;
+            int units;
+            if constexpr (JK == 0) {
+                // exact: every partial sum is a multiple of 2^-18 below 2^6
+                float SJ = J[p][0] * (float)v[0];
+#pragma unroll
+                for (int k = 1; k < 6; ++k) SJ = SJ + J[p][k] * (float)v[k];
+                const float dE = (2.0f * (float)si) * (SJ + d.h32);
+                accept = (dE <= 0.0f) | (u24_of(word) < exp_ea32(-(b32 * dE)));
+                units = (int)(SJ * 262144.0f);
+            } else {
+                units = 0;
+#pragma unroll
+                for (int k = 0; k < 6; ++k) units += J[p][k] * v[k];
+                const float fi = (float)units + d.h32;  // its sign is exact
+                accept = (si * fi <= 0.0f) | (word < lut[(t * 2 + ((si + 1) >> 1)) * 7 + ((units + 6) >> 1)]);
+            }
+            accept = accept && on;
+            if (accept) {
+                s[p] = -si;
+                S[w * N + p * HALF + h] = (int8_t)-si;
+            }
+            flips += __popcll(__ballot(accept) & lanes);
+            down += __popcll(__ballot(s[p] < 0) & lanes);
+            // minus the walker's E_J: every bond joins one even and one odd
+            // site, and the even spins change no more (at most 32 x 6 2^21)
+            if (p == 1) {
+                ej = s[1] * units;
+                if constexpr (HALF == 4) ej = group_sum_dpp<4>(ej);
+                else {
+                    ej = group_sum_dpp<16>(ej);
+                    ej += __shfl_xor(ej, 16);
+                }
+            }
+            if (p == 0) __syncthreads();
+        }
+        const double E = (double)-ej * unit - hd * (double)(N - 2 * down);
+        if (lead) {
+            Es[it & 1][t] = E;
+            fl[t] += flips;
+        }
+        __syncthreads();
+        // exchange of slots lo and lo + 1: each walker decides for itself
+        const bool odd = n & 1;
+        const int lo = odd ? (t - 1) | 1 : t & ~1, other = t == lo ? t + 1 : t - 1;
+        const bool pair = on && lo >= 0 && lo + 1 < nT;
+        const int to = pair ? other : t;
+        const double Eo = Es[it & 1][to], db = pair ? b64[lo] - b64[lo + 1] : 0.0;
+        const u32x4 q = philox4x32_10(0u, (uint32_t)n, (PURPOSE_EXCHANGE << 28) | ((uint32_t)lo << 1) | (uint32_t)r,
+                                      d.sample_id, A.key0, A.key1);
+        if (exchange_accept(q.x, q.y, db * (t == lo ? E - Eo : Eo - E)) && pair) {
+            if (t == lo && lead) sw[lo] += 1;
+            t = other;
+            b32 = A.beta32[d.slot_off + t];
+        }
+        if (n + 1 == next_meas) {
+            next_meas += A.measure_every;
+            if (lead) {
+                map[t] = w;
+                A.frameE[f * 2 * A.total_slots + gi + t] = E;
+            }
+            __syncthreads();
+            uint32_t *dst = A.frames + f * A.frame_words + d.frame_off + (size_t)r * nT * L * L;
+            for (int i = tid; i < nT * L * L; i += blockDim.x) {
+                const int ts = i / (L * L);
+                dst[i] = pack_row_lds<L>(S + map[ts] * N, i - ts * (L * L));
+            }
+            ++f;
+            __syncthreads();
+        }
+    }
+    if (on) {
+        glob[h] = (int8_t)s[0];
+        glob[HALF + h] = (int8_t)s[1];
+    }
+    if (lead) {
+        A.was[gi + t] = w;
+        if (A.K > 0) {
+            A.EJ[gi + w] = -ej;
+            A.M[gi + w] = N - 2 * down;
+        }
+    }
+    __syncthreads();
+    for (int i = tid; i < nT; i += blockDim.x) {
+        A.flips[gi + i] += fl[i];
+        A.swaps[gi + i] += sw[i];
     }
 }
 
@@ -72,6 +256,14 @@ EA_SITE(12)
 EA_SITE(14)
 EA_SITE(16)
 #undef EA_SITE
+#define EA_TINY(Lv)                                               \
+    template __global__ void tiny_sweep_kernel<Lv, 0, 0>(SweepArgs); \
+    template __global__ void tiny_sweep_kernel<Lv, 1, 0>(SweepArgs); \
+    template __global__ void tiny_sweep_kernel<Lv, 0, 1>(SweepArgs); \
+    template __global__ void tiny_sweep_kernel<Lv, 1, 1>(SweepArgs);
+EA_TINY(2)
+EA_TINY(4)
+#undef EA_TINY
 template __global__ void row_sweep_kernel<8, 0, true>(SweepArgs);
 template __global__ void row_sweep_kernel<8, 1, true>(SweepArgs);
 template __global__ void row_sweep_kernel<16, 0, true>(SweepArgs);

@@ -861,6 +861,17 @@ def test_row_engine_with_and_without_the_site_group_table(torch_cuda, nTs):
     check(work, 5, plan=dict(chunk=3))
 
 
+@pytest.mark.parametrize("jk", [W.J_GAUSS, W.J_PM1])
+@pytest.mark.parametrize("L, nTs", [(2, [1, 2, 5, 33, 64]), (4, [1, 2, 3, 9, 32]), (4, [7, 33])])
+def test_tiny_chains(torch_cuda, L, nTs, jk):
+    # a lane per site pair up to 1024 of them (32 temperatures at L = 4), with
+    # waves that hold idle lanes; one larger chain (33) sends its class to the
+    # four-sites-a-thread kernel
+    work = W.make_workload([L] * len(nTs), nTs, (0.4, 1.5), 0.3, jkind=jk, measure_every=3, measure_start=2,
+                           name="tiny chains")
+    check(work, 17, plan=dict(chunk=7), tier=3)
+
+
 def test_engine_routing(torch_cuda):
     """Which engine each sample runs on, by size, coupling kind, field and tier."""
     from paper_1403_4560_amd import binding
