@@ -321,7 +321,7 @@ enum {
     EA_ENGINE_ROW = 1,    /* LDS, int8x4 words of one walker (Gaussian, 8, 16)  */
     EA_ENGINE_GROUP = 2,  /* LDS, int8x4 words of one site of four walkers      */
     EA_ENGINE_BITS = 3,   /* LDS, one bit per spin (+-1, L = 8, 16, 32)         */
-    EA_ENGINE_HBM = 4     /* HBM-resident, four launches per sweep              */
+    EA_ENGINE_HBM = 4     /* HBM-resident, one launch per sweep                 */
 };
 ea_status ea_query_engines(const ea_ensemble *ens, int32_t *engines_host);
 

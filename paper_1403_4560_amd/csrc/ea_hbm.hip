@@ -1,5 +1,6 @@
 // ea_hbm.hip -- HBM-resident tier: chains too large for LDS (L = 24, and L = 32
-// with Gaussian couplings or long ladders).
+// with Gaussian couplings or long ladders), and few large chains of the row and
+// one-bit engines (spread_class in ea_host.cpp).
 //
 // Spins stay in HBM in the sublattice layout.  A sweep is one launch with one
 // workgroup per slot: the spins (N bytes) of the slot's walker are loaded into
@@ -208,7 +209,9 @@ __device__ __forceinline__ void hbm_rows(const uint32_t *S, int L, uint32_t *dst
 // Whether a measurement is due after done sweeps, and its frame in this chunk.
 __device__ __forceinline__ bool hbm_due(const SweepArgs &A, int64_t done, int64_t &f)
 {
-    if (A.measure_every <= 0 || done <= A.measure_start || (done - A.measure_start) % A.measure_every != 0) return false;
+    if (A.measure_every <= 0 || done <= A.measure_start) return false;
+    const int64_t x = done - A.measure_start;  // (a 64-bit division takes about 0.6 us of a lone wave)
+    if (x >> 31 == 0 ? (uint32_t)x % (uint32_t)A.measure_every != 0 : x % A.measure_every != 0) return false;
     f = measurements_upto(done, A.measure_every, A.measure_start) -
         measurements_upto(A.state[0], A.measure_every, A.measure_start) - 1;
     return true;
@@ -231,6 +234,7 @@ __global__ void __launch_bounds__(hbm_threads(L)) hbm_sweep_kernel(SweepArgs A)
     // this slot's walker, after the exchange that follows the sweep before
     // (every thread alike; the first sweep of a chunk finds it done)
     int w = A.was[gi + t];
+    const float b32 = A.beta32[d.slot_off + t];
     double Et = 0.0;
     if (A.it > 0) {
         const bool odd = (n - 1) & 1;
@@ -247,7 +251,7 @@ __global__ void __launch_bounds__(hbm_threads(L)) hbm_sweep_kernel(SweepArgs A)
                                       d.sample_id, A.key0, A.key1);
         Et = E;
         if (pair && exchange_accept(q.x, q.y, D)) {
-            if (t == lo && tid == 0) A.swaps[gi + lo] += 1;  // one writer per pair and launch
+            if (t == lo && tid == 0) atomicAdd((unsigned long long *)&A.swaps[gi + lo], 1ull);
             w = wo;
             Et = Eo;
         }
@@ -275,7 +279,7 @@ __global__ void __launch_bounds__(hbm_threads(L)) hbm_sweep_kernel(SweepArgs A)
         __syncthreads();
     }
     HbmSlot sl;
-    const float b32 = A.beta32[d.slot_off + t], cp = two_beta_log2e(b32);
+    const float cp = two_beta_log2e(b32);
     sl.ka = cp * 0x1p-18f;
     sl.kb = cp * (d.h32 - (float)d.hgrid * 0x1p-18f);
     sl.b2 = 2.0f * b32;
@@ -295,7 +299,8 @@ __global__ void __launch_bounds__(hbm_threads(L)) hbm_sweep_kernel(SweepArgs A)
     // E_J = -(sum of s' S_u over the odd sites): accE + nd1 sums s' (S_u +
     // hgrid), less hgrid sum s' (a thread has at most 16 odd sites)
     const long long e = wave_sum_i64((long long)ty.accE + (1 + 2 * (long long)d.hgrid * (JK == 0)) * ty.nd1);
-    const int fl = wave_sum_i32(ty.bf), nd = wave_sum_i32(ty.nd);
+    // set bits of the flip masks (at most 7 x 4096 sites a wave) and down spins
+    const int s2 = wave_sum_i32(ty.bf + (ty.nd << 16)), fl = s2 & 0xFFFF, nd = s2 >> 16;
     if ((tid & 63) == 0) {
         se[tid >> 6] = e;
         sc[0][tid >> 6] = fl;
@@ -315,7 +320,7 @@ __global__ void __launch_bounds__(hbm_threads(L)) hbm_sweep_kernel(SweepArgs A)
         }
         A.EJ_next[gi + t] = (JK == 0 ? (long long)d.hgrid * (N / 2) : 0) - E;
         A.M_next[gi + t] = N - 2 * down;
-        A.flips[gi + t] += bf / 7;
+        atomicAdd((unsigned long long *)&A.flips[gi + t], (unsigned long long)(bf / 7));
     }
 }
 

@@ -142,7 +142,7 @@ struct ea_ensemble {
     // device buffers
     DevBuf samples, items, spins, J, beta, beta32, lut, was, EJ, M, flips, swaps, acc, frames, frameE,
         state, slot_sample, costab, sintab, scratchE, scratchM, finout, walkers, dEJ, dM, sow, Ju, mslots, Jbits,
-        sel, fincols, stage, hbm_was;
+        sel, fincols, stage, hbm_was, spread_walkers, spread_Ju;
     int64_t frames_cap = 0;  // frames allocated
     std::vector<double> beta_host;  // [total_slots], to check that a finalize selection is one system
     std::vector<int32_t> sel_idx;   // [S] a finalize call's selection (no allocation per call)
@@ -168,6 +168,7 @@ struct ea_ensemble {
         int group_min_threads = 64;
         bool row_table = true;  // row engine: the site groups' Philox words in LDS
         bool tiny = false;      // site engine: a lane per odd site of the ladder
+        int spread = 0, wspread = 0;  // few chains: their walkers and first entry in spread_walkers (0: not spread)
     };
     std::vector<Class> classes;
     std::vector<int> item_pos;  // sample -> index of its chain-a item in the sorted item list
@@ -330,7 +331,8 @@ void destroy_all(ea_ensemble *e)
                       &e->was, &e->EJ, &e->M, &e->flips, &e->swaps, &e->acc, &e->frames,
                       &e->frameE, &e->state, &e->slot_sample, &e->costab, &e->sintab,
                       &e->scratchE, &e->scratchM, &e->finout, &e->walkers, &e->dEJ, &e->dM,
-                      &e->sow, &e->Ju, &e->mslots, &e->Jbits, &e->sel, &e->jkrep, &e->batchbuf, &e->fincols, &e->stage, &e->hbm_was};
+                      &e->sow, &e->Ju, &e->mslots, &e->Jbits, &e->sel, &e->jkrep, &e->batchbuf, &e->fincols, &e->stage, &e->hbm_was,
+                      &e->spread_walkers, &e->spread_Ju};
     for (DevBuf *b : bufs) dfree(*b);
     if (e->own_stream && e->stream) (void)hipStreamDestroy(e->stream);
     delete e;
@@ -405,7 +407,7 @@ SweepArgs sweep_args(const ea_ensemble *e, int K, const int32_t *items, int n_it
     A.measure_every = e->m;
     A.measure_start = e->mstart;
     A.sow = (const int32_t *)e->sow.p;
-    A.Ju = (const int32_t *)e->Ju.p;
+    A.Ju = (const int32_t *)(e->Ju.p ? e->Ju.p : e->spread_Ju.p);
     A.Jbits = (const uint32_t *)e->Jbits.p;
     A.jkind = e->jkind;
     return A;
@@ -510,7 +512,7 @@ ea_status upload_couplings(ea_ensemble *e, const void *host)
         if (jsz == 4)
             hipLaunchKernelGGL(split_couplings_kernel<float>, dim3(next - s, 3), dim3(256), 0, e->stream,
                                (const SampleDev *)e->samples.p, s, base, (const float *)e->stage.p, (float *)e->J.p,
-                               (int32_t *)e->Ju.p);
+                               (int32_t *)(e->Ju.p ? e->Ju.p : e->spread_Ju.p));
         else
             hipLaunchKernelGGL(split_couplings_kernel<int8_t>, dim3(next - s, 3), dim3(256), 0, e->stream,
                                (const SampleDev *)e->samples.p, s, base, (const int8_t *)e->stage.p, (int8_t *)e->J.p,
@@ -739,16 +741,72 @@ SweepFn hbm_fn(int L, int jk, bool unbatched)
 #undef EA_CASE
 }
 
+// Few chains: a class of large chains on the row or one-bit engine (one
+// workgroup per chain) that leaves most compute units idle runs the HBM tier's
+// kernels, a workgroup per walker, on the same state; chunks of fewer sweeps
+// than SPREAD_MIN_SWEEPS stay (the tier's two closing launches are 6 us).
+// Per sweep, the chain's engine and spread: L = 16 Gaussian, 24 temperatures, 1
+// / 16 / 32 / 48 samples 21.9 / 22.0 / 22.6 / 23.0 us and 6.5 / 10.1 / 16.7 /
+// 23.4, 5 temperatures, 32 samples 11.7 and 7.7; L = 32 +-1, 24 temperatures, 1 /
+// 16 / 32 / 64 samples 90.2 / 90.9 / 91.2 / 92.4 and 16.2 / 39.7 / 74.8 / 127, 5
+// temperatures, 32 / 64 samples 33.8 / 34.2 and 26.9 / 38.5:
+// it wins at every ladder up to a chain for every fourth compute unit.  +-1
+// L = 16 and smaller chains take less than a launch per sweep.
+constexpr int SPREAD_MIN_SWEEPS = 4;
+
+bool spread_class(const ea_ensemble::Class &c, int cus)
+{
+    return ((c.row && c.L == 16) || (c.bits && c.L == 32)) && 4 * c.count <= cus;
+}
+
+// The walker table of the spread classes, and their couplings as int32.  They
+// cost memory that the engines do without: without room for it nothing is
+// spread.
+void plan_spread(ea_ensemble *e)
+{
+    std::vector<int32_t> codes;
+    for (auto &c : e->classes) {
+        if (!spread_class(c, e->cus)) continue;
+        c.wspread = (int)codes.size();
+        for (int i = 0; i < c.count; i += 2) {
+            const int s = e->sorted_samples[(c.begin + i) / 2];
+            for (int rw = 0; rw < 2 * e->smp[s].nT; ++rw)
+                codes.push_back((s << 7) | ((rw / e->smp[s].nT) << 6) | (rw % e->smp[s].nT));
+        }
+        c.spread = (int)codes.size() - c.wspread;
+    }
+    if (codes.empty()) return;
+    const auto give_up = [&] {
+        for (auto &c : e->classes) c.spread = 0;
+        for (DevBuf *b : {&e->spread_walkers, &e->spread_Ju}) {
+            e->device_bytes -= (int64_t)b->bytes;
+            dfree(*b);
+        }
+    };
+    if (dalloc(e, e->spread_walkers, sizeof(int32_t) * codes.size()) != EA_OK ||
+        (e->jkind == EA_J_GAUSS_F32 && !e->Ju.p &&
+         dalloc(e, e->spread_Ju, sizeof(int32_t) * (size_t)e->J_elems) != EA_OK) ||
+        (!e->hbm_was.p && dalloc(e, e->hbm_was, sizeof(int32_t) * 2 * (size_t)e->total_slots) != EA_OK))
+        return give_up();
+    if (hipMemcpyAsync(e->spread_walkers.p, codes.data(), sizeof(int32_t) * codes.size(), hipMemcpyHostToDevice,
+                       e->stream) != hipSuccess ||
+        hipStreamSynchronize(e->stream) != hipSuccess) {
+        (void)hipGetLastError();
+        give_up();
+    }
+}
+
 bool hbm_size(int L) { return L == 8 || L == 16 || L == 24 || L == 32; }
 
 // K sweeps of an HBM-tier range: a launch per sweep, which also decides the
 // exchange and takes the snapshot of the sweep before; then those of the last
 // sweep.  The map, the energies and the magnetisations alternate between the
 // ensemble's buffers (in which a chunk starts and ends) and a second set.
-hipError_t launch_hbm(ea_ensemble *e, int L, int K, int item_first, int n_items, int w_first, int n_walk, bool unbatched)
+hipError_t launch_hbm(ea_ensemble *e, int L, int K, int item_first, int n_items, const void *walkers, int w_first,
+                      int n_walk, bool unbatched)
 {
     SweepArgs A = sweep_args(e, K, (const int32_t *)e->items.p + item_first, n_items);
-    A.walkers = (const int32_t *)e->walkers.p + w_first;
+    A.walkers = (const int32_t *)walkers + w_first;
     SweepFn fn = hbm_fn(L, e->jkind, unbatched);
     if (!fn) return hipErrorInvalidDeviceFunction;
     const auto buffers = [&](int read, int write) {
@@ -901,8 +959,8 @@ hipError_t enqueue_chunk(ea_ensemble *e, int K, bool unbatched)
         for (int s = 0; s < e->S; ++s) {
             const auto &c = e->classes[e->sample_class[s]];
             if (c.hbm) {
-                if ((st = launch_hbm(e, c.L, K, e->item_pos[s], 2, e->walker_pos[s], 2 * e->smp[s].nT, true)) !=
-                    hipSuccess)
+                if ((st = launch_hbm(e, c.L, K, e->item_pos[s], 2, e->walkers.p, e->walker_pos[s], 2 * e->smp[s].nT,
+                                     true)) != hipSuccess)
                     return st;
             } else if ((st = launch_class(e, c, K, e->item_pos[s], 2, true)) != hipSuccess) {
                 return st;
@@ -914,10 +972,16 @@ hipError_t enqueue_chunk(ea_ensemble *e, int K, bool unbatched)
         for (size_t ci = 0; ci < e->classes.size(); ++ci) {
             const auto &c = e->classes[ci];
             if (c.hbm || (batch && e->class_P[ci] > 0)) continue;
+            if (c.spread && K >= SPREAD_MIN_SWEEPS) {
+                st = launch_hbm(e, c.L, K, c.begin, c.count, e->spread_walkers.p, c.wspread, c.spread, false);
+                if (st != hipSuccess) return st;
+                continue;
+            }
             if ((st = launch_class(e, c, K, c.begin, c.count, false)) != hipSuccess) return st;
         }
         for (const auto &c : e->classes)
-            if (c.hbm && (st = launch_hbm(e, c.L, K, c.begin, c.count, c.wbegin, c.wcount, false)) != hipSuccess)
+            if (c.hbm && (st = launch_hbm(e, c.L, K, c.begin, c.count, e->walkers.p, c.wbegin, c.wcount, false)) !=
+                             hipSuccess)
                 return st;
     }
     if (e->timing && (st = hipEventRecord(ev.second, e->stream)) != hipSuccess) return st;
@@ -1559,6 +1623,7 @@ ea_status ea_create_ensemble(const ea_desc *d, void *hip_stream, ea_ensemble **o
             return fs;
         }
     }
+    plan_spread(e);
 #define H2D(buf, src, bytes)                                                                          \
     do {                                                                                              \
         hipError_t c_ = hipMemcpyAsync(e->buf.p, (src), (bytes), hipMemcpyHostToDevice, e->stream); \

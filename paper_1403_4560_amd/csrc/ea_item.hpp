@@ -63,24 +63,6 @@ __device__ __forceinline__ void copy_walkers(int8_t *lds, size_t lstride, int8_t
     }
 }
 
-__device__ __forceinline__ long long wave_sum_i64(long long v)
-{
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) {
-        const int lo = __shfl_xor((int)(unsigned long long)v, m);
-        const int hi = __shfl_xor((int)((unsigned long long)v >> 32), m);
-        v += (long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
-    }
-    return v;
-}
-
-__device__ __forceinline__ int wave_sum_i32(int v)
-{
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m);
-    return v;
-}
-
 // Pointers into the dynamic LDS of one work item.
 struct ItemLds {
     int8_t *S;
@@ -183,6 +165,27 @@ __device__ __forceinline__ V group_sum_dpp(V v)
         v += row_rotate<1>(v);
     }
     return v;
+}
+
+// Sums over a wave, every lane of it active: within the rows by rotations, then
+// one lane of each row by scalar adds (a shuffle through LDS for each of the
+// six steps took about a third of the HBM tier's end of sweep).
+__device__ __forceinline__ int wave_sum_i32(int v)
+{
+    v = group_sum_dpp<16>(v);
+    return __builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16) + __builtin_amdgcn_readlane(v, 32) +
+           __builtin_amdgcn_readlane(v, 48);
+}
+
+__device__ __forceinline__ long long wave_sum_i64(long long v)
+{
+    v = group_sum_dpp<16>(v);
+    const auto row = [&](int lane) {
+        const uint32_t lo = __builtin_amdgcn_readlane((int)(unsigned long long)v, lane);
+        const uint32_t hi = __builtin_amdgcn_readlane((int)((unsigned long long)v >> 32), lane);
+        return (long long)((unsigned long long)hi << 32 | lo);
+    };
+    return row(0) + row(16) + row(32) + row(48);
 }
 
 // Sum of v over the lanes of this lane's row of 16 whose index agrees with

@@ -38,12 +38,14 @@ constexpr int LDS_MAX_L = 16; // largest lattice of the LDS-resident tier
 constexpr int ROW_MAX_THREADS = 768;  // row engine: one thread per (walker, column)
 constexpr int GROUP_MAX_THREADS = 512;  // group engine workgroup size cap
 
-// Threads of an HBM-tier workgroup: half of what the words of one class of rows
-// (half a sublattice, L L / 2 rows of L / 8 words) take in as few steps as 1024
-// threads allow.  The whole count was slower everywhere (50 sweeps, Gaussian:
-// L = 24, 16 temperatures, 8 samples 723 us against 681, 64 samples 4404 against
-// 3392), a quarter faster only at many walkers (809 and 3066).
-constexpr int hbm_threads(int L) { return L == 32 ? 512 : L == 24 ? 448 : L == 16 ? 128 : 64; }
+// Threads of an HBM-tier workgroup.  One class of rows (half a sublattice) has
+// L L / 2 rows of L / 8 words.  L = 24, 32: half of what it takes in as few
+// steps as 1024 threads allow; the whole count was slower (50 sweeps, Gaussian:
+// L = 24, 16 temperatures, 8 samples 707 us against 669, 64 samples 4281 against
+// 3412), a quarter faster only at many walkers (809 and 3066).  L = 16: a word
+// each (24 temperatures, 1 / 8 / 64 samples 343 / 408 / 1471 us, half as many
+// threads 410 / 486 / 1431).
+constexpr int hbm_threads(int L) { return L == 32 ? 512 : L == 24 ? 448 : L == 16 ? 256 : 64; }
 
 struct SampleDev {
     int32_t L;

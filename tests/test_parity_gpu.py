@@ -872,6 +872,18 @@ def test_tiny_chains(torch_cuda, L, nTs, jk):
     check(work, 17, plan=dict(chunk=7), tier=3)
 
 
+@pytest.mark.parametrize("chunk", [3, 4, 7])
+@pytest.mark.parametrize("jk, L, nTs", [(W.J_GAUSS, 16, [1, 2, 9]), (W.J_GAUSS, 16, [24]), (W.J_PM1, 32, [1, 4, 3])])
+def test_few_large_chains(torch_cuda, jk, L, nTs, chunk):
+    # few chains of L = 16 (Gaussian) or L = 32 (+-1): chunks of four sweeps on
+    # run a workgroup per walker, shorter ones (and the rest of a call) a
+    # workgroup per chain, one after the other on the same state; another size
+    # beside them
+    work = W.make_workload([L] * len(nTs) + [8], nTs + [3], (0.4, 1.5), 0.1, jkind=jk, measure_every=2, measure_start=1,
+                           name="few chains")
+    check(work, 10, plan=dict(chunk=chunk))
+
+
 def test_engine_routing(torch_cuda):
     """Which engine each sample runs on, by size, coupling kind, field and tier."""
     from paper_1403_4560_amd import binding
