@@ -27,6 +27,7 @@
 #include <type_traits>
 
 #include "ea_device.hpp"
+#include "ea_group.hpp"
 #include "ea_item.hpp"
 #include "ea_types.hpp"
 #include "ea_update.hpp"
@@ -196,6 +197,13 @@ __device__ __forceinline__ void hbm_rows(const uint32_t *S, int L, uint32_t *dst
     for (int row = first; row < L * L; row += step) {
         const int yz = ((row % L) + row / L) & 1;
         uint32_t bits = 0;
+        if (L & 7) {
+            const int8_t *Sb = (const int8_t *)S;
+            for (int x = 0; x < L; ++x)
+                bits |= (uint32_t)(Sb[((x + yz) & 1) * (L * L * L / 2) + ((x + L * row) >> 1)] < 0) << x;
+            dst[row] = bits;
+            continue;
+        }
         for (int k = 0; k < wpr; ++k) {
             // signs at bits 7, 15, 23, 31 to bits 0, 2, 4, 6
             const uint32_t even = (((S[row * wpr + k] >> 7) & 0x01010101u) * 0x01041040u) >> 24 & 0x55u;
@@ -217,6 +225,58 @@ __device__ __forceinline__ bool hbm_due(const SweepArgs &A, int64_t done, int64_
     return true;
 }
 
+// Slot t's walker in a sweep, after the exchange that follows the sweep before
+// (the first sweep of a chunk finds it done), and its energy then: first all
+// loads, so that a caller can do other work while they are on the way, then the
+// decision.
+struct SlotWalker {
+    int w, wo, lo;
+    bool pair;
+    int64_t ej, ejo;
+    int32_t m, mo;
+    double bt, bo, E;
+
+    __device__ __forceinline__ void load(const SweepArgs &A, const SampleDev &d, int64_t n, int gi, int t)
+    {
+        w = A.was[gi + t];
+        E = 0.0;
+        if (A.it > 0) {
+            const bool odd = (n - 1) & 1;
+            lo = odd ? (t - 1) | 1 : t & ~1;
+            pair = lo >= 0 && lo + 1 < d.n_T;
+            const int to = !pair ? t : t == lo ? t + 1 : t - 1;
+            wo = A.was[gi + to];
+            ej = A.EJ[gi + t];
+            ejo = A.EJ[gi + to];
+            m = A.M[gi + t];
+            mo = A.M[gi + to];
+            bt = A.beta[d.slot_off + t];
+            bo = A.beta[d.slot_off + to];
+        }
+    }
+
+    // count: this thread counts the swap of the pair (one thread per slot)
+    template <int JK>
+    __device__ __forceinline__ void decide(const SweepArgs &A, const SampleDev &d, int r, int64_t n, int gi, int t,
+                                           bool count)
+    {
+        if (A.it > 0) {
+            const double unit = JK == 0 ? 0x1p-18 : 1.0, hd = (double)d.h32;
+            const double Eo = (double)ejo * unit - hd * (double)mo;
+            E = (double)ej * unit - hd * (double)m;
+            const double D = t == lo ? (bt - bo) * (E - Eo) : (bo - bt) * (Eo - E);
+            const u32x4 q = philox4x32_10(0u, (uint32_t)(n - 1),
+                                          (PURPOSE_EXCHANGE << 28) | ((uint32_t)lo << 1) | (uint32_t)r, d.sample_id,
+                                          A.key0, A.key1);
+            if (pair && exchange_accept(q.x, q.y, D)) {
+                if (t == lo && count) atomicAdd((unsigned long long *)&A.swaps[gi + lo], 1ull);
+                w = wo;
+                E = Eo;
+            }
+        }
+    }
+};
+
 template <int L, int JK, int VAR>
 __global__ void __launch_bounds__(hbm_threads(L)) hbm_sweep_kernel(SweepArgs A)
 {
@@ -231,31 +291,12 @@ __global__ void __launch_bounds__(hbm_threads(L)) hbm_sweep_kernel(SweepArgs A)
     const int r = (code >> 6) & 1, t = code & 63, tid = threadIdx.x;
     const int nT = d.n_T, gi = 2 * d.slot_off + r * nT;
     const int64_t n = A.state[0] + A.it;
-    // this slot's walker, after the exchange that follows the sweep before
-    // (every thread alike; the first sweep of a chunk finds it done)
-    int w = A.was[gi + t];
     const float b32 = A.beta32[d.slot_off + t];
-    double Et = 0.0;
-    if (A.it > 0) {
-        const bool odd = (n - 1) & 1;
-        const int lo = odd ? (t - 1) | 1 : t & ~1, other = t == lo ? t + 1 : t - 1;
-        const bool pair = lo >= 0 && lo + 1 < nT;
-        const int to = pair ? other : t;
-        const double unit = JK == 0 ? 0x1p-18 : 1.0, hd = (double)d.h32;
-        const int wo = A.was[gi + to];
-        const double E = (double)A.EJ[gi + t] * unit - hd * (double)A.M[gi + t];
-        const double Eo = (double)A.EJ[gi + to] * unit - hd * (double)A.M[gi + to];
-        const double bt = A.beta[d.slot_off + t], bo = A.beta[d.slot_off + to];
-        const double D = t == lo ? (bt - bo) * (E - Eo) : (bo - bt) * (Eo - E);
-        const u32x4 q = philox4x32_10(0u, (uint32_t)(n - 1), (PURPOSE_EXCHANGE << 28) | ((uint32_t)lo << 1) | (uint32_t)r,
-                                      d.sample_id, A.key0, A.key1);
-        Et = E;
-        if (pair && exchange_accept(q.x, q.y, D)) {
-            if (t == lo && tid == 0) atomicAdd((unsigned long long *)&A.swaps[gi + lo], 1ull);
-            w = wo;
-            Et = Eo;
-        }
-    }
+    SlotWalker sw;
+    sw.load(A, d, n, gi, t);
+    sw.decide<JK>(A, d, r, n, gi, t, tid == 0);
+    const int w = sw.w;
+    const double Et = sw.E;
     uint4 *glob = (uint4 *)(A.spins + d.spin_off + ((size_t)r * nT + w) * N);
     constexpr int CHUNKS = N / 16, PER = (CHUNKS + T - 1) / T;
     static_assert(PER <= 4);
@@ -374,11 +415,191 @@ __global__ void __launch_bounds__(256) hbm_snapshot_kernel(SweepArgs A)
     if (!hbm_due(A, A.state[0] + A.it + 1, f)) return;
     const int code = A.walkers[blockIdx.x];
     const SampleDev d = A.samples[code >> 7];
-    const int r = (code >> 6) & 1, t = code & 63, nT = d.n_T, L = d.L;
-    const uint32_t *Sw =
-        (const uint32_t *)(A.spins + d.spin_off + ((size_t)r * nT + A.was[2 * d.slot_off + r * nT + t]) * L * L * L);
-    hbm_rows(Sw, L, A.frames + f * A.frame_words + d.frame_off + ((size_t)r * nT + t) * L * L, threadIdx.x, blockDim.x);
+    const int r = (code >> 6) & 1, nT = d.n_T, L = d.L;
+    const size_t base = d.spin_off + (size_t)r * nT * L * L * L;
+    for (int t = code & 63; t < min((code & 63) + A.per, nT); ++t) {
+        const uint32_t *Sw = (const uint32_t *)(A.spins + base + (size_t)A.was[2 * d.slot_off + r * nT + t] * L * L * L);
+        hbm_rows(Sw, L, A.frames + f * A.frame_words + d.frame_off + ((size_t)r * nT + t) * L * L, threadIdx.x, blockDim.x);
+    }
 }
+
+// Few chains of the group engine (Gaussian couplings, L = 12 and 14): the same
+// form with a workgroup per four consecutive slots, whose walkers are brought
+// into the group engine's words (a word: one site of the four) in LDS; its
+// update and neighbour table, one site group per thread and half-sweep.
+// Bound: as above; the table and the couplings are formed while the map and
+// the energies are on the way.
+// At 16 samples x 21 temperatures, L = 14, a sweep takes 12.3 us (21.3 by the
+// group engine, a workgroup per chain), half of it the two half-sweeps; forming
+// the table after the exchange's loads came back took 13.0.
+// Bytes i of four words to word i: rows and columns of a 4 x 4 byte matrix.
+__device__ __forceinline__ void transpose_bytes(uint32_t a[4])
+{
+    const uint32_t p = __builtin_amdgcn_perm(a[1], a[0], 0x05010400u), q = __builtin_amdgcn_perm(a[3], a[2], 0x05010400u);
+    const uint32_t u = __builtin_amdgcn_perm(a[1], a[0], 0x07030602u), v = __builtin_amdgcn_perm(a[3], a[2], 0x07030602u);
+    a[0] = __builtin_amdgcn_perm(q, p, 0x05040100u);
+    a[1] = __builtin_amdgcn_perm(q, p, 0x07060302u);
+    a[2] = __builtin_amdgcn_perm(v, u, 0x05040100u);
+    a[3] = __builtin_amdgcn_perm(v, u, 0x07060302u);
+}
+
+template <int L>
+__global__ void __launch_bounds__(quad_threads(L), 4) quad_sweep_kernel(SweepArgs A)
+{
+    constexpr int N = L * L * L, HALF = N / 2, PS = HALF + 1, G4 = HALF / 4, T = quad_threads(L), W = T / 64;
+    static_assert(T >= G4, "a thread takes one site group of a half-sweep");
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    uint4 *NB = (uint4 *)smem;
+    int *Jl = (int *)(NB + HALF);
+    uint32_t *SG = (uint32_t *)(Jl + 3 * N);
+    __shared__ long long se[4][W];
+    __shared__ int sc[4][W];
+    __shared__ float b32[4];
+    const int code = A.walkers[xcd_block(blockIdx.x, gridDim.x)];
+    const SampleDev d = sample_of_item(A.samples, code >> 7);
+    const int r = (code >> 6) & 1, t0 = code & 63, tid = threadIdx.x;
+    const int nT = d.n_T, gi = 2 * d.slot_off + r * nT;
+    const int64_t n = A.state[0] + A.it;
+    // lane i mod 4 decides slot t0 + i (beyond the ladder: its last slot, and
+    // the result is not used)
+    const int own = min(t0 + (tid & 3), nT - 1);
+    const bool real = t0 + (tid & 3) < nT;
+    SlotWalker sw;
+    sw.load(A, d, n, gi, own);
+    const float b = A.beta32[d.slot_off + own];
+    constexpr int JQ = 3 * N / 4, JPER = (JQ + T - 1) / T;
+    const float4 *src = (const float4 *)((const float *)A.J + d.J_off);  // J_off is a multiple of 4
+    float4 v[JPER];
+#pragma unroll
+    for (int k = 0; k < JPER; ++k) v[k] = src[min(k * T + tid, JQ - 1)];
+    __builtin_amdgcn_sched_barrier(0);
+    for (int h = tid; h < HALF; h += T) NB[(h & 3) * G4 + (h >> 2)] = nbr_entry<L>(h);
+    sw.decide<0>(A, d, r, n, gi, own, real && tid < 4);
+    if (tid < 4) {
+        b32[tid] = b;
+        if (real) A.was_next[gi + own] = sw.w;
+    }
+    // couplings as exact int32 multiples of 2^-18
+#pragma unroll
+    for (int k = 0; k < JPER; ++k)
+        if (k * T + tid < JQ)
+            ((int4 *)Jl)[k * T + tid] = make_int4((int)(v[k].x * 262144.0f), (int)(v[k].y * 262144.0f),
+                                                  (int)(v[k].z * 262144.0f), (int)(v[k].w * 262144.0f));
+    // spins: four sites of each walker, to four words (padding walkers: +1)
+    uint32_t *glob[4], valid = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int w = __builtin_amdgcn_readlane(sw.w, i);
+        glob[i] = (uint32_t *)(A.spins + d.spin_off + ((size_t)r * nT + w) * N);
+        valid |= (t0 + i < nT ? 0xFFu : 0u) << (8 * i);
+    }
+    uint32_t in[2][4];
+    const int st = min(tid, G4 - 1);
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) in[p][i] = glob[i][p * G4 + st];
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+        if (tid < G4) {
+            uint32_t a[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) a[i] = t0 + i < nT ? in[p][i] : 0x01010101u;
+            transpose_bytes(a);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) SG[p * PS + 4 * tid + k] = a[k];
+        }
+    __syncthreads();
+    int64_t f;
+    if (A.it > 0 && hbm_due(A, n, f)) {
+        uint32_t *dst = A.frames + f * A.frame_words + d.frame_off + ((size_t)r * nT + t0) * L * L;
+        for (int i = tid; i < 4 * L * L; i += T) {
+            const int k = i / (L * L), row = i - k * (L * L), e = ((row % L) + row / L) & 1;
+            if (t0 + k >= nT) break;
+            uint32_t bits = 0;
+            for (int x = 0; x < L; ++x)
+                bits |= (SG[((x + e) & 1) * PS + row * (L / 2) + (x >> 1)] >> (8 * k + 7) & 1u) << x;
+            dst[i] = bits;
+        }
+        if (tid < 4 && real) A.frameE[f * 2 * A.total_slots + gi + own] = sw.E;
+        __syncthreads();
+    }
+    GroupLane ln;
+    int ts[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        ts[i] = min(t0 + i, nT - 1);
+        const float cp = two_beta_log2e(b32[i]);
+        ln.ka[i] = cp * 0x1p-18f;
+        ln.kb[i] = cp * (d.h32 - (float)d.hgrid * 0x1p-18f);
+        ln.t[i] = i;
+    }
+    ln.valid = valid;
+    ln.h32 = d.h32;
+    RoundKeys key;
+    key.init(A.key0, A.key1);
+    GroupTally ty;
+    const auto slot_words = [&](int p) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            ln.ps[i].init((uint32_t)(2 * n + p), (PURPOSE_METROPOLIS << 28) | ((uint32_t)ts[i] << 1) | (uint32_t)r, A.key0,
+                          A.key1);
+    };
+    slot_words(0);
+    if (tid < G4) group_item<L, 0>(A, d, SG, Jl, b32, NB, 1, 0, tid, key, ln, ty);
+    __syncthreads();
+    slot_words(1);
+    if (tid < G4) group_item<L, 1>(A, d, SG, Jl, b32, NB, 1, 0, tid, key, ln, ty);
+    // back to four sites of each walker (the odd ones are the thread's own, the
+    // even ones have the barrier)
+    int down[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) in[p][k] = SG[p * PS + 4 * st + k];
+        transpose_bytes(in[p]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) down[i] += tid < G4 ? __builtin_popcount(in[p][i] & 0x80808080u) : 0;
+    }
+    // a thread's (S_u + hgrid) XOR m' over four sites is at most 48 2^21 + 4, a
+    // row of sixteen below 2^31; down spins and flips of a wave at most 512 each
+    const int hg1 = 2 * d.hgrid + 1;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int e16 = group_sum_dpp<16>(ty.accE[i]);
+        const int c = wave_sum_i32(down[i] | ((int)(ty.flips >> (8 * i)) & 0xFF) << 16);
+        const int nd = wave_sum_i32((int)(ty.nd >> (8 * i)) & 0xFF);
+        const long long e = (long long)__builtin_amdgcn_readlane(e16, 0) + __builtin_amdgcn_readlane(e16, 16) +
+                            __builtin_amdgcn_readlane(e16, 32) + __builtin_amdgcn_readlane(e16, 48);
+        if ((tid & 63) == 0) {
+            se[i][tid >> 6] = e + (long long)hg1 * nd;
+            sc[i][tid >> 6] = c;
+        }
+    }
+    __syncthreads();
+    // (stores after the last barrier, which would wait for them)
+    if (tid < G4) {
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (t0 + i < nT) glob[i][p * G4 + tid] = in[p][i];
+    }
+    if (tid < 4 && real) {
+        long long E = -(long long)d.hgrid * HALF;
+        int c = 0;
+        for (int k = 0; k < W; ++k) {
+            E += se[tid][k];
+            c += sc[tid][k];
+        }
+        A.EJ_next[gi + own] = -E;
+        A.M_next[gi + own] = N - 2 * (c & 0xFFFF);
+        atomicAdd((unsigned long long *)&A.flips[gi + own], (unsigned long long)(c >> 16));
+    }
+}
+
+template __global__ void quad_sweep_kernel<12>(SweepArgs);
+template __global__ void quad_sweep_kernel<14>(SweepArgs);
 
 #define EA_HBM(Lv)                                                   \
     template __global__ void hbm_sweep_kernel<Lv, 0, 0>(SweepArgs); \

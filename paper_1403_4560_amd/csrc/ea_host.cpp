@@ -29,6 +29,7 @@ template <int L, int VAR, bool TAB> __global__ void row_sweep_kernel(SweepArgs A
 template <int L, int VAR> __global__ void bits_sweep_kernel(SweepArgs A);
 template <int L, int JK, int VAR> __global__ void group_sweep_kernel(SweepArgs A);
 template <int L, int JK, int VAR> __global__ void hbm_sweep_kernel(SweepArgs A);
+template <int L> __global__ void quad_sweep_kernel(SweepArgs A);
 __global__ void hbm_exchange_kernel(SweepArgs A);
 __global__ void hbm_snapshot_kernel(SweepArgs A);
 template <int L> __global__ void measure_kernel(MeasureArgs A);
@@ -406,7 +407,6 @@ SweepArgs sweep_args(const ea_ensemble *e, int K, const int32_t *items, int n_it
     A.key1 = (uint32_t)(e->seed >> 32);
     A.measure_every = e->m;
     A.measure_start = e->mstart;
-    A.sow = (const int32_t *)e->sow.p;
     A.Ju = (const int32_t *)(e->Ju.p ? e->Ju.p : e->spread_Ju.p);
     A.Jbits = (const uint32_t *)e->Jbits.p;
     A.jkind = e->jkind;
@@ -741,22 +741,33 @@ SweepFn hbm_fn(int L, int jk, bool unbatched)
 #undef EA_CASE
 }
 
-// Few chains: a class of large chains on the row or one-bit engine (one
-// workgroup per chain) that leaves most compute units idle runs the HBM tier's
-// kernels, a workgroup per walker, on the same state; chunks of fewer sweeps
-// than SPREAD_MIN_SWEEPS stay (the tier's two closing launches are 6 us).
-// Per sweep, the chain's engine and spread: L = 16 Gaussian, 24 temperatures, 1
-// / 16 / 32 / 48 samples 21.9 / 22.0 / 22.6 / 23.0 us and 6.5 / 10.1 / 16.7 /
-// 23.4, 5 temperatures, 32 samples 11.7 and 7.7; L = 32 +-1, 24 temperatures, 1 /
-// 16 / 32 / 64 samples 90.2 / 90.9 / 91.2 / 92.4 and 16.2 / 39.7 / 74.8 / 127, 5
-// temperatures, 32 / 64 samples 33.8 / 34.2 and 26.9 / 38.5:
-// it wins at every ladder up to a chain for every fourth compute unit.  +-1
-// L = 16 and smaller chains take less than a launch per sweep.
+// Few chains: a class of large chains on an LDS engine (one workgroup per
+// chain) that leaves most compute units idle runs the HBM tier's kernels, a
+// workgroup per walker or per four slots, on the same state; chunks of fewer
+// sweeps than SPREAD_MIN_SWEEPS stay (the closing launches are 6 us).  us per
+// sweep, the chain's engine and spread:
+//   L = 16 Gaussian, 24 temperatures, 1 / 16 / 32 / 48 samples 21.9 / 22.0 / 22.6
+//   / 23.0 and 6.5 / 10.1 / 16.7 / 23.4; 5 temperatures, 32 samples 11.7 and 7.7.
+//   L = 32 +-1, 24 temperatures, 1 / 16 / 32 / 64 samples 90.2 / 90.9 / 91.2 /
+//   92.4 and 16.2 / 39.7 / 74.8 / 127; 5 temperatures, 32 / 64 samples 33.8 / 34.2
+//   and 26.9 / 38.5: both up to a chain for every fourth compute unit.
+//   L = 14 Gaussian, 8 / 12 / 21 temperatures, 16 samples 11.3 / 13.7 / 21.3 and
+//   11.6 / 11.9 / 12.3, 21 temperatures, 37 / 45 samples 21.5 / 21.7 and 17.6 /
+//   24.6; L = 12, 16 / 24 / 32 temperatures, 16 samples 11.0 / 16.3 / 19.3 and 10.0
+//   / 10.2 / 10.4, 32 samples 11.0 / 16.0 / 19.4 and 11.2 / 12.8 / 13.3: up to a
+//   workgroup per compute unit, or two at six workgroups a chain.
+// +-1 L = 16 and smaller chains take little more than a launch per sweep.
 constexpr int SPREAD_MIN_SWEEPS = 4;
 
-bool spread_class(const ea_ensemble::Class &c, int cus)
+// Slots of a workgroup of a spread class with ladders of nT_max at most, 0 for
+// other classes.
+int spread_slots(const ea_ensemble::Class &c, int nT_max, int jk, int cus)
 {
-    return ((c.row && c.L == 16) || (c.bits && c.L == 32)) && 4 * c.count <= cus;
+    if ((c.row && c.L == 16) || (c.bits && c.L == 32)) return 4 * c.count <= cus ? 1 : 0;
+    const int quads = (nT_max + 3) / 4;
+    if (c.group && jk == EA_J_GAUSS_F32 && ((c.L == 12 && quads >= 4) || (c.L == 14 && quads >= 3)))
+        return c.count * quads <= (quads >= 6 ? 2 * cus : cus) ? 4 : 0;
+    return 0;
 }
 
 // The walker table of the spread classes, and their couplings as int32.  They
@@ -765,13 +776,17 @@ bool spread_class(const ea_ensemble::Class &c, int cus)
 void plan_spread(ea_ensemble *e)
 {
     std::vector<int32_t> codes;
+    bool need_Ju = false;
     for (auto &c : e->classes) {
-        if (!spread_class(c, e->cus)) continue;
+        int nT_max = 1;
+        for (int i = 0; i < c.count; i += 2) nT_max = std::max(nT_max, e->smp[e->sorted_samples[(c.begin + i) / 2]].nT);
+        const int per = spread_slots(c, nT_max, e->jkind, e->cus);
+        if (per == 0) continue;
+        need_Ju |= e->jkind == EA_J_GAUSS_F32 && per == 1;
         c.wspread = (int)codes.size();
-        for (int i = 0; i < c.count; i += 2) {
+        for (int i = 0; i < c.count; ++i) {
             const int s = e->sorted_samples[(c.begin + i) / 2];
-            for (int rw = 0; rw < 2 * e->smp[s].nT; ++rw)
-                codes.push_back((s << 7) | ((rw / e->smp[s].nT) << 6) | (rw % e->smp[s].nT));
+            for (int t = 0; t < e->smp[s].nT; t += per) codes.push_back((s << 7) | ((i & 1) << 6) | t);
         }
         c.spread = (int)codes.size() - c.wspread;
     }
@@ -784,8 +799,7 @@ void plan_spread(ea_ensemble *e)
         }
     };
     if (dalloc(e, e->spread_walkers, sizeof(int32_t) * codes.size()) != EA_OK ||
-        (e->jkind == EA_J_GAUSS_F32 && !e->Ju.p &&
-         dalloc(e, e->spread_Ju, sizeof(int32_t) * (size_t)e->J_elems) != EA_OK) ||
+        (need_Ju && !e->Ju.p && dalloc(e, e->spread_Ju, sizeof(int32_t) * (size_t)e->J_elems) != EA_OK) ||
         (!e->hbm_was.p && dalloc(e, e->hbm_was, sizeof(int32_t) * 2 * (size_t)e->total_slots) != EA_OK))
         return give_up();
     if (hipMemcpyAsync(e->spread_walkers.p, codes.data(), sizeof(int32_t) * codes.size(), hipMemcpyHostToDevice,
@@ -807,8 +821,12 @@ hipError_t launch_hbm(ea_ensemble *e, int L, int K, int item_first, int n_items,
 {
     SweepArgs A = sweep_args(e, K, (const int32_t *)e->items.p + item_first, n_items);
     A.walkers = (const int32_t *)walkers + w_first;
-    SweepFn fn = hbm_fn(L, e->jkind, unbatched);
+    const bool quads = !hbm_size(L);  // (few chains of the group engine only)
+    SweepFn fn = L == 14 ? quad_sweep_kernel<14> : L == 12 ? quad_sweep_kernel<12> : hbm_fn(L, e->jkind, unbatched);
     if (!fn) return hipErrorInvalidDeviceFunction;
+    const int threads = quads ? quad_threads(L) : hbm_threads(L);
+    const size_t lds = quads ? quad_lds(L) : 0;
+    A.per = quads ? 4 : 1;
     const auto buffers = [&](int read, int write) {
         A.EJ = (int64_t *)(read ? e->dEJ.p : e->EJ.p);
         A.M = (int32_t *)(read ? e->dM.p : e->M.p);
@@ -822,7 +840,7 @@ hipError_t launch_hbm(ea_ensemble *e, int L, int K, int item_first, int n_items,
     for (int it = 0; it < K; ++it) {
         A.it = it;
         buffers(it & 1, (it + 1) & 1);
-        hipLaunchKernelGGL(fn, dim3(n_walk), dim3(hbm_threads(L)), 0, e->stream, A);
+        hipLaunchKernelGGL(fn, dim3(n_walk), dim3(threads), lds, e->stream, A);
         if ((st = hipGetLastError()) != hipSuccess) return st;
     }
     A.it = K - 1;
@@ -1458,6 +1476,8 @@ ea_status ea_create_ensemble(const ea_desc *d, void *hip_stream, ea_ensemble **o
                                                   (int)lds_max);
             }
         }
+        for (const auto fn : {quad_sweep_kernel<12>, quad_sweep_kernel<14>})
+            (void)hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)quad_lds(14));
         e->sorted_samples = order;
         // batch launch: default teams per class; the batch kernel's LDS limit
         int nb = 0;

@@ -47,6 +47,12 @@ constexpr int GROUP_MAX_THREADS = 512;  // group engine workgroup size cap
 // threads 410 / 486 / 1431).
 constexpr int hbm_threads(int L) { return L == 32 ? 512 : L == 24 ? 448 : L == 16 ? 256 : 64; }
 
+// Few chains of the group engine: a workgroup per four slots, a thread per site
+// group of a half-sweep; neighbour table, couplings and four walkers' spins in
+// LDS.
+constexpr int quad_threads(int L) { return (L * L * L / 8 + 63) / 64 * 64; }
+constexpr size_t quad_lds(int L) { return 16 * (L * L * L / 2) + 12 * L * L * L + 8 * (L * L * L / 2 + 1); }
+
 struct SampleDev {
     int32_t L;
     int32_t n_T;
@@ -84,14 +90,13 @@ struct SweepArgs {
     const int64_t *state;       // [0] sweeps completed before this launch
     uint32_t key0, key1;
     int32_t measure_every;
-    int32_t pad;
+    int32_t per;                // slots of a workgroup (one launch per sweep)
     int64_t measure_start;
-    // HBM-resident tier (one launch per sweep): EJ, M, was, sow as the launch
+    // HBM-resident tier (one launch per sweep): EJ, M, was as the launch
     // before left them, and the buffers this launch writes
-    const int32_t *walkers;     // (sample << 7) | (chain << 6) | walker-or-slot
+    const int32_t *walkers;     // (sample << 7) | (chain << 6) | first slot, one per workgroup
     int32_t it;                 // sweep index within the chunk: n = state[0] + it
     int32_t jkind;              // 0 Gaussian (energy unit 2^-18), 1 +-1 (unit 1)
-    const int32_t *sow;         // per walker: its slot during the sweep before
     int64_t *EJ_next;
     int32_t *M_next;
     int32_t *was_next;
