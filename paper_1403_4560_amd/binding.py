@@ -193,6 +193,9 @@ class Ensemble:
         self.slot_off = np.concatenate([[0], np.cumsum(self.nT)])
         self.N = k["L"].astype(np.int64) ** 3
         self.spin_off = np.concatenate([[0], np.cumsum(2 * self.nT * self.N)])
+        # runs of consecutive samples with one ladder length
+        edges = np.concatenate([[0], np.flatnonzero(np.diff(self.nT)) + 1, [self.S]])
+        self._runs = [(int(a), int(b), int(self.nT[a])) for a, b in zip(edges[:-1], edges[1:])]
 
     # -- lifetime ----------------------------------------------------------
     def close(self):
@@ -223,21 +226,28 @@ class Ensemble:
         _check(load().ea_synchronize(self._h))
 
     # -- results ------------------------------------------------------------
-    def _per_sample(self, flat, width):
-        return [flat[self.slot_off[s] * width // 1:self.slot_off[s + 1] * width // 1]
-                for s in range(self.S)]
+    def _per_sample(self, flat, shape):
+        """Views of a flat array per sample; ``shape(n_T)`` of one sample.  A run
+        of samples of one shape is split in one go (a slice and a reshape for
+        each sample took 0.9 us, longer than the transfer)."""
+        out, at = [], 0
+        for a, b, nT in self._runs:
+            one = shape(nT)
+            end = at + (b - a) * int(np.prod(one))
+            out.extend(flat[at:end].reshape((b - a,) + one))
+            at = end
+        return out
 
     def measure(self, now: bool = False):
         TS = self.total_slots
-        acc = np.zeros(TS * NACC, dtype=np.float64)
-        flips = np.zeros(2 * TS, dtype=np.int64)
-        swaps = np.zeros(2 * TS, dtype=np.int64)
+        acc = np.empty(TS * NACC, dtype=np.float64)
+        flips = np.empty(2 * TS, dtype=np.int64)
+        swaps = np.empty(2 * TS, dtype=np.int64)
         _check(load().ea_measure(self._h, MEASURE_NOW if now else 0, _p(acc), _p(flips), _p(swaps)))
-        so = self.slot_off
         return {
-            "acc": [acc[so[s] * NACC:so[s + 1] * NACC].reshape(self.nT[s], NACC) for s in range(self.S)],
-            "flips": [flips[2 * so[s]:2 * so[s + 1]].reshape(2, self.nT[s]) for s in range(self.S)],
-            "swaps": [swaps[2 * so[s]:2 * so[s + 1]].reshape(2, self.nT[s]) for s in range(self.S)],
+            "acc": self._per_sample(acc, lambda nT: (nT, NACC)),
+            "flips": self._per_sample(flips, lambda nT: (2, nT)),
+            "swaps": self._per_sample(swaps, lambda nT: (2, nT)),
         }
 
     def read_state(self):
@@ -247,12 +257,11 @@ class Ensemble:
         E = np.zeros(2 * TS, dtype=np.float64)
         sweep = ctypes.c_int64()
         _check(load().ea_read_state(self._h, _p(spins), _p(was), _p(E), ctypes.byref(sweep)))
-        so = self.slot_off
         return {
             "spins": [spins[self.spin_off[s]:self.spin_off[s + 1]].reshape(2, self.nT[s], int(self.N[s]))
                       for s in range(self.S)],
-            "walker_at_slot": [was[2 * so[s]:2 * so[s + 1]].reshape(2, self.nT[s]) for s in range(self.S)],
-            "E": [E[2 * so[s]:2 * so[s + 1]].reshape(2, self.nT[s]) for s in range(self.S)],
+            "walker_at_slot": self._per_sample(was, lambda nT: (2, nT)),
+            "E": self._per_sample(E, lambda nT: (2, nT)),
             "sweep": sweep.value,
         }
 

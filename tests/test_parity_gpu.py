@@ -885,6 +885,28 @@ def test_few_large_chains(torch_cuda, jk, L, nTs, chunk):
     check(work, 10, plan=dict(chunk=chunk))
 
 
+@pytest.mark.parametrize("S", [1, 12, 13, 100])
+def test_results_read_back(torch_cuda, S):
+    # through the page-locked buffer (256 KiB: up to 12 samples) and straight to
+    # the caller's arrays; runs of equal ladders of one and of many samples
+    from paper_1403_4560_amd import binding
+    nTs = [64 if s % 9 else 61 for s in range(S)]
+    work = W.make_workload([2] * S, nTs, (0.4, 1.5), 0.1, name="read back")
+    rng = np.random.default_rng(S)
+    acc = [rng.standard_normal((n, binding.NACC)) for n in nTs]
+    flips, swaps = ([rng.integers(0, 1 << 40, (2, n)) for n in nTs] for _ in range(2))
+    with binding.Ensemble(work) as e:
+        for _ in range(2):
+            e.load_accumulators(acc, flips, swaps)
+            m = e.measure()
+            for key, want in (("acc", acc), ("flips", flips), ("swaps", swaps)):
+                assert len(m[key]) == S
+                for got, ref in zip(m[key], want):
+                    assert got.dtype == ref.dtype and got.shape == ref.shape and (got == ref).all()
+                    assert got.flags.writeable
+            acc = [a + 1.0 for a in acc]
+
+
 def test_engine_routing(torch_cuda):
     """Which engine each sample runs on, by size, coupling kind, field and tier."""
     from paper_1403_4560_amd import binding
