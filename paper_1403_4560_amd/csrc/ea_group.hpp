@@ -16,6 +16,14 @@
 // updates.  Walkers beyond n_T in the last quad are padding: spins +1, never
 // flipped, never tallied.
 //
+// Bound: VALU issue, about 470 cycles of a wave for the four Philox calls and
+// 470 for each site's four updates (in cycles an operation: multiply-add 4.8,
+// fast ones 2.5, SDWA, conversions and what has a scalar operand 4.4).  Down
+// spins are counted after the update, not flipped ones before it, and the
+// accepted bytes are masked once, by the walkers that there are: 13 cycles a
+// site less.  attempts/ns, 16 temperatures, 1024 samples: L = 12 985 -> 1018, L =
+// 10 905 -> 927, L = 6 662 -> 679; L = 14 x 17, 484 samples 686 -> 699.
+//
 // Device functions only: the per-class kernel (ea_group.hip) and the batch
 // kernel (ea_batch.hip) instantiate them.
 #pragma once
@@ -79,14 +87,14 @@ struct GroupLane {
     float ka[4], kb[4];     // per walker: the folded exponent's constants (update_word_gauss)
     PhiloxSlot ps[4];       // per walker: its slot's Philox words of this half-sweep
     int t[4];               // per walker: its slot
-    uint32_t valid;         // 0xFF in the bytes of real walkers
+    uint32_t flip, one;     // 0xFE and 0x01 in the bytes of real walkers
     float h32;              // the sample's field, held in a vector register
 };
 
 struct GroupTally {
     uint32_t flips = 0;     // per byte: flipped sites of that walker
-    uint32_t fdown = 0;     // per byte: flipped sites that were -1
-    uint32_t nd = 0;        // per byte, second half: -1 spins after the update
+    uint32_t nd0 = 0;       // per byte, first half: -1 spins after the update
+    uint32_t nd1 = 0;       // per byte, second half: likewise
     int accE[4] = {0, 0, 0, 0};  // second half: sum of (S_u + hgrid) XOR m' per walker (Gaussian)
 };
 
@@ -133,18 +141,18 @@ __device__ __forceinline__ void group_item(const SweepArgs &A, const SampleDev &
         const int Jz[4] = {jz, jz, jz, jz}, Jzn[4] = {jzm, jzm, jzm, jzm};
         // the exact path reads 2 beta32 of walker i's slot
         // Sus = S_u + hgrid (the field's grid part folded into the integer field)
-        const uint32_t fm = update_word_gauss<true>(Sv, X[0], X[1], X[2], X[3], X[4], X[5], Ja, Js, Jy, Jyn, Jz, Jzn, rk,
-                                     ln.ka, ln.kb, [&](int i) { return 2.0f * b32[ln.t[i]]; },
-                                     ln.h32, d.hgrid, Sus) &
-             ln.valid;
-        Sp[h] = Sv ^ fm;
-        ty.flips += (fm >> 7) & 0x01010101u;
-        ty.fdown += ((fm & Sv) >> 7) & 0x01010101u;
+        const uint32_t am = update_word_gauss<true>(Sv, X[0], X[1], X[2], X[3], X[4], X[5], Ja, Js, Jy, Jyn, Jz, Jzn, rk,
+                                                    ln.ka, ln.kb, [&](int i) { return 2.0f * b32[ln.t[i]]; }, ln.h32,
+                                                    d.hgrid, Sus);
+        const uint32_t Sn = Sv ^ (am & ln.flip);
+        Sp[h] = Sn;
+        ty.flips += am & ln.one;
         if constexpr (P == 1) {
-            const uint32_t Sn = Sv ^ fm;
 #pragma unroll
             for (int i = 0; i < 4; ++i) ty.accE[i] += Sus[i] ^ __builtin_amdgcn_sbfe((int)Sn, 8 * i + 7, 1);
-            ty.nd += (Sn >> 7) & 0x01010101u;
+            ty.nd1 += (Sn >> 7) & 0x01010101u;
+        } else {
+            ty.nd0 += (Sn >> 7) & 0x01010101u;
         }
     }
 }
@@ -163,7 +171,6 @@ __device__ __forceinline__ void run_group_item(const SweepArgs &A, const SampleD
     ItemLds I{};
     I.was = (int32_t *)(smem + o.was);
     I.sow = (int32_t *)(smem + o.sow);
-    I.M = (int32_t *)(smem + o.M);
     I.dM = (int32_t *)(smem + o.dM);
     I.fl = (int32_t *)(smem + o.fl);
     I.sw = (int32_t *)(smem + o.sw);
@@ -199,10 +206,9 @@ __device__ __forceinline__ void run_group_item(const SweepArgs &A, const SampleD
     for (int i = tid; i < nT; i += T) {
         I.was[i] = A.was[gi + i];
         I.sow[A.was[gi + i]] = i;  // kept by the exchange from here on
-        // walker totals: E_J = -dEJ, magnetisation M + dM (see the sweep loop)
+        // walker totals: E_J = -dEJ, dM the number of down spins (see the sweep loop)
         I.dEJ[i] = -A.EJ[gi + i];
-        I.dM[i] = 0;
-        I.M[i] = A.M[gi + i];
+        I.dM[i] = (N - A.M[gi + i]) / 2;
         I.fl[i] = 0;
         I.sw[i] = 0;
         I.b32[i] = A.beta32[d.slot_off + i];
@@ -243,24 +249,23 @@ __device__ __forceinline__ void run_group_item(const SweepArgs &A, const SampleD
     const int q = vt % NQ, gs = vt / NQ;
     const bool on = gs < TPQ;
     uint32_t valid = 0;
-    for (int i = 0; i < 4; ++i) valid |= (4 * q + i < nT ? 0xFFu : 0u) << (8 * i);
+    for (int i = 0; i < 4; ++i) valid |= (4 * q + i < nT ? 0xFEu : 0u) << (8 * i);
     const double hd = (double)d.h32;
     const int hg = d.hgrid;  // the field's grid part folded into S_u
     const int64_t n0 = A.state[0];
     int64_t next_meas = next_measurement(n0, A.measure_every, A.measure_start);
     int64_t f = 0;  // frame of the next measurement within this chunk
     // Energy of walker w after a sweep: its second half-sweep's tallies leave
-    // minus E_J in dEJ and the magnetisation change in dM; both are folded in
-    // at the start of the next sweep, before its own tallies (which follow the
+    // minus E_J in dEJ and the number of down spins in dM; both are cleared at
+    // the start of the next sweep, before its own tallies (which follow the
     // first half-sweep's barrier), so no pass of their own is needed.
-    const auto energy = [&](int w) { return (double)(-I.dEJ[w]) * 0x1p-18 - hd * (double)(I.M[w] + I.dM[w]); };
+    const auto energy = [&](int w) { return (double)(-I.dEJ[w]) * 0x1p-18 - hd * (double)(N - 2 * I.dM[w]); };
     RoundKeys key;
     key.init(A.key0, A.key1);
     for (int it = 0; it < A.K; ++it) {
         const int64_t n = n0 + it;
 #pragma unroll 1
         for (int i = tid; i < nT; i += T) {
-            I.M[i] += I.dM[i];
             I.dM[i] = 0;
             I.dEJ[i] = -(long long)hg * HALF;
         }
@@ -274,7 +279,8 @@ __device__ __forceinline__ void run_group_item(const SweepArgs &A, const SampleD
             ln.kb[i] = cp * (d.h32 - (float)d.hgrid * 0x1p-18f);
             ln.t[i] = ts[i];
         }
-        ln.valid = valid;
+        ln.flip = valid;
+        ln.one = (valid >> 1) & 0x01010101u;
         ln.h32 = d.h32;
         asm volatile("" : "+v"(ln.h32));
         GroupTally ty;
@@ -313,7 +319,7 @@ __device__ __forceinline__ void run_group_item(const SweepArgs &A, const SampleD
         // sites of |(S_u + hgrid) XOR m'| <= 12 2^21 + 1, below 2^31).
         const int hg1 = 2 * hg + 1;  // |hgrid| <= 6 2^21
         if (NQ == 4 && 5 * TPQ >= G4) {
-            int cf = (int)ty.flips, cd = (int)ty.fdown, cn = (int)ty.nd;
+            int cf = (int)ty.flips, cd = (int)ty.nd0, cn = (int)ty.nd1;
             cf += row_rotate<4>(cf);
             cd += row_rotate<4>(cd);
             cn += row_rotate<4>(cn);
@@ -330,19 +336,19 @@ __device__ __forceinline__ void run_group_item(const SweepArgs &A, const SampleD
             asm volatile("" : "+v"(tl));
             const int sel = (tl >> 2) & 3, w = 4 * (tl & 3) + sel, sh = 8 * sel;
             const int fl = (int)(((uint32_t)cf >> sh) & 0xFFu);
-            const int fd = (int)(((uint32_t)cd >> sh) & 0xFFu);
+            const int nd0 = (int)(((uint32_t)cd >> sh) & 0xFFu);
             const int nd = (int)(((uint32_t)cn >> sh) & 0xFFu);
             const int ea = sel == 0 ? e[0] : sel == 1 ? e[1] : sel == 2 ? e[2] : e[3];
             const int t = sel == 0 ? ts[0] : sel == 1 ? ts[1] : sel == 2 ? ts[2] : ts[3];
             if (w < nT) {
                 atomicAdd((unsigned long long *)&I.dEJ[w], (unsigned long long)((long long)ea + (long long)hg1 * nd));
-                atomicAdd(&I.dM[w], -2 * (fl - 2 * fd));
+                atomicAdd(&I.dM[w], nd0 + nd);
                 atomicAdd(&I.fl[t], fl);
             }
         } else if (T >= 256 && NQ <= 4 && NQ != 3) {
             uint32_t c[6] = {ty.flips & 0x00FF00FFu, (ty.flips >> 8) & 0x00FF00FFu,
-                             ty.fdown & 0x00FF00FFu, (ty.fdown >> 8) & 0x00FF00FFu,
-                             ty.nd & 0x00FF00FFu,    (ty.nd >> 8) & 0x00FF00FFu};
+                             ty.nd0 & 0x00FF00FFu,   (ty.nd0 >> 8) & 0x00FF00FFu,
+                             ty.nd1 & 0x00FF00FFu,   (ty.nd1 >> 8) & 0x00FF00FFu};
             for (int k = 0; k < 6; ++k) c[k] = (uint32_t)row_residue_sum((int)c[k], NQ);
             long long e[4];
             for (int i = 0; i < 4; ++i) e[i] = row_residue_sum((long long)ty.accE[i], NQ);
@@ -354,23 +360,23 @@ __device__ __forceinline__ void run_group_item(const SweepArgs &A, const SampleD
             const int j = tl & 15, sel = (j >> (NQ >> 1)) & 3, w = 4 * (tl & (NQ - 1)) + sel, sh = 16 * (sel >> 1);
             const bool odd = sel & 1;
             const int fl = (int)(((odd ? c[1] : c[0]) >> sh) & 0xFFFFu);
-            const int fd = (int)(((odd ? c[3] : c[2]) >> sh) & 0xFFFFu);
+            const int nd0 = (int)(((odd ? c[3] : c[2]) >> sh) & 0xFFFFu);
             const int nd = (int)(((odd ? c[5] : c[4]) >> sh) & 0xFFFFu);
             const long long ea = sel == 0 ? e[0] : sel == 1 ? e[1] : sel == 2 ? e[2] : e[3];
             const int t = sel == 0 ? ts[0] : sel == 1 ? ts[1] : sel == 2 ? ts[2] : ts[3];
             if (j < 4 * NQ && w < nT) {
                 atomicAdd((unsigned long long *)&I.dEJ[w], (unsigned long long)(ea + (long long)hg1 * nd));
-                atomicAdd(&I.dM[w], -2 * (fl - 2 * fd));
+                atomicAdd(&I.dM[w], nd0 + nd);
                 atomicAdd(&I.fl[t], fl);
             }
         } else {
             for (int i = 0; i < 4; ++i) {
                 const int w = 4 * q + i;
                 if (w < nT) {
-                    const int fl = (int)((ty.flips >> (8 * i)) & 0xFFu), fd = (int)((ty.fdown >> (8 * i)) & 0xFFu);
-                    const int nd = (int)((ty.nd >> (8 * i)) & 0xFFu);
+                    const int fl = (int)((ty.flips >> (8 * i)) & 0xFFu), nd0 = (int)((ty.nd0 >> (8 * i)) & 0xFFu);
+                    const int nd = (int)((ty.nd1 >> (8 * i)) & 0xFFu);
                     atomicAdd((unsigned long long *)&I.dEJ[w], (unsigned long long)(ty.accE[i] + (long long)hg1 * nd));
-                    atomicAdd(&I.dM[w], -2 * (fl - 2 * fd));
+                    atomicAdd(&I.dM[w], nd0 + nd);
                     atomicAdd(&I.fl[ts[i]], fl);
                 }
             }
@@ -427,7 +433,7 @@ __device__ __forceinline__ void run_group_item(const SweepArgs &A, const SampleD
     for (int i = tid; !tm.ghost && i < nT; i += T) {
         A.was[gi + i] = I.was[i];
         A.EJ[gi + i] = -I.dEJ[i];
-        A.M[gi + i] = I.M[i] + I.dM[i];
+        A.M[gi + i] = N - 2 * I.dM[i];
         A.flips[gi + i] += I.fl[i];
         A.swaps[gi + i] += I.sw[i];
     }

@@ -171,7 +171,8 @@ __device__ __forceinline__ void hbm_class(const SweepArgs &A, const SampleDev &d
             const int Jz[4] = {b.z.x, b.z.y, b.z.z, b.z.w}, Jzn[4] = {b.zm.x, b.zm.y, b.zm.z, b.zm.w};
             const float kav[4] = {sl.ka, sl.ka, sl.ka, sl.ka}, kbv[4] = {sl.kb, sl.kb, sl.kb, sl.kb};
             fm = update_word_gauss<true>(Sv, Xa, Xs, Yp, Ym, Zp, Zm, Ja, Js, Jy, Jyn, Jz, Jzn, rw, kav, kbv,
-                                         [&](int) { return sl.b2; }, sl.h32, d.hgrid, Sus);
+                                         [&](int) { return sl.b2; }, sl.h32, d.hgrid, Sus) &
+                 0xFEFEFEFEu;
         } else {
             const uint32_t Ja = EPS ? b.v : b.x, Js = EPS ? b.x : __builtin_amdgcn_perm(b.v, b.e, 0x06050403u);
             fm = update_word_pm1(Sv, Xa, Xs, Yp, Ym, Zp, Zm, Ja, Js, b.y, b.ym, b.z, b.zm, rw, sl.thr, d.down_mask, Sus);
@@ -491,7 +492,7 @@ __global__ void __launch_bounds__(quad_threads(L), 4) quad_sweep_kernel(SweepArg
     for (int i = 0; i < 4; ++i) {
         const int w = __builtin_amdgcn_readlane(sw.w, i);
         glob[i] = (uint32_t *)(A.spins + d.spin_off + ((size_t)r * nT + w) * N);
-        valid |= (t0 + i < nT ? 0xFFu : 0u) << (8 * i);
+        valid |= (t0 + i < nT ? 0xFEu : 0u) << (8 * i);
     }
     uint32_t in[2][4];
     const int st = min(tid, G4 - 1);
@@ -534,7 +535,8 @@ __global__ void __launch_bounds__(quad_threads(L), 4) quad_sweep_kernel(SweepArg
         ln.kb[i] = cp * (d.h32 - (float)d.hgrid * 0x1p-18f);
         ln.t[i] = i;
     }
-    ln.valid = valid;
+    ln.flip = valid;
+    ln.one = (valid >> 1) & 0x01010101u;
     ln.h32 = d.h32;
     RoundKeys key;
     key.init(A.key0, A.key1);
@@ -552,14 +554,11 @@ __global__ void __launch_bounds__(quad_threads(L), 4) quad_sweep_kernel(SweepArg
     if (tid < G4) group_item<L, 1>(A, d, SG, Jl, b32, NB, 1, 0, tid, key, ln, ty);
     // back to four sites of each walker (the odd ones are the thread's own, the
     // even ones have the barrier)
-    int down[4] = {0, 0, 0, 0};
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) in[p][k] = SG[p * PS + 4 * st + k];
         transpose_bytes(in[p]);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) down[i] += tid < G4 ? __builtin_popcount(in[p][i] & 0x80808080u) : 0;
     }
     // a thread's (S_u + hgrid) XOR m' over four sites is at most 48 2^21 + 4, a
     // row of sixteen below 2^31; down spins and flips of a wave at most 512 each
@@ -567,8 +566,10 @@ __global__ void __launch_bounds__(quad_threads(L), 4) quad_sweep_kernel(SweepArg
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int e16 = group_sum_dpp<16>(ty.accE[i]);
-        const int c = wave_sum_i32(down[i] | ((int)(ty.flips >> (8 * i)) & 0xFF) << 16);
-        const int nd = wave_sum_i32((int)(ty.nd >> (8 * i)) & 0xFF);
+        const int nd1 = (int)(ty.nd1 >> (8 * i)) & 0xFF;
+        const int c = wave_sum_i32((nd1 + ((int)(ty.nd0 >> (8 * i)) & 0xFF)) |
+                                   ((int)(ty.flips >> (8 * i)) & 0xFF) << 16);
+        const int nd = wave_sum_i32(nd1);
         const long long e = (long long)__builtin_amdgcn_readlane(e16, 0) + __builtin_amdgcn_readlane(e16, 16) +
                             __builtin_amdgcn_readlane(e16, 32) + __builtin_amdgcn_readlane(e16, 48);
         if ((tid & 63) == 0) {

@@ -211,8 +211,9 @@ __device__ __forceinline__ void row_word(const SweepArgs &A, const SampleDev &d,
     const float kav[4] = {ka, ka, ka, ka}, kbv[4] = {kb, kb, kb, kb};
     int Sus[4];
     const uint32_t fm = update_word_gauss<true>(
-        Sv, Xa, Xs, Yp, Ym, Zp, Zm, Ja, Js, Jy, Jyn, Jz, Jzn, rw, kav, kbv,
-        [&](int) { return 2.0f * A.beta32[d.slot_off + t]; }, h32, d.hgrid, Sus);
+                            Sv, Xa, Xs, Yp, Ym, Zp, Zm, Ja, Js, Jy, Jyn, Jz, Jzn, rw, kav, kbv,
+                            [&](int) { return 2.0f * A.beta32[d.slot_off + t]; }, h32, d.hgrid, Sus) &
+                        0xFEFEFEFEu;
     if constexpr (P == 1) tally_final(Sv, fm, Sus, accE);
     const uint32_t Sn = Sv ^ fm;
     *(uint32_t *)(Sw + P * HALF + o_y0 + zo) = Sn;

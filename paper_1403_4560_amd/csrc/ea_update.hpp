@@ -38,8 +38,8 @@ __device__ __forceinline__ float flip_by_byte(float f, uint32_t m, int i)
 // bytes are four sites of one walker (row and HBM engines) or one site of four
 // walkers (group engine).  rw holds byte i's Philox word in word i; b2_of(i)
 // returns 2 beta32 of byte i's slot (read only on the exact path).  Returns
-// the flip mask (0xFE in the bytes of accepted sites) and the integer local
-// field of every byte in Sus: S_u (S_J = S_u 2^-18), or with FOLD S_u + hgrid.
+// the accepted bytes as a mask (0xFF; flipping is an xor with its 0xFE bits) and
+// the integer local field of every byte in Sus: S_u (S_J = S_u 2^-18), or with FOLD S_u + hgrid.
 //
 // Decision: with f = fl32(S_J + h) and g = -s_i f (exact), x = -fl32(beta32 dE)
 // is fl32(2 beta32 g) (the same real number, rounded once), dE <= 0 iff x >= 0,
@@ -91,14 +91,13 @@ __device__ __forceinline__ uint32_t update_word_gauss(uint32_t Sv, uint32_t Xa, 
     // With every |gap| above M a byte is accepted iff its gap is negative:
     // byte permutes with selectors 9 and 11 replicate the sign bit of the low
     // and high source word into a whole byte.
-    uint32_t fm = (__builtin_amdgcn_perm(__float_as_uint(gap[1]), __float_as_uint(gap[0]), 0x0C0C0B09u) |
-                   __builtin_amdgcn_perm(__float_as_uint(gap[3]), __float_as_uint(gap[2]), 0x0B090C0Cu)) &
-                  0xFEFEFEFEu;
+    uint32_t am = __builtin_amdgcn_perm(__float_as_uint(gap[1]), __float_as_uint(gap[0]), 0x0C0C0B09u) |
+                  __builtin_amdgcn_perm(__float_as_uint(gap[3]), __float_as_uint(gap[2]), 0x0B090C0Cu);
     // If any lane of the wave has a byte with |gap| <= M, every lane takes the
     // exact test for all four bytes, which the gap only anticipates.  One
     // wave-uniform branch per word lets the four bytes' chains interleave.
     if (__builtin_amdgcn_ballot_w64(gmin <= ACCEPT_MARGIN) != 0) {
-        fm = 0;
+        am = 0;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             // S_u taken back from the stored sum here only (the empty asm keeps
@@ -110,10 +109,10 @@ __device__ __forceinline__ uint32_t update_word_gauss(uint32_t Sv, uint32_t Xa, 
             const float g = flip_by_byte(__builtin_fmaf((float)su, 0x1p-18f, h32), up, i);  // -s_i f
             const float x = b2_of(i) * g;                                                  // = -fl32(beta dE)
             const bool accept = x >= 0.0f || (float)(words[i] >> 8) * 0x1p-24f < exp_ea32(x);
-            fm |= accept ? 0xFEu << (8 * i) : 0u;
+            am |= accept ? 0xFFu << (8 * i) : 0u;
         }
     }
-    return fm;
+    return am;
 }
 
 // After the update: accE += (S_u XOR m') over all four bytes, m' from the
