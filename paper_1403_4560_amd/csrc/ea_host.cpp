@@ -778,12 +778,16 @@ SweepFn hbm_fn(int L, int jk, bool unbatched)
 //   L = 32 +-1, 24 temperatures, 1 / 16 / 32 / 64 samples 90.2 / 90.9 / 91.2 /
 //   92.4 and 16.2 / 39.7 / 74.8 / 127; 5 temperatures, 32 / 64 samples 33.8 / 34.2
 //   and 26.9 / 38.5: both up to a chain for every fourth compute unit.
+//   L = 16 +-1, 8 / 12 / 16 / 24 temperatures, 8 samples 6.0 / 7.7 / 9.4 / 13.3 and
+//   5.8 / 6.0 / 6.0 / 7.0, 16 samples 6.0 / 7.8 / 9.5 / 13.4 and 5.9 / 7.0 / 7.2 /
+//   8.7, 32 samples 6.1 / 7.8 / 9.6 / 13.5 and 7.1 / 8.8 / 10.1 / 13.3: from 12
+//   temperatures up to a chain for every eighth, from 20 for every fourth.
 //   L = 14 Gaussian, 8 / 12 / 21 temperatures, 16 samples 11.3 / 13.7 / 21.3 and
 //   11.6 / 11.9 / 12.3, 21 temperatures, 37 / 45 samples 21.5 / 21.7 and 17.6 /
 //   24.6; L = 12, 16 / 24 / 32 temperatures, 16 samples 11.0 / 16.3 / 19.3 and 10.0
 //   / 10.2 / 10.4, 32 samples 11.0 / 16.0 / 19.4 and 11.2 / 12.8 / 13.3: up to a
 //   workgroup per compute unit, or two at six workgroups a chain.
-// +-1 L = 16 and smaller chains take little more than a launch per sweep.
+// Smaller chains take little more than a launch per sweep.
 constexpr int SPREAD_MIN_SWEEPS = 4;
 
 // Slots of a workgroup of a spread class with ladders of nT_max at most, 0 for
@@ -791,6 +795,7 @@ constexpr int SPREAD_MIN_SWEEPS = 4;
 int spread_slots(const ea_ensemble::Class &c, int nT_max, int jk, int cus)
 {
     if ((c.row && c.L == 16) || (c.bits && c.L == 32)) return 4 * c.count <= cus ? 1 : 0;
+    if (c.bits && c.L == 16) return nT_max >= 12 && (nT_max >= 20 ? 4 : 8) * c.count <= cus ? 1 : 0;
     const int quads = (nT_max + 3) / 4;
     if (c.group && jk == EA_J_GAUSS_F32 && ((c.L == 12 && quads >= 4) || (c.L == 14 && quads >= 3)))
         return c.count * quads <= (quads >= 6 ? 2 * cus : cus) ? 4 : 0;

@@ -874,9 +874,9 @@ def test_tiny_chains(torch_cuda, L, nTs, jk):
 
 @pytest.mark.parametrize("chunk", [3, 4, 7])
 @pytest.mark.parametrize("jk, L, nTs", [(W.J_GAUSS, 16, [1, 2, 9]), (W.J_GAUSS, 16, [24]), (W.J_PM1, 32, [1, 4, 3]),
-                                        (W.J_GAUSS, 14, [9, 1, 8]), (W.J_GAUSS, 12, [4, 15, 2])])
+                                        (W.J_PM1, 16, [12, 5]), (W.J_GAUSS, 14, [9, 1, 8]), (W.J_GAUSS, 12, [4, 15, 2])])
 def test_few_large_chains(torch_cuda, jk, L, nTs, chunk):
-    # few chains of L = 12, 14, 16 (Gaussian) or L = 32 (+-1): chunks of four
+    # few chains of L = 12, 14, 16 (Gaussian) or L = 16, 32 (+-1): chunks of four
     # sweeps on run a workgroup per walker or per four slots (ladders that four
     # does not divide), shorter ones (and the rest of a call) a workgroup per
     # chain, one after the other on the same state; another size beside them
