@@ -899,7 +899,7 @@ hipError_t launch_class(ea_ensemble *e, const ea_ensemble::Class &c, int K, int 
                                                         : std::max(std::min(c.threads, e->plan.threads),
                                                                    c.group_min_threads))
                                   : e->plan.threads;
-    hipLaunchKernelGGL(fn, dim3(n_items), dim3(threads), c.tiny ? 0 : c.lds, e->stream, A);
+    hipLaunchKernelGGL(fn, dim3(n_items), dim3(threads), c.tiny ? 16 * threads : c.lds, e->stream, A);
     return hipGetLastError();
 }
 

@@ -57,20 +57,26 @@ __global__ void __launch_bounds__(1024) site_sweep_kernel(SweepArgs A)
 // sweep, and every walker decides its own exchange from the energies of its
 // slot and the other's: two barriers a sweep.
 //
-// Bound: one wave's chain of instructions, about 5 cycles each (a Philox call
-// per half-sweep and one for the exchange, the field, the exponential); a
-// quarter of the Philox calls would do, at four sites in a row per lane.
+// The exchange's random words are drawn ahead of time, a thread per (sweep,
+// pair), so a sweep only reads them.
+//
+// Bound: one wave's chain of instructions, about 2100 cycles a sweep at few
+// chains (a half-sweep 500, energies and a barrier 450, the exchange 500).
 // 100 sweeps, by the site engine in workgroups of 1024 threads and now: L = 4,
-// 8 temperatures, 16 / 512 / 4096 samples 424 / 1639 / 13024 us and 111 / 230 /
-// 1449; +-1 16 / 4096 samples 376 / 11582 and 105 / 1268; L = 2, 16
-// temperatures, 4096 samples 9240 and 389.
+// 8 temperatures, 16 / 512 / 4096 samples 424 / 1639 / 13024 us and 99 / 184 /
+// 1112; +-1 16 / 4096 samples 376 / 11582 and 93 / 1098; L = 2, 16 temperatures,
+// 4096 samples 9240 and 311.  Every sweep's words drawn in it, the exact test
+// for every site and exchange tables in global memory: 108 / 224 / 1430, 100 /
+// 1227, 385.
 template <int L, int JK, int VAR>
 __global__ void __launch_bounds__(1024) tiny_sweep_kernel(SweepArgs A)
 {
     constexpr int N = L * L * L, HALF = N / 2, HL = L / 2;
     __shared__ int8_t S[2 * 1024];
-    __shared__ double Es[2][MAX_T], b64[MAX_T];
+    __shared__ double Es[2][MAX_T], db[MAX_T];  // db: of beta, slots t and t + 1
+    __shared__ float beta[MAX_T];
     __shared__ int32_t map[MAX_T], fl[MAX_T], sw[MAX_T];
+    extern __shared__ uint2 ex[];  // [2][threads]
     __shared__ uint32_t lut[JK == 1 ? 14 * MAX_T : 1];
     const int code = A.items[blockIdx.x];
     const SampleDev d = sample_of_item(A.samples, code >> 1);
@@ -81,7 +87,8 @@ __global__ void __launch_bounds__(1024) tiny_sweep_kernel(SweepArgs A)
         map[A.was[gi + i]] = i;
         fl[i] = 0;
         sw[i] = 0;
-        b64[i] = A.beta[d.slot_off + i];
+        db[i] = A.beta[d.slot_off + i] - A.beta[d.slot_off + min(i + 1, nT - 1)];
+        beta[i] = A.beta32[d.slot_off + i];
     }
     if (JK == 1)
         for (int i = tid; i < 14 * nT; i += blockDim.x) lut[i] = A.lut[(size_t)d.slot_off * 14 + i];
@@ -124,8 +131,20 @@ __global__ void __launch_bounds__(1024) tiny_sweep_kernel(SweepArgs A)
     RoundKeys key;
     key.init(A.key0, A.key1);
     const uint4 pg = philox_group((uint32_t)(h >> 2), d.sample_id, A.key1);
-    float b32 = A.beta32[d.slot_off + t];
+    float b32 = beta[t], c2l = two_beta_log2e(b32);
     int ej = 0, down = 0;
+    // The exchange's random words: a thread each for (sweep, pair), ahead of
+    // time for as many sweeps as the threads give, into either half of ex in turn
+    const int pairs = nT / 2 > 0 ? nT / 2 : 1, ahead = (int)blockDim.x / pairs, my = tid / pairs;
+    const auto draw = [&](int64_t first, int half) {
+        const int64_t n = first + my;
+        const int lo = 2 * (tid - my * pairs) + (int)(n & 1);
+        const u32x4 q = philox4x32_10(0u, (uint32_t)n, (PURPOSE_EXCHANGE << 28) | ((uint32_t)lo << 1) | (uint32_t)r,
+                                      d.sample_id, A.key0, A.key1);
+        ex[half * blockDim.x + tid] = make_uint2(q.x, q.y);
+    };
+    int half = 0, use = 0;  // of the sweep at hand
+    draw(n0, 0);
     for (int it = 0; it < A.K; ++it) {
         const int64_t n = n0 + it;
         const uint32_t c2 = (PURPOSE_METROPOLIS << 28) | ((uint32_t)t << 1) | (uint32_t)r;
@@ -148,8 +167,14 @@ __global__ void __launch_bounds__(1024) tiny_sweep_kernel(SweepArgs A)
                 float SJ = J[p][0] * (float)v[0];
 #pragma unroll
                 for (int k = 1; k < 6; ++k) SJ = SJ + J[p][k] * (float)v[k];
-                const float dE = (2.0f * (float)si) * (SJ + d.h32);
-                accept = (dE <= 0.0f) | (u24_of(word) < exp_ea32(-(b32 * dE)));
+                // the binary32 estimate decides where it is safe (accept_gap; y
+                // is c' times the exact -s_i f), as in the word engines
+                const float sf = (float)si * (SJ + d.h32), g = accept_gap(c2l * -sf, (float)word);
+                accept = g < 0.0f;
+                if (__builtin_amdgcn_ballot_w64(__builtin_fabsf(g) <= ACCEPT_MARGIN) != 0) {
+                    const float dE = 2.0f * sf;
+                    accept = (dE <= 0.0f) | (u24_of(word) < exp_ea32(-(b32 * dE)));
+                }
                 units = (int)(SJ * 262144.0f);
             } else {
                 units = 0;
@@ -172,15 +197,17 @@ __global__ void __launch_bounds__(1024) tiny_sweep_kernel(SweepArgs A)
                 if constexpr (HALF == 4) ej = group_sum_dpp<4>(ej);
                 else {
                     ej = group_sum_dpp<16>(ej);
-                    ej += __shfl_xor(ej, 16);
+                    const auto rows = __builtin_amdgcn_permlane16_swap(ej, ej, false, false);
+                    ej = (int)(rows[0] + rows[1]);  // rows 0 and 1, 2 and 3
                 }
             }
             if (p == 0) __syncthreads();
         }
+        if (use + 1 == ahead) draw(n + 1, half ^ 1);
         const double E = (double)-ej * unit - hd * (double)(N - 2 * down);
         if (lead) {
             Es[it & 1][t] = E;
-            fl[t] += flips;
+            atomicAdd(&fl[t], flips);
         }
         __syncthreads();
         // exchange of slots lo and lo + 1: each walker decides for itself
@@ -188,13 +215,17 @@ __global__ void __launch_bounds__(1024) tiny_sweep_kernel(SweepArgs A)
         const int lo = odd ? (t - 1) | 1 : t & ~1, other = t == lo ? t + 1 : t - 1;
         const bool pair = on && lo >= 0 && lo + 1 < nT;
         const int to = pair ? other : t;
-        const double Eo = Es[it & 1][to], db = pair ? b64[lo] - b64[lo + 1] : 0.0;
-        const u32x4 q = philox4x32_10(0u, (uint32_t)n, (PURPOSE_EXCHANGE << 28) | ((uint32_t)lo << 1) | (uint32_t)r,
-                                      d.sample_id, A.key0, A.key1);
-        if (exchange_accept(q.x, q.y, db * (t == lo ? E - Eo : Eo - E)) && pair) {
-            if (t == lo && lead) sw[lo] += 1;
+        const double Eo = Es[it & 1][to], dE = t == lo ? E - Eo : Eo - E;
+        const uint2 q = ex[half * blockDim.x + use * pairs + (pair ? lo >> 1 : 0)];
+        if (++use == ahead) {
+            use = 0;
+            half ^= 1;
+        }
+        if (exchange_accept(q.x, q.y, db[pair ? lo : 0] * dE) && pair) {
+            if (t == lo && lead) atomicAdd(&sw[lo], 1);
             t = other;
-            b32 = A.beta32[d.slot_off + t];
+            b32 = beta[t];
+            c2l = two_beta_log2e(b32);
         }
         if (n + 1 == next_meas) {
             next_meas += A.measure_every;
