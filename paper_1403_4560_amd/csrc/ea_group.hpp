@@ -141,7 +141,7 @@ __device__ __forceinline__ void group_item(const SweepArgs &A, const SampleDev &
         const int Jz[4] = {jz, jz, jz, jz}, Jzn[4] = {jzm, jzm, jzm, jzm};
         // the exact path reads 2 beta32 of walker i's slot
         // Sus = S_u + hgrid (the field's grid part folded into the integer field)
-        const uint32_t am = update_word_gauss<true>(Sv, X[0], X[1], X[2], X[3], X[4], X[5], Ja, Js, Jy, Jyn, Jz, Jzn, rk,
+        const uint32_t am = update_word_gauss(Sv, X[0], X[1], X[2], X[3], X[4], X[5], Ja, Js, Jy, Jyn, Jz, Jzn, rk,
                                                     ln.ka, ln.kb, [&](int i) { return 2.0f * b32[ln.t[i]]; }, ln.h32,
                                                     d.hgrid, Sus);
         const uint32_t Sn = Sv ^ (am & ln.flip);

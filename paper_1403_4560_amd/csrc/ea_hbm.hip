@@ -170,7 +170,7 @@ __device__ __forceinline__ void hbm_class(const SweepArgs &A, const SampleDev &d
             const int Jy[4] = {b.y.x, b.y.y, b.y.z, b.y.w}, Jyn[4] = {b.ym.x, b.ym.y, b.ym.z, b.ym.w};
             const int Jz[4] = {b.z.x, b.z.y, b.z.z, b.z.w}, Jzn[4] = {b.zm.x, b.zm.y, b.zm.z, b.zm.w};
             const float kav[4] = {sl.ka, sl.ka, sl.ka, sl.ka}, kbv[4] = {sl.kb, sl.kb, sl.kb, sl.kb};
-            fm = update_word_gauss<true>(Sv, Xa, Xs, Yp, Ym, Zp, Zm, Ja, Js, Jy, Jyn, Jz, Jzn, rw, kav, kbv,
+            fm = update_word_gauss(Sv, Xa, Xs, Yp, Ym, Zp, Zm, Ja, Js, Jy, Jyn, Jz, Jzn, rw, kav, kbv,
                                          [&](int) { return sl.b2; }, sl.h32, d.hgrid, Sus) &
                  0xFEFEFEFEu;
         } else {

@@ -210,7 +210,7 @@ __device__ __forceinline__ void row_word(const SweepArgs &A, const SampleDev &d,
     const int Jz[4] = {Jpz.x, Jpz.y, Jpz.z, Jpz.w}, Jzn[4] = {Jzm.x, Jzm.y, Jzm.z, Jzm.w};
     const float kav[4] = {ka, ka, ka, ka}, kbv[4] = {kb, kb, kb, kb};
     int Sus[4];
-    const uint32_t fm = update_word_gauss<true>(
+    const uint32_t fm = update_word_gauss(
                             Sv, Xa, Xs, Yp, Ym, Zp, Zm, Ja, Js, Jy, Jyn, Jz, Jzn, rw, kav, kbv,
                             [&](int) { return 2.0f * A.beta32[d.slot_off + t]; }, h32, d.hgrid, Sus) &
                         0xFEFEFEFEu;

@@ -267,7 +267,7 @@ __host__ __device__ inline GroupLdsOff group_lds_offsets(int L, int nT)
     o.nb = align16(o.J + 3 * N * 4);
     o.was = o.nb + (N / 2) * 16;
     o.sow = o.was + 4 * T4;
-    o.M = o.sow + 4 * T4;
+    o.M = o.sow + 4 * T4;  // (not used)
     o.dM = o.M + 4 * T4;
     o.fl = o.dM + 4 * T4;
     o.sw = o.fl + 4 * T4;

@@ -39,7 +39,7 @@ __device__ __forceinline__ float flip_by_byte(float f, uint32_t m, int i)
 // walkers (group engine).  rw holds byte i's Philox word in word i; b2_of(i)
 // returns 2 beta32 of byte i's slot (read only on the exact path).  Returns
 // the accepted bytes as a mask (0xFF; flipping is an xor with its 0xFE bits) and
-// the integer local field of every byte in Sus: S_u (S_J = S_u 2^-18), or with FOLD S_u + hgrid.
+// the integer local field of every byte in Sus: S_u + hgrid (S_J = S_u 2^-18).
 //
 // Decision: with f = fl32(S_J + h) and g = -s_i f (exact), x = -fl32(beta32 dE)
 // is fl32(2 beta32 g) (the same real number, rounded once), dE <= 0 iff x >= 0,
@@ -48,14 +48,13 @@ __device__ __forceinline__ float flip_by_byte(float f, uint32_t m, int i)
 // x >= 0 or U 2^-24 < exp_ea32(x), the contract's rule; one wave-uniform
 // branch per word takes that test for all four bytes in every lane as soon as
 // one byte of one lane needs it.  The exponent y estimates x log2(e):
-//   FOLD = false: y = fl32(c' g), ka[i] = c' = two_beta_log2e(beta32);
-//   FOLD = true:  y = -s_i fl32(fl32(S_u + hgrid) ka[i] + kb[i]) with
-//     ka[i] = c' 2^-18 and kb[i] = fl32(c' (h - hgrid 2^-18)), one fused
-//     operation for the field and the temperature together.
+//   y = -s_i fl32(fl32(S_u + hgrid) ka[i] + kb[i]), ka[i] = c' 2^-18,
+//   kb[i] = fl32(c' (h - hgrid 2^-18)), c' = two_beta_log2e(beta32),
+// one fused operation for the field and the temperature together.
 // ea_verify_exp_bracket proves both signs of the gap safe for every binary32 x
-// and every y the two forms can produce (within a relative 2^-21 of x log2(e)
-// plus 2^-20; the bound on the second form needs beta32 <= 2^20).
-template <bool FOLD, class B2>
+// and every y that this or the plain form fl32(c' g) can produce (within a
+// relative 2^-21 of x log2(e) plus 2^-20; the bound needs beta32 <= 2^20).
+template <class B2>
 __device__ __forceinline__ uint32_t update_word_gauss(uint32_t Sv, uint32_t Xa, uint32_t Xs, uint32_t Yp,
                                                       uint32_t Ym, uint32_t Zp, uint32_t Zm, const int Ja[4],
                                                       const int Js[4], const int Jy[4], const int Jyn[4],
@@ -76,15 +75,9 @@ __device__ __forceinline__ uint32_t update_word_gauss(uint32_t Sv, uint32_t Xa, 
         Su += __mul24(__builtin_amdgcn_sbfe((int)Ym, sh, 8), Jyn[i]);
         Su += __mul24(__builtin_amdgcn_sbfe((int)Zp, sh, 8), Jz[i]);
         Su += __mul24(__builtin_amdgcn_sbfe((int)Zm, sh, 8), Jzn[i]);
-        if constexpr (FOLD) Su += hgrid;
+        Su += hgrid;
         Sus[i] = Su;
-        float y;
-        if constexpr (FOLD) {
-            y = flip_by_byte(__builtin_fmaf((float)Su, ka[i], kb[i]), up, i);
-        } else {
-            // f = fl32(S_J + h): S_J = Su 2^-18 exactly, so the fused form rounds once, as the sum does
-            y = ka[i] * flip_by_byte(__builtin_fmaf((float)Su, 0x1p-18f, h32), up, i);  // c' (-s_i f)
-        }
+        const float y = flip_by_byte(__builtin_fmaf((float)Su, ka[i], kb[i]), up, i);
         gap[i] = accept_gap(y, (float)words[i]);
         gmin = __builtin_fminf(gmin, __builtin_fabsf(gap[i]));
     }
@@ -105,7 +98,8 @@ __device__ __forceinline__ uint32_t update_word_gauss(uint32_t Sv, uint32_t Xa, 
             // which would cost the main path a separate add)
             int su = Sus[i];
             asm volatile("" : "+v"(su));
-            if constexpr (FOLD) su -= hgrid;
+            su -= hgrid;
+            // f = fl32(S_J + h): S_J = su 2^-18 exactly, so the fused form rounds once, as the sum does
             const float g = flip_by_byte(__builtin_fmaf((float)su, 0x1p-18f, h32), up, i);  // -s_i f
             const float x = b2_of(i) * g;                                                  // = -fl32(beta dE)
             const bool accept = x >= 0.0f || (float)(words[i] >> 8) * 0x1p-24f < exp_ea32(x);
