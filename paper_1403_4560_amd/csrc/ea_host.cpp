@@ -25,7 +25,7 @@
 namespace ea {
 template <int L, int JK, int VAR> __global__ void site_sweep_kernel(SweepArgs A);
 template <int L, int JK, int VAR> __global__ void tiny_sweep_kernel(SweepArgs A);
-template <int L, int VAR, bool TAB> __global__ void row_sweep_kernel(SweepArgs A);
+template <int L, int VAR, bool TAB, bool SPLIT> __global__ void row_sweep_kernel(SweepArgs A);
 template <int L, int VAR> __global__ void bits_sweep_kernel(SweepArgs A);
 template <int L, int JK, int VAR> __global__ void group_sweep_kernel(SweepArgs A);
 template <int L, int JK, int VAR> __global__ void hbm_sweep_kernel(SweepArgs A);
@@ -628,7 +628,13 @@ int tiny_threads(int L, int nT)
     return (L == 2 || L == 4) && lanes <= 1024 ? (lanes + 63) / 64 * 64 : 0;
 }
 
-SweepFn sweep_fn(int L, int jk, bool row, bool table, bool bits, bool group, bool tiny, bool unbatched)
+template <int L, bool TAB, bool SPLIT>
+SweepFn row_fn(bool unbatched)
+{
+    return unbatched ? row_sweep_kernel<L, 1, TAB, SPLIT> : row_sweep_kernel<L, 0, TAB, SPLIT>;
+}
+
+SweepFn sweep_fn(int L, int jk, bool row, bool table, bool split, bool bits, bool group, bool tiny, bool unbatched)
 {
     if (tiny) return tiny_fn(L, jk, unbatched);
     if (group) return unbatched ? group_fn<1>(L, jk) : group_fn<0>(L, jk);
@@ -639,9 +645,10 @@ SweepFn sweep_fn(int L, int jk, bool row, bool table, bool bits, bool group, boo
         return nullptr;
     }
     if (row) {
-        if (L == 8) return unbatched ? row_sweep_kernel<8, 1, true> : row_sweep_kernel<8, 0, true>;
-        if (L == 16 && table) return unbatched ? row_sweep_kernel<16, 1, true> : row_sweep_kernel<16, 0, true>;
-        if (L == 16) return unbatched ? row_sweep_kernel<16, 1, false> : row_sweep_kernel<16, 0, false>;
+        const bool u = unbatched;
+        if (L == 8) return split ? row_fn<8, true, true>(u) : row_fn<8, true, false>(u);
+        if (L == 16 && table) return split ? row_fn<16, true, true>(u) : row_fn<16, true, false>(u);
+        if (L == 16) return split ? row_fn<16, false, true>(u) : row_fn<16, false, false>(u);
         return nullptr;
     }
     return unbatched ? site_fn<1>(L, jk) : site_fn<0>(L, jk);
@@ -884,17 +891,34 @@ hipError_t launch_hbm(ea_ensemble *e, int L, int K, int item_first, int n_items,
     return hipGetLastError();
 }
 
+// Whether a row-engine launch takes twice the waves, each with half of the z
+// planes: where that puts more waves on a compute unit (LDS holds R chains, the
+// registers four waves a SIMD at L = 8 and three at L = 16), or as many with all
+// of the launch's chains resident at once.  100 sweeps, whole and split: L = 8 x
+// 16 temperatures, 8 / 256 / 512 / 1024 samples 628 / 899 / 1064 / 1685 us and 413
+// / 585 / 907 / 1758; L = 16 x 12, 64 / 128 / 512 samples (more waves) 1618 / 1697 /
+// 6353 and 1217 / 1307 / 4847; L = 16 x 5, 64 / 192 samples (as many) 1132 / 1678
+// and 906 / 1794.
+bool row_split(const ea_ensemble *e, const ea_ensemble::Class &c, int n_items)
+{
+    if (2 * c.threads > ROW_MAX_THREADS) return false;
+    const int room = (c.L == 8 ? 1024 : 768) / c.threads, chains = (int)(e->lds_per_cu / c.lds);
+    const int whole = std::min(chains, room), split = std::min(chains, room / 2);
+    return 2 * split > whole || (split > 0 && n_items <= split * e->cus);
+}
+
 hipError_t launch_class(ea_ensemble *e, const ea_ensemble::Class &c, int K, int first, int n_items, bool unbatched)
 {
     SweepArgs A = sweep_args(e, K, (const int32_t *)e->items.p + first, n_items);
-    SweepFn fn = sweep_fn(c.L, e->jkind, c.row, c.row_table, c.bits, c.group, c.tiny, unbatched);
+    const bool split = c.row && row_split(e, c, n_items);
+    SweepFn fn = sweep_fn(c.L, e->jkind, c.row, c.row_table, split, c.bits, c.group, c.tiny, unbatched);
     if (!fn) return hipErrorInvalidDeviceFunction;
     // the group engine runs the team size the plan gives its class (the batch
     // launch's teams: BATCH_THREADS / teams per workgroup), which keeps a
     // thread's share within 16 site groups per half-sweep (its int32 energy
     // tallies); the site engine runs the plan's workgroup size
     const size_t ci = (size_t)(&c - e->classes.data());
-    const int threads = c.row || c.bits || c.tiny ? c.threads
+    const int threads = split ? 2 * c.threads : c.row || c.bits || c.tiny ? c.threads
                         : c.group ? (e->class_P[ci] > 0 ? BATCH_THREADS / e->class_P[ci]
                                                         : std::max(std::min(c.threads, e->plan.threads),
                                                                    c.group_min_threads))
@@ -1502,9 +1526,11 @@ ea_status ea_create_ensemble(const ea_desc *d, void *hip_stream, ea_ensemble **o
         for (const auto &c : e->classes) {
             if (c.hbm) continue;
             for (int v = 0; v < 2; ++v) {
-                SweepFn fn = sweep_fn(c.L, e->jkind, c.row, c.row_table, c.bits, c.group, c.tiny, v == 1);
-                if (fn) (void)hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                  (int)lds_max);
+                for (const bool split : {false, true}) {
+                    SweepFn fn = sweep_fn(c.L, e->jkind, c.row, c.row_table, split, c.bits, c.group, c.tiny, v == 1);
+                    if (fn) (void)hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                      (int)lds_max);
+                }
             }
         }
         for (const auto fn : {quad_sweep_kernel<12>, quad_sweep_kernel<14>})

@@ -263,13 +263,13 @@ __global__ void __launch_bounds__(1024) tiny_sweep_kernel(SweepArgs A)
 
 // L = 8 chains are small (two waves for 16 walkers), so their workgroups are
 // held to 128 VGPRs to keep four waves per SIMD resident.
-template <int L, int VAR, bool TAB>
+template <int L, int VAR, bool TAB, bool SPLIT>
 __global__ void __launch_bounds__(ROW_MAX_THREADS, L == 8 ? 4 : 1) row_sweep_kernel(SweepArgs A)
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     for (int item = blockIdx.x; item < A.n_items; item += gridDim.x) {
         const int code = A.items[item];
-        run_item<L, 0, true, TAB>(A, sample_of_item(A.samples, code >> 1), code & 1, smem);
+        run_item<L, 0, true, TAB, SPLIT>(A, sample_of_item(A.samples, code >> 1), code & 1, smem);
     }
 }
 
@@ -295,12 +295,15 @@ EA_SITE(16)
 EA_TINY(2)
 EA_TINY(4)
 #undef EA_TINY
-template __global__ void row_sweep_kernel<8, 0, true>(SweepArgs);
-template __global__ void row_sweep_kernel<8, 1, true>(SweepArgs);
-template __global__ void row_sweep_kernel<16, 0, true>(SweepArgs);
-template __global__ void row_sweep_kernel<16, 1, true>(SweepArgs);
-template __global__ void row_sweep_kernel<16, 0, false>(SweepArgs);
-template __global__ void row_sweep_kernel<16, 1, false>(SweepArgs);
+#define EA_ROW(Lv, TABv)                                                    \
+    template __global__ void row_sweep_kernel<Lv, 0, TABv, false>(SweepArgs); \
+    template __global__ void row_sweep_kernel<Lv, 1, TABv, false>(SweepArgs); \
+    template __global__ void row_sweep_kernel<Lv, 0, TABv, true>(SweepArgs);  \
+    template __global__ void row_sweep_kernel<Lv, 1, TABv, true>(SweepArgs);
+EA_ROW(8, true)
+EA_ROW(16, true)
+EA_ROW(16, false)
+#undef EA_ROW
 
 // ---------------------------------------------------------------------------
 // Overlap measurement (eq. 2).  One wave per (sample, slot).  For each snapshot

@@ -221,11 +221,12 @@ __device__ __forceinline__ void row_word(const SweepArgs &A, const SampleDev &d,
     nd += __builtin_popcount(Sn & 0x80808080u);
 }
 
-// Half-sweep P of one walker's column (k, y); E0 = eps of the even z planes.
+// Half-sweep P of planes z0 .. z1 - 1 of one walker's column (k, y); E0 = eps of
+// the even z planes.
 template <int L, int P, int E0, bool TAB>
 __device__ __forceinline__ void row_half_sweep(const SweepArgs &A, const SampleDev &d, int r, int64_t n,
-                                               const ItemLds &I, const RoundKeys &key, int w, int y, int k, int t,
-                                               int &accE, int &nd, int &bf)
+                                               const ItemLds &I, const RoundKeys &key, int w, int y, int k, int z0,
+                                               int z1, int t, int &accE, int &nd, int &bf)
 {
     constexpr int WPR = L / 8, HL = L / 2;
     const int yp = (y + 1) & (L - 1), ym = (y - 1) & (L - 1);
@@ -243,7 +244,7 @@ __device__ __forceinline__ void row_half_sweep(const SweepArgs &A, const SampleD
     const float ka = cp * 0x1p-18f, kb = cp * (d.h32 - (float)d.hgrid * 0x1p-18f);
     float h32 = d.h32;  // exact path only
 #pragma unroll 1
-    for (int z = 0; z < L; z += 4) {
+    for (int z = z0; z < z1; z += 4) {
         const int zm = z == 0 ? L - 1 : z - 1, z4 = z + 4 == L ? 0 : z + 4;
         row_word<L, P, E0, TAB>(A, d, Sw, J, I.ph, o_y0, o_yp, o_ym, o_x, j_y0, j_ym, je_prev, z, z + 1, zm, ps, t, key, ka,
                            kb, h32, accE, nd, bf);
@@ -294,8 +295,9 @@ __device__ __forceinline__ uint32_t pack_row_lds(const int8_t *Sw, int row)
 
 // ---------------------------------------------------------------------------
 // The per-item frame shared by both engines (TAB: the row engine keeps the
-// site groups' Philox words in LDS, 2 N bytes).
-template <int L, int JK, bool ROW, bool TAB = ROW>
+// site groups' Philox words in LDS, 2 N bytes; SPLIT: it has twice the waves, and
+// a wave takes half of the z planes).
+template <int L, int JK, bool ROW, bool TAB = ROW, bool SPLIT = false>
 __device__ __forceinline__ void run_item(const SweepArgs &A, const SampleDev &d, int r, char *smem,
                                          const Team tm = whole_block())
 {
@@ -355,7 +357,8 @@ __device__ __forceinline__ void run_item(const SweepArgs &A, const SampleDev &d,
     const int rw_wave = tid_r >> 6, rw_lane = tid_r & 63;
     const int rw_par = __builtin_amdgcn_readfirstlane(rw_wave & 1);
     const int rw_rem = rw_lane % CPW;
-    const int rw_w = (rw_wave >> 1) * WPW + rw_lane / CPW;
+    const int rw_w = (rw_wave >> (SPLIT ? 2 : 1)) * WPW + rw_lane / CPW;
+    const int rw_z0 = SPLIT ? (rw_wave >> 1 & 1) * (L / 2) : 0, rw_z1 = SPLIT ? rw_z0 + L / 2 : L;
     const int rw_k = rw_rem % WPR, rw_y = 2 * (rw_rem / WPR) + rw_par;
 
     const double unit = JK == 0 ? 0x1p-18 : 1.0;
@@ -395,19 +398,19 @@ __device__ __forceinline__ void run_item(const SweepArgs &A, const SampleDev &d,
             const int t = on ? I.sow[rw_w] : 0;
             int accE = 0, nd0 = 0, nd = 0, bf = 0;
             if (on) {
-                if (rw_par) row_half_sweep<L, 0, 1, TAB>(A, d, r, n, I, key, rw_w, rw_y, rw_k, t, accE, nd0, bf);
-                else row_half_sweep<L, 0, 0, TAB>(A, d, r, n, I, key, rw_w, rw_y, rw_k, t, accE, nd0, bf);
+                if (rw_par) row_half_sweep<L, 0, 1, TAB>(A, d, r, n, I, key, rw_w, rw_y, rw_k, rw_z0, rw_z1, t, accE, nd0, bf);
+                else row_half_sweep<L, 0, 0, TAB>(A, d, r, n, I, key, rw_w, rw_y, rw_k, rw_z0, rw_z1, t, accE, nd0, bf);
             }
             __syncthreads();
             if (on) {
-                if (rw_par) row_half_sweep<L, 1, 0, TAB>(A, d, r, n, I, key, rw_w, rw_y, rw_k, t, accE, nd, bf);
-                else row_half_sweep<L, 1, 1, TAB>(A, d, r, n, I, key, rw_w, rw_y, rw_k, t, accE, nd, bf);
+                if (rw_par) row_half_sweep<L, 1, 0, TAB>(A, d, r, n, I, key, rw_w, rw_y, rw_k, rw_z0, rw_z1, t, accE, nd, bf);
+                else row_half_sweep<L, 1, 1, TAB>(A, d, r, n, I, key, rw_w, rw_y, rw_k, rw_z0, rw_z1, t, accE, nd, bf);
                 // accE + nd = sum of s' (S_u + hgrid) over this thread's 4 L odd
-                // sites, |accE| <= 64 sites x 12 2^21 < 2^31; less hgrid sum s'
+                // sites (half of them if SPLIT), |accE| <= 64 sites x 12 2^21 < 2^31; less hgrid sum s'
                 // leaves sum s' S_u, at most 4 L x 6 2^21 in size per thread:
                 // a group of four threads (L = 8) sums it in int32 (128 sites
                 // x 6 2^21 < 2^31), a row of sixteen (L = 16) in int64.
-                const long long own = (long long)accE + nd - (long long)d.hgrid * (4 * L - 2 * nd);
+                const long long own = (long long)accE + nd - (long long)d.hgrid * (4 * L / (SPLIT ? 2 : 1) - 2 * nd);
                 long long sE;
                 if constexpr (CPW == 4) sE = group_sum_dpp<CPW>((int)own);
                 else sE = group_sum_dpp<CPW>(own);

@@ -907,6 +907,16 @@ def test_results_read_back(torch_cuda, S):
             acc = [a + 1.0 for a in acc]
 
 
+@pytest.mark.parametrize("L, nTs, chunk", [(8, [64], 5), (8, [48, 1], 5), (8, [17, 16, 5], 5), (8, [1], 5),
+                                           (16, [12, 5], 3), (16, [13], 3)])
+def test_row_engine_whole_and_split_columns(torch_cuda, L, nTs, chunk):
+    # few chains: a wave takes half of the z planes where twice the threads fit
+    # a workgroup (48 temperatures at L = 8, 12 at L = 16; a chunk of three keeps
+    # L = 16 on this engine), else whole columns; waves without walkers
+    work = W.make_workload([L] * len(nTs), nTs, (0.4, 1.5), 0.2, measure_every=2, name="row columns")
+    check(work, 7, plan=dict(chunk=chunk))
+
+
 def test_engine_routing(torch_cuda):
     """Which engine each sample runs on, by size, coupling kind, field and tier."""
     from paper_1403_4560_amd import binding
