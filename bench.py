@@ -38,8 +38,8 @@ sys.path.insert(0, ROOT)
 
 METRIC = "spin-flip attempts/ns at L=16 batched vs unbatched; bit-exact spins"
 SWEEPS_PER_STEP = 100
-KERNEL = {"L16_gauss": "row_sweep_kernel<16, 0>", "L8_gauss": "row_sweep_kernel<8, 0>",
-          "L4_gauss": "site_sweep_kernel<4, 0, 0>", "mixed_L6_12": "group/row sweep kernels (4 sizes)",
+KERNEL = {"L16_gauss": "row_sweep_kernel<16, 0, true, false>", "L8_gauss": "row_sweep_kernel<8, 0, true, false>",
+          "L4_gauss": "tiny_sweep_kernel<4, 0, 0>", "mixed_L6_12": "group/row sweep kernels (4 sizes)",
           "L32_pm1": "bits_sweep_kernel<32, 0>"}
 WORKLOAD_TEXT = {
     "L16_gauss": "L16_gauss: L=16, 2048 samples, 24 temperatures geometric in T=[0.4,1.5], 2 replicas, "
@@ -55,9 +55,9 @@ WORKLOAD_TEXT = {
 # Algorithmic work of one Metropolis attempt: the VALU instructions (one lane
 # each) that a minimal gfx950 implementation of the numeric contract issues,
 # per 4-site word (one Philox call), divided by 4.
-#   Philox4x32-10: 10 rounds x (2 32x32->64 multiply-adds + 2 three-input
-#     xors), less the 3 that depend only on (walker, sweep): the counter's
-#     word 2 product and xor of round 0 and the word 0 product of round 1 = 37
+#   Philox4x32-10: rounds 2 to 9 of 2 32x32->64 multiply-adds and 2
+#     three-input xors, and 2 xors; the products of rounds 0 and 1 depend on
+#     the site group alone or on (walker, sweep) alone and are made once  = 34
 #   shifted x-neighbour word (one byte permute)                        =  1
 #   per site, Gaussian couplings: 6 byte-select multiplies and 3 adds for
 #     S_u plus the field's grid part, conversion (1), one fused operation for
@@ -67,20 +67,20 @@ WORKLOAD_TEXT = {
 #   the word's spin-sign mask (1)                                      =  1
 #   flip mask from the gaps' sign bits: 2 byte permutes and 1 and       =  3
 #   exact-path test: least |gap| by 2 three-way minimums, 1 compare     =  3
-#   word tail: new spins (1), flip and down-flip counts (3)            =  4
+#   word tail: new spins (1), flip and down-spin counts (3)            =  4
 #   energy, second half-sweep only: per site sign-extend and xor (2), two
 #     adds per word, down count (2): 12 per word, 6 on average        =  6
-# Gaussian: (37 + 1 + 60 + 1 + 3 + 3 + 4 + 6) / 4 = 28.75.
+# Gaussian: (34 + 1 + 60 + 1 + 3 + 3 + 4 + 6) / 4 = 28.
 # +-1 couplings, one bit per spin, per 32-site word / 32:
-#   Philox 8 x 37 = 296; per site: table address (1), compare and carry-in
+#   Philox 8 x 34 = 272; per site: table address (1), compare and carry-in
 #   (2) = 96; class bytes: 3 spread-table addresses (2 each) and 4 merges per
 #   8 sites = 40; neighbours (x rotations 6, x selects 2, y funnels 2), six
 #   unsatisfied-bond words (6), the count c (8), dE <= 0 (8), class planes
 #   (3), new spins (1), flip and down-flip counts (3), energy on the second
-#   half only (7, 3.5 on average) = 42.5: 474.5 / 32 = 14.83.
-BYTE_PM1_OPS_PER_ATTEMPT = 25.5
-ALG_OPS_PER_ATTEMPT = {"L16_gauss": 28.75, "L8_gauss": 28.75, "mixed_L6_12": 28.75, "L4_gauss": 28.75,
-                       "L32_pm1": 474.5 / 32}
+#   half only (7, 3.5 on average) = 42.5: 450.5 / 32 = 14.08.
+BYTE_PM1_OPS_PER_ATTEMPT = 24.75
+ALG_OPS_PER_ATTEMPT = {"L16_gauss": 28.0, "L8_gauss": 28.0, "mixed_L6_12": 28.0, "L4_gauss": 28.0,
+                       "L32_pm1": 450.5 / 32}
 # Peak: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz = non-packed VALU lane-instructions/s.
 VALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 
@@ -88,8 +88,8 @@ VALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 # (FETCH_SIZE scaled by 2.0 and WRITE_SIZE by 1.0, the factors a plain copy of
 # known size reads), keyed by a fingerprint of the kernel sources they were
 # taken on; reported as null once the kernels change.
-MEASURED_TRAFFIC = {"L16_gauss": ("bbc1b9be80475284", 2.0324e9), "L32_pm1": ("bbc1b9be80475284", 3.5397e9),
-                    "mixed_L6_12": ("bbc1b9be80475284", 0.7665e9), "L8_gauss": ("bbc1b9be80475284", 0.1367e9)}
+MEASURED_TRAFFIC = {"L16_gauss": ("940c1bce14c370c1", 2.0324e9), "L32_pm1": ("940c1bce14c370c1", 3.6097e9),
+                    "mixed_L6_12": ("940c1bce14c370c1", 0.8596e9), "L8_gauss": ("940c1bce14c370c1", 0.1511e9)}
 KERNEL_SOURCES = tuple("paper_1403_4560_amd/csrc/" + f for f in (
     "ea_kernels.hip", "ea_bits.hip", "ea_group.hip", "ea_hbm.hip", "ea_batch.hip", "ea_row.hpp", "ea_group.hpp",
     "ea_groupbits.hpp", "ea_bitops.hpp", "ea_item.hpp", "ea_update.hpp", "ea_device.hpp", "ea_types.hpp"))
@@ -107,23 +107,23 @@ def kernel_fingerprint():
 # Instruction mix of the algorithmic count per attempt, priced at the unit
 # rates measured on the device (ea_measure_peaks): 32x32->64 multiply-adds,
 # hardware exponentials and simple 32-bit operations.
-#   Gaussian, per 4-site word: Philox 18 multiply-adds; 4 exponentials; the
-#     other 93 operations simple (115 in all).
-#   +-1 one bit per spin, per 32-site word: 8 Philox calls = 144 multiply-adds,
-#     330.5 simple (474.5 in all).
-OP_MIX = {"gauss": {"mad": 18 / 4, "exp": 4 / 4, "simple": 93 / 4},
-          "bits": {"mad": 144 / 32, "exp": 0.0, "simple": 330.5 / 32}}
+#   Gaussian, per 4-site word: Philox 16 multiply-adds; 4 exponentials; the
+#     other 92 operations simple (112 in all).
+#   +-1 one bit per spin, per 32-site word: 8 Philox calls = 128 multiply-adds,
+#     322.5 simple (450.5 in all).
+OP_MIX = {"gauss": {"mad": 16 / 4, "exp": 4 / 4, "simple": 92 / 4},
+          "bits": {"mad": 128 / 32, "exp": 0.0, "simple": 322.5 / 32}}
 # LDS bytes one attempt reads and writes by design (the dominant kernel):
 #   row engine, per 4-site word: 7 spin words (28 B), 6 coupling vectors of 4
 #     int32 (96 B) and on half the words one more coupling (2 B on average),
-#     the updated word (4 B): 130 B / 4;
+#     the site group's Philox words (16 B), the updated word (4 B): 146 B / 4;
 #   group engine, per site of a quad (4 attempts): own and 6 neighbour words
 #     (28 B), the neighbour table entry (16 B), 6 couplings (24 B), the store
 #     (4 B): 72 B / 4;
 #   one-bit engine, per 32-site word: own, 4 neighbour words and the x word
 #     (24 B), 6 bond words (24 B), 8 threshold reads per 8 sites, 3 spreading
 #     reads per 8 sites (44 B), the store (4 B): 96 B / 32.
-LDS_BYTES_PER_ATTEMPT = {"row": 130 / 4, "group": 72 / 4, "bits": 96 / 32}
+LDS_BYTES_PER_ATTEMPT = {"row": 146 / 4, "group": 72 / 4, "bits": 96 / 32}
 # LDS read bandwidth: 256 B per clock per CU on gfx950 (twice CDNA3's 128 B; the
 # measured 16-byte read rate, about 245 B per clock per CU, agrees)
 LDS_PEAK_TBPS = 256 * 256 * 2.4e9 / 1e12
@@ -364,7 +364,7 @@ def main():
             progress("unbatched, HBM-resident spread: %.1f attempts/ns" % v2)
             unbatched["spread_form"] = {"value": v2, "samples": sub2.n_samples, "sweeps": SWEEPS_PER_STEP,
                                         "batched_over_spread": value / v2,
-                                        "kernels": "HBM-resident half-sweep, exchange, snapshot per sweep"}
+                                        "kernels": "HBM-resident: a launch per sweep, a workgroup per walker"}
 
     extra = None
     if not args.no_extra and args.workload == "L16_gauss" and args.tier == 0:
