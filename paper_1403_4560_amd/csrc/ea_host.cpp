@@ -778,7 +778,8 @@ SweepFn hbm_fn(int L, int jk, bool unbatched)
 // Few chains: a class of large chains on an LDS engine (one workgroup per
 // chain) that leaves most compute units idle runs the HBM tier's kernels, a
 // workgroup per walker or per four slots, on the same state; chunks of fewer
-// sweeps than SPREAD_MIN_SWEEPS stay (the closing launches are 6 us).  us per
+// sweeps than SPREAD_MIN_SWEEPS stay (the closing launches are 6 us), and of more
+// than SPREAD_MAX_SWEEPS (a captured chunk would hold a node per sweep).  us per
 // sweep, the chain's engine and spread:
 //   L = 16 Gaussian, 24 temperatures, 1 / 16 / 32 / 48 samples 21.9 / 22.0 / 22.6
 //   / 23.0 and 6.5 / 10.1 / 16.7 / 23.4; 5 temperatures, 32 samples 11.7 and 7.7.
@@ -795,7 +796,7 @@ SweepFn hbm_fn(int L, int jk, bool unbatched)
 //   / 10.2 / 10.4, 32 samples 11.0 / 16.0 / 19.4 and 11.2 / 12.8 / 13.3: up to a
 //   workgroup per compute unit, or two at six workgroups a chain.
 // Smaller chains take little more than a launch per sweep.
-constexpr int SPREAD_MIN_SWEEPS = 4;
+constexpr int SPREAD_MIN_SWEEPS = 4, SPREAD_MAX_SWEEPS = 1000;
 
 // Slots of a workgroup of a spread class with ladders of nT_max at most, 0 for
 // other classes.
@@ -1046,7 +1047,7 @@ hipError_t enqueue_chunk(ea_ensemble *e, int K, bool unbatched)
         for (size_t ci = 0; ci < e->classes.size(); ++ci) {
             const auto &c = e->classes[ci];
             if (c.hbm || (batch && e->class_P[ci] > 0)) continue;
-            if (c.spread && K >= SPREAD_MIN_SWEEPS) {
+            if (c.spread && K >= SPREAD_MIN_SWEEPS && K <= SPREAD_MAX_SWEEPS) {
                 st = launch_hbm(e, c.L, K, c.begin, c.count, e->spread_walkers.p, c.wspread, c.spread, false);
                 if (st != hipSuccess) return st;
                 continue;
