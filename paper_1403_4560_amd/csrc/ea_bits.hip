@@ -348,7 +348,7 @@ __device__ __forceinline__ void run_bits_item(const SweepArgs &A, const SampleDe
         }
         __syncthreads();
         if (tid < 64)
-            exchange_slots(A, d, r, n, I, tid, [&](int w) { return (double)EJ[w] - hd * (double)I.M[w]; });
+            exchange_slots<L != 32>(A, d, r, n, I, tid, key, [&](int w) { return (double)EJ[w] - hd * (double)I.M[w]; });
         __syncthreads();
         // Snapshot for the overlap measurement, in slot order: row (y, z) of
         // L bits interleaves the two sublattices' rows.

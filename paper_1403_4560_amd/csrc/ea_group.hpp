@@ -382,7 +382,7 @@ __device__ __forceinline__ void run_group_item(const SweepArgs &A, const SampleD
             }
         }
         __syncthreads();
-        if (tid < 64) exchange_slots(A, d, r, n, I, tid, energy);
+        if (tid < 64) exchange_slots(A, d, r, n, I, tid, key, energy);
         __syncthreads();
         // Snapshot for the overlap measurement, in slot order.
         const int64_t done = n + 1;

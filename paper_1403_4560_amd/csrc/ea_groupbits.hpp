@@ -559,7 +559,7 @@ __device__ __forceinline__ void run_group_bits_item(const SweepArgs &A, const Sa
         else group_bits_sweep<L, 8>(A, d, G, key, s, gs, TPS, valid, tid, I, U, ND);
         __syncthreads();
         if (tid < 64) {
-            const int w = exchange_slots(A, d, r, n, I, tid, energy);
+            const int w = exchange_slots(A, d, r, n, I, tid, key, energy);
             slot_words(n + 1, w);
         }
         const int64_t done = n + 1;

@@ -395,7 +395,9 @@ __global__ void __launch_bounds__(64) hbm_exchange_kernel(SweepArgs A)
     I.sow = sow;
     I.sw = sw;
     I.b64 = b64;
-    const int w0 = t < nT ? was[t] : t, w = exchange_slots(A, d, r, n, I, t, [&](int ww) { return E[ww]; });
+    RoundKeys key;
+    key.init(A.key0, A.key1);
+    const int w0 = t < nT ? was[t] : t, w = exchange_slots(A, d, r, n, I, t, key, [&](int ww) { return E[ww]; });
     __syncthreads();
     if (t < nT) {
         A.was_next[gi + t] = w;

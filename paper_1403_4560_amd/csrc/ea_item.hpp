@@ -222,36 +222,59 @@ __device__ __forceinline__ int pair_other(int v, int lane, bool odd)
 //
 // By one whole wave, lane t for slot t: both lanes of a pair form its decision
 // from the same operands, and the slots' walkers and energies cross between
-// the lanes in registers (two dependent LDS reads, hidden in part behind the
-// random words).  Nothing is kept between sweeps: held in registers, it would
-// be spilled.  Returns the walker now at slot t (t itself from n_T on).
-template <class Energy>
+// the lanes in registers.  A lone wave's chain that the others wait for, so it
+// has no branch before the decision (lanes without a slot or a pair read those
+// at hand) and the random words, with the round keys that the caller holds in
+// vector registers (VKEYS), run while the loads are on the way: 1600 cycles of a
+// sweep before; us a sweep, before and now: L = 6 x 16 temperatures 4.12 and 3.97,
+// L = 8 x 16 4.08 and 3.87, L = 10 x 16 5.67 and 5.47 (few chains), +-1 L = 8 x 56
+// 5.66 and 5.53.  Not for the one-bit engine at L = 32, whose words take 2 % longer
+// with the keys live here (113.6 and 116.1).  Nothing is kept between sweeps: held
+// in registers, it would be spilled.  Returns the walker now at slot t (t itself
+// from n_T on).
+template <bool VKEYS = true, class Energy>
 __device__ __forceinline__ int exchange_slots(const SweepArgs &A, const SampleDev &d, int r, int64_t n, const ItemLds &I,
-                                              int t, Energy energy)
+                                              int t, const RoundKeys &key, Energy energy)
 {
     const int nT = d.n_T;
-    const bool odd = n & 1, slot = t < nT;
+    const bool odd = n & 1;
     const int lo = odd ? (t - 1) | 1 : t & ~1;  // the pair's lower slot
     const bool pair = lo >= 0 && lo + 1 < nT;
-    int w = slot ? I.was[t] : t;
-    const double db = pair ? I.b64[lo] - I.b64[lo + 1] : 0.0;
-    const double E = slot ? energy(w) : 0.0;
-    const u32x4 q = philox4x32_10(0u, (uint32_t)n, (PURPOSE_EXCHANGE << 28) | ((uint32_t)lo << 1) | (uint32_t)r,
-                                  d.sample_id, A.key0, A.key1);
+    const int lc = pair ? lo : 0;
+    int w = I.was[min(t, nT - 1)];
+    const double b0 = I.b64[lc], b1 = I.b64[min(lc + 1, nT - 1)];
+    __builtin_amdgcn_sched_barrier(0);
+    const uint32_t c2 = (PURPOSE_EXCHANGE << 28) | ((uint32_t)lo << 1) | (uint32_t)r;
+    u32x4 q;
+    double E;
+    if constexpr (VKEYS) {
+        PhiloxSlot ps;
+        ps.init((uint32_t)n, c2, A.key0, A.key1);
+        q = ps.start(philox_group(0u, d.sample_id, A.key1));
+#pragma unroll
+        for (int k = 0; k < 3; ++k) q = philox_round(q, key.a[k], key.b[k]);
+        __builtin_amdgcn_sched_barrier(0);
+        E = energy(w);
+#pragma unroll
+        for (int k = 3; k < 8; ++k) q = philox_round(q, key.a[k], key.b[k]);
+    } else {
+        E = energy(w);
+        q = philox4x32_10(0u, (uint32_t)n, c2, d.sample_id, A.key0, A.key1);
+    }
     typedef int int2v __attribute__((ext_vector_type(2)));
     int2v e = __builtin_bit_cast(int2v, E);
     e.x = pair_other(e.x, t, odd);
     e.y = pair_other(e.y, t, odd);
     const double Eo = __builtin_bit_cast(double, e);
     const int wo = pair_other(w, t, odd);
-    const double D = db * (t == lo ? E - Eo : Eo - E);
+    const double D = (b0 - b1) * (t == lo ? E - Eo : Eo - E);
     if (pair && exchange_accept(q.x, q.y, D)) {
         w = wo;
         if (t == lo) atomicAdd(&I.sw[t], 1);
         I.was[t] = w;
         I.sow[w] = t;
     }
-    return w;
+    return t < nT ? w : t;
 }
 
 }  // namespace ea

@@ -381,7 +381,7 @@ __device__ __forceinline__ void run_item(const SweepArgs &A, const SampleDev &d,
                    : (double)I.EJ[w] * unit - hd * (double)I.M[w];
     };
     RoundKeys key;
-    if constexpr (ROW) key.init(A.key0, A.key1);
+    key.init(A.key0, A.key1);
     for (int it = 0; it < A.K; ++it) {
         const int64_t n = n0 + it;
         if constexpr (ROW) {
@@ -439,7 +439,7 @@ __device__ __forceinline__ void run_item(const SweepArgs &A, const SampleDev &d,
             }
             __syncthreads();
         }
-        if (tid < 64) exchange_slots(A, d, r, n, I, tid, energy);
+        if (tid < 64) exchange_slots(A, d, r, n, I, tid, key, energy);
         __syncthreads();
         // Snapshot for the overlap measurement, in slot order.
         const int64_t done = n + 1;
