@@ -204,10 +204,10 @@ __device__ __forceinline__ void add_totals(uint32_t (&fl)[PF], uint32_t (&nd)[PF
 
 // The spreading tables: entry v of table k holds, in bytes 0 .. 7, 4 << k for
 // the set bits of v.  One copy per workgroup, at an LDS address known to the
-// compiler.
+// compiler (the host counts them beside the frames: SPREAD_BYTES).
 __device__ __forceinline__ uint2 *spread_tables()
 {
-    __shared__ uint2 tab[3 * 256];
+    __shared__ uint2 tab[SPREAD_BYTES / sizeof(uint2)];
     return tab;
 }
 

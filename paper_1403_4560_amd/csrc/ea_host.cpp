@@ -1105,7 +1105,7 @@ ea_status plan_samples(const ea_desc *d, size_t lds_max, std::vector<SampleHost>
         // spreads them over more lanes
         h.group = !h.hbm && !h.bits && d->tier != EA_TIER_SITE && !row_engine(h.L, h.nT, jk) &&
                   h.L <= LDS_MAX_L && group_items(h.L, h.nT) >= 64 &&
-                  group_lds(h.L, h.nT, jk) <= lds_max;
+                  group_lds(h.L, h.nT, jk) <= frames_lds_max(jk, lds_max);
         if (h.hbm && !hbm_size(h.L))
             return fail(EA_EUNSUPPORTED,
                         "sample %d: L=%d with %d temperatures does not fit LDS (%zu of %zu B) and the HBM tier "
@@ -1301,8 +1301,8 @@ ea_status run_finalize(ea_ensemble *e, const int32_t *sel, int32_t n, double *ou
 }
 
 // Autotuner support.  Candidate team counts for batchable class ci: P in
-// {1, 2, 4, 8} with teams of at least the class's threads and P item frames
-// within one workgroup's LDS.
+// {1, 2, 4, 8} with teams of at least the class's threads and P item frames,
+// beside the kernel's static LDS, within one workgroup's LDS.
 std::vector<int> batch_candidates(const ea_ensemble *e, size_t ci)
 {
     std::vector<int> out;
@@ -1319,9 +1319,8 @@ std::vector<int> batch_candidates(const ea_ensemble *e, size_t ci)
         const int items = group_items(c.L, nTmax);
         min_threads = std::max(min_threads, (items / 16 + 63) / 64 * 64);
     }
-    const size_t ldsc = (c.lds + 15) & ~(size_t)15;
     for (int P = 1; P <= 8; P *= 2)
-        if (BATCH_THREADS / P >= min_threads && P * ldsc <= e->lds_max) out.push_back(P);
+        if (batch_teams_fit(P, min_threads, c.lds, e->jkind, e->lds_max)) out.push_back(P);
     return out;
 }
 
@@ -1529,8 +1528,9 @@ ea_status ea_create_ensemble(const ea_desc *d, void *hip_stream, ea_ensemble **o
             for (int v = 0; v < 2; ++v) {
                 for (const bool split : {false, true}) {
                     SweepFn fn = sweep_fn(c.L, e->jkind, c.row, c.row_table, split, c.bits, c.group, c.tiny, v == 1);
+                    const size_t most = c.group ? frames_lds_max(e->jkind, lds_max) : lds_max;
                     if (fn) (void)hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                      (int)lds_max);
+                                                      (int)most);
                 }
             }
         }
@@ -1542,16 +1542,14 @@ ea_status ea_create_ensemble(const ea_desc *d, void *hip_stream, ea_ensemble **o
         for (const auto &c : e->classes) {
             const int need = batch_need(c);
             int P = need > 0 ? default_P(need) : 0;
-            const size_t ldsc = (c.lds + 15) & ~(size_t)15;
-            while (P > 1 && P * ldsc > lds_max) P /= 2;
-            if (P == 1 && ldsc > lds_max) P = 0;
+            while (P > 0 && !batch_teams_fit(P, 0, c.lds, e->jkind, lds_max)) P /= 2;
             e->class_P.push_back(P);
             nb += P > 0;
         }
         if (nb < 2) e->plan.batch = 0;  // one class: its own launch is the same shape
         for (int v = 0; v < 2; ++v)
             (void)hipFuncSetAttribute(v ? (const void *)batch_sweep_kernel<1> : (const void *)batch_sweep_kernel<0>,
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_max);
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)frames_lds_max(v, lds_max));
         int cus = 0, ldscu = 0;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, e->device) != hipSuccess) cus = 1;
         if (hipDeviceGetAttribute(&ldscu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, e->device) !=

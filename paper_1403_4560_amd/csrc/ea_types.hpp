@@ -132,6 +132,24 @@ struct MeasureArgs {
 enum { BATCH_SITE = 0, BATCH_ROW = 1, BATCH_GROUP = 2 };
 constexpr int BATCH_THREADS = 512;
 
+// Bytes of LDS that the +-1 kernels of the group engine and of the batch launch
+// hold beside the frames of their items (spread_tables in ea_groupbits.hpp; one
+// copy per workgroup).
+constexpr size_t SPREAD_BYTES = 3 * 256 * 8;
+
+// The frames that such a workgroup may hold: what its static LDS leaves.
+__host__ __device__ constexpr size_t frames_lds_max(int jkind, size_t lds_max)
+{
+    return jkind == 1 ? lds_max - SPREAD_BYTES : lds_max;
+}
+
+// Whether P teams of a batch workgroup can run items that need min_threads
+// threads and frames of lds bytes each.
+__host__ __device__ constexpr bool batch_teams_fit(int P, int min_threads, size_t lds, int jkind, size_t lds_max)
+{
+    return BATCH_THREADS / P >= min_threads && P * ((lds + 15) & ~(size_t)15) <= frames_lds_max(jkind, lds_max);
+}
+
 struct BatchUnit {
     int32_t kind;   // engine << 8 | L
     int32_t first;  // index of the unit's first item in the item list

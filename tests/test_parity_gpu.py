@@ -948,3 +948,39 @@ def test_measure_peaks_runs(torch_cuda):
     for k in ("valu_xor_ops", "valu_mad_u64_ops", "valu_mul_hi_ops", "valu_exp_ops"):
         assert 0 < r[k] < 2 * 256 * 64 * 2.4e9
     assert 0 < r["lds_read_bytes"] and 0 < r["hbm_copy_bytes"] < 2e13
+
+
+@pytest.mark.parametrize("nT", [21, 24])
+def test_batch_plan_counts_the_static_lds(torch_cuda, monkeypatch, nT):
+    """+-1 couplings at L = 8 on the group engine: eight frames fit a workgroup's
+    LDS only without the kernel's own spreading tables, so eight teams are
+    refused, the handle stays usable, the autotuner does not try them, and every
+    plan that is accepted equals the oracle."""
+    from paper_1403_4560_amd import binding
+    monkeypatch.delenv("EA_TUNE_CACHE", raising=False)
+    work = W.make_workload([6, 8, 8, 6], [16, nT, nT, 9], None, [0.1, 0.4, -0.3, 0.2], jkind=W.J_PM1, measure_every=2,
+                           beta_range=(0.1, 1.8), name="static LDS")
+    sweeps = 9
+    ref = O.OracleEnsemble(work).run(sweeps)
+    with binding.Ensemble(work, tier=binding.TIER_BYTES) as ens:
+        assert ens.engines() == ["group"] * 4 and ens.get_plan().batch == 1
+        plan = ens.batch_plan()
+        at = [int(x) for x in plan["L"]].index(8)
+        for P in (8, 4, 2, 1):
+            teams = list(plan["teams"])
+            teams[at] = P
+            if P == 8:
+                with pytest.raises(binding.EAError) as err:
+                    ens.set_batch_plan(teams)
+                assert err.value.status == -1
+            else:
+                print("case: static LDS n_T=%d teams %s" % (nT, teams), flush=True)
+                ens.set_batch_plan(teams)
+                ens.sweep_pt(1)
+        ens.autotune(trial_sweeps=2)
+        ens.set_plan(chunk=4)
+        ens.sweep_pt(sweeps - 3)
+        st = ens.read_state()
+        ms = ens.measure()
+        assert ens.check_energies() == 0
+    assert_same(work, st, ms, ref)
