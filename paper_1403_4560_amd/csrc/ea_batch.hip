@@ -58,7 +58,7 @@ __global__ void __launch_bounds__(BATCH_THREADS, 4) batch_sweep_kernel(SweepArgs
     const BatchUnit U = B.units[u];
     const int T = BATCH_THREADS / U.P;
     const int team = __builtin_amdgcn_readfirstlane((int)threadIdx.x / T);
-    const Team tm{(int)threadIdx.x - team * T, T, team >= U.count};
+    const Team tm = make_team(team, T, team >= U.count);
     const int code = A.items[U.first + (team < U.count ? team : 0)];
     batch_dispatch<JK>(A, U.kind, sample_of_item(A.samples, code >> 1), code & 1, smem + (size_t)team * U.lds, tm);
 }

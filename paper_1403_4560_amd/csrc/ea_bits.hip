@@ -270,7 +270,7 @@ __device__ __forceinline__ void run_bits_item(const SweepArgs &A, const SampleDe
         SB[i] = pack4(v0.x) | pack4(v0.y) << 4 | pack4(v0.z) << 8 | pack4(v0.w) << 12 | pack4(v1.x) << 16 |
                 pack4(v1.y) << 20 | pack4(v1.z) << 24 | pack4(v1.w) << 28;
     }
-    block_copy(JB, A.Jbits + d.jb_off, (size_t)12 * G * 4);
+    block_copy(JB, A.Jbits + d.jb_off, (size_t)12 * G * 4, T, tid);
     // k_s: smallest c with dE <= 0 for s = +1 (a = 1, b = 6 - c) and s = -1 (a = 0, b = c); 7 if none
     int k0 = 7, k1 = 7;
     for (int c = 6; c >= 0; --c) {

@@ -10,12 +10,10 @@ template <int L, int JK, int VAR>
 __global__ void __launch_bounds__(GROUP_MAX_THREADS, 4) group_sweep_kernel(SweepArgs A)
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    for (int item = blockIdx.x; item < A.n_items; item += gridDim.x) {
-        const int code = A.items[item];
-        const SampleDev d = sample_of_item(A.samples, code >> 1);
-        if constexpr (JK == 0) run_group_item<L>(A, d, code & 1, smem);
-        else run_group_bits_item<L>(A, d, code & 1, smem, whole_block());
-    }
+    const int code = A.items[blockIdx.x];
+    const SampleDev d = sample_of_item(A.samples, code >> 1);
+    if constexpr (JK == 0) run_group_item<L>(A, d, code & 1, smem);
+    else run_group_bits_item<L>(A, d, code & 1, smem, whole_block());
 }
 
 #define EA_GROUP(Lv)                                                 \

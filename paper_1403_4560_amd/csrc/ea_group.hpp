@@ -163,7 +163,7 @@ __device__ __forceinline__ void run_group_item(const SweepArgs &A, const SampleD
 {
     constexpr int N = L * L * L, HALF = N / 2, G4 = HALF / 4;
     const int nT = d.n_T, NQ = (nT + 3) / 4;
-    const int T = tm.T, tid = tm.tid;
+    const int T = tm.T, tid = tm.tid();
     const GroupLdsOff o = group_lds_offsets(L, nT);
     uint32_t *SG = (uint32_t *)(smem + o.spins);
     int *Jl = (int *)(smem + o.J);
@@ -265,7 +265,7 @@ __device__ __forceinline__ void run_group_item(const SweepArgs &A, const SampleD
     for (int it = 0; it < A.K; ++it) {
         const int64_t n = n0 + it;
 #pragma unroll 1
-        for (int i = tid; i < nT; i += T) {
+        for (int i = tm.tid(); i < nT; i += T) {
             I.dM[i] = 0;
             I.dEJ[i] = -(long long)hg * HALF;
         }
@@ -332,8 +332,7 @@ __device__ __forceinline__ void run_group_item(const SweepArgs &A, const SampleD
                 e[i] += row_rotate<4>(e[i]);
                 e[i] += row_rotate<8>(e[i]);
             }
-            int tl = tid;
-            asm volatile("" : "+v"(tl));
+            const int tl = tm.tid();
             const int sel = (tl >> 2) & 3, w = 4 * (tl & 3) + sel, sh = 8 * sel;
             const int fl = (int)(((uint32_t)cf >> sh) & 0xFFu);
             const int nd0 = (int)(((uint32_t)cd >> sh) & 0xFFu);
@@ -352,10 +351,7 @@ __device__ __forceinline__ void run_group_item(const SweepArgs &A, const SampleD
             for (int k = 0; k < 6; ++k) c[k] = (uint32_t)row_residue_sum((int)c[k], NQ);
             long long e[4];
             for (int i = 0; i < 4; ++i) e[i] = row_residue_sum((long long)ty.accE[i], NQ);
-            // (lane roles from an opaque copy of the thread index: derived per
-            // sweep, not hoisted out of the item loop and spilled)
-            int tl = tid;
-            asm volatile("" : "+v"(tl));
+            const int tl = tm.tid();
             // (NQ = 1, 2, 4: j / NQ = j >> (NQ >> 1))
             const int j = tl & 15, sel = (j >> (NQ >> 1)) & 3, w = 4 * (tl & (NQ - 1)) + sel, sh = 16 * (sel >> 1);
             const bool odd = sel & 1;
@@ -382,7 +378,7 @@ __device__ __forceinline__ void run_group_item(const SweepArgs &A, const SampleD
             }
         }
         __syncthreads();
-        if (tid < 64) exchange_slots(A, d, r, n, I, tid, key, energy);
+        if (tm.wave == 0) exchange_slots(A, d, r, n, I, tm.tid(), key, energy);
         __syncthreads();
         // Snapshot for the overlap measurement, in slot order.
         const int64_t done = n + 1;
@@ -395,7 +391,8 @@ __device__ __forceinline__ void run_group_item(const SweepArgs &A, const SampleD
             // hi: x >= 8).  Site x of row (y, z) is sublattice site
             // row L/2 + x/2 of parity (x + y + z) & 1.
             constexpr int HL = L / 2, PS = HALF + 1;
-            for (int i = tid; !tm.ghost && i < NQ * L * L; i += T) {
+            const int ti = tm.tid();
+            for (int i = ti; !tm.ghost && i < NQ * L * L; i += T) {
                 const int q = i / (L * L), row = i - q * (L * L);
                 const int e = ((row % L) + row / L) & 1;  // parity of the even x
                 const uint32_t *ev = SG + (e * NQ + q) * PS + row * HL;
@@ -413,7 +410,7 @@ __device__ __forceinline__ void run_group_item(const SweepArgs &A, const SampleD
                     if (w < nT) dst[I.sow[w] * L * L + row] = ((lo >> (8 * b)) & 0xFFu) | (((hi >> (8 * b)) & 0xFFu) << 8);
                 }
             }
-            for (int t = tid; !tm.ghost && t < nT; t += T) {
+            for (int t = ti; !tm.ghost && t < nT; t += T) {
                 const int w = I.was[t];
                 A.frameE[f * 2 * A.total_slots + gi + t] = energy(w);
             }
@@ -422,7 +419,8 @@ __device__ __forceinline__ void run_group_item(const SweepArgs &A, const SampleD
         }
     }
     __syncthreads();
-    for (int j = tid; !tm.ghost && j < 2 * HALF * NQ; j += T) {
+    const int te = tm.tid();
+    for (int j = te; !tm.ghost && j < 2 * HALF * NQ; j += T) {
         const int q2 = j % NQ, ph = j / NQ;
         const uint32_t wv = SG[gidx<L>(ph / HALF, ph % HALF, q2, NQ)];
         for (int i = 0; i < 4; ++i) {
@@ -430,7 +428,7 @@ __device__ __forceinline__ void run_group_item(const SweepArgs &A, const SampleD
             if (w < nT) A.spins[sbase + (size_t)w * N + ph] = (int8_t)((wv >> (8 * i)) & 0xFFu);
         }
     }
-    for (int i = tid; !tm.ghost && i < nT; i += T) {
+    for (int i = te; !tm.ghost && i < nT; i += T) {
         A.was[gi + i] = I.was[i];
         A.EJ[gi + i] = -I.dEJ[i];
         A.M[gi + i] = N - 2 * I.dM[i];

@@ -155,9 +155,6 @@ __device__ __forceinline__ void add_totals(uint32_t (&fl)[PF], uint32_t (&nd)[PF
                                            const int32_t *sow, int32_t *flips, int32_t *ND, int32_t *U)
 {
     static_assert(PU == PF + 1, "digits of the folded sums");
-    // (from an opaque copy of the lane: formed here each sweep, not held across
-    // the updates, which spills)
-    asm volatile("" : "+v"(lane));
     RowTranspose tr;
     tr.init(lane);
     const int i = WS > 8 ? lane & 15 : lane & 7, w = s * WS + i;
@@ -320,13 +317,8 @@ __device__ __forceinline__ void group_bits_item(const SweepArgs &A, const Sample
     const uint4 pg = philox_group((uint32_t)g4, d.sample_id, A.key1);
     uint32_t pw = G.pw + P * G.pws + 16 * (s * G.WS);
     const uint32_t sp = lds_addr(spread_tables());
-    uint32_t e[4][3];
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-#pragma unroll
-        for (int b = 0; b < 3; ++b) e[k][b] = E[k][b];
 #pragma unroll 1
-    for (int left = G.WS; left > 0; left -= 8, pw += 128) {
+    for (int at = 0; at < G.WS; at += 8, pw += 128) {
         uint4 w[4];
         uint32_t Ql[4], Qh[4];
         load_walkers(pw, w);
@@ -334,19 +326,15 @@ __device__ __forceinline__ void group_bits_item(const SweepArgs &A, const Sample
 #pragma unroll
         for (int k = 0; k < 4; ++k)
 #pragma unroll
-            for (int b = 0; b < 3; ++b) t[k][b] = lds_load2(sp + 2048 * b + 8 * (e[k][b] & 0xFFu));
+            for (int b = 0; b < 3; ++b) t[k][b] = lds_load2(sp + 2048 * b + 8 * __builtin_amdgcn_ubfe(E[k][b], at, 8));
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             Ql[k] = xor3(t[k][0].x, t[k][1].x, t[k][2].x);
             Qh[k] = xor3(t[k][0].y, t[k][1].y, t[k][2].y);
         }
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-#pragma unroll
-            for (int b = 0; b < 3; ++b) e[k][b] >>= 8;
         group_bits_quad(w, Ql, pg, key, F);
-        if (left > 4) {
+        if (at + 4 < G.WS) {
             load_walkers(pw + 64, w);
             group_bits_quad(w, Qh, pg, key, F);
         }
@@ -372,8 +360,8 @@ __device__ __forceinline__ void group_bits_item(const SweepArgs &A, const Sample
 // half-sweep) and the walkers' totals of it.
 template <int L, int REP>
 __device__ __forceinline__ void group_bits_sweep(const SweepArgs &A, const SampleDev &d, const GroupBitsItem &G,
-                                                 const RoundKeys &key, int s, int gs, int TPS, uint32_t valid,
-                                                 int tid, const ItemLds &I, int32_t *U, int32_t *ND)
+                                                 const RoundKeys &key, int s, int TPS, const Team &tm,
+                                                 const ItemLds &I, int32_t *U, int32_t *ND)
 {
     constexpr int G4 = L * L * L / 8;
     // sums of 8 REP flips and down spins and of 24 REP unsatisfied bonds
@@ -382,6 +370,17 @@ __device__ __forceinline__ void group_bits_sweep(const SweepArgs &A, const Sampl
     uint32_t fl[PF] = {}, nd[PF] = {}, un[PU] = {};
     const bool on = s < G.NS;
     uint32_t F[4], Sn[4], V[4][3], n[3];
+    // the thread's first site group and the walkers of its set, formed here in
+    // either half-sweep (held across the sweep, they spill)
+    int gs;
+    uint32_t valid;
+    const auto share = [&] {
+        asm volatile("" : "+v"(s));
+        gs = tm.tid() - s * TPS;
+        const int bits = on ? min(G.WS, d.n_T - s * G.WS) : 0;
+        valid = bits >= 32 ? ~0u : (1u << bits) - 1u;
+    };
+    share();
     if (on) {
 #pragma unroll 1
         for (int g4 = gs; g4 < G4; g4 += TPS) {
@@ -401,6 +400,7 @@ __device__ __forceinline__ void group_bits_sweep(const SweepArgs &A, const Sampl
         }
     }
     __syncthreads();
+    share();
     if (on) {
 #pragma unroll 1
         for (int g4 = gs; g4 < G4; g4 += TPS) {
@@ -423,7 +423,7 @@ __device__ __forceinline__ void group_bits_sweep(const SweepArgs &A, const Sampl
         }
     }
     // (TPS is 16, 32 or whole waves, so a row holds one set; idle lanes hold zeros)
-    add_totals(fl, nd, un, tid & 63, TPS, G.WS, s, d.n_T, I.sow, I.fl, ND, U);
+    add_totals(fl, nd, un, tm.tid() & 63, TPS, G.WS, s, d.n_T, I.sow, I.fl, ND, U);
 }
 
 template <int L>
@@ -432,7 +432,7 @@ __device__ __forceinline__ void run_group_bits_item(const SweepArgs &A, const Sa
 {
     constexpr int N = L * L * L, HALF = N / 2, G4 = HALF / 4, HL = L / 2;
     const int nT = d.n_T;
-    const int T = tm.T, tid = tm.tid;
+    const int T = tm.T, tid = tm.tid();
     const GroupBitsLdsOff o = group_bits_lds_offsets(L, nT);
     const GroupSets gsz = group_sets(L, nT, T);
     const int NS = gsz.NS, WS = gsz.WS;
@@ -530,8 +530,9 @@ __device__ __forceinline__ void run_group_bits_item(const SweepArgs &A, const Sa
     // (from n_T on: the padding of the last set, whose bits are never used;
     // whole sets never reach past 64 walkers)
     const auto slot_words = [&](int64_t n, int w) {
-        const uint32_t th = lds_addr(TH + 8 * min(tid, nT - 1));
-        const uint32_t c2 = (PURPOSE_METROPOLIS << 28) | ((uint32_t)tid << 1) | (uint32_t)r;
+        const int t = tm.tid();
+        const uint32_t th = lds_addr(TH + 8 * min(t, nT - 1));
+        const uint32_t c2 = (PURPOSE_METROPOLIS << 28) | ((uint32_t)t << 1) | (uint32_t)r;
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
             PhiloxSlot ps;
@@ -539,13 +540,11 @@ __device__ __forceinline__ void run_group_bits_item(const SweepArgs &A, const Sa
             PW[p * MAX_T + w] = make_uint4(ps.x, ps.y, ps.z, th);
         }
     };
-    if (tid < 64) slot_words(n0, tid < nT ? I.was[tid] : tid);
+    if (tm.wave == 0) slot_words(n0, tid < nT ? I.was[tid] : tid);
     __syncthreads();
 
     const int TPS = gsz.TPS;
-    const int s = tid / TPS, gs = tid - s * TPS;
-    const uint32_t bits = s < NS ? (uint32_t)min(WS, nT - s * WS) : 0u;
-    const uint32_t valid = bits >= 32 ? ~0u : (1u << bits) - 1u;
+    const int s = tid / TPS;
     RoundKeys key;
     key.init(A.key0, A.key1);
     const double hd = (double)d.h32;
@@ -555,18 +554,19 @@ __device__ __forceinline__ void run_group_bits_item(const SweepArgs &A, const Sa
     const auto energy = [&](int w) { return (double)(2 * U[w] - 3 * N) - hd * (double)(N - 2 * ND[w]); };
     for (int it = 0; it < A.K; ++it) {
         const int64_t n = n0 + it;
-        if (TPS >= G4) group_bits_sweep<L, 1>(A, d, G, key, s, gs, TPS, valid, tid, I, U, ND);
-        else group_bits_sweep<L, 8>(A, d, G, key, s, gs, TPS, valid, tid, I, U, ND);
+        if (TPS >= G4) group_bits_sweep<L, 1>(A, d, G, key, s, TPS, tm, I, U, ND);
+        else group_bits_sweep<L, 8>(A, d, G, key, s, TPS, tm, I, U, ND);
         __syncthreads();
-        if (tid < 64) {
-            const int w = exchange_slots(A, d, r, n, I, tid, key, energy);
+        if (tm.wave == 0) {
+            const int w = exchange_slots(A, d, r, n, I, tm.tid(), key, energy);
             slot_words(n + 1, w);
         }
         const int64_t done = n + 1;
         const bool meas = done == next_meas, last = it + 1 == A.K;
         if (!meas && !last) {
             // (U and ND: read by the exchange above, cleared by the same wave)
-            if (tid < 64 && tid < nT) U[tid] = ND[tid] = 0;
+            const int ti = tm.tid();
+            if (ti < 64 && ti < nT) U[ti] = ND[ti] = 0;
             __syncthreads();
             continue;
         }
@@ -575,7 +575,8 @@ __device__ __forceinline__ void run_group_bits_item(const SweepArgs &A, const Sa
             // snapshot in slot order: one (set, row) per step
             next_meas += A.measure_every;
             uint32_t *dst = A.frames + f * A.frame_words + d.frame_off + (size_t)r * nT * L * L;
-            for (int i = tid; !tm.ghost && i < NS * L * L; i += T) {
+            const int ti = tm.tid();
+            for (int i = ti; !tm.ghost && i < NS * L * L; i += T) {
                 const int ss = i / (L * L), row = i - ss * (L * L);
                 const int e = ((row % L) + row / L) & 1;  // parity of the even x
                 uint32_t w[L];
@@ -594,16 +595,18 @@ __device__ __forceinline__ void run_group_bits_item(const SweepArgs &A, const Sa
                     dst[I.sow[ss * WS + j] * L * L + row] = b >> (32 - L);
                 }
             }
-            for (int t = tid; !tm.ghost && t < nT; t += T) A.frameE[f * 2 * A.total_slots + gi + t] = energy(I.was[t]);
+            for (int t = ti; !tm.ghost && t < nT; t += T) A.frameE[f * 2 * A.total_slots + gi + t] = energy(I.was[t]);
             ++f;
             __syncthreads();  // the next sweep changes the spins read here
         }
         if (!last) {
-            for (int w = tid; w < nT; w += T) U[w] = ND[w] = 0;
+            const int ti = tm.tid();
+            for (int w = ti; w < nT; w += T) U[w] = ND[w] = 0;
             // (tallied again only after the next half-sweep's barrier)
         }
     }
-    for (int i = tid; !tm.ghost && i < 2 * NS * G4; i += T) {
+    const int te = tm.tid();
+    for (int i = te; !tm.ghost && i < 2 * NS * G4; i += T) {
         const int g = i % G4, ps = i / G4, p = ps / NS, ss = ps - p * NS;
         uint32_t w[4];
         for (int k = 0; k < 4; ++k) w[k] = SW[ps * HALF + k * G4 + g];
@@ -613,7 +616,7 @@ __device__ __forceinline__ void run_group_bits_item(const SweepArgs &A, const Sa
             *(uint32_t *)(A.spins + sbase + (size_t)(ss * WS + j) * N + p * HALF + 4 * g) = v;
         }
     }
-    for (int i = tid; !tm.ghost && i < nT; i += T) {
+    for (int i = te; !tm.ghost && i < nT; i += T) {
         A.was[gi + i] = I.was[i];
         A.EJ[gi + i] = 2 * U[i] - 3 * N;
         A.M[gi + i] = N - 2 * ND[i];

@@ -14,19 +14,37 @@ namespace ea {
 // computes like a real one on a copy of a real item but writes nothing to
 // global memory (it fills a batch unit that has fewer items than teams).
 struct Team {
-    int tid;     // thread index within the team
     int T;       // threads in the team
     bool ghost;
+    int wave;    // index within the team of this wave's first thread
+
+    // This thread's index within the team, formed where it is called: what
+    // follows from it is then not hoisted out of a sweep loop and kept across
+    // it, in the end in scratch memory.  A kernel that uses any pays for it at
+    // every launch and wave: one sweep a call at two chains a compute unit took
+    // 40.2 us with 80 bytes and takes 32.7 without (L = 12 x 8 temperatures),
+    // +-1 couplings at L = 10 x 56 60.8 and 54.1 (200 bytes).
+    __device__ __forceinline__ int tid() const
+    {
+        int lane;
+        asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
+        return wave + lane;
+    }
 };
 
-__device__ __forceinline__ Team whole_block() { return Team{(int)threadIdx.x, (int)blockDim.x, false}; }
-
-// Team-cooperative byte copy, 16 bytes at a time when both ends allow it;
-// four copies in flight per thread.
-__device__ __forceinline__ void block_copy(void *__restrict__ dst, const void *__restrict__ src, size_t bytes,
-                                           const Team tm = whole_block())
+// Team index of a workgroup split into teams of T threads (whole waves).
+__device__ __forceinline__ Team make_team(int team, int T, bool ghost)
 {
-    const int T = tm.T, tid = tm.tid;
+    return Team{T, ghost, (__builtin_amdgcn_readfirstlane((int)threadIdx.x) & ~63) - team * T};
+}
+
+__device__ __forceinline__ Team whole_block() { return make_team(0, (int)blockDim.x, false); }
+
+// Byte copy by T threads, 16 bytes at a time when both ends allow it; four
+// copies in flight per thread.
+__device__ __forceinline__ void block_copy(void *__restrict__ dst, const void *__restrict__ src, size_t bytes,
+                                           int T, int tid)
+{
     if ((((uintptr_t)dst | (uintptr_t)src | bytes) & 15) == 0) {
         int4 *__restrict__ d = (int4 *)dst;
         const int4 *__restrict__ s = (const int4 *)src;
@@ -52,10 +70,10 @@ __device__ __forceinline__ void block_copy(void *__restrict__ dst, const void *_
 __device__ __forceinline__ void copy_walkers(int8_t *lds, size_t lstride, int8_t *glob, int count, size_t bytes,
                                              bool to_lds, const Team tm = whole_block())
 {
-    const int T = tm.T, tid = tm.tid;
-    const size_t per = bytes / 8, total = per * (size_t)count;
-    for (size_t i = tid; i < total; i += T) {
-        const size_t w = i / per, j = i - w * per;
+    const int T = tm.T, tid = tm.tid();
+    const int per = (int)bytes / 8, total = per * count;
+    for (int i = tid; i < total; i += T) {
+        const int w = i / per, j = i - w * per;
         uint2 *l = (uint2 *)(lds + w * lstride) + j;
         uint2 *g = (uint2 *)(glob + w * bytes) + j;
         if (to_lds) *l = *g;

@@ -43,10 +43,8 @@ template <int L, int JK, int VAR>
 __global__ void __launch_bounds__(1024) site_sweep_kernel(SweepArgs A)
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    for (int item = blockIdx.x; item < A.n_items; item += gridDim.x) {
-        const int code = A.items[item];
-        run_item<L, JK, false>(A, A.samples[code >> 1], code & 1, smem);
-    }
+    const int code = A.items[blockIdx.x];
+    run_item<L, JK, false>(A, A.samples[code >> 1], code & 1, smem);
 }
 
 // Tiny chains (L = 2 or 4, at most 1024 odd sites over the ladder): a lane per
@@ -267,10 +265,8 @@ template <int L, int VAR, bool TAB, bool SPLIT>
 __global__ void __launch_bounds__(ROW_MAX_THREADS, L == 8 ? 4 : 1) row_sweep_kernel(SweepArgs A)
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    for (int item = blockIdx.x; item < A.n_items; item += gridDim.x) {
-        const int code = A.items[item];
-        run_item<L, 0, true, TAB, SPLIT>(A, sample_of_item(A.samples, code >> 1), code & 1, smem);
-    }
+    const int code = A.items[blockIdx.x];
+    run_item<L, 0, true, TAB, SPLIT>(A, sample_of_item(A.samples, code >> 1), code & 1, smem);
 }
 
 #define EA_SITE(Lv)                                               \

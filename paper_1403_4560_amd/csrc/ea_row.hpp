@@ -26,7 +26,7 @@ __device__ __forceinline__ void site_half_sweep(const SweepArgs &A, const Sample
 {
     constexpr int N = L * L * L, HALF = N / 2, G = HALF / 4, HL = L / 2;
     const int nT = d.n_T;
-    const int T = tm.T, tid = tm.tid;
+    const int T = tm.T, tid = tm.tid();
     const int total = nT * G;
     const uint32_t c1 = (uint32_t)(2 * n + p);
     const uint32_t c2base = (PURPOSE_METROPOLIS << 28) | (uint32_t)r;
@@ -303,7 +303,7 @@ __device__ __forceinline__ void run_item(const SweepArgs &A, const SampleDev &d,
 {
     constexpr int N = L * L * L;
     const int nT = d.n_T;
-    const int T = tm.T, tid = tm.tid;
+    const int T = tm.T, tid = tm.tid();
     const ItemLds I = item_lds(smem, L, nT, JK);
 
     const size_t sbase = (size_t)d.spin_off + (size_t)r * nT * N;
@@ -327,7 +327,7 @@ __device__ __forceinline__ void run_item(const SweepArgs &A, const SampleDev &d,
             for (int g = tid; g < HALF / 4; g += T) I.ph[g] = philox_group((uint32_t)g, d.sample_id, A.key1);
     } else {
         block_copy(I.J, (const char *)A.J + (size_t)d.J_off * (JK == 0 ? 4 : 1),
-                   (size_t)3 * N * (JK == 0 ? 4 : 1), tm);
+                   (size_t)3 * N * (JK == 0 ? 4 : 1), T, tid);
     }
     for (int i = tid; i < nT; i += T) {
         I.was[i] = A.was[gi + i];
@@ -350,10 +350,7 @@ __device__ __forceinline__ void run_item(const SweepArgs &A, const SampleDev &d,
     // row engine: this thread's walker and column (see RowMap)
     constexpr int CPW = RowMap<(L >= 8 ? L : 8)>::CPW, WPW = RowMap<(L >= 8 ? L : 8)>::WPW;
     constexpr int WPR = L / 8 > 0 ? L / 8 : 1;
-    // (from an opaque copy of the thread index: derived here, after the loads,
-    // not hoisted to the kernel's start and kept across them, which spills)
-    int tid_r = tid;
-    asm volatile("" : "+v"(tid_r));
+    const int tid_r = tm.tid();
     const int rw_wave = tid_r >> 6, rw_lane = tid_r & 63;
     const int rw_par = __builtin_amdgcn_readfirstlane(rw_wave & 1);
     const int rw_rem = rw_lane % CPW;
@@ -364,12 +361,7 @@ __device__ __forceinline__ void run_item(const SweepArgs &A, const SampleDev &d,
     const double unit = JK == 0 ? 0x1p-18 : 1.0;
     const double hd = (double)d.h32;
     const int64_t n0 = A.state[0];
-    // (the period from an opaque copy: the division's set-up is then made
-    // here, per item, rather than hoisted out of the item loop of a
-    // persistent kernel and held in registers across it, which spills)
-    int32_t every = A.measure_every;
-    asm volatile("" : "+s"(every));
-    int64_t next_meas = next_measurement(n0, every, A.measure_start);
+    int64_t next_meas = next_measurement(n0, A.measure_every, A.measure_start);
     int64_t f = 0;  // frame of the next measurement within this chunk
     // Energy of walker w after a sweep.  Row engine: the second half-sweep's
     // tallies leave minus E_J in dEJ and the number of down spins in dM; both
@@ -386,7 +378,7 @@ __device__ __forceinline__ void run_item(const SweepArgs &A, const SampleDev &d,
         const int64_t n = n0 + it;
         if constexpr (ROW) {
 #pragma unroll 1
-            for (int i = tid; i < nT; i += T) {
+            for (int i = tm.tid(); i < nT; i += T) {
                 I.dM[i] = 0;
                 I.dEJ[i] = 0;
             }
@@ -417,10 +409,12 @@ __device__ __forceinline__ void run_item(const SweepArgs &A, const SampleDev &d,
                 // flips (bits) and down spins in one word: at most 16 lanes x
                 // 128 sites x 7 < 2^15 and 16 x 128 < 2^12
                 const int s2 = group_sum_dpp<CPW>(bf + ((nd0 + nd) << 16));
+                int rt = rw_w;  // (the cells' addresses formed here, not held across the sweep)
+                asm volatile("" : "+v"(rt));
                 if (rw_rem == 0) {
                     // dEJ collects minus the new E_J (both waves of the walker add)
-                    atomicAdd((unsigned long long *)&I.dEJ[rw_w], (unsigned long long)sE);
-                    atomicAdd(&I.dM[rw_w], s2 >> 16);
+                    atomicAdd((unsigned long long *)&I.dEJ[rt], (unsigned long long)sE);
+                    atomicAdd(&I.dM[rt], s2 >> 16);
                     atomicAdd(&I.fl[t], (int)((unsigned)(s2 & 0xFFFF) / 7u));
                 }
             }
@@ -431,7 +425,7 @@ __device__ __forceinline__ void run_item(const SweepArgs &A, const SampleDev &d,
         }
         __syncthreads();
         if constexpr (!ROW) {
-            for (int i = tid; i < nT; i += T) {
+            for (int i = tm.tid(); i < nT; i += T) {
                 I.EJ[i] += I.dEJ[i];
                 I.M[i] += I.dM[i];
                 I.dEJ[i] = 0;  // cleared for the next sweep's tallies
@@ -439,18 +433,19 @@ __device__ __forceinline__ void run_item(const SweepArgs &A, const SampleDev &d,
             }
             __syncthreads();
         }
-        if (tid < 64) exchange_slots(A, d, r, n, I, tid, key, energy);
+        if (tm.wave == 0) exchange_slots(A, d, r, n, I, tm.tid(), key, energy);
         __syncthreads();
         // Snapshot for the overlap measurement, in slot order.
         const int64_t done = n + 1;
         if (done == next_meas) {
             next_meas += A.measure_every;
             uint32_t *dst = A.frames + f * A.frame_words + d.frame_off + (size_t)r * nT * L * L;
-            for (int i = tid; !tm.ghost && i < nT * L * L; i += T) {
+            const int ti = tm.tid();
+            for (int i = ti; !tm.ghost && i < nT * L * L; i += T) {
                 const int t = i / (L * L), row = i - t * (L * L);
                 dst[i] = pack_row_lds<L>(I.S + (size_t)I.was[t] * item_walker_stride(L), row);
             }
-            for (int t = tid; !tm.ghost && t < nT; t += T) {
+            for (int t = ti; !tm.ghost && t < nT; t += T) {
                 const int w = I.was[t];
                 A.frameE[f * 2 * A.total_slots + gi + t] = energy(w);
             }
@@ -459,14 +454,8 @@ __device__ __forceinline__ void run_item(const SweepArgs &A, const SampleDev &d,
         }
     }
     __syncthreads();
-    // Write-back addresses are derived again from an opaque copy of the thread
-    // index rather than kept from the load phase: held across the sweep loop
-    // they would be spilled to scratch memory (the L = 16 row kernel uses
-    // every register it may have).
-    Team tw = tm;
-    asm volatile("" : "+v"(tw.tid));
-    if (!tw.ghost) copy_walkers(I.S, item_walker_stride(L), A.spins + sbase, nT, N, false, tw);
-    for (int i = tw.tid; !tw.ghost && i < nT; i += T) {
+    if (!tm.ghost) copy_walkers(I.S, item_walker_stride(L), A.spins + sbase, nT, N, false, tm);
+    for (int i = tm.tid(); !tm.ghost && i < nT; i += T) {
         A.was[gi + i] = I.was[i];
         A.EJ[gi + i] = ROW ? -I.dEJ[i] : I.EJ[i];
         A.M[gi + i] = ROW ? N - 2 * I.dM[i] : I.M[i];
