@@ -109,7 +109,9 @@ struct RowTranspose {
 // walkers: lo for walker i = lane mod 16 (WS <= 8: mod 8, in two lanes whose
 // values add), hi for walker 16 + i (WS > 16).  Planes are packed to fill the
 // transposition: one per word for WS > 16, two for WS > 8, four for WS <= 8.
-template <int NP>
+// HALVES (WS <= 8): the row's first eight lanes hold one set, lo, the others
+// another, hi.
+template <bool HALVES, int NP>
 __device__ __forceinline__ void row_totals(const RowTranspose &tr, const uint32_t (&p)[NP], int WS, int lane, int &lo,
                                            int &hi)
 {
@@ -136,9 +138,15 @@ __device__ __forceinline__ void row_totals(const RowTranspose &tr, const uint32_
             if (4 * k + 2 < NP) v |= p[4 * k + 2] << 16;
             if (4 * k + 3 < NP) v |= p[4 * k + 3] << 24;
             const uint32_t x = tr(v);
-            lo = 16 * lo + __builtin_popcount(x & 0xFFFFu) + 4 * __builtin_popcount(x >> 16);
+            if constexpr (HALVES) {
+                lo = 16 * lo + __builtin_popcount(x & 0xFFu) + 4 * __builtin_popcount(x & 0xFF0000u);
+                hi = 16 * hi + __builtin_popcount(x & 0xFF00u) + 4 * __builtin_popcount(x >> 24);
+            } else {
+                lo = 16 * lo + __builtin_popcount(x & 0xFFFFu) + 4 * __builtin_popcount(x >> 16);
+            }
         }
         lo <<= (lane & 15) >> 3;
+        hi <<= (lane & 15) >> 3;
     }
 }
 
@@ -148,8 +156,8 @@ __device__ __forceinline__ void row_totals(const RowTranspose &tr, const uint32_
 // down spins leaves one quantity in each half, whose two parts are then added
 // (half the additions of summing both everywhere), and likewise the rows
 // between those and the unsatisfied bonds; the transpositions then run over 6
-// planes, not 13.
-template <int PF, int PU>
+// planes, not 13.  EIGHT: a set may be eight lanes wide.
+template <bool EIGHT, int PF, int PU>
 __device__ __forceinline__ void add_totals(uint32_t (&fl)[PF], uint32_t (&nd)[PF],
                                            uint32_t (&un)[PU], int lane, int TPS, int WS, int s, int nT,
                                            const int32_t *sow, int32_t *flips, int32_t *ND, int32_t *U)
@@ -176,7 +184,7 @@ __device__ __forceinline__ void add_totals(uint32_t (&fl)[PF], uint32_t (&nd)[PF
         }
         add_planes(z, un);  // rows: flips, unsatisfied bonds, down spins, unsatisfied bonds
         int lo, hi;
-        row_totals(tr, z, WS, lane, lo, hi);
+        row_totals<false>(tr, z, WS, lane, lo, hi);
         const int row = lane >> 4;
         int32_t *cell = row == 0 ? flips : row == 2 ? ND : U;
         if (ok) atomicAdd(&cell[row == 0 ? sow[w] : w], lo);
@@ -184,19 +192,27 @@ __device__ __forceinline__ void add_totals(uint32_t (&fl)[PF], uint32_t (&nd)[PF
         return;
     }
     int f0, f1, d0, d1, u0, u1;
-    row_totals(tr, fl, WS, lane, f0, f1);
-    row_totals(tr, nd, WS, lane, d0, d1);
-    row_totals(tr, un, WS, lane, u0, u1);
-    if (ok) {
-        atomicAdd(&flips[sow[w]], f0);
-        atomicAdd(&ND[w], d0);
-        atomicAdd(&U[w], u0);
+    const auto add = [&](int w, int f, int d, int u) {
+        atomicAdd(&flips[sow[w]], f);
+        atomicAdd(&ND[w], d);
+        atomicAdd(&U[w], u);
+    };
+    if constexpr (EIGHT) {
+        if (TPS == 8) {
+            row_totals<true>(tr, fl, WS, lane, f0, f1);
+            row_totals<true>(tr, nd, WS, lane, d0, d1);
+            row_totals<true>(tr, un, WS, lane, u0, u1);
+            const int v = (s & ~1) * WS + i;  // the row's first set is even
+            if (i < WS && v < nT) add(v, f0, d0, u0);
+            if (i < WS && v + WS < nT) add(v + WS, f1, d1, u1);
+            return;
+        }
     }
-    if (ok2) {
-        atomicAdd(&flips[sow[w + 16]], f1);
-        atomicAdd(&ND[w + 16], d1);
-        atomicAdd(&U[w + 16], u1);
-    }
+    row_totals<false>(tr, fl, WS, lane, f0, f1);
+    row_totals<false>(tr, nd, WS, lane, d0, d1);
+    row_totals<false>(tr, un, WS, lane, u0, u1);
+    if (ok) add(w, f0, d0, u0);
+    if (ok2) add(w + 16, f1, d1, u1);
 }
 
 // The spreading tables: entry v of table k holds, in bytes 0 .. 7, 4 << k for
@@ -422,8 +438,9 @@ __device__ __forceinline__ void group_bits_sweep(const SweepArgs &A, const Sampl
             }
         }
     }
-    // (TPS is 16, 32 or whole waves, so a row holds one set; idle lanes hold zeros)
-    add_totals(fl, nd, un, tm.tid() & 63, TPS, G.WS, s, d.n_T, I.sow, I.fl, ND, U);
+    // (TPS is 16, 32 or whole waves, so a row holds one set, or 8 and it holds two;
+    // idle lanes hold zeros)
+    add_totals<G4 <= 8>(fl, nd, un, tm.tid() & 63, TPS, G.WS, s, d.n_T, I.sow, I.fl, ND, U);
 }
 
 template <int L>

@@ -153,6 +153,7 @@ struct ea_ensemble {
     // batch launch (ea_batch.hip) of the classes of the small LDS-resident engines
     DevBuf batchbuf;                // 256 reserved bytes, then the units (longest first)
     std::vector<int> class_P;       // per class: teams per batch workgroup, 0 = not batchable
+    std::vector<int> class_unit;    // per class: its first unit
     int n_units = 0;
     size_t batch_lds = 0;
     int cus = 0;                    // compute units of the device
@@ -731,20 +732,25 @@ int bits_threads(int L, int nT) { return ((nT * bits_tpw(L, nT) + 63) / 64) * 64
 // GROUP_MAX_THREADS; the launch takes the smaller of this and the plan's size.
 int group_items(int L, int nT) { return ((nT + 3) / 4) * (L * L * L / 8); }
 
-int group_threads(int L, int nT, int jk)
+int group_threads(int L, int nT, int jk, int chains, int cus)
 {
     if (jk == EA_J_PM1_I8) {
-        // One site group per thread and set on two to eight waves, and, as
-        // long as the team stays within four waves, as many sets as leave
-        // eight walkers each: more waves hide more of a sweep's latency until
-        // the work done per set (the field, the tallies) outweighs it.  attempts/ns at 512, 256,
-        // 128, 64 threads: L = 6 x 56 temperatures 237, 269, 187 (64
-        // samples) and 701, 1099, 902 (1024); L = 6 x 16 250, 424, 727, 739;
-        // L = 10 x 56 1414, 1648 (256); L = 10 x 20 814, 998, 794; L = 12 x
-        // 16 1159, 1542, 1060.
-        int T = 128;
+        // One site group per thread and set, on one to eight waves.  Few chains
+        // are bound by the latency of a sweep: as many sets, within four waves,
+        // as leave four walkers each.  Many are bound by issue: eight walkers
+        // share the work done per set (the field, the tallies).  The line is two
+        // chains a compute unit, three where a set is narrower than a wave (L <=
+        // 6).  us a sweep at 256, 128, 64 threads: L = 6 x 24 temperatures, 64 /
+        // 256 / 384 / 512 / 1024 samples 4.3 / 5.9 / 7.6 / 9.4 / 16.9, 5.1 / 7.2 / 9.6 /
+        // 9.9 / 13.4 and 6.1 / 6.6 / 8.9 / 9.5 / 13.1; L = 10 x 8, 64 / 256 / 320 / 1024
+        // 4.4 / 5.9 / 7.6 / 17.2, 5.2 / 7.0 / 7.1 / 18.0 and 9.1 / 9.5 / 9.5 / 23.8; L = 4 x 32,
+        // 64 / 512 / 1024 4.1 / 9.4 / 17.3, 3.9 / 7.5 / 10.4 and 4.0 / 6.2 / 8.7.
+        // More than four waves only to hold the site groups: L = 6 x 56 at 512
+        // and 256, 64 / 1024 samples 6.2 / 35.6 and 5.6 / 25.2.
+        const int WS = chains <= (L <= 6 ? 3 : 2) * cus ? 4 : 8;
+        int T = 64;
         while (T < GROUP_MAX_THREADS && group_sets(L, nT, T).TPS < L * L * L / 8) T *= 2;
-        while (T < 256 && group_sets(L, nT, T).WS > 8) T *= 2;
+        while (T < 256 && group_sets(L, nT, T).WS > WS) T *= 2;
         return T;
     }
     return std::min(GROUP_MAX_THREADS, ((group_items(L, nT) + 63) / 64) * 64);
@@ -908,8 +914,30 @@ bool row_split(const ea_ensemble *e, const ea_ensemble::Class &c, int n_items)
     return 2 * split > whole || (split > 0 && n_items <= split * e->cus);
 }
 
+// Whether a launch of a +-1 group class of 64-thread teams runs its units of
+// eight teams (the batch kernel on this class alone), which share one copy of
+// the spreading tables: where more chains are then resident on a compute unit
+// (sixteen waves of 128 registers) and there are enough for that to matter.  us
+// a sweep, a workgroup per chain and eight: L = 4 x 32 temperatures (12 and 16
+// resident), 1024 / 1536 / 2048 / 4096 samples 9.1 / 14.0 / 16.7 / 28.2 and 8.9 / 13.8
+// / 14.6 / 27.8; x 64 (9 and 8), 4096 samples 43.5 and 48.4; L = 6 x 16, 2048 19.5 and
+// 15.2.
+bool eight_teams(const ea_ensemble *e, const ea_ensemble::Class &c, size_t ci)
+{
+    if (!c.group || e->jkind != EA_J_PM1_I8 || e->class_P[ci] != 8) return false;
+    const size_t ldsc = (c.lds + 15) & ~(size_t)15;
+    const int alone = std::min(16, (int)(e->lds_per_cu / (ldsc + SPREAD_BYTES)));
+    const int together = std::min(16, 8 * (int)(e->lds_per_cu / (8 * ldsc + SPREAD_BYTES)));
+    return together > alone && c.count >= alone * e->cus;
+}
+
+hipError_t launch_units(ea_ensemble *e, int K, int first, int count, size_t lds);
+
 hipError_t launch_class(ea_ensemble *e, const ea_ensemble::Class &c, int K, int first, int n_items, bool unbatched)
 {
+    const size_t ci = (size_t)(&c - e->classes.data());
+    if (!unbatched && eight_teams(e, c, ci))
+        return launch_units(e, K, e->class_unit[ci], (c.count + 7) / 8, 8 * ((c.lds + 15) & ~(size_t)15));
     SweepArgs A = sweep_args(e, K, (const int32_t *)e->items.p + first, n_items);
     const bool split = c.row && row_split(e, c, n_items);
     SweepFn fn = sweep_fn(c.L, e->jkind, c.row, c.row_table, split, c.bits, c.group, c.tiny, unbatched);
@@ -918,7 +946,6 @@ hipError_t launch_class(ea_ensemble *e, const ea_ensemble::Class &c, int K, int 
     // launch's teams: BATCH_THREADS / teams per workgroup), which keeps a
     // thread's share within 16 site groups per half-sweep (its int32 energy
     // tallies); the site engine runs the plan's workgroup size
-    const size_t ci = (size_t)(&c - e->classes.data());
     const int threads = split ? 2 * c.threads : c.row || c.bits || c.tiny ? c.threads
                         : c.group ? (e->class_P[ci] > 0 ? BATCH_THREADS / e->class_P[ci]
                                                         : std::max(std::min(c.threads, e->plan.threads),
@@ -960,6 +987,7 @@ ea_status build_batch(ea_ensemble *e)
 {
     std::vector<std::pair<double, BatchUnit>> q;
     size_t lds = 0;
+    e->class_unit.assign(e->classes.size(), 0);
     for (size_t ci = 0; ci < e->classes.size(); ++ci) {
         const auto &c = e->classes[ci];
         const int P = e->class_P[ci];
@@ -989,6 +1017,9 @@ ea_status build_batch(ea_ensemble *e)
         return fail(EA_EINVAL, "internal error: %d batch units exceed the unit table", e->n_units);
     std::vector<BatchUnit> units(q.size());
     for (size_t i = 0; i < q.size(); ++i) units[i] = q[i].second;
+    // (a class's units have one cost: they stay together, in order)
+    for (size_t ci = 0; ci < e->classes.size(); ++ci)
+        while (e->class_P[ci] > 0 && units[e->class_unit[ci]].first != e->classes[ci].begin) ++e->class_unit[ci];
     HIP_TRY(e, hipMemcpyAsync((char *)e->batchbuf.p + 256, units.data(), sizeof(BatchUnit) * units.size(),
                               hipMemcpyHostToDevice, e->stream));
     HIP_TRY(e, hipStreamSynchronize(e->stream));
@@ -996,19 +1027,16 @@ ea_status build_batch(ea_ensemble *e)
     return EA_OK;
 }
 
-hipError_t launch_batch(ea_ensemble *e, int K)
+// Units first .. first + count - 1, in workgroups of lds bytes.
+hipError_t launch_units(ea_ensemble *e, int K, int first, int count, size_t lds)
 {
     SweepArgs A = sweep_args(e, K, (const int32_t *)e->items.p, 2 * e->S);
     BatchArgs B{};
-    B.units = (const BatchUnit *)((const char *)e->batchbuf.p + 256);
-    B.n_units = e->n_units;
+    B.units = (const BatchUnit *)((const char *)e->batchbuf.p + 256) + first;
+    B.n_units = count;
     B.counter = nullptr;
-    if (e->jkind == EA_J_GAUSS_F32)
-        hipLaunchKernelGGL(batch_sweep_kernel<0>, dim3((unsigned)e->n_units), dim3(BATCH_THREADS), e->batch_lds,
-                           e->stream, A, B);
-    else
-        hipLaunchKernelGGL(batch_sweep_kernel<1>, dim3((unsigned)e->n_units), dim3(BATCH_THREADS), e->batch_lds,
-                           e->stream, A, B);
+    hipLaunchKernelGGL(e->jkind == EA_J_GAUSS_F32 ? batch_sweep_kernel<0> : batch_sweep_kernel<1>,
+                       dim3((unsigned)count), dim3(BATCH_THREADS), lds, e->stream, A, B);
     return hipGetLastError();
 }
 
@@ -1043,7 +1071,7 @@ hipError_t enqueue_chunk(ea_ensemble *e, int K, bool unbatched)
         }
     } else {
         const bool batch = batch_active(e);
-        if (batch && (st = launch_batch(e, K)) != hipSuccess) return st;
+        if (batch && (st = launch_units(e, K, 0, e->n_units, e->batch_lds)) != hipSuccess) return st;
         for (size_t ci = 0; ci < e->classes.size(); ++ci) {
             const auto &c = e->classes[ci];
             if (c.hbm || (batch && e->class_P[ci] > 0)) continue;
@@ -1449,6 +1477,10 @@ ea_status ea_create_ensemble(const ea_desc *d, void *hip_stream, ea_ensemble **o
         delete e;
         return fail(EA_EDEVICE, "no HIP device");
     }
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, e->device) != hipSuccess) cus = 1;
+    (void)hipGetLastError();
+    e->cus = std::max(cus, 1);
     const size_t lds_max = max_lds_bytes();
     SampleTotals tot;
     if ((st = plan_samples(d, lds_max, e->smp, tot)) != EA_OK) {
@@ -1509,7 +1541,7 @@ ea_status ea_create_ensemble(const ea_desc *d, void *hip_stream, ea_ensemble **o
                 c.threads = std::max(c.threads, bits_threads(h.L, h.nT));
             } else if (h.group) {
                 c.lds = std::max(c.lds, group_lds(h.L, h.nT, e->jkind));
-                c.threads = std::max(c.threads, group_threads(h.L, h.nT, e->jkind));
+                c.threads = std::max(c.threads, group_threads(h.L, h.nT, e->jkind, 2 * e->S, e->cus));
                 c.group_min_threads = std::max(c.group_min_threads, (group_items(h.L, h.nT) / 16 + 63) / 64 * 64);
             } else {
                 const bool row = d->tier != EA_TIER_SITE && row_engine(h.L, h.nT, e->jkind);
@@ -1550,13 +1582,11 @@ ea_status ea_create_ensemble(const ea_desc *d, void *hip_stream, ea_ensemble **o
         for (int v = 0; v < 2; ++v)
             (void)hipFuncSetAttribute(v ? (const void *)batch_sweep_kernel<1> : (const void *)batch_sweep_kernel<0>,
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)frames_lds_max(v, lds_max));
-        int cus = 0, ldscu = 0;
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, e->device) != hipSuccess) cus = 1;
+        int ldscu = 0;
         if (hipDeviceGetAttribute(&ldscu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, e->device) !=
             hipSuccess)
             ldscu = (int)lds_max;
         (void)hipGetLastError();
-        e->cus = std::max(cus, 1);
         e->lds_per_cu = (size_t)std::max(ldscu, (int)lds_max);
         e->lds_max = lds_max;
     }

@@ -298,8 +298,8 @@ __host__ __device__ inline GroupLdsOff group_lds_offsets(int L, int nT)
 }
 
 // The group engine's +-1 form (ea_groupbits.hpp) on a team of T threads: NS
-// sets of WS walkers (a multiple of 4, at most 32), TPS threads a set (16, 32
-// or whole waves).  More sets than the walkers need, as far as threads are
+// sets of WS walkers (a multiple of 4, at most 32), TPS threads a set (8, for at
+// most 8 site groups, 16, 32 or whole waves).  More sets than the walkers need, as far as threads are
 // left to take them (a thread per site group and set), so that small lattices
 // fill the team.
 struct GroupSets {
@@ -308,14 +308,14 @@ struct GroupSets {
 
 __host__ __device__ inline GroupSets group_sets(int L, int nT, int T)
 {
-    const int G4 = L * L * L / 8, want = G4 <= 16 ? 16 : G4 <= 32 ? 32 : (G4 + 63) & ~63;
+    const int G4 = L * L * L / 8, want = G4 <= 8 ? 8 : G4 <= 16 ? 16 : G4 <= 32 ? 32 : (G4 + 63) & ~63;
     const int least = (nT + 31) / 32, fill = T / want;
     GroupSets g;
     g.NS = fill > least ? fill : least;
     g.WS = ((nT + g.NS - 1) / g.NS + 3) & ~3;
     g.NS = (nT + g.WS - 1) / g.WS;
     g.TPS = T / g.NS;
-    g.TPS = g.TPS >= 64 ? g.TPS & ~63 : g.TPS >= 32 ? 32 : 16;
+    g.TPS = g.TPS >= 64 ? g.TPS & ~63 : g.TPS >= 32 ? 32 : g.TPS >= 16 ? 16 : 8;
     return g;
 }
 

@@ -984,3 +984,65 @@ def test_batch_plan_counts_the_static_lds(torch_cuda, monkeypatch, nT):
         ms = ens.measure()
         assert ens.check_energies() == 0
     assert_same(work, st, ms, ref)
+
+
+@pytest.mark.parametrize("nT", [29, 33, 40, 57, 64])
+def test_group_engine_pm1_eight_lane_sets(torch_cuda, nT):
+    """L = 4, +-1 couplings: a set's eight site groups take eight lanes, so a row of
+    sixteen holds two sets of four or eight walkers (an odd number of sets, the
+    last one partly filled); every team size equals the oracle bit for bit."""
+    from paper_1403_4560_amd import binding
+    work = W.make_workload([4] * 3, nT, None, [0.1, -0.4, 7.0], jkind=W.J_PM1, measure_every=2, beta_range=(0.1, 1.8),
+                           name="eight-lane sets")
+    sweeps = 7
+    ref = O.OracleEnsemble(work).run(sweeps)
+    for P in (1, 2, 4, 8):
+        with binding.Ensemble(work) as ens:
+            assert ens.engines() == ["group"] * 3
+            print("case: eight-lane sets n_T=%d teams=%d" % (nT, P), flush=True)
+            ens.set_batch_plan([P])
+            ens.set_plan(chunk=3)
+            ens.sweep_pt(sweeps)
+            st = ens.read_state()
+            ms = ens.measure()
+            assert ens.check_energies() == 0
+        assert_same(work, st, ms, ref)
+
+
+@pytest.mark.parametrize("L,nT,few,many", [(6, 24, 2, 4), (10, 8, 2, 4), (4, 32, 8, 8), (6, 56, 2, 2)])
+def test_pm1_team_size_follows_the_number_of_chains(torch_cuda, L, nT, few, many):
+    # few chains: sets of four walkers on up to four waves; many: sets of eight
+    from paper_1403_4560_amd import binding
+    cus = torch_cuda.cuda.get_device_properties(0).multi_processor_count
+    line = (3 if L <= 6 else 2) * cus // 2  # samples (two chains each)
+    for S, want in ((1, few), (line, few), (line + 1, many)):
+        one = W.make_workload([L], nT, (0.5, 2.0), 0.3, jkind=W.J_PM1, measure_every=0)
+        work = W.Workload(L=np.repeat(one.L, S), n_temps=np.repeat(one.n_temps, S), h=np.repeat(one.h, S),
+                          sample_id=np.arange(S, dtype=np.uint32), jkind=W.J_PM1, seed=1, measure_every=0, measure_start=0,
+                          beta=np.tile(one.beta, S), J=np.tile(one.J, S), spins0=np.tile(one.spins0, S))
+        with binding.Ensemble(work) as ens:
+            assert ens.engines() == ["group"] * S
+            assert ens.batch_plan()["teams"] == [want], S
+
+
+def test_many_small_pm1_chains_eight_to_a_workgroup(torch_cuda):
+    """Enough chains of 64-thread teams run eight to a workgroup though their class
+    has a launch of its own (the last workgroup with six ghost teams): samples
+    from both ends and the middle equal the oracle, which the same samples in a
+    small ensemble (a workgroup per chain) do too."""
+    from paper_1403_4560_amd import binding
+    S, nT, sweeps = 1537, 32, 7
+    assert 2 * S >= 12 * torch_cuda.cuda.get_device_properties(0).multi_processor_count
+    work = W.make_workload([4] * S, nT, None, 0.3, jkind=W.J_PM1, measure_every=2, beta_range=(0.1, 1.8), name="many small")
+    pick = [0, 1, 777, 1535, 1536]
+    print("case: %d small pm1 chains" % (2 * S), flush=True)
+    with binding.Ensemble(work) as ens:
+        assert ens.batch_plan()["teams"] == [8] and ens.get_plan().batch == 0
+        ens.set_plan(chunk=3)
+        ens.sweep_pt(sweeps)
+        st = ens.read_state()
+        ms = ens.measure()
+        assert ens.check_energies() == 0
+    ref = O.OracleEnsemble(work.subset(pick)).run(sweeps)
+    assert_same(work, st, ms, ref, samples=pick)
+    check(work.subset(pick), sweeps)
