@@ -31,12 +31,12 @@ __device__ __forceinline__ void batch_dispatch(const SweepArgs &A, int kind, con
         else run_group_bits_item<Lv>(A, d, r, mem, tm);                         \
         break;
 #define EA_S(Lv) \
-    case (BATCH_SITE << 8) | Lv: run_item<Lv, JK, false>(A, d, r, mem, tm); break;
+    case (BATCH_SITE << 8) | Lv: run_item<Lv, JK, false>(A, d, r, mem, tm, tm.tid()); break;
     switch (kind) {
         EA_G(2) EA_G(4) EA_G(6) EA_G(8) EA_G(10) EA_G(12) EA_G(14) EA_G(16)
         EA_S(2) EA_S(4)
     case (BATCH_ROW << 8) | 8:
-        if constexpr (JK == 0) run_item<8, 0, true>(A, d, r, mem, tm);
+        if constexpr (JK == 0) run_item<8, 0, true>(A, d, r, mem, tm, tm.tid());
         break;
     default: break;
     }

@@ -38,7 +38,10 @@ __device__ __forceinline__ Team make_team(int team, int T, bool ghost)
     return Team{T, ghost, (__builtin_amdgcn_readfirstlane((int)threadIdx.x) & ~63) - team * T};
 }
 
-__device__ __forceinline__ Team whole_block() { return make_team(0, (int)blockDim.x, false); }
+__device__ __forceinline__ Team whole_block()
+{
+    return Team{(int)blockDim.x, false, __builtin_amdgcn_readfirstlane((int)threadIdx.x) & ~63};
+}
 
 // Byte copy by T threads, 16 bytes at a time when both ends allow it; four
 // copies in flight per thread.
@@ -68,12 +71,11 @@ __device__ __forceinline__ void block_copy(void *__restrict__ dst, const void *_
 // count walkers of bytes each (a multiple of 8) from consecutive blocks at
 // glob to blocks lstride bytes apart at lds (to_lds), or back, in 8-byte words.
 __device__ __forceinline__ void copy_walkers(int8_t *lds, size_t lstride, int8_t *glob, int count, size_t bytes,
-                                             bool to_lds, const Team tm = whole_block())
+                                             bool to_lds, uint32_t T, uint32_t tid)
 {
-    const int T = tm.T, tid = tm.tid();
-    const int per = (int)bytes / 8, total = per * count;
-    for (int i = tid; i < total; i += T) {
-        const int w = i / per, j = i - w * per;
+    const uint32_t per = (uint32_t)bytes / 8, total = per * (uint32_t)count;
+    for (uint32_t i = tid; i < total; i += T) {
+        const uint32_t w = i / per, j = i - w * per;
         uint2 *l = (uint2 *)(lds + w * lstride) + j;
         uint2 *g = (uint2 *)(glob + w * bytes) + j;
         if (to_lds) *l = *g;

@@ -43,8 +43,10 @@ template <int L, int JK, int VAR>
 __global__ void __launch_bounds__(1024) site_sweep_kernel(SweepArgs A)
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    const int code = A.items[blockIdx.x];
-    run_item<L, JK, false>(A, A.samples[code >> 1], code & 1, smem);
+    for (int item = blockIdx.x; item < A.n_items; item += gridDim.x) {
+        const int code = A.items[item];
+        run_item<L, JK, false>(A, A.samples[code >> 1], code & 1, smem, whole_block(), (int)threadIdx.x);
+    }
 }
 
 // Tiny chains (L = 2 or 4, at most 1024 odd sites over the ladder): a lane per
@@ -266,7 +268,8 @@ __global__ void __launch_bounds__(ROW_MAX_THREADS, L == 8 ? 4 : 1) row_sweep_ker
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int code = A.items[blockIdx.x];
-    run_item<L, 0, true, TAB, SPLIT>(A, sample_of_item(A.samples, code >> 1), code & 1, smem);
+    const Team tm = whole_block();
+    run_item<L, 0, true, TAB, SPLIT>(A, sample_of_item(A.samples, code >> 1), code & 1, smem, tm, tm.tid());
 }
 
 #define EA_SITE(Lv)                                               \

@@ -22,11 +22,10 @@ namespace ea {
 // neighbour each other, so the updates of a half-sweep are independent.
 template <int L, int JK>
 __device__ __forceinline__ void site_half_sweep(const SweepArgs &A, const SampleDev &d, int r, int p,
-                                                int64_t n, const ItemLds &I, const Team tm)
+                                                int64_t n, const ItemLds &I, int T, int tid)
 {
     constexpr int N = L * L * L, HALF = N / 2, G = HALF / 4, HL = L / 2;
     const int nT = d.n_T;
-    const int T = tm.T, tid = tm.tid();
     const int total = nT * G;
     const uint32_t c1 = (uint32_t)(2 * n + p);
     const uint32_t c2base = (PURPOSE_METROPOLIS << 28) | (uint32_t)r;
@@ -296,19 +295,21 @@ __device__ __forceinline__ uint32_t pack_row_lds(const int8_t *Sw, int row)
 // ---------------------------------------------------------------------------
 // The per-item frame shared by both engines (TAB: the row engine keeps the
 // site groups' Philox words in LDS, 2 N bytes; SPLIT: it has twice the waves, and
-// a wave takes half of the z planes).
+// a wave takes half of the z planes).  tid0: the thread's index, which the site
+// engine holds: it has registers to spare and gains by what is hoisted (20 sweeps
+// of L = 16 x 16 temperatures 966 us, 1303 with the index formed where it is used).
 template <int L, int JK, bool ROW, bool TAB = ROW, bool SPLIT = false>
 __device__ __forceinline__ void run_item(const SweepArgs &A, const SampleDev &d, int r, char *smem,
-                                         const Team tm = whole_block())
+                                         const Team tm, int tid0)
 {
     constexpr int N = L * L * L;
     const int nT = d.n_T;
-    const int T = tm.T, tid = tm.tid();
+    const int T = tm.T, tid = ROW ? tm.tid() : tid0;
     const ItemLds I = item_lds(smem, L, nT, JK);
 
     const size_t sbase = (size_t)d.spin_off + (size_t)r * nT * N;
     const int gi = 2 * d.slot_off + r * nT;
-    copy_walkers(I.S, item_walker_stride(L), A.spins + sbase, nT, N, true, tm);
+    copy_walkers(I.S, item_walker_stride(L), A.spins + sbase, nT, N, true, T, tid);
     if constexpr (ROW) {
         // couplings as exact int32 multiples of 2^-18, rows of each z plane
         // placed by row_slot (4 consecutive elements stay within one row)
@@ -350,7 +351,8 @@ __device__ __forceinline__ void run_item(const SweepArgs &A, const SampleDev &d,
     // row engine: this thread's walker and column (see RowMap)
     constexpr int CPW = RowMap<(L >= 8 ? L : 8)>::CPW, WPW = RowMap<(L >= 8 ? L : 8)>::WPW;
     constexpr int WPR = L / 8 > 0 ? L / 8 : 1;
-    const int tid_r = tm.tid();
+    int tid_r = ROW ? tm.tid() : tid;
+    asm volatile("" : "+v"(tid_r));
     const int rw_wave = tid_r >> 6, rw_lane = tid_r & 63;
     const int rw_par = __builtin_amdgcn_readfirstlane(rw_wave & 1);
     const int rw_rem = rw_lane % CPW;
@@ -419,13 +421,13 @@ __device__ __forceinline__ void run_item(const SweepArgs &A, const SampleDev &d,
                 }
             }
         } else {
-            site_half_sweep<L, JK>(A, d, r, 0, n, I, tm);
+            site_half_sweep<L, JK>(A, d, r, 0, n, I, T, tid);
             __syncthreads();
-            site_half_sweep<L, JK>(A, d, r, 1, n, I, tm);
+            site_half_sweep<L, JK>(A, d, r, 1, n, I, T, tid);
         }
         __syncthreads();
         if constexpr (!ROW) {
-            for (int i = tm.tid(); i < nT; i += T) {
+            for (int i = tid; i < nT; i += T) {
                 I.EJ[i] += I.dEJ[i];
                 I.M[i] += I.dM[i];
                 I.dEJ[i] = 0;  // cleared for the next sweep's tallies
@@ -433,14 +435,14 @@ __device__ __forceinline__ void run_item(const SweepArgs &A, const SampleDev &d,
             }
             __syncthreads();
         }
-        if (tm.wave == 0) exchange_slots(A, d, r, n, I, tm.tid(), key, energy);
+        if (ROW ? tm.wave == 0 : tid < 64) exchange_slots(A, d, r, n, I, ROW ? tm.tid() : tid, key, energy);
         __syncthreads();
         // Snapshot for the overlap measurement, in slot order.
         const int64_t done = n + 1;
         if (done == next_meas) {
             next_meas += A.measure_every;
             uint32_t *dst = A.frames + f * A.frame_words + d.frame_off + (size_t)r * nT * L * L;
-            const int ti = tm.tid();
+            const int ti = ROW ? tm.tid() : tid;
             for (int i = ti; !tm.ghost && i < nT * L * L; i += T) {
                 const int t = i / (L * L), row = i - t * (L * L);
                 dst[i] = pack_row_lds<L>(I.S + (size_t)I.was[t] * item_walker_stride(L), row);
@@ -454,8 +456,9 @@ __device__ __forceinline__ void run_item(const SweepArgs &A, const SampleDev &d,
         }
     }
     __syncthreads();
-    if (!tm.ghost) copy_walkers(I.S, item_walker_stride(L), A.spins + sbase, nT, N, false, tm);
-    for (int i = tm.tid(); !tm.ghost && i < nT; i += T) {
+    const int te = ROW ? tm.tid() : tid;
+    if (!tm.ghost) copy_walkers(I.S, item_walker_stride(L), A.spins + sbase, nT, N, false, T, te);
+    for (int i = te; !tm.ghost && i < nT; i += T) {
         A.was[gi + i] = I.was[i];
         A.EJ[gi + i] = ROW ? -I.dEJ[i] : I.EJ[i];
         A.M[gi + i] = ROW ? N - 2 * I.dM[i] : I.M[i];
