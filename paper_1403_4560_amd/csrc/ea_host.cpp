@@ -1365,15 +1365,16 @@ std::vector<int> batch_candidates(const ea_ensemble *e, size_t ci)
     return out;
 }
 
-// A plan cache entry is keyed by what decides the launches: the device
-// architecture and compute units, the coupling kind and every class (engine,
-// L, items, largest n_T).
+// A plan cache entry is keyed by what decides the launches: the kernels (the
+// version, raised when plans ranked on earlier ones should be timed again), the
+// device architecture and compute units, the coupling kind and every class
+// (engine, L, items, largest n_T).
 std::string plan_signature(const ea_ensemble *e)
 {
     hipDeviceProp_t prop{};
     (void)hipGetDeviceProperties(&prop, e->device);
     (void)hipGetLastError();
-    std::string k = std::string("ea-plan-v1;") + prop.gcnArchName + ";cu" + std::to_string(e->cus) + ";j" +
+    std::string k = std::string("ea-plan-v2;") + prop.gcnArchName + ";cu" + std::to_string(e->cus) + ";j" +
                     std::to_string(e->jkind);
     for (const auto &c : e->classes) {
         int nTmax = 1;

@@ -1046,3 +1046,33 @@ def test_many_small_pm1_chains_eight_to_a_workgroup(torch_cuda):
     ref = O.OracleEnsemble(work.subset(pick)).run(sweeps)
     assert_same(work, st, ms, ref, samples=pick)
     check(work.subset(pick), sweeps)
+
+
+def test_autotune_does_not_apply_plans_ranked_on_earlier_kernels(torch_cuda, tmp_path, monkeypatch):
+    """A plan cache entry under the key of an earlier kernel version (the FNV-1a
+    hash of the version, device and launch classes) is left alone: the ensemble
+    is timed, and its plan stored under the present key beside the old entry."""
+    from paper_1403_4560_amd import binding
+    cache = tmp_path / "plans.txt"
+    monkeypatch.setenv("EA_TUNE_CACHE", str(cache))
+    work = W.config_workload("mixed_L6_12", samples=range(8), measure_start=0)
+    prop = torch_cuda.cuda.get_device_properties(0)
+    with binding.Ensemble(work) as ens:
+        plan = ens.batch_plan()
+
+        def key(version):
+            text = "ea-plan-v%d;%s;cu%d;j%d" % (version, prop.gcnArchName, prop.multi_processor_count, work.jkind)
+            for L, engine in zip(plan["L"], plan["engine"]):
+                mine = [s for s in range(work.n_samples) if work.L[s] == L]
+                text += ";%d/%d/%d/%d" % (["site", "row", "group", "bits", "hbm"].index(engine), L, 2 * len(mine),
+                                          max(int(work.n_temps[s]) for s in mine))
+            h = 1469598103934665603
+            for ch in text.encode():
+                h = ((h ^ ch) * 1099511628211) % 2 ** 64
+            return "%016x" % h
+
+        assert plan["signature"] == key(2)
+        old = "%s batch=1 threads=256 P=%s\n" % (key(1), ",".join("1" if t else "0" for t in plan["teams"]))
+        cache.write_text(old)
+        ens.autotune(trial_sweeps=2)
+        assert cache.read_text().startswith(old) and ("\n" + key(2) + " batch=") in cache.read_text()
