@@ -155,6 +155,7 @@ struct ea_ensemble {
     DevBuf batchbuf;                // 256 reserved bytes, then the units (longest first)
     std::vector<int> class_P;       // per class: teams per batch workgroup, 0 = not batchable
     std::vector<int> class_unit;    // per class: its first unit
+    int trial_chunk = 0;            // autotuner: the chunk length its trials stand for
     int n_units = 0;
     size_t batch_lds = 0;
     int cus = 0;                    // compute units of the device
@@ -829,6 +830,14 @@ int spread_slots(const ea_ensemble::Class &c, int nT_max, int jk, int cus)
     return 0;
 }
 
+// Whether a chunk of K sweeps (in the autotuner's trials, one of the length they
+// stand for) of a class with launches of its own runs spread.
+bool spread_runs(const ea_ensemble *e, const ea_ensemble::Class &c, int K)
+{
+    const int chunk = e->trial_chunk ? e->trial_chunk : K;
+    return c.spread > 0 && chunk >= SPREAD_MIN_SWEEPS && chunk <= SPREAD_MAX_SWEEPS;
+}
+
 // The walker table of the spread classes, and their couplings as int32.  They
 // cost memory that the engines do without: without room for it nothing is
 // spread.
@@ -1088,7 +1097,7 @@ hipError_t enqueue_chunk(ea_ensemble *e, int K, bool unbatched)
         for (size_t ci = 0; ci < e->classes.size(); ++ci) {
             const auto &c = e->classes[ci];
             if (c.hbm || (batch && e->class_P[ci] > 0)) continue;
-            if (c.spread && K >= SPREAD_MIN_SWEEPS && K <= SPREAD_MAX_SWEEPS) {
+            if (spread_runs(e, c, K)) {
                 st = launch_hbm(e, c.L, K, c.begin, c.count, e->spread_walkers.p, c.wspread, c.spread, false);
                 if (st != hipSuccess) return st;
                 continue;
@@ -2078,6 +2087,13 @@ ea_status ea_autotune(ea_ensemble *e, int32_t trial_sweeps)
     HIP_TRY(e, hipEventCreate(&ea));
     HIP_TRY(e, hipEventCreate(&eb));
     ea_status result = EA_OK;
+    // The trials run the forms that chunks of the plan's length run: a class that
+    // those spread is spread, over enough sweeps that its closing launches weigh
+    // no more than they ever do.
+    bool spread = false;
+    for (const auto &c : e->classes) spread |= spread_runs(e, c, e->plan.chunk);
+    if (spread) trial_sweeps = std::max(trial_sweeps, SPREAD_MIN_SWEEPS);
+    e->trial_chunk = e->plan.chunk;
     // time of trial_sweeps sweeps under the current choices (best of two runs);
     // the state is restored after each run
     auto trial = [&](double *ms) -> ea_status {
@@ -2114,7 +2130,8 @@ ea_status ea_autotune(ea_ensemble *e, int32_t trial_sweeps)
     //    its own launches
     auto tune_teams = [&]() {
         for (size_t ci = 0; ci < e->classes.size() && result == EA_OK; ++ci) {
-            if (e->class_P[ci] <= 0) continue;
+            // (a spread class's own launches have no teams: nothing to choose)
+            if (e->class_P[ci] <= 0 || (!batch_active(e) && spread_runs(e, e->classes[ci], 0))) continue;
             const int keepP = e->class_P[ci];
             int bestP = keepP;
             for (int P : batch_candidates(e, ci)) {
@@ -2167,6 +2184,7 @@ ea_status ea_autotune(ea_ensemble *e, int32_t trial_sweeps)
         }
         e->plan.threads = bestT;
     }
+    e->trial_chunk = 0;
     HIP_TRY(e, hipStreamSynchronize(e->stream));
     (void)hipEventDestroy(ea);
     (void)hipEventDestroy(eb);

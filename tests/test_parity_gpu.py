@@ -1076,3 +1076,32 @@ def test_autotune_does_not_apply_plans_ranked_on_earlier_kernels(torch_cuda, tmp
         cache.write_text(old)
         ens.autotune(trial_sweeps=2)
         assert cache.read_text().startswith(old) and ("\n" + key(2) + " batch=") in cache.read_text()
+
+
+@pytest.mark.parametrize("trial_sweeps", [1, 4])
+def test_autotune_times_the_launches_that_chunks_run(torch_cuda, monkeypatch, trial_sweeps):
+    """Few large chains run a workgroup per four slots in chunks of four sweeps and
+    more: the tuner's trials run that form too, however short, so that it does not
+    prefer a batch launch to it or pick teams that no launch has."""
+    from paper_1403_4560_amd import binding
+    monkeypatch.delenv("EA_TUNE_CACHE", raising=False)
+    work = W.make_workload([14] * 4, 21, (0.4, 1.5), 0.1, measure_every=2, name="tune few chains")
+    print("case: autotune few large chains, trials of %d" % trial_sweeps, flush=True)
+    with binding.Ensemble(work) as ens:
+        teams = ens.batch_plan()["teams"]
+        for _ in range(3):
+            plan = ens.autotune(trial_sweeps=trial_sweeps)
+            assert plan.batch == 0 and ens.batch_plan()["teams"] == teams
+        ens.sweep_pt(9)
+        st = ens.read_state()
+        ms = ens.measure()
+        assert ens.check_energies() == 0
+    assert_same(work, st, ms, O.OracleEnsemble(work).run(9))
+
+
+@pytest.mark.parametrize("chunk", [1000, 1001])
+def test_few_large_chains_around_the_longest_spread_chunk(torch_cuda, chunk):
+    # chunks of up to 1000 sweeps run a workgroup per walker, longer ones a
+    # workgroup per chain; the rest of the call is a chunk of the other form
+    work = W.make_workload([16], [2], (0.4, 1.5), 0.1, measure_every=50, measure_start=0, name="long chunks")
+    check(work, chunk + 2, plan=dict(chunk=chunk))
