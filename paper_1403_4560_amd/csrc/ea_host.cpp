@@ -643,6 +643,16 @@ int tiny_threads(int L, int nT)
     return (L == 2 || L == 4) && lanes <= 1024 ? (lanes + 63) / 64 * 64 : 0;
 }
 
+// Whether beta dE may be 0 times infinity in binary32 (a temperature whose
+// binary32 beta is 0, a field whose dE is beyond binary32): the exact test then
+// rejects, the estimate that the tiny kernel decides by accepts.
+bool exact_test_only(const SampleHost &h, const double *beta, int jk)
+{
+    bool zero = false;
+    for (int t = 0; t < h.nT; ++t) zero |= (float)beta[h.slot_off + t] == 0.0f;
+    return jk == EA_J_GAUSS_F32 && zero && std::fabs(h.h) >= 0x1p126f;
+}
+
 template <int L, bool TAB, bool SPLIT>
 SweepFn row_fn(bool unbatched)
 {
@@ -1571,7 +1581,7 @@ ea_status ea_create_ensemble(const ea_desc *d, void *hip_stream, ea_ensemble **o
                 if (row) c.row_table = c.row_table && row_table(h.L, h.nT, lds_max);
                 c.lds = std::max(c.lds, lds_offsets(h.L, h.nT, e->jkind, row && row_table(h.L, h.nT, lds_max)).total);
                 c.row = c.row && row;
-                c.tiny = c.tiny && tiny_threads(h.L, h.nT) > 0;
+                c.tiny = c.tiny && tiny_threads(h.L, h.nT) > 0 && !exact_test_only(h, d->beta, e->jkind);
                 if (row) c.threads = std::max(c.threads, row_threads(h.L, h.nT));
                 else if (c.tiny) c.threads = std::max(c.threads, tiny_threads(h.L, h.nT));
             }

@@ -1105,3 +1105,14 @@ def test_few_large_chains_around_the_longest_spread_chunk(torch_cuda, chunk):
     # workgroup per chain; the rest of the call is a chunk of the other form
     work = W.make_workload([16], [2], (0.4, 1.5), 0.1, measure_every=50, measure_start=0, name="long chunks")
     check(work, chunk + 2, plan=dict(chunk=chunk))
+
+
+def test_tiny_chains_where_beta_dE_is_not_a_number(torch_cuda):
+    # a temperature whose binary32 beta is 0 (the binary64 one is not) in a field
+    # whose energy change is beyond binary32: 0 times infinity, which the
+    # contract's test rejects; beside it each of the two alone
+    for L, nTs in ((4, [3, 2]), (2, [5, 1])):
+        for hs in ([3e38, -3e38], [0.3, 3e38], [1e37, -0.2]):
+            work = W.make_workload([L] * 2, nTs, None, hs, measure_every=3, beta_range=(1e-46, 1.0), name="beta dE")
+            assert np.float32(work.beta[0]) == 0.0 and work.beta[0] > 0.0
+            check(work, 9, plan=dict(chunk=4))
