@@ -401,7 +401,6 @@ __global__ void __launch_bounds__(64) hbm_exchange_kernel(SweepArgs A)
     __syncthreads();
     if (t < nT) {
         A.was_next[gi + t] = w;
-        A.sow_next[gi + t] = sow[t];
         A.EJ_next[gi + w0] = ej;
         A.M_next[gi + w0] = m;
         A.swaps[gi + t] += sw[t];

@@ -142,7 +142,7 @@ struct ea_ensemble {
     int device = 0;
     // device buffers
     DevBuf samples, items, spins, J, beta, beta32, lut, was, EJ, M, flips, swaps, acc, frames, frameE,
-        state, slot_sample, costab, sintab, scratchE, scratchM, finout, walkers, dEJ, dM, sow, Ju, mslots, Jbits,
+        state, slot_sample, costab, sintab, scratchE, scratchM, finout, walkers, dEJ, dM, Ju, mslots, Jbits,
         sel, fincols, stage, hbm_was, spread_walkers, spread_Ju;
     char *pin = nullptr;  // page-locked host buffer of read_back (PIN_BYTES), if there is one
     int small_reads = 0;  // calls of read_back that it would have served (counted to 2)
@@ -336,7 +336,7 @@ void destroy_all(ea_ensemble *e)
                       &e->was, &e->EJ, &e->M, &e->flips, &e->swaps, &e->acc, &e->frames,
                       &e->frameE, &e->state, &e->slot_sample, &e->costab, &e->sintab,
                       &e->scratchE, &e->scratchM, &e->finout, &e->walkers, &e->dEJ, &e->dM,
-                      &e->sow, &e->Ju, &e->mslots, &e->Jbits, &e->sel, &e->jkrep, &e->batchbuf, &e->fincols, &e->stage, &e->hbm_was,
+                      &e->Ju, &e->mslots, &e->Jbits, &e->sel, &e->jkrep, &e->batchbuf, &e->fincols, &e->stage, &e->hbm_was,
                       &e->spread_walkers, &e->spread_Ju};
     for (DevBuf *b : bufs) dfree(*b);
     if (e->pin) (void)hipHostFree(e->pin);
@@ -912,7 +912,6 @@ hipError_t launch_hbm(ea_ensemble *e, int L, int K, int item_first, int n_items,
         A.EJ_next = (int64_t *)(write ? e->dEJ.p : e->EJ.p);
         A.M_next = (int32_t *)(write ? e->dM.p : e->M.p);
         A.was_next = (int32_t *)(write ? e->hbm_was.p : e->was.p);
-        A.sow_next = (int32_t *)e->sow.p;
     };
     hipError_t st;
     for (int it = 0; it < K; ++it) {
@@ -1192,7 +1191,7 @@ ea_status plan_samples(const ea_desc *d, size_t lds_max, std::vector<SampleHost>
 // The persistent device buffers, in arena order (ea_bind_buffers), and their
 // sizes.  The snapshot frames (sized by the plan's chunk) and the scratch of
 // ea_check_energies stay outside.
-constexpr int NARENA = 27;
+constexpr int NARENA = 26;
 constexpr size_t ARENA_ALIGN = 256;
 
 void arena_buffers(ea_ensemble *e, DevBuf *b[NARENA])
@@ -1200,7 +1199,7 @@ void arena_buffers(ea_ensemble *e, DevBuf *b[NARENA])
     DevBuf *list[NARENA] = {&e->samples, &e->items, &e->spins, &e->J, &e->beta, &e->beta32, &e->lut,
                             &e->was, &e->EJ, &e->M, &e->flips, &e->swaps, &e->acc, &e->state,
                             &e->slot_sample, &e->costab, &e->sintab, &e->finout, &e->dEJ, &e->dM,
-                            &e->sow, &e->walkers, &e->Ju, &e->mslots, &e->Jbits, &e->sel, &e->batchbuf};
+                            &e->walkers, &e->Ju, &e->mslots, &e->Jbits, &e->sel, &e->batchbuf};
     for (int k = 0; k < NARENA; ++k) b[k] = list[k];
 }
 
@@ -1214,7 +1213,7 @@ void arena_sizes(int S, int jkind, const SampleTotals &t, size_t sz[NARENA])
         sizeof(int32_t) * 2 * TS, sizeof(int64_t) * 2 * TS, sizeof(int64_t) * 2 * TS,
         sizeof(double) * NACC * TS, 64, sizeof(int32_t) * TS, sizeof(double) * (MAX_L + 1) * MAX_L,
         sizeof(double) * (MAX_L + 1) * MAX_L, sizeof(double) * 2 * MAX_T * EA_NOBS, sizeof(int64_t) * 2 * TS,
-        sizeof(int32_t) * 2 * TS, sizeof(int32_t) * 2 * TS, sizeof(int32_t) * (size_t)t.hbm_walkers,
+        sizeof(int32_t) * 2 * TS, sizeof(int32_t) * (size_t)t.hbm_walkers,
         t.any_hbm && jkind == EA_J_GAUSS_F32 ? sizeof(int32_t) * (size_t)t.J_elems : 0, sizeof(int32_t) * TS,
         sizeof(uint32_t) * (size_t)t.jbits_words, sizeof(int32_t) * S, 256 + sizeof(BatchUnit) * 2 * (size_t)S};
     for (int k = 0; k < NARENA; ++k) sz[k] = sizes[k];
@@ -1740,8 +1739,8 @@ ea_status ea_create_ensemble(const ea_desc *d, void *hip_stream, ea_ensemble **o
             sizeof(double) * beta.size(), sizeof(float) * beta32.size(), sizeof(uint32_t) * lut.size(),
             sizeof(int32_t) * was.size(), sz[8], sz[9], sz[10], sz[11], sz[12], sz[13],
             sizeof(int32_t) * slot_sample.size(), sizeof(double) * costab.size(), sizeof(double) * sintab.size(),
-            sz[17], sz[18], sz[19], sz[20], sizeof(int32_t) * wtab.size(), sz[22],
-            sizeof(int32_t) * mslots.size(), sizeof(uint32_t) * Jbits.size(), sz[25], sz[26]};
+            sz[17], sz[18], sz[19], sizeof(int32_t) * wtab.size(), sz[21],
+            sizeof(int32_t) * mslots.size(), sizeof(uint32_t) * Jbits.size(), sz[24], sz[25]};
         DevBuf *bufs[NARENA];
         arena_buffers(e, bufs);
         for (int k = 0; k < NARENA; ++k) {
@@ -1778,7 +1777,6 @@ ea_status ea_create_ensemble(const ea_desc *d, void *hip_stream, ea_ensemble **o
     H2D(lut, lut.data(), sizeof(uint32_t) * 14 * TS);
     H2D(was, was.data(), sizeof(int32_t) * 2 * TS);
     H2D(slot_sample, slot_sample.data(), sizeof(int32_t) * TS);
-    H2D(sow, was.data(), sizeof(int32_t) * 2 * TS);  // identity, like walker_at_slot
     if (!wtab.empty()) H2D(walkers, wtab.data(), sizeof(int32_t) * wtab.size());
     H2D(mslots, mslots.data(), sizeof(int32_t) * mslots.size());
     if (!Jbits.empty()) H2D(Jbits, Jbits.data(), sizeof(uint32_t) * Jbits.size());
@@ -1897,7 +1895,7 @@ ea_status ea_write_state(ea_ensemble *e, const int8_t *spins_in, const int32_t *
     if (!usable(e)) return EA_ESTATE;
     if (!spins_in) return fail(EA_EINVAL, "spins is NULL");
     if (sweep < 0 || sweep > ((int64_t)1 << 31) - 1) return fail(EA_EINVAL, "sweep out of range");
-    std::vector<int32_t> was(2 * e->total_slots), sow(2 * e->total_slots);
+    std::vector<int32_t> was(2 * e->total_slots);
     std::vector<char> seen;
     for (int s = 0; s < e->S; ++s) {
         const SampleHost &h = e->smp[s];
@@ -1911,7 +1909,6 @@ ea_status ea_write_state(ea_ensemble *e, const int8_t *spins_in, const int32_t *
                     return fail(EA_EINVAL, "sample %d chain %d: walker_at_slot is not a permutation", s, r);
                 seen[w] = 1;
                 was[base + t] = w;
-                sow[base + w] = t;
             }
             const int64_t n = (int64_t)h.nT * h.N;
             if (bad_spin(spins_in + h.spin_off + r * n, n) >= 0) return fail(EA_EINVAL, "sample %d: spin not +-1", s);
@@ -1920,7 +1917,6 @@ ea_status ea_write_state(ea_ensemble *e, const int8_t *spins_in, const int32_t *
     ea_status us = ensure_stage(e, (size_t)e->spin_bytes, (size_t)e->N_max);
     if (us) return us;
     HIP_TRY(e, hipMemcpyAsync(e->was.p, was.data(), e->was.bytes, hipMemcpyHostToDevice, e->stream));
-    HIP_TRY(e, hipMemcpyAsync(e->sow.p, sow.data(), e->sow.bytes, hipMemcpyHostToDevice, e->stream));
     // slot t's spins become walker was[t]'s
     if ((us = transfer_spins(e, const_cast<int8_t *>(spins_in), false)) != EA_OK) return us;
     int64_t sw = sweep;
@@ -2075,7 +2071,7 @@ ea_status ea_autotune(ea_ensemble *e, int32_t trial_sweeps)
         return build_batch(e);
     }
     // back up the mutable state, time each candidate, restore
-    DevBuf *mut[] = {&e->spins, &e->was, &e->EJ, &e->M, &e->flips, &e->swaps, &e->acc, &e->state, &e->sow};
+    DevBuf *mut[] = {&e->spins, &e->was, &e->EJ, &e->M, &e->flips, &e->swaps, &e->acc, &e->state};
     constexpr int NMUT = sizeof mut / sizeof mut[0];
     std::vector<DevBuf> bak(NMUT);
     for (int i = 0; i < NMUT; ++i) {

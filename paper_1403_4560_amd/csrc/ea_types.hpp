@@ -100,7 +100,6 @@ struct SweepArgs {
     int64_t *EJ_next;
     int32_t *M_next;
     int32_t *was_next;
-    int32_t *sow_next;
     const int32_t *Ju;          // Gaussian couplings as int32 multiples of 2^-18, Jsub layout
     const uint32_t *Jbits;      // bit engine: per sample [2 parities][6 bonds][N/64] words
 };
