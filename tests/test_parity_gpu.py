@@ -502,6 +502,13 @@ def test_finalize_at_tile_edges(torch_cuda, S):
             same_obs({k: v[1] for k, v in j.items()}, {k: v[1] for k, v in rjk.items()})
 
 
+@pytest.mark.parametrize("S", [16, 17])
+def test_finalize_at_replicate_tile_edges(torch_cuda, S):
+    """The same at a replicate tile's own edge (FIN_VAL_TILE = 16 samples): one
+    full tile, and one sample more."""
+    test_finalize_at_tile_edges(torch_cuda, S)
+
+
 def test_failed_frame_allocation_leaves_the_ensemble_usable(torch_cuda):
     """A chunk whose snapshot frames cannot be allocated fails with
     EA_ENOMEM and leaves the ensemble as it was (old frames and capacity):
