@@ -99,7 +99,9 @@ typedef struct {
                                     EA_TIER_BYTES: as AUTO without the
                                     one-bit engine; EA_TIER_SITE: every
                                     LDS-resident sample on the one-site-per-
-                                    thread engine.  Results are identical. */
+                                    thread engine (L = 2, and L = 4 up to 32
+                                    temperatures, on the lane-per-site-pair
+                                    kernel).  Results are identical. */
 } ea_desc;
 
 enum { EA_TIER_AUTO = 0, EA_TIER_HBM = 1, EA_TIER_BYTES = 2, EA_TIER_SITE = 3 };
@@ -108,7 +110,9 @@ enum { EA_TIER_AUTO = 0, EA_TIER_HBM = 1, EA_TIER_BYTES = 2, EA_TIER_SITE = 3 };
 typedef struct {
     int32_t chunk;      /* sweeps per persistent launch (>= 1)                  */
     int32_t threads;    /* threads per workgroup of the site engine's own
-                           launches: 256, 512 or 1024                           */
+                           launches: 256, 512 or 1024 (no effect at L = 2, or
+                           at L = 4 with up to 32 temperatures, whose kernel
+                           sizes its workgroups itself)                         */
     int32_t use_graph;  /* 1: replay each chunk from a captured hipGraph       */
     int32_t batch;      /* 1: the lattice-size classes of the group engine,
                            the L = 8 row engine and the L <= 4 site engine
@@ -129,8 +133,8 @@ ea_status ea_create_ensemble(const ea_desc *desc, void *hip_stream, ea_ensemble 
 /* Lattice sizes: every even L in [2, 16] runs LDS-resident (one workgroup per
  * (sample, chain) holding the chain for a chunk of sweeps), and so does L = 32
  * with +-1 couplings when the chain fits LDS at one bit per spin (n_T <= 32);
- * other L in {24, 32} (and 8, 16 under EA_TIER_HBM) run HBM-resident (four
- * launches per sweep).  Other sizes above 16 return EA_EUNSUPPORTED. */
+ * other L in {24, 32} (and 8, 16 under EA_TIER_HBM) run HBM-resident (one
+ * launch per sweep, two more per chunk).  Other sizes above 16 return EA_EUNSUPPORTED. */
 
 /* Advance every sample by n_sweeps sweeps (half-sweep p=0, half-sweep p=1,
  * replica exchange, measurement if due; Methods).  Asynchronous on the bound
@@ -263,7 +267,8 @@ ea_status ea_autotune(ea_ensemble *ens, int32_t trial_sweeps);
  * side by side (1, 2, 4 or 8 teams of 512/teams threads), 0 for a class the
  * batch launch does not take (one-bit, HBM-resident, and row-engine L = 16
  * classes keep their own launches).  With the batch launch off, a group-engine
- * class runs its own launch with workgroups of the same team size.
+ * class runs its own launch with workgroups of the same team size (+-1
+ * couplings: with eight teams and many chains, eight chains to a workgroup).
  * signature (17 bytes, may be NULL) receives the key under which ea_autotune
  * caches this ensemble's plan. */
 ea_status ea_get_batch_plan(const ea_ensemble *ens, int32_t *n_classes, int32_t *class_L, int32_t *class_engine,
@@ -294,9 +299,14 @@ ea_status ea_query(const ea_ensemble *ens, int32_t *n_samples, int64_t *total_sl
 /* Device bytes of the persistent buffers an ensemble created from desc would
  * hold (samples, couplings, spins, temperatures, walker maps, energies,
  * counters, accumulators, tables), laid out as one arena of 256-byte aligned
- * slices: the size of the caller memory ea_bind_buffers takes.  The snapshot
- * frames (sized by the plan's chunk) and the scratch of ea_check_energies are
- * not part of it and stay library-owned.  Validates desc as
+ * slices: the size of the caller memory ea_bind_buffers takes.  Not part of it
+ * and library-owned until ea_destroy: the snapshot frames (sized by the plan's
+ * chunk), the scratch of ea_check_energies and of the jackknife replicates,
+ * the column sums of ea_finalize, a staging buffer of at most 64 MiB, where
+ * classes run HBM-resident or few large chains do (ea_query_engines) a second
+ * walker map, of the latter also a walker table and, L = 16 Gaussian, int32
+ * couplings; and 256 KiB of page-locked host memory from the second small copy
+ * to the host on.  Validates desc as
  * ea_create_ensemble does and asks the current device for its LDS size (which
  * decides the engines); allocates nothing.  EA_EDEVICE without a device. */
 ea_status ea_query_sizes(const ea_desc *desc, size_t *device_bytes);
@@ -315,11 +325,16 @@ ea_status ea_bind_buffers(ea_ensemble *ens, void *const *device_ptrs, size_t are
 
 /* The engine that runs each sample's sweeps (chosen at creation from L, n_T,
  * the coupling kind, the field, the LDS size and the tier option).
- * engines_host [S] (caller-owned) receives one ea_engine value per sample. */
+ * engines_host [S] (caller-owned) receives one ea_engine value per sample.
+ * Few large chains (L = 16 row and bits, L = 32 bits, L = 12 and 14 Gaussian
+ * group) keep their engine's value although chunks of 4 to 1000 sweeps run them
+ * by the HBM tier's kernels; EA_ENGINE_SITE stands for the kernel of L = 2 and
+ * 4 too. */
 enum {
     EA_ENGINE_SITE = 0,   /* LDS, one site of one walker per thread step        */
     EA_ENGINE_ROW = 1,    /* LDS, int8x4 words of one walker (Gaussian, 8, 16)  */
-    EA_ENGINE_GROUP = 2,  /* LDS, int8x4 words of one site of four walkers      */
+    EA_ENGINE_GROUP = 2,  /* LDS, one site of four walkers (int8x4 words; +-1
+                             couplings: of up to 32, a bit each)               */
     EA_ENGINE_BITS = 3,   /* LDS, one bit per spin (+-1, L = 8, 16, 32)         */
     EA_ENGINE_HBM = 4     /* HBM-resident, one launch per sweep                 */
 };

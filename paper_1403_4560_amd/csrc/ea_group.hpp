@@ -305,9 +305,9 @@ __device__ __forceinline__ void run_group_item(const SweepArgs &A, const SampleD
         // Per-walker tallies (idle lanes hold zeros).  dEJ collects minus the
         // new E_J: the second half-sweep summed (S_u + hgrid) XOR m' = s'(S_u +
         // hgrid) - [s' = -1] over the odd sites, so a thread adds accE +
-        // (1 + 2 hgrid) nd and dEJ starts the sweep at -hgrid N/2 .  Per thread a byte counter holds at most 128
-        // (at most 16 site groups per half-sweep), so a sum over 16 lanes fits
-        // a 16-bit lane.  Teams of four or more waves with NQ = 1, 2 or 4 sum
+        // (1 + 2 hgrid) nd and dEJ starts the sweep at -hgrid N/2.  Per thread
+        // a byte counter holds at most 128 (at most 16 site groups per half-
+        // sweep), so a sum over 16 lanes fits a 16-bit lane.  Teams of four or more waves with NQ = 1, 2 or 4 sum
         // the lanes of a row of 16 that share a quad (lane = quad mod NQ)
         // first (byte counters as 16-bit lanes, walkers 0 and 2 in one word,
         // 1 and 3 in another); lane j of the row then adds walker (j / NQ) mod

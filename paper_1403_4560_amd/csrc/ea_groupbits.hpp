@@ -25,7 +25,7 @@
 // per quad), sweep kernel attempts/ns: L = 10 x 56 temperatures 909 -> 1599
 // (256 samples), L = 12 x 16 852 -> 1468 (512), L = 14 x 32 723 -> 1463 (256),
 // L = 6 x 56 649 -> 1021 (1024); few chains are bound by the latency of a
-// sweep: L = 6 x 56, 64 samples 6.7 -> 5.8 us.
+// sweep: L = 6 x 56, 64 samples 6.7 -> 5.4 us.
 //
 // Sites are stored by position within their group of four ((h & 3) N/8 + h /
 // 4), so that the lanes of a wave, which take consecutive groups, read

@@ -1,6 +1,6 @@
 // ea_hbm.hip -- HBM-resident tier: chains too large for LDS (L = 24, and L = 32
-// with Gaussian couplings or long ladders), and few large chains of the row and
-// one-bit engines (spread_class in ea_host.cpp).
+// with Gaussian couplings or long ladders), and few large chains of the row,
+// one-bit and (quad_sweep_kernel) group engines (spread_slots in ea_host.cpp).
 //
 // Spins stay in HBM in the sublattice layout.  A sweep is one launch with one
 // workgroup per slot: the spins (N bytes) of the slot's walker are loaded into
@@ -339,7 +339,8 @@ __global__ void __launch_bounds__(hbm_threads(L)) hbm_sweep_kernel(SweepArgs A)
     hbm_class<L, JK, 1, 0>(A, d, S, sl, key, ty);
     hbm_class<L, JK, 1, 1>(A, d, S, sl, key, ty);
     // E_J = -(sum of s' S_u over the odd sites): accE + nd1 sums s' (S_u +
-    // hgrid), less hgrid sum s' (a thread has at most 16 odd sites)
+    // hgrid), less hgrid sum s' (a thread has at most 32 odd sites,
+    // L = 32: 32 x 12 2^21 < 2^31)
     const long long e = wave_sum_i64((long long)ty.accE + (1 + 2 * (long long)d.hgrid * (JK == 0)) * ty.nd1);
     // set bits of the flip masks (at most 7 x 4096 sites a wave) and down spins
     const int s2 = wave_sum_i32(ty.bf + (ty.nd << 16)), fl = s2 & 0xFFFF, nd = s2 >> 16;

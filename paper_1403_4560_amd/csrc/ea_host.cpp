@@ -809,7 +809,8 @@ SweepFn hbm_fn(int L, int jk, bool unbatched)
 // chain) that leaves most compute units idle runs the HBM tier's kernels, a
 // workgroup per walker or per four slots, on the same state; chunks of fewer
 // sweeps than SPREAD_MIN_SWEEPS stay (the closing launches are 6 us), and of more
-// than SPREAD_MAX_SWEEPS (a captured chunk would hold a node per sweep).  us per
+// than SPREAD_MAX_SWEEPS (a captured chunk would hold a node per sweep; the line
+// holds without a graph too, so that use_graph does not choose the form).  us per
 // sweep, the chain's engine and spread:
 //   L = 16 Gaussian, 24 temperatures, 1 / 16 / 32 / 48 samples 21.9 / 22.0 / 22.6
 //   / 23.0 and 6.5 / 10.1 / 16.7 / 23.4; 5 temperatures, 32 samples 11.7 and 7.7.
@@ -822,9 +823,13 @@ SweepFn hbm_fn(int L, int jk, bool unbatched)
 //   temperatures up to a chain for every eighth, from 20 for every fourth.
 //   L = 14 Gaussian, 8 / 12 / 21 temperatures, 16 samples 11.3 / 13.7 / 21.3 and
 //   11.6 / 11.9 / 12.3, 21 temperatures, 37 / 45 samples 21.5 / 21.7 and 17.6 /
-//   24.6; L = 12, 16 / 24 / 32 temperatures, 16 samples 11.0 / 16.3 / 19.3 and 10.0
-//   / 10.2 / 10.4, 32 samples 11.0 / 16.0 / 19.4 and 11.2 / 12.8 / 13.3: up to a
-//   workgroup per compute unit, or two at six workgroups a chain.
+//   24.6; 12 temperatures, 42 samples 12.7 and 11.7; L = 12, 24 / 32 temperatures,
+//   16 samples 16.3 / 19.3 and 10.2 / 10.4, 32 samples 16.0 / 19.4 and 12.8 / 13.3;
+//   16 temperatures, 32 samples 10.1 and 9.6: up to a workgroup per compute unit, or
+//   two at six workgroups a chain.  Between: five workgroups a chain (L = 12 x 20),
+//   26 / 50 / 56 samples 12.3 / 12.3 / 12.3 and 11.5 / 12.2 / 14.1; four at 33 and
+//   more 16-19 % slower spread; six at 46 to 50 samples 14-16 % slower at L = 14, 3-5
+//   % faster at 46 to 56 at L = 12.
 // Smaller chains take little more than a launch per sweep.
 constexpr int SPREAD_MIN_SWEEPS = 4, SPREAD_MAX_SWEEPS = 1000;
 

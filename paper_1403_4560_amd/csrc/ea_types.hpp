@@ -270,6 +270,8 @@ __host__ __device__ inline BitsLdsOff bits_lds_offsets(int L, int nT)
 // quad words [2][ceil(n_T/4)][N/2 + 1], couplings (int32 units of 2^-18)
 // [2][3][N/2], the neighbour table [N/2] (16 B per site), then the
 // per-walker/slot arrays of the common frame.
+// (M holds nothing: without its room more teams of a few ladders would fit a
+// batch workgroup than ever ran, L = 6 x 57 .. 60 temperatures eight.)
 struct GroupLdsOff {
     size_t spins, J, nb, was, sow, M, dM, fl, sw, EJ, dEJ, b32, b64, total;
 };
@@ -298,9 +300,9 @@ __host__ __device__ inline GroupLdsOff group_lds_offsets(int L, int nT)
 
 // The group engine's +-1 form (ea_groupbits.hpp) on a team of T threads: NS
 // sets of WS walkers (a multiple of 4, at most 32), TPS threads a set (8, for at
-// most 8 site groups, 16, 32 or whole waves).  More sets than the walkers need, as far as threads are
-// left to take them (a thread per site group and set), so that small lattices
-// fill the team.
+// most 8 site groups, 16, 32 or whole waves).  More sets than the walkers need,
+// as far as threads are left to take them (a thread per site group and set), so
+// that small lattices fill the team.
 struct GroupSets {
     int NS, WS, TPS;
 };
