@@ -264,8 +264,10 @@ __device__ __forceinline__ void run_group_item(const SweepArgs &A, const SampleD
     key.init(A.key0, A.key1);
     for (int it = 0; it < A.K; ++it) {
         const int64_t n = n0 + it;
+        // (a held index: with it formed here the mixed sizes' batch launch ran 0.6 %
+        // slower, 1003 attempts/ns for 1009)
 #pragma unroll 1
-        for (int i = tm.tid(); i < nT; i += T) {
+        for (int i = tid; i < nT; i += T) {
             I.dM[i] = 0;
             I.dEJ[i] = -(long long)hg * HALF;
         }
