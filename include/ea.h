@@ -305,8 +305,7 @@ ea_status ea_query(const ea_ensemble *ens, int32_t *n_samples, int64_t *total_sl
  * the column sums of ea_finalize, a staging buffer of at most 64 MiB, where
  * classes run HBM-resident or few large chains do (ea_query_engines) a second
  * walker map, of the latter also a walker table and, L = 16 Gaussian, int32
- * couplings; and 256 KiB of page-locked host memory from the second small copy
- * to the host on.  Validates desc as
+ * couplings; and 256 KiB of page-locked host memory.  Validates desc as
  * ea_create_ensemble does and asks the current device for its LDS size (which
  * decides the engines); allocates nothing.  EA_EDEVICE without a device. */
 ea_status ea_query_sizes(const ea_desc *desc, size_t *device_bytes);

@@ -145,7 +145,6 @@ struct ea_ensemble {
         state, slot_sample, costab, sintab, scratchE, scratchM, finout, walkers, dEJ, dM, Ju, mslots, Jbits,
         sel, fincols, stage, hbm_was, spread_walkers, spread_Ju;
     char *pin = nullptr;  // page-locked host buffer of read_back (PIN_BYTES), if there is one
-    int small_reads = 0;  // calls of read_back that it would have served (counted to 2)
     int64_t frames_cap = 0;  // frames allocated
     std::vector<double> beta_host;  // [total_slots], to check that a finalize selection is one system
     std::vector<int32_t> sel_idx;   // [S] a finalize call's selection (no allocation per call)
@@ -450,8 +449,9 @@ void launch_energies(const ea_ensemble *e, const DevBuf &EJ, const DevBuf &M)
 // memory waits for itself, about 17 us each, so small results go through a
 // page-locked buffer of the ensemble with one wait: three arrays of 46 kB in 26
 // us for 60.  At a megabyte both take 76 us (copying out is half of it).  The
-// buffer is made by the second such call: it takes 43 us, which a handle that is
-// read once would pay for nothing (creation of the smallest 218 us without it).
+// buffer is made at the end of creation, while the device works on what was
+// launched; made by the second small read instead, it cost that read 43 us and
+// the first one 20 (the smallest created, and read twice: 267 us and 301).
 struct HostCopy {
     void *dst;
     const void *src;  // device
@@ -459,20 +459,10 @@ struct HostCopy {
 };
 constexpr size_t PIN_BYTES = (size_t)256 << 10;
 
-ea_status read_back(ea_ensemble *e, const HostCopy *part, int n, bool may_allocate = true)
+ea_status read_back(ea_ensemble *e, const HostCopy *part, int n)
 {
     size_t total = 0;
     for (int i = 0; i < n; ++i) total += part[i].bytes;
-    if (total <= PIN_BYTES && may_allocate && e->small_reads < 2 && ++e->small_reads == 2) {
-        // (a capture on another thread of the caller is none of its business)
-        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-        (void)hipThreadExchangeStreamCaptureMode(&mode);
-        if (hipHostMalloc((void **)&e->pin, PIN_BYTES, hipHostMallocDefault) != hipSuccess) {
-            (void)hipGetLastError();
-            e->pin = nullptr;
-        }
-        (void)hipThreadExchangeStreamCaptureMode(&mode);
-    }
     const bool pin = e->pin && total <= PIN_BYTES;
     char *at = e->pin;
     for (int i = 0; i < n; at += part[i++].bytes)
@@ -1326,7 +1316,7 @@ size_t jk_rep_doubles(int nT, int count) { return (size_t)nT * (size_t)count * 1
 ea_status run_finalize(ea_ensemble *e, const int32_t *sel, int32_t n, double *out_mean, double *out_err,
                        double *rep)
 {
-    const bool jk = out_err != nullptr, noalloc = rep != nullptr;
+    const bool jk = out_err != nullptr;
     int count = 0, s0 = 0;
     ea_status st = finalize_selection(e, sel, n, jk ? 2 : 1, &count, &s0);
     if (st) return st;
@@ -1361,7 +1351,7 @@ ea_status run_finalize(ea_ensemble *e, const int32_t *sel, int32_t n, double *ou
     }
     const size_t bytes = sizeof(double) * nT * EA_NOBS;
     const HostCopy part[2] = {{out_mean, dm, bytes}, {out_err, de, bytes}};
-    return read_back(e, part, jk ? 2 : 1, !noalloc);
+    return read_back(e, part, jk ? 2 : 1);
 }
 
 // Autotuner support.  Candidate team counts for batchable class ci: P in
@@ -1820,6 +1810,11 @@ ea_status ea_create_ensemble(const ea_desc *d, void *hip_stream, ea_ensemble **o
     // initial energies from scratch on the device
     launch_energies(e, e->EJ, e->M);
     hipError_t le = hipGetLastError();
+    // (here, while the device works on what was launched)
+    if (hipHostMalloc((void **)&e->pin, PIN_BYTES, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        e->pin = nullptr;
+    }
     if (le == hipSuccess) le = hipStreamSynchronize(e->stream);
     if (le != hipSuccess) {
         destroy_all(e);
