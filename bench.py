@@ -88,8 +88,8 @@ VALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 # (FETCH_SIZE scaled by 2.0 and WRITE_SIZE by 1.0, the factors a plain copy of
 # known size reads), keyed by a fingerprint of the kernel sources they were
 # taken on; reported as null once the kernels change.
-MEASURED_TRAFFIC = {"L16_gauss": ("df6681439a77e2cb", 2.0324e9), "L32_pm1": ("df6681439a77e2cb", 3.6097e9),
-                    "mixed_L6_12": ("df6681439a77e2cb", 0.8596e9), "L8_gauss": ("df6681439a77e2cb", 0.1511e9)}
+MEASURED_TRAFFIC = {"L16_gauss": ("bc6d6335c95f12e9", 2.0325e9), "L32_pm1": ("bc6d6335c95f12e9", 3.6123e9),
+                    "mixed_L6_12": ("bc6d6335c95f12e9", 0.7665e9), "L8_gauss": ("bc6d6335c95f12e9", 0.1368e9)}
 KERNEL_SOURCES = tuple("paper_1403_4560_amd/csrc/" + f for f in (
     "ea_kernels.hip", "ea_bits.hip", "ea_group.hip", "ea_hbm.hip", "ea_batch.hip", "ea_row.hpp", "ea_group.hpp",
     "ea_groupbits.hpp", "ea_bitops.hpp", "ea_item.hpp", "ea_update.hpp", "ea_device.hpp", "ea_types.hpp"))
